@@ -592,6 +592,48 @@ static hipError_t launch_transpose(const void *src, void *dst, int dtype, int N,
     return hipGetLastError();
 }
 
+// A transposition whose result rows are padded with zeros: src[n][r][q] -> dst[n][q][r], rows of Rp >= R elements, Rp a
+// multiple of the 16-byte vector; any R and Q.  What makes a channel count that is no multiple of the vector readable by the
+// vector-load contraction kernels.  64 x 64 tiles through LDS: rows are read along q, written as 16-byte vectors along r.
+template <typename T>
+__global__ __launch_bounds__(256) void transpose_pad_kernel(const T *__restrict__ src, T *__restrict__ dst, int R, int Q, int Rp)
+{
+    constexpr int VEC = 16 / (int)sizeof(T), VPR = 64 / VEC;
+    __shared__ T tile[64][66];                        // [r][q]
+    const int q0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+    const T *s = src + (int64_t)blockIdx.z * R * Q;
+    T *d = dst + (int64_t)blockIdx.z * Q * Rp;
+    const int tq = threadIdx.x & 63, tr = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int r = tr + 4 * k;
+        tile[r][tq] = r0 + r < R && q0 + tq < Q ? s[(int64_t)(r0 + r) * Q + q0 + tq] : T(0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 64 * VPR / 256; ++i) {
+        const int v = threadIdx.x + 256 * i, rv = (v % VPR) * VEC, q = v / VPR;
+        if (q0 + q >= Q || r0 + rv >= Rp) continue;
+        u32x4 o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (sizeof(T) == 4) o[k] = __builtin_bit_cast(uint32_t, tile[rv + k][q]);
+            else o[k] = (uint32_t)tile[rv + 2 * k][q] | ((uint32_t)tile[rv + 2 * k + 1][q] << 16);
+        }
+        *(u32x4 *)(d + (int64_t)(q0 + q) * Rp + r0 + rv) = o;
+    }
+}
+
+hipError_t launch_transpose_pad(const void *src, void *dst, int32_t dtype, int32_t N, int32_t R, int32_t Q, int32_t Rp, hipStream_t s)
+{
+    const int vec = dtype == DT_BF16 ? 8 : 4;
+    const dim3 grid((Q + 63) / 64, (Rp + 63) / 64, N);
+    if (R < 1 || Q < 1 || Rp < R || Rp % vec || N < 1 || N > 65535 || grid.y > 65535 || ((uintptr_t)dst & 15)) return hipErrorInvalidValue;
+    if (dtype == DT_BF16) hipLaunchKernelGGL(transpose_pad_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)src, (uint16_t *)dst, R, Q, Rp);
+    else hipLaunchKernelGGL(transpose_pad_kernel<float>, grid, dim3(256), 0, s, (const float *)src, (float *)dst, R, Q, Rp);
+    return hipGetLastError();
+}
+
 // general permutation: one element per thread, result-major (the writes coalesce, the reads gather)
 template <typename T>
 __global__ __launch_bounds__(256) void permute_kernel(const PermuteParams p)

@@ -181,6 +181,22 @@ bool conv_wgrad_ok(int32_t NB, int32_t O, int32_t C, int32_t KH, int32_t KW, int
 hipError_t launch_conv_wgrad(const WgradParams &p, hipStream_t s);
 hipError_t launch_wgrad_reduce(const float *part, void *out, int32_t out_dtype, int32_t chunks, int32_t T, int32_t O, int32_t C, hipStream_t s);
 
+// ---- contraction over the slow axis of both operands: weight gradients (igemm_tn.hip) ----
+struct TnParams {
+    const void *a; uint32_t a_bytes;        // [P][lda]: rows are what the contraction runs over, M columns are used
+    const void *b; uint32_t b_bytes;        // [image][H][W][ldb] (conv) or [P][ldb], C columns are used
+    float *partial;                         // splits > 1: [splits][M][N] fp32
+    void *y; int32_t y_dtype;               // [Mout][Cout][T]
+    int32_t M, N, P, C, T, Mout, Cout;      // N = T * C, column j = (tap, c); M and C as laid out (padded), Mout and Cout as declared
+    int32_t lda, ldb;
+    int32_t conv;                           // 0: row(p) = p, one tap
+    int32_t H, W, OW, OHW, KW, s, ph, pw;
+    uint32_t div_ohw_mul, div_ohw_sh, div_ow_mul, div_ow_sh;
+    int32_t splits, split_tiles;            // K tiles (128 bytes of rows' elements: 64 bf16 / 32 f32 rows) per slice
+    int32_t nblk_m, nblk_n;                 // filled by the launcher
+};
+hipError_t launch_igemm_tn(const TnParams &p, int32_t dtype, int32_t tile, hipStream_t s);     // tile: 128 or 64 (square)
+
 // ---- one LSTM step on a precomputed input projection (lstm_step.hip) ------
 struct LstmStepParams {
     const void *h_prev;                 // [B, H] bf16
@@ -227,6 +243,8 @@ hipError_t launch_gavgpool_nhwc(const PoolParams &p, hipStream_t s);   // y: [N,
 // dst[n, p, c] (pixel-major, channel-last) <-> src[n, c, p]
 hipError_t launch_nchw_to_nhwc(const void *src, void *dst, int32_t dtype, int32_t N, int32_t C, int32_t P, hipStream_t s);
 hipError_t launch_nhwc_to_nchw(const void *src, void *dst, int32_t dtype, int32_t N, int32_t C, int32_t P, hipStream_t s);
+// src[n][r][q] -> dst[n][q][Rp], elements R .. Rp-1 of a row zero; Rp a multiple of the 16-byte vector
+hipError_t launch_transpose_pad(const void *src, void *dst, int32_t dtype, int32_t N, int32_t R, int32_t Q, int32_t Rp, hipStream_t s);
 // any permutation of up to six axes (element gather): y[i0..] = x[sum_k i_k * xstride[k]], i over ydims
 struct PermuteParams {
     const void *x; void *y; int32_t dtype; int32_t rank;

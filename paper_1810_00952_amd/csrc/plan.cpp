@@ -29,6 +29,7 @@ struct Planner {
     std::vector<int> phys[2];              // [layout][value] -> buffer index or -1
     std::set<int> out_set;
     std::vector<std::vector<int>> consumers;
+    std::map<int, int> padded_rows;        // value -> buffer of its channels-fastest rows padded to whole 16-byte vectors
 
     Planner(const Graph &g_, Plan &p_, std::string &m_) : g(g_), plan(p_), msg(m_) {}
 
@@ -756,6 +757,7 @@ struct Planner {
                 }
             }
         }
+        if (o.kind == RL_OP_DENSE_GRAD_W && tn_ok(o)) return plan_tn(gi, oi);
         p.C = 1; p.H = p.W = p.KH = p.KW = p.OH = p.OW = p.OHW = 1; p.sh = p.sw = 1;
         if (o.kind == RL_OP_DENSE_GRAD_X) {
             const int M = (int)ta.dims[0], N = (int)ta.dims[1], K = (int)tb.dims[1];
@@ -788,10 +790,15 @@ struct Planner {
             const int Nb = (int)ta.dims[0], O = (int)ta.dims[1], OH = (int)ta.dims[2], OW = (int)ta.dims[3];
             const int C = (int)tb.dims[1], H = (int)tb.dims[2], W = (int)tb.dims[3], KH = (int)ty.dims[2], KW = (int)ty.dims[3];
             if (o.attrs.stride[0] != o.attrs.stride[1]) return fail(RL_ERR_UNSUPPORTED, "conv2d_grad_w: strides must agree");
+            // bf16 batches of 64 whose operands are both channel-first still: transposed to images-last; once one of them is held
+            // channel-last, the rows are contracted as they are
+            const bool rows_held = phys[L_NHWC][va] >= 0 || phys[L_NHWC][vb] >= 0;
+            if (rows_held && tn_ok(o)) return plan_tn(gi, oi);
             if (dt == RL_BF16 && conv_wgrad_ok(Nb, O, C, KH, KW, o.attrs.stride[0]) && o.attrs.pad[0] < KH && o.attrs.pad[1] < KW &&
                 bytes_of(va) < ((size_t)1 << 31) && bytes_of(vb) < ((size_t)1 << 31) && !plan.opts.no_wgrad)
                 return plan_wgrad(gi, oi);
             if ((int64_t)Nb * OH * OW > 0x7ffffff0) return fail(RL_ERR_UNSUPPORTED, "conv2d_grad_w too large");
+            if (tn_ok(o)) return plan_tn(gi, oi);
             p.M = C * KH * KW; p.N = O; p.K = Nb * OH * OW; p.C = Nb;
             p.H = H; p.W = W; p.KH = OH; p.KW = OW; p.OH = KH; p.OW = KW; p.OHW = KH * KW;
             p.sh = p.sw = 1; p.ph = o.attrs.pad[0]; p.pw = o.attrs.pad[1];
@@ -864,6 +871,117 @@ struct Planner {
         s.slot[SL_X] = abuf; s.slot[SL_W] = wbuf; s.slot[SL_Y] = ybuf; s.slot[SL_PART] = part_buf;
         if (il.splits > 1) s.kernel += "_splitk";
         s.flops = 2.0 * p.M * (double)p.N * p.K / (double)((p.in_dil_m1 + 1) * (p.in_dil_m1 + 1));     // the zeros between dy's pixels are no work
+        s.bytes = (double)bytes_of(va) + (double)bytes_of(vb) + (double)bytes_of(vy);
+        return RL_OK;
+    }
+
+    // Rows of value v with its channels (features) fastest, each a whole number of 16-byte vectors long: v's own storage where
+    // it has that form, else a copy padded with zeros by a step of the plan.  ld: elements per row.
+    rl_status need_rows(int gi, int v, int &buf, int &ld)
+    {
+        const rl_type &t = T(v);
+        const int KV = kv_of(t.dtype), C = (int)t.dims[1];
+        ld = (int)round_up(C, KV);
+        if (ld == C) return need(v, t.rank == 4 ? L_NHWC : L_NATIVE, buf);
+        auto it = padded_rows.find(v);
+        if (it != padded_rows.end()) { buf = it->second; return RL_OK; }
+        const int64_t P = t.rank == 4 ? t.dims[2] * t.dims[3] : 1;
+        const bool cl = t.rank == 2 || phys[L_NHWC][v] >= 0;
+        int src;
+        rl_status st = need(v, t.rank == 4 && cl ? L_NHWC : L_NATIVE, src);
+        if (st != RL_OK) return st;
+        buf = new_ws((size_t)t.dims[0] * P * ld * dtype_size(t.dtype));
+        Step &s = add_step(cl ? S_PACK : S_PAD_NHWC, "padded rows", cl ? "pack_gather" : "nchw_to_nhwc_padded");
+        s.group = gi;
+        if (cl) {
+            s.gp.dtype = t.dtype; s.gp.R = (int)(t.dims[0] * P); s.gp.Kp = ld; s.gp.T = s.gp.TW = 1; s.gp.Cq = C; s.gp.s_row = C; s.gp.s_c = 1;
+        } else {
+            s.t_dtype = t.dtype; s.t_N = (int)t.dims[0]; s.t_C = C; s.t_P = (int)P; s.st_W = ld;
+        }
+        s.slot[SL_X] = src; s.slot[SL_Y] = buf;
+        s.bytes = (double)bytes_of(v) + (double)t.dims[0] * P * ld * dtype_size(t.dtype);
+        padded_rows[v] = buf;
+        return RL_OK;
+    }
+
+    // Whether a weight gradient runs on the kernel that contracts over the rows of both operands (igemm_tn.hip).  The element
+    // gather it replaces reads single elements and needs its operand packed first; below these sizes its few K tiles are not
+    // what the call's time is.
+    bool tn_ok(const OpNode &o) const
+    {
+        const int va = o.in[0], vb = o.in[1];
+        const rl_type &ta = T(va), &tb = T(vb);
+        if (plan.opts.no_wgrad || g.values[va].role == ROLE_PARAM || g.values[vb].role == ROLE_PARAM) return false;
+        const bool conv = o.kind == RL_OP_CONV2D_GRAD_W;
+        const int64_t P = conv ? ta.dims[0] * ta.dims[2] * ta.dims[3] : ta.dims[0], T_ = conv ? numel(T(o.out[0])) / (ta.dims[1] * tb.dims[1]) : 1;
+        const double macs = (double)P * ta.dims[1] * tb.dims[1] * T_;
+        if (macs < (conv ? 3.3e7 : 4e6)) return false;
+        const int es = (int)dtype_size(ta.dtype), KV = kv_of(ta.dtype);
+        const int64_t lda = round_up(ta.dims[1], KV), ldb = round_up(tb.dims[1], KV), lim = (int64_t)1 << 31;
+        const int64_t brows = conv ? tb.dims[0] * tb.dims[2] * tb.dims[3] : P;
+        return P * lda * es < lim && brows * ldb * es < lim && lda * ldb * T_ < ((int64_t)1 << 28) && ta.dims[0] <= 65535;
+    }
+
+    rl_status plan_tn(int gi, int oi)
+    {
+        const OpNode &o = g.ops[oi];
+        const int va = o.in[0], vb = o.in[1], vy = o.out[0];
+        const rl_type &ta = T(va), &tb = T(vb), &ty = T(vy);
+        const bool conv = o.kind == RL_OP_CONV2D_GRAD_W;
+        const int dt = ta.dtype, es = (int)dtype_size(dt);
+        TnParams p{};
+        int abuf, bbuf;
+        rl_status st = need_rows(gi, va, abuf, p.lda);
+        if (st != RL_OK) return st;
+        st = need_rows(gi, vb, bbuf, p.ldb);
+        if (st != RL_OK) return st;
+        p.Mout = (int)ta.dims[1]; p.Cout = (int)tb.dims[1];
+        p.M = p.lda; p.C = p.ldb; p.T = 1; p.KW = 1;
+        p.P = (int)ta.dims[0];
+        p.H = p.W = p.OW = p.OHW = 1; p.s = 1;
+        int64_t brows = p.P;
+        if (conv) {
+            p.OW = (int)ta.dims[3]; p.OHW = (int)(ta.dims[2] * ta.dims[3]);
+            p.P = (int)(ta.dims[0] * p.OHW);
+            p.H = (int)tb.dims[2]; p.W = (int)tb.dims[3];
+            p.KW = (int)ty.dims[3]; p.T = (int)(ty.dims[2] * ty.dims[3]);
+            p.s = o.attrs.stride[0]; p.ph = o.attrs.pad[0]; p.pw = o.attrs.pad[1];
+            brows = tb.dims[0] * p.H * p.W;
+            p.conv = !(p.T == 1 && p.s == 1 && p.ph == 0 && p.pw == 0);      // else output pixel p is input pixel p
+        }
+        p.N = p.T * p.C;
+        p.a_bytes = (uint32_t)((int64_t)p.P * p.lda * es);
+        p.b_bytes = (uint32_t)(brows * p.ldb * es);
+        make_fast_div((uint32_t)p.OHW, p.div_ohw_mul, p.div_ohw_sh);
+        make_fast_div((uint32_t)p.OW, p.div_ow_mul, p.div_ow_sh);
+        // Tile and K slices by a cost in shader cycles (fitted to a sweep of both tiles over 1 to 85 slices, 64x128x28x28 bf16 and
+        // 32x64x28x28 f32 through 3x3): a K tile takes `alone` cycles where a CU holds one workgroup and `share` per workgroup
+        // where it holds several (three 64x64 ones fit); 4000 to start and end; 6500 for the adding launch, and the traffic of
+        // the partial sums at 2200 bytes per cycle.
+        const int nk = (p.P + 128 / es - 1) / (128 / es);
+        int tile = 64;
+        double best = 1e30;
+        for (int tl : {64, 128}) {
+            const int64_t tiles = (int64_t)((p.M + tl - 1) / tl) * ((p.N + tl - 1) / tl);
+            const double alone = es == 2 ? (tl == 128 ? 1330 : 680) : (tl == 128 ? 4550 : 1450);
+            const double share = es == 2 ? (tl == 128 ? 1330 : 390) : (tl == 128 ? 4550 : 1100);
+            for (int sp = 1; sp <= std::min(nk, 512); ++sp) {
+                const int per = (nk + sp - 1) / sp;
+                if ((nk + per - 1) / per != sp || (int64_t)sp * p.M * p.N >= (int64_t)1 << 27) continue;
+                const double cost = per * std::max(alone, share * (double)((tiles * sp + 255) / 256)) + 4000.0 +
+                                    (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
+                if (cost < best) { best = cost; tile = tl; p.splits = sp; p.split_tiles = per; }
+            }
+        }
+        const int part = p.splits > 1 ? new_ws((size_t)p.splits * p.M * p.N * 4) : -1;
+        const int ybuf = out_buf(vy, L_NATIVE);
+        p.y_dtype = ty.dtype;
+        Step &s = add_step(S_TN, std::string(op_name(o.kind)) + "#" + std::to_string(oi), std::string("igemm_") + op_name(o.kind) + (dt == RL_BF16 ? "_bf16_" : "_f32_") +
+                           (tile == 128 ? "128x128" : "64x64") + "_rows" + (p.splits > 1 ? "_splitk" : ""));
+        s.group = gi;
+        s.tn = p; s.tn_tile = tile; s.t_dtype = dt;
+        s.slot[SL_X] = abuf; s.slot[SL_X2] = bbuf; s.slot[SL_Y] = ybuf; s.slot[SL_PART] = part;
+        s.flops = 2.0 * p.P * (double)p.Mout * p.Cout * p.T;
         s.bytes = (double)bytes_of(va) + (double)bytes_of(vb) + (double)bytes_of(vy);
         return RL_OK;
     }
@@ -1416,6 +1534,15 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
             er = launch_conv_wgrad(q, stream);
             break;
         }
+        case S_TN: {
+            TnParams q = s.tn;
+            q.a = P(s, SL_X); q.b = P(s, SL_X2); q.y = P(s, SL_Y); q.partial = (float *)P(s, SL_PART);
+            er = launch_igemm_tn(q, s.t_dtype, s.tn_tile, stream);
+            break;
+        }
+        case S_PAD_NHWC:
+            er = launch_transpose_pad(P(s, SL_X), P(s, SL_Y), s.t_dtype, s.t_N, s.t_C, s.t_P, s.st_W, stream);
+            break;
         case S_DILATE:
             er = launch_dilate_nhwc(P(s, SL_X), P(s, SL_Y), s.t_N, s.st_H, s.st_W, s.st_Hp, s.st_Wp, s.t_C, s.st_ph, stream);
             break;

@@ -1,0 +1,70 @@
+"""Kernels against the oracle at the sizes where they can go wrong: edges of tiles, remainders, ends of their ranges."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import workloads as W
+from oracle import graph as OG
+from helpers import assert_close, error_budget, run_hip
+
+
+def steps_of(spec, opts=None):
+    from paper_1810_00952_amd import binding
+    return [st["kernel"] for st in binding.Plan(binding.graph_from_spec(binding.Context(), spec), opts).describe()["steps"]]
+
+
+def check(spec, data, dtype, what, opts=None):
+    print(what, steps_of(spec, opts), flush=True)
+    ref = OG.run(spec, data)
+    got, _ = run_hip(spec, data, opts=opts)
+    for v in spec.outputs:
+        dt = spec.values[v].type.dtype
+        assert_close(got[v], ref[v], dt, what, budget=(lambda: error_budget(spec, data)[v]) if dt == "f32" else None)
+
+
+# ---- weight gradients that contract over the rows of both operands (igemm_tn.hip) ---------------------------------------
+ROWS_CASES = [
+    # kind           dims                        stride pad
+    ("dense_grad_w", (512, 1000, 784), 1, 0),            # 64 x 64 tiles, ragged last ones, one slice
+    ("dense_grad_w", (20, 192, 1536), 1, 0),             # fewer rows than a K tile
+    ("dense_grad_w", (4099, 72, 40), 1, 0),              # long and narrow: slices, a last K tile of three rows
+    ("dense_grad_w", (167, 391, 173), 1, 0),             # both feature counts padded to whole vectors
+    ("conv2d_grad_w", (5, 64, 31, 30, 64, 3), 1, 1),     # odd batch, taps outside the image, slices
+    ("conv2d_grad_w", (6, 40, 33, 29, 72, 3), 2, 1),     # stride 2: (H + 2p - K) % s = 0 for both; tiles that span taps
+    ("conv2d_grad_w", (2, 93, 20, 19, 36, 5), 1, 2),     # 25 taps, x padded to whole vectors
+    ("conv2d_grad_w", (7, 128, 24, 26, 136, 1), 1, 0),   # 1x1: rows as they lie
+    ("conv2d_grad_w", (12, 128, 23, 21, 200, 1), 2, 0),   # the strided projection
+    ("conv2d_grad_w", (1, 512, 7, 7, 512, 3), 1, 1),     # one K tile and a remainder, many tiles: no slices
+    ("conv2d_grad_w", (40, 128, 36, 1, 72, 3), 1, 1),    # rows of one pixel
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", ROWS_CASES, ids=[f"rows{i}" for i in range(len(ROWS_CASES))])
+def test_weight_gradient_over_rows(dtype, case):
+    kind, dims, stride, pad = case
+    for out_dtype in (None, "f32") if dtype == "bf16" else (None,):
+        spec, data = W.grad_case(kind, dims, dtype, stride, pad, second_is_param=False, out_dtype=out_dtype)
+        assert any("_rows" in k for k in steps_of(spec)), steps_of(spec)
+        check(spec, data, dtype, f"rows {case} {dtype} {out_dtype}")
+
+
+def test_weight_gradient_over_rows_beside_the_input_gradient():
+    # a batch of 64 in bf16, both gradients in one graph: dy is held channel-last for the first, so the second takes the rows;
+    # 128 x 128 tiles on both sides
+    import numpy as np
+    for dtype, n in (("bf16", 64), ("f32", 5)):
+        rng = np.random.default_rng(7)
+        g = W.GraphSpec("layer_backward")
+        dy = g.input("dy", dtype, (n, 128, 17, 16)); w = g.param("w", dtype, (128, 192, 3, 3)); x = g.input("x", dtype, (n, 192, 17, 16))
+        at = dict(stride=(1, 1), pad=(1, 1))
+        o, (dx,) = g.op("conv2d_grad_x", [dy, w], [(dtype, (n, 192, 17, 16))], **at); g.group([o])
+        o, (dw,) = g.op("conv2d_grad_w", [dy, x], [("f32", (128, 192, 3, 3))], out_dtype="f32", **at); g.group([o])
+        g.output(dx); g.output(dw)
+        data = {"dy": W.as_dtype(rng.standard_normal((n, 128, 17, 16)), dtype), "x": W.as_dtype(rng.standard_normal((n, 192, 17, 16)), dtype),
+                "w": W.as_dtype(rng.standard_normal((128, 192, 3, 3)) / 40, dtype)}
+        assert any("_rows" in k for k in steps_of(g)), steps_of(g)
+        check(g, data, dtype, f"layer backward {dtype}")
+        first, _ = run_hip(g, data)
+        again, _ = run_hip(g, data)
+        np.testing.assert_array_equal(first[dw], again[dw])           # slices are added in a fixed order
