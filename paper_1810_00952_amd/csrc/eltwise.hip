@@ -737,7 +737,7 @@ __global__ __launch_bounds__(256) void pack_gather_kernel(const T *__restrict__ 
         if (k < Kreal) {
             const int tap = k / g.Cq, c = k - tap * g.Cq;
             const int ti = tap / g.TW, tj = tap - ti * g.TW;
-            v = src[g.base + r * g.s_row + (int64_t)c * g.s_c + (int64_t)ti * g.s_ti + (int64_t)tj * g.s_tj];
+            if (g.Creal == 0 || c < g.Creal) v = src[g.base + r * g.s_row + (int64_t)c * g.s_c + (int64_t)ti * g.s_ti + (int64_t)tj * g.s_tj];
         }
         dst[idx] = v;
     }

@@ -17,6 +17,14 @@
 // position p of row r holds chunk p ^ ((r >> 1) & 7), so the 16 rows read by a
 // quarter-wave fragment load cover all 64 banks once.
 //
+// TAPS form: channel counts that are a multiple of the 16-byte vector only.  A K tile then spans filter taps; every lane
+// decodes, per K tile, the tap and channel of its own 16-byte chunk (two chunks per lane: the swizzle key alternates with the
+// row group) by multiply-high, and its rows' taps are checked against the image one by one.  What it replaces staged the
+// same tiles through registers: 17x96x29x29 -> 136 3x3 bf16 with residual, contraction alone 58 us against 15.
+//
+// STORE_ANY form: results in Shape order (channel-first) or with ragged N, kept apart from the row-wise form so that neither
+// pays for the other's registers and code.
+//
 // Padding taps and rows past M get a buffer offset outside the descriptor's
 // range: the hardware then writes zeros into LDS without touching memory.
 //
@@ -78,9 +86,13 @@ constexpr uint32_t OOB = 0x80000000u;
 
 }  // namespace
 
-template <typename T, int BM, int BN, bool GATES>
+// MODE of the result: rows of channels 16 bytes at a time, the LSTM gates, or any order
+enum { STORE_ROWS = 0, STORE_GATES = 1, STORE_ANY = 2 };
+
+template <typename T, int BM, int BN, int MODE, bool TAPS>
 __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
 {
+    constexpr bool GATES = MODE == STORE_GATES;
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
     constexpr int KV = Elem<T>::KV;
     constexpr int ES = (int)sizeof(T);
@@ -123,6 +135,8 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
     const int r8 = lane >> 3, pos = lane & 7;
     uint32_t a_voff[AG], a_mask[AG], a2_voff[AG], b_voff[BG];
     int a_kc[AG];                       // first K element (within a tile) of the 16-byte chunk this lane fetches
+    int t_ih[AG], t_iw[AG];             // TAPS: input coordinate of tap (0, 0)
+    static_assert(AG % 2 == 0 && BG % 2 == 0, "a lane's chunk depends on the parity of its row group only");
 #pragma unroll
     for (int i = 0; i < AG; ++i) {
         const int row = wave * 8 * AG + 8 * i + r8;
@@ -136,14 +150,17 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
             int oh = pix / p.OW;
             int ow = pix - oh * p.OW;
             int ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw;
+            t_ih[i] = ih0; t_iw[i] = iw0;
+            if (!TAPS)
             for (int kh = 0; kh < p.KH; ++kh)
                 for (int kw = 0; kw < p.KW; ++kw)
                     if ((unsigned)(ih0 + kh) < (unsigned)p.H && (unsigned)(iw0 + kw) < (unsigned)p.W) mask |= 1u << (kh * p.KW + kw);
             off = ((int64_t)img * p.xs_n + (int64_t)ih0 * p.xs_h + (int64_t)iw0 * p.xs_w) * ES;
         }
+        if (m >= p.M) { t_ih[i] = -(1 << 24); t_iw[i] = 0; }
         a_mask[i] = mask;
         a_kc[i] = chunk * KV;
-        a_voff[i] = (uint32_t)(off + bias) + chunk * 16;
+        a_voff[i] = (uint32_t)(off + bias) + (TAPS ? 0 : chunk * 16);
         a2_voff[i] = (uint32_t)((int64_t)m * p.x2s_n * ES) + chunk * 16;     // second operand of a concatenation: row m
     }
 #pragma unroll
@@ -152,8 +169,9 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
         const int chunk = pos ^ ((row >> 1) & 7);
         int n = n0 + row;
         if (n > p.N - 1) n = p.N - 1;          // rows past N are computed on valid memory and never stored
-        b_voff[j] = (uint32_t)((int64_t)n * p.Kp * ES) + chunk * 16;
+        b_voff[j] = (uint32_t)((int64_t)n * p.Kp * ES) + (TAPS ? 0 : chunk * 16);
     }
+    const uint32_t one_c = p.C == 1 ? ~0u : 0u, one_kw = p.KW == 1 ? ~0u : 0u;
 
     // ---- wave-uniform K state of the tile to be issued next.  Issuing is unconditional so that
     // every K-loop body has the same number of DMA instructions in flight (the explicit vmcnt
@@ -167,14 +185,14 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
     const int kt0 = p.splits > 1 ? split * p.split_tiles : 0;
     const int nk = p.splits > 1 ? min(nk_all, kt0 + p.split_tiles) : nk_all;
     int f_kt = kt0, f_c0 = 0, f_tap = 0, f_kh = 0, f_kw = 0;
-    if (kt0 > 0) {
+    if (!TAPS && kt0 > 0) {
         const int tpt = p.KH * p.KW == 1 ? nk_all : p.C / BKE;      // K tiles per filter tap
         f_tap = kt0 / tpt;
         f_c0 = (kt0 - f_tap * tpt) * BKE;
         f_kh = f_tap / p.KW;
         f_kw = f_tap - f_kh * p.KW;
     }
-#define RL_ISSUE(ST)                                                                                                  \
+#define RL_ISSUE_UNIFORM(ST)                                                                                                  \
     {                                                                                                                 \
         const bool live = f_kt < nk;                                                                                  \
         const int k0 = f_kt * BKE;                                                                                    \
@@ -203,6 +221,35 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
             if (++f_kw == p.KW) { f_kw = 0; ++f_kh; }                                                                 \
         }                                                                                                             \
     }
+
+#define RL_ISSUE_TAPS(ST)                                                                                             \
+    {                                                                                                                 \
+        const bool live = f_kt < nk;                                                                                  \
+        uint32_t toff[2], koff[2];                                                                                    \
+        int tkh[2], tkw[2];                                                                                           \
+        bool oka[2], okb[2];                                                                                          \
+        _Pragma("unroll") for (int e = 0; e < 2; ++e) {                                                               \
+            const uint32_t k = (uint32_t)(f_kt * BKE + a_kc[e]);                                                      \
+            const uint32_t tap = (__umulhi(k, p.div_c_mul) + (k & one_c)) >> p.div_c_sh;                              \
+            tkh[e] = (int)((__umulhi(tap, p.div_kw_mul) + (tap & one_kw)) >> p.div_kw_sh);                            \
+            tkw[e] = (int)tap - tkh[e] * p.KW;                                                                        \
+            toff[e] = (uint32_t)(((int)k - (int)tap * p.C + tkh[e] * (int)p.xs_h + tkw[e] * (int)p.xs_w) * ES);       \
+            koff[e] = k * ES;                                                                                         \
+            oka[e] = live && k < (uint32_t)p.K;                                                                       \
+            okb[e] = live && k < (uint32_t)p.Kp;                                                                      \
+        }                                                                                                             \
+        _Pragma("unroll") for (int i = 0; i < AG; ++i) {                                                              \
+            const int e = i & 1;                                                                                      \
+            const bool ok = oka[e] && (unsigned)(t_ih[i] + tkh[e]) < (unsigned)p.H && (unsigned)(t_iw[i] + tkw[e]) < (unsigned)p.W; \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, RL_LDS_PTR(ST + (wave * AG + i) * 1024), 16, ok ? a_voff[i] + toff[e] : OOB, 0, 0, 0); \
+        }                                                                                                             \
+        _Pragma("unroll") for (int j = 0; j < BG; ++j)                                                                \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, RL_LDS_PTR(ST + A_BYTES + (wave * BG + j) * 1024), 16,       \
+                                                     okb[j & 1] ? b_voff[j] + koff[j & 1] : OOB, 0, 0, 0);            \
+        ++f_kt;                                                                                                       \
+    }
+
+#define RL_ISSUE(ST) { if constexpr (TAPS) RL_ISSUE_TAPS(ST) else RL_ISSUE_UNIFORM(ST) }
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -259,12 +306,14 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
 #undef RL_BODY
 #undef RL_COMPUTE
 #undef RL_ISSUE
+#undef RL_ISSUE_TAPS
+#undef RL_ISSUE_UNIFORM
 
     // ---- epilogue: 32 rows at a time through LDS (stage 0's array), then 8 channels per thread;
     // the residual rows of the next pass are fetched while this pass is staged and stored
     using TE = TileEpilogue<BN>;
     float *sC = (float *)st0;
-    if (!GATES && p.splits > 1) {
+    if (MODE == STORE_ROWS && p.splits > 1) {
         // a slice of K: the bare fp32 sums, row-major [M][N], into this slice's part of the scratch tensor
         float *dst = p.partial + (int64_t)split * p.M * p.N;
 #pragma unroll
@@ -289,9 +338,32 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
         }
         return;
     }
-    const bool rowmajor = (p.ys_n == (int64_t)p.OHW * p.ys_p) && p.ys_c == 1;
-    const bool vec_ok = !GATES && rowmajor && (p.N & 7) == 0 && (p.ys_p & 7) == 0;
-    const bool pre = vec_ok && p.epi.simple;
+    if constexpr (MODE == STORE_ANY) {
+        // the loop stays rolled (its pass inlined BM / 32 times costs the registers of a second workgroup per CU), rows BN + 1
+        // floats apart for the reads down a column
+#pragma unroll 1
+        for (int q = 0; q < BM / 32; ++q) {
+            wg_barrier();                           // previous pass read out / last K tile consumed
+            if (wm == q / TM) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    if (i == q % TM) {
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                int row = 8 * (r >> 2) + 4 * fhalf + (r & 3);
+                                int col = wn * WTN + j * 32 + frow;
+                                sC[row * (BN + 1) + col] = acc[i][j][r];
+                            }
+                    }
+            }
+            __syncthreads();
+            TE::store_pass_scalar(p, sC, BN + 1, t, m0 + q * 32, n0);
+        }
+        return;
+    }
+    const bool pre = !GATES && p.epi.simple;
     float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     OperandRegs<TE::NV> cur = {}, nxt = {};
     if (pre) {
@@ -315,8 +387,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
         __syncthreads();
         const int mq = m0 + q * 32;
         if (GATES) TE::gates_pass(p, sC, LDC, t, mq, bn);
-        else if (vec_ok) TE::store_pass(p, sC, LDC, t, mq, n0, bias8, cur);
-        else TE::store_pass_scalar(p, sC, LDC, t, mq, n0);
+        else TE::store_pass(p, sC, LDC, t, mq, n0, bias8, cur);
         cur = nxt;
     }
 #endif
@@ -405,18 +476,23 @@ hipError_t launch_reduce_dense(const ReduceDenseParams &p, hipStream_t s)
 
 // explicit instantiations (the host-side launch stubs of a kernel template with function-local
 // __shared__ arrays are not emitted implicitly)
-#define RL_INST(T, BM, BN, G) template __global__ void igemm_dma_kernel<T, BM, BN, G>(const IgemmParams);
-RL_INST(uint16_t, 128, 128, false) RL_INST(uint16_t, 128, 64, false) RL_INST(uint16_t, 64, 64, false) RL_INST(uint16_t, 64, 64, true)
-RL_INST(float, 128, 128, false) RL_INST(float, 128, 64, false) RL_INST(float, 64, 64, false) RL_INST(float, 64, 64, true)
+#define RL_INST(T, BM, BN, MODE, TAPS) template __global__ void igemm_dma_kernel<T, BM, BN, MODE, TAPS>(const IgemmParams);
+#define RL_INST4(T, BM, BN) RL_INST(T, BM, BN, STORE_ROWS, false) RL_INST(T, BM, BN, STORE_ANY, false) RL_INST(T, BM, BN, STORE_ROWS, true) RL_INST(T, BM, BN, STORE_ANY, true)
+RL_INST4(uint16_t, 128, 128) RL_INST4(uint16_t, 128, 64) RL_INST4(uint16_t, 64, 64) RL_INST(uint16_t, 64, 64, STORE_GATES, false)
+RL_INST4(float, 128, 128) RL_INST4(float, 128, 64) RL_INST4(float, 64, 64) RL_INST(float, 64, 64, STORE_GATES, false)
+#undef RL_INST4
 #undef RL_INST
 
-template <typename T, int BM, int BN, bool GATES>
+template <typename T, int BM, int BN, bool GATES, bool TAPS>
 static hipError_t launch_dma(const IgemmParams &p0, hipStream_t s)
 {
     IgemmParams p = p0;
-    {
+    constexpr int BKE = 128 / (int)sizeof(T);
+    if (TAPS) {
+        // chunks of one tap and channel run, no concatenation
+        if (p.C % (16 / (int)sizeof(T)) != 0 || p.K != p.C * p.KH * p.KW || p.K1 != p.K || p.x2 || p.Kp < p.K || GATES) return hipErrorInvalidValue;
+    } else {
         // a partial last K tile: one tap, no concatenation, weight rows padded to whole tiles
-        constexpr int BKE = 128 / (int)sizeof(T);
         if (p.K % BKE != 0 && (p.KH * p.KW != 1 || p.K1 != p.K || p.x2 || p.Kp % BKE != 0 || p.Kp < p.K || GATES)) return hipErrorInvalidValue;
     }
     p.nblk_m = (p.M + BM - 1) / BM;
@@ -424,39 +500,41 @@ static hipError_t launch_dma(const IgemmParams &p0, hipStream_t s)
     int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
     if (p.splits > 1) {
-        constexpr int BKE = 128 / (int)sizeof(T);
         const int nk = (p.K + BKE - 1) / BKE;
         // every slice holds at least one K tile and the slices cover K exactly once
         if (GATES || !p.partial || p.splits > 64 || (int64_t)p.M * p.N * p.splits >= (int64_t)1 << 31 || p.split_tiles < 1 || (int64_t)(p.splits - 1) * p.split_tiles >= nk ||
-            (int64_t)p.splits * p.split_tiles < nk || (p.C % BKE != 0 && p.KH * p.KW != 1) || p.K1 != p.K)
+            (int64_t)p.splits * p.split_tiles < nk || (!TAPS && p.C % BKE != 0 && p.KH * p.KW != 1) || p.K1 != p.K)
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, GATES>), dim3((unsigned)nblk, (unsigned)p.splits), dim3(256), 0, s, p);
+        hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS>), dim3((unsigned)nblk, (unsigned)p.splits), dim3(256), 0, s, p);
         hipError_t er = hipGetLastError();
         if (er != hipSuccess || p.skip_reduce) return er;
         return launch_splitk_reduce(p, s);
     }
-    hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, GATES>), dim3((unsigned)nblk), dim3(256), 0, s, p);
+    const bool rows = p.ys_n == (int64_t)p.OHW * p.ys_p && p.ys_c == 1 && (p.N & 7) == 0 && (p.ys_p & 7) == 0;
+    if (GATES) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, STORE_GATES, false>), dim3((unsigned)nblk), dim3(256), 0, s, p);
+    else if (rows) hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS>), dim3((unsigned)nblk), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ANY, TAPS>), dim3((unsigned)nblk), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, bool TAPS>
 static hipError_t launch_dma_typed(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s)
 {
     if (l.gates) {
-        if (l.tile != TILE_64x64) return hipErrorInvalidValue;
-        return launch_dma<T, 64, 64, true>(p, s);
+        if (l.tile != TILE_64x64 || TAPS) return hipErrorInvalidValue;
+        return launch_dma<T, 64, 64, true, false>(p, s);
     }
     switch (l.tile) {
-    case TILE_128x128: return launch_dma<T, 128, 128, false>(p, s);
-    case TILE_128x64: return launch_dma<T, 128, 64, false>(p, s);
-    default: return launch_dma<T, 64, 64, false>(p, s);
+    case TILE_128x128: return launch_dma<T, 128, 128, false, TAPS>(p, s);
+    case TILE_128x64: return launch_dma<T, 128, 64, false, TAPS>(p, s);
+    default: return launch_dma<T, 64, 64, false, TAPS>(p, s);
     }
 }
 
 hipError_t launch_igemm_dma(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s)
 {
-    if (p.in_dtype == DT_BF16) return launch_dma_typed<uint16_t>(p, l, s);
-    return launch_dma_typed<float>(p, l, s);
+    if (p.in_dtype == DT_BF16) return l.taps ? launch_dma_typed<uint16_t, true>(p, l, s) : launch_dma_typed<uint16_t, false>(p, l, s);
+    return l.taps ? launch_dma_typed<float, true>(p, l, s) : launch_dma_typed<float, false>(p, l, s);
 }
 
 }  // namespace rl

@@ -112,21 +112,132 @@ struct TileEpilogue {
         }
     }
 
-    // any output strides / ragged N: one element at a time, consecutive threads on consecutive rows
+    // K values through a simple chain (one switch per step, not per value)
+    template <int K> static __device__ __forceinline__ void finish(const Epilogue &e, float (&val)[K], const float (&bias)[K], const float (&tt)[K])
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) val[k] += bias[k];
+        if (e.t_op >= 0) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) val[k] = binop(e.t_op, val[k], tt[k]);
+        }
+        uint64_t codes = e.rest_ops;
+        for (int s = 0; s < e.rest_n; ++s, codes >>= 8) {
+            const int op = (int)(codes & 0xff);
+            if (op == E_RELU) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) val[k] = val[k] > 0.0f ? val[k] : 0.0f;
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k) val[k] = unary_step(op, val[k]);
+            }
+        }
+    }
+
+    // Results in Shape order (channel-first) and ragged N.  What bounds this pass is how its stores and operand loads
+    // coalesce, and the index arithmetic: an element at a time with two divisions and the interpreted chain each took most of
+    // a 77 us convolution (17x96x29x29 -> 136, bf16, residual).  A thread keeps its pixels for the pass (decoded once, by
+    // multiply-high) and walks channels, operands requested a few channels at a time: four pixels of one channel as one store
+    // where images are whole groups of four pixels, one pixel otherwise; results with channels fastest walk channels across
+    // lanes.  sC rows are ldc floats apart: BN + 1 spreads the columns read here over the banks.
+    // (Loops are kept rolled: the pass inlined once per 32 rows took 230 VGPRs and one wave per SIMD.)
     static __device__ __forceinline__ void store_pass_scalar(const IgemmParams &p, const float *sC, int ldc, int t, int mq, int n0)
     {
         const Epilogue &e = p.epi;
-        for (int idx = t; idx < 32 * BN; idx += 256) {
-            int col = idx / 32, row = idx - col * 32;
-            int m = mq + row, n = n0 + col;
-            if (m < p.M && n < p.N) {
-                int img = m / p.OHW;
-                int pix = m - img * p.OHW;
-                int64_t off = (int64_t)img * p.ys_n + (int64_t)pix * p.ys_p + (int64_t)n * p.ys_c;
+        const bool tload = e.t_op >= 0;
+        const bool chan_fast = p.ys_c == 1;
+        if (e.simple && chan_fast) {
+            // channels fastest, N no multiple of eight: a thread keeps its channel, four rows at a time
+            constexpr int RS = 256 / BN;
+            const int col = t % BN, n = n0 + col;
+            if (n >= p.N) return;
+            const float b = e.has_bias ? load_as_f32(e.bias_ptr, e.bias_dtype, n) : 0.0f;
+#pragma unroll 1
+            for (int r0 = t / BN; r0 < 32; r0 += 4 * RS) {
+                float v[4], bias[4], tt[4];
+                int64_t off[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int m = mq + r0 + RS * i;
+                    const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+                    off[i] = (int64_t)img * p.ys_n + (int64_t)(m - img * p.OHW) * p.ys_p + n;
+                    v[i] = sC[(r0 + RS * i) * ldc + col];
+                    bias[i] = b;
+                    tt[i] = tload && m < p.M ? load_as_f32(e.t_ptr, e.t_dtype, off[i]) : 0.0f;
+                }
+                finish<4>(e, v, bias, tt);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (mq + r0 + RS * i < p.M) store_from_f32(p.y, p.y_dtype, off[i], v[i]);
+            }
+            return;
+        }
+        if (!e.simple) {
+            // element by element along the fastest axis of the result
+#pragma unroll 1
+            for (int idx = t; idx < 32 * BN; idx += 256) {
+                const int col = chan_fast ? idx % BN : idx / 32, row = chan_fast ? idx / BN : idx % 32;
+                const int m = mq + row, n = n0 + col;
+                if (m >= p.M || n >= p.N) continue;
+                const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+                const int64_t off = (int64_t)img * p.ys_n + (int64_t)(m - img * p.OHW) * p.ys_p + (int64_t)n * p.ys_c;
                 float val = sC[row * ldc + col];
                 for (int s = 0; s < e.n_ops; ++s) val = epi_step(e, s, val, off, n);
                 store_from_f32(p.y, p.y_dtype, off, val);
             }
+            return;
+        }
+        if (p.ys_p == 1 && (p.OHW & 3) == 0 && (p.ys_c & 3) == 0 && (p.ys_n & 3) == 0 && (((uintptr_t)p.y | (uintptr_t)e.t_ptr) & 15) == 0) {
+            // four pixels (m a multiple of four: never across an image) of one channel per thread; 8 groups of pixels x 32 channels
+            const int row = (t & 7) * 4, m = mq + row;
+            if (m >= p.M) return;                         // M is a multiple of four here
+            const int img = (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+            const int64_t base = (int64_t)img * p.ys_n + (m - img * p.OHW);
+#pragma unroll 1
+            for (int col = t >> 3; col < BN; col += 32) {
+                const int n = n0 + col;
+                if (n >= p.N) break;
+                const int64_t off = base + (int64_t)n * p.ys_c;
+                float v[4], bias[4], tt[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (tload && e.t_dtype == DT_F32) {
+                    const f32x4 f = *(const f32x4 *)((const float *)e.t_ptr + off);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) tt[k] = f[k];
+                } else if (tload) {
+                    const u32x2 h = *(const u32x2 *)((const uint16_t *)e.t_ptr + off);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) tt[k] = __uint_as_float((k & 1) ? h[k >> 1] & 0xffff0000u : h[k >> 1] << 16);
+                }
+                const float b = e.has_bias ? load_as_f32(e.bias_ptr, e.bias_dtype, n) : 0.0f;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) { bias[k] = b; v[k] = sC[(row + k) * ldc + col]; }
+                finish<4>(e, v, bias, tt);
+                if (p.y_dtype == DT_F32) *(f32x4 *)((float *)p.y + off) = f32x4{v[0], v[1], v[2], v[3]};
+                else *(u32x2 *)((uint16_t *)p.y + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+            }
+            return;
+        }
+        const int row = t & 31, m = mq + row;
+        if (m >= p.M) return;
+        const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+        const int64_t base = (int64_t)img * p.ys_n + (int64_t)(m - img * p.OHW) * p.ys_p;
+#pragma unroll 1
+        for (int c0 = t >> 5; c0 < BN; c0 += 32) {
+            if (n0 + c0 >= p.N) break;
+            float v[4], bias[4], tt[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = n0 + c0 + 8 * i;
+                tt[i] = bias[i] = 0.0f;
+                v[i] = sC[row * ldc + c0 + 8 * i];
+                if (n >= p.N) continue;
+                if (e.has_bias) bias[i] = load_as_f32(e.bias_ptr, e.bias_dtype, n);
+                if (tload) tt[i] = load_as_f32(e.t_ptr, e.t_dtype, base + (int64_t)n * p.ys_c);
+            }
+            finish<4>(e, v, bias, tt);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (n0 + c0 + 8 * i < p.N) store_from_f32(p.y, p.y_dtype, base + (int64_t)(n0 + c0 + 8 * i) * p.ys_c, v[i]);
         }
     }
 

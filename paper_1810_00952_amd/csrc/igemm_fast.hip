@@ -225,6 +225,9 @@ __global__ __launch_bounds__(256) void igemm_fast_kernel(const IgemmParams p)
 
     // ---- stage fp32 accumulators in LDS: sC[row][col], row stride LDC floats
     float *sC = (float *)smem;
+    const bool rowmajor = (p.ys_n == (int64_t)p.OHW * p.ys_p) && p.ys_c == 1;
+    const bool vec_ok = !GATES && rowmajor && (p.N & 7) == 0 && (p.ys_p & 7) == 0;
+    const int ldc = GATES || vec_ok || p.splits > 1 ? LDC : BN + 1;      // 16-byte reads along a row, or single reads down a column
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(256) void igemm_fast_kernel(const IgemmParams p)
             for (int r = 0; r < 16; ++r) {
                 int row = wm * WTM + i * 32 + 8 * (r >> 2) + 4 * fhalf + (r & 3);
                 int col = wn * WTN + j * 32 + frow;
-                sC[row * LDC + col] = acc[i][j][r];
+                sC[row * ldc + col] = acc[i][j][r];
             }
     __syncthreads();
 
@@ -250,8 +253,6 @@ __global__ __launch_bounds__(256) void igemm_fast_kernel(const IgemmParams p)
     // ---- 32-row passes over the staged tile; the residual rows of the next pass are in flight
     // while this pass is stored
     using TE = TileEpilogue<BN>;
-    const bool rowmajor = (p.ys_n == (int64_t)p.OHW * p.ys_p) && p.ys_c == 1;
-    const bool vec_ok = !GATES && rowmajor && (p.N & 7) == 0 && (p.ys_p & 7) == 0;
     const bool pre = vec_ok && p.epi.simple;
     float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     OperandRegs<TE::NV> cur = {}, nxt = {};
@@ -259,14 +260,14 @@ __global__ __launch_bounds__(256) void igemm_fast_kernel(const IgemmParams p)
         TE::load_bias(p, t, n0, bias8);
         TE::prefetch(p, t, m0, n0, cur);
     }
-#pragma unroll
+#pragma unroll 1
     for (int q = 0; q < BM / 32; ++q) {
         if (pre && q + 1 < BM / 32) TE::prefetch(p, t, m0 + (q + 1) * 32, n0, nxt);
         const int mq = m0 + q * 32;
-        const float *sq = sC + q * 32 * LDC;
+        const float *sq = sC + q * 32 * ldc;
         if (GATES) TE::gates_pass(p, sq, LDC, t, mq, bn);
         else if (vec_ok) TE::store_pass(p, sq, LDC, t, mq, n0, bias8, cur);
-        else TE::store_pass_scalar(p, sq, LDC, t, mq, n0);
+        else TE::store_pass_scalar(p, sq, ldc, t, mq, n0);
         cur = nxt;
     }
 }

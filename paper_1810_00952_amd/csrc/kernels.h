@@ -82,6 +82,7 @@ struct IgemmParams {
     uint32_t seg_stride;                   // bytes between the two 64-byte halves of an A row's K tile (64: contiguous)
     int64_t ts_h, ts_w;                    // element strides of one filter-tap step (xs_h, xs_w unless the taps are regrouped)
     uint32_t div_ohw_mul, div_ohw_sh, div_ow_mul, div_ow_sh;   // m / OHW and pix / OW by multiply-high (make_fast_div)
+    uint32_t div_c_mul, div_c_sh, div_kw_mul, div_kw_sh;       // k / C and tap / KW (direct-load variant, K tiles that span taps)
     uint32_t tap_rep;                      // bit kh*KW set for every kh < KH (KH*KW <= 32)
     // K split over `splits` workgroups per tile (direct-load variant only; 0 or 1: no split): workgroup (tile, z)
     // multiplies K tiles [z*per, (z+1)*per) and writes its fp32 sums to partial[z][M][N]; a second kernel adds the
@@ -103,6 +104,7 @@ struct IgemmLaunch {
     int32_t avec;       // 1: A rows are 16-byte-vector loadable (channel-contiguous, aligned)
     int32_t gates;      // 1: LSTM gate epilogue (tile must be TILE_64x64)
     int32_t dma;        // 1: K tiles go global -> LDS directly (needs avec, C and K multiples of the K tile, >= 2 tiles)
+    int32_t taps;       // 1 (with dma): K tiles span filter taps: C a multiple of the 16-byte vector only, any tap count, any K
     int32_t lp;         // 1: pixel-on-lane variant with the register epilogue (bf16, [bias] [+residual] [relu])
     int32_t ws;         // 1 (with lp): weights-stationary persistent variant (N <= 64, K <= 576)
     int32_t c64;        // 1 (with lp): 3x3 / stride 1 / pad 1, 64 -> 64 channels, image rows of at most 63 pixels (conv3x3_c64.hip)
@@ -276,6 +278,7 @@ hipError_t launch_stem_pad(const void *src, void *dst, int32_t N, int32_t C, int
 struct GatherPack {
     int32_t dtype, R, Kp, T, Cq, TW;
     int64_t base, s_row, s_c, s_ti, s_tj;
+    int32_t Creal;                      // > 0: of the Cq indices of a tap only the first Creal exist, the rest are zeros
 };
 hipError_t launch_pack_gather(const void *src, void *dst, const GatherPack &g, hipStream_t s);
 hipError_t launch_pack_weight_stem(const void *src, void *dst, int32_t O, int32_t C, int32_t KH, int32_t KW, int32_t Kp, hipStream_t s);

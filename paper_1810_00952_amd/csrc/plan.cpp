@@ -210,6 +210,27 @@ struct Planner {
         int xH = 0, xW = 0;
     };
 
+    // Whether a contraction whose channels (features) are no multiple of the 16-byte vector gets zero-padded rows, written by a
+    // step of its own, for the vector-load kernels.  The element gather it takes otherwise needs no extra launch and is level
+    // at a few K tiles on few workgroups (f32 dense 2 x 90 -> 8: 9 us either way; 10 x 1446 -> 128: 87 us against 16).
+    bool pad_k(int x, int wv, int C, int KV, int64_t M, int64_t N, int64_t K, bool concat, int64_t bytes_per_channel) const
+    {
+        if (C % KV == 0 || concat || plan.opts.no_dma || g.values[x].role == ROLE_PARAM || consumers[wv].size() != 1) return false;
+        const int64_t nk = (K + 8 * KV - 1) / (8 * KV), tiles = ((M + 63) / 64) * ((N + 63) / 64), ld = round_up(C, KV), lim = (int64_t)1 << 30;
+        return (nk >= 4 || tiles * nk >= 512) && bytes_per_channel * ld < lim && N * (K / C) * ld * 4 < lim && T(x).dims[0] <= 65535;
+    }
+    // the weight packing and the contraction's sizes with C filled up to ld
+    void pad_gather(PackSpec &pack, IgemmParams &p, const AnchorView *ov, int ld, int KV) const
+    {
+        const int T_ = p.KH * p.KW;
+        pack.gather = 1;
+        if (ov) pack.gp = ov->gp;
+        else { pack.gp.R = p.N; pack.gp.T = T_; pack.gp.TW = p.KW; pack.gp.s_row = (int64_t)p.C * T_; pack.gp.s_c = T_; pack.gp.s_ti = p.KW; pack.gp.s_tj = 1; }
+        pack.gp.dtype = p.in_dtype;
+        pack.gp.Cq = ld; pack.gp.Creal = p.C;
+        p.C = ld; p.K = p.K1 = ld * T_; p.Kp = (int)round_up(p.K, KV);
+    }
+
     rl_status plan_anchor(int gi, const std::vector<int> &ops, const AnchorView *ov = nullptr)
     {
         std::set<int> gset(ops.begin(), ops.end());
@@ -246,7 +267,7 @@ struct Planner {
         IgemmParams p{};
         IgemmLaunch il{};
         PackSpec pack;
-        bool need_pack = false;
+        bool need_pack = false, padded = false;       // padded: contraction channels (features) filled up with zeros to whole vectors
         int xbuf = -1, x2buf = -1;
         double flops = 0.0;
         size_t x_extent = 0;                 // bytes of the tensor the kernel reads as x
@@ -291,7 +312,6 @@ struct Planner {
                 out_layout = L_NHWC;
             if (out_layout == L_NHWC) { p.ys_n = (int64_t)p.OHW * p.N; p.ys_p = p.N; p.ys_c = 1; }
             else { p.ys_n = (int64_t)p.N * p.OHW; p.ys_p = 1; p.ys_c = p.OHW; }
-            flops = 2.0 * p.M * (double)p.N * p.K;
             // Few-channel stem (e.g. 3 -> 64, 7x7, stride 2): gathering single elements starves the MFMAs.  Copy the
             // input into a zero-padded 4-channel channel-last frame instead; a K tile then holds two filter rows of
             // 8 pixels x 4 channels and travels by direct loads like any other (see launch_stem_pad).
@@ -320,6 +340,18 @@ struct Planner {
                 il.avec = 1;
                 need_pack = true;
                 x_extent = frame;
+            } else if (pad_k(x, wv, p.C, KV, p.M, p.N, p.K, x2 >= 0, xt.dims[0] * (int64_t)p.H * p.W * dtype_size(in_dt)) && !xov) {
+                // a channel count that is no multiple of the vector: rows padded with zeros, weights likewise
+                int ld;
+                st = need_rows(gi, x, xbuf, ld);
+                if (st != RL_OK) return st;
+                pad_gather(pack, p, ov, ld, KV);
+                p.xs_n = (int64_t)p.H * p.W * ld; p.xs_h = (int64_t)p.W * ld; p.xs_w = ld; p.xs_c = 1;
+                p.ts_h = p.xs_h; p.ts_w = p.xs_w; p.seg_stride = 64;
+                il.avec = 1;
+                need_pack = padded = true;
+                pack.dtype = in_dt; pack.O = p.N; pack.C = p.C; pack.T = p.KH * p.KW; pack.Kp = p.Kp; pack.perm_block = -3;
+                x_extent = (size_t)xt.dims[0] * p.H * p.W * ld * dtype_size(in_dt);
             } else {
                 il.avec = (p.C % KV == 0);
                 int xl;
@@ -344,15 +376,25 @@ struct Planner {
             p.K1 = x2 >= 0 ? (int)T(x).dims[1] : p.K;
             const int K2 = p.K - p.K1;
             il.avec = (p.K1 % KV == 0) && (K2 % KV == 0);
-            st = need(x, L_NATIVE, xbuf);
+            // a layer of at most 64 outputs behind another layer keeps its own rows: it may ride on that layer's adding launch
+            const bool may_chain = p.N <= REDUCE_DENSE_MAX_N2 && g.values[x].producer >= 0;
+            if (!il.avec && !gates && !may_chain && pad_k(x, wv, p.K, KV, p.M, p.N, p.K, x2 >= 0, (int64_t)p.M * dtype_size(in_dt))) {
+                int ld;
+                flops = 2.0 * p.M * (double)p.N * p.K;
+                st = need_rows(gi, x, xbuf, ld);
+                if (st != RL_OK) return st;
+                pad_gather(pack, p, ov, ld, KV);
+                il.avec = 1;
+                padded = true;
+            } else st = need(x, L_NATIVE, xbuf);
             if (st != RL_OK) return st;
             if (x2 >= 0) { st = need(x2, L_NATIVE, x2buf); if (st != RL_OK) return st; }
             p.xs_n = p.K1; p.xs_c = 1; p.xs_h = 0; p.xs_w = 0; p.x2s_n = K2;
             p.ts_h = 0; p.ts_w = 0; p.seg_stride = 64;
-            flops = 2.0 * p.M * (double)p.N * p.K;
-            x_extent = bytes_of(x);
-            need_pack = (p.K % KV != 0) || gates || ov;
-            pack.dtype = in_dt; pack.O = p.N; pack.C = p.K; pack.T = 1; pack.Kp = p.Kp; pack.perm_block = gates ? 64 : 0;
+            if (!padded) flops = 2.0 * p.M * (double)p.N * p.K;
+            x_extent = padded ? (size_t)p.M * p.K * dtype_size(in_dt) : bytes_of(x);
+            need_pack = (p.K % KV != 0) || gates || ov || padded;
+            pack.dtype = in_dt; pack.O = p.N; pack.C = p.K; pack.T = 1; pack.Kp = p.Kp; pack.perm_block = padded ? -3 : gates ? 64 : 0;
             p.ys_n = p.N; p.ys_p = p.N; p.ys_c = 1;
         }
         // 3x3 bf16 weights from 64 to 64 channels carry, behind the matrix, a second copy in the fragment order of the
@@ -390,6 +432,12 @@ struct Planner {
                         bytes_of(vout) < lim;
             il.lp = stem || (il.avec && in_dt == RL_BF16 && p.C % bke == 0 && p.K % bke == 0 && p.KH * p.KW <= 32 && x2 < 0 && !gates &&
                              x_extent + halo < lim && epi_any && y_ok && !plan.opts.no_lp);
+            // everything else whose chunks are whole: K tiles that span taps (or a dense of less than two)
+            if (!il.dma && !il.lp && il.avec && !stem && !gates && x2 < 0 && x_extent + halo < lim && pack.bytes < lim && !plan.opts.no_dma) {
+                il.dma = il.taps = 1;
+                make_fast_div((uint32_t)p.C, p.div_c_mul, p.div_c_sh);
+                make_fast_div((uint32_t)p.KW, p.div_kw_mul, p.div_kw_sh);
+            }
             il.anyact = il.lp && !stem && !relu_form;
             // weights-stationary persistent variant: pays off when the weights leave LDS for a deep ring (K <= 320);
             // the plan option ws_all also takes it up to K = 576, where its shallower ring is latency-bound
@@ -407,7 +455,8 @@ struct Planner {
             if (p.KH * p.KW <= 32)
                 for (int kh = 0; kh < p.KH; ++kh) p.tap_rep |= 1u << (kh * p.KW);
         }
-        if (ov) { pack.gather = 1; pack.gp = ov->gp; pack.gp.Kp = pack.Kp; pack.perm_block = -3; }
+        if (ov && !padded) { pack.gather = 1; pack.gp = ov->gp; pack.perm_block = -3; }
+        if (pack.gather) pack.gp.Kp = pack.Kp;
         if (need_pack) {
             auto it = plan.packs.find(wv);
             if (it != plan.packs.end() && (ov || it->second.perm_block != pack.perm_block || it->second.Kp != pack.Kp))
@@ -428,6 +477,16 @@ struct Planner {
             p.h_dtype = T(g.ops[ops.back()].out[1]).dtype;
         } else if (!il.avec) {
             il.tile = TILE_64x64;
+        } else if (il.taps) {
+            // by the padding of the last tiles and how the grid fills 256 CUs, in cycles per K tile: `alone` where a CU holds one
+            // workgroup, `share` per workgroup where it holds several
+            static const int tb[3][2] = {{128, 128}, {128, 64}, {64, 64}};
+            static const double alone[2][3] = {{4400, 2300, 1450}, {1400, 900, 680}}, share[2][3] = {{4400, 2100, 1100}, {1200, 600, 390}};
+            double best = 1e30;
+            for (int i = 0; i < 3; ++i) {
+                const double c = std::max(alone[in_dt == RL_BF16][i], share[in_dt == RL_BF16][i] * (double)((nblk(tb[i][0], tb[i][1]) + 255) / 256));
+                if (c < best) { best = c; il.tile = i; }
+            }
         } else if (il.lp && p.N > 64 && nblk(256, 128) >= 190 && !plan.opts.no_lp_256) {
             il.tile = TILE_256x128;        // a quarter fewer operand bytes per MFMA than 128x128
         } else if (p.N > 64 && nblk(128, 128) >= 192) {
@@ -491,7 +550,7 @@ struct Planner {
         }
         static const char *tile_names[] = {"128x128", "128x64", "64x64", "256x128"};
         std::string kname = (ov ? std::string("igemm_") + op_name(an.kind) + "_" : std::string(akind == RL_OP_CONV2D ? "igemm_conv2d_" : "igemm_dense_")) + (in_dt == RL_BF16 ? "bf16_" : "f32_") +
-                            (il.c64 ? "3x3_c64" : il.ws ? "128x64_ws" : tile_names[il.tile]) + (il.c64 || il.ws ? "" : il.run ? "_run" : il.lp ? "_lp" : il.avec ? (il.dma ? "_dma" : "") : "_gather") + (gates ? "_gates" : "") +
+                            (il.c64 ? "3x3_c64" : il.ws ? "128x64_ws" : tile_names[il.tile]) + (il.c64 || il.ws ? "" : il.run ? "_run" : il.lp ? "_lp" : il.avec ? (il.dma ? (il.taps ? "_dma_taps" : "_dma") : "") : "_gather") + (gates ? "_gates" : "") +
                             (il.splits > 1 ? "_splitk" : "");
         Step &s = add_step(S_IGEMM, std::string(op_name(an.kind)) + "#" + std::to_string(ops[ai]), kname);
         s.group = gi;

@@ -68,3 +68,43 @@ def test_weight_gradient_over_rows_beside_the_input_gradient():
         first, _ = run_hip(g, data)
         again, _ = run_hip(g, data)
         np.testing.assert_array_equal(first[dw], again[dw])           # slices are added in a fixed order
+
+
+# ---- contractions whose K tiles span filter taps, padded channels, results in Shape order (igemm_dma.hip) ------------------
+TAPS_CASES = [
+    # batch cin cout h  w  k s p residual relu acts tail
+    (17, 96, 136, 29, 29, 3, 1, 1, True, True, (), False),       # tiles across taps, ragged N, images of 841 pixels (one-pixel stores)
+    (3, 8, 24, 20, 22, 3, 1, 1, True, False, (), False),         # eight taps per bf16 K tile; four-pixel stores
+    (2, 24, 40, 17, 16, 7, 2, 3, False, True, (), False),        # 49 taps
+    (40, 5, 12, 33, 31, 3, 1, 1, False, True, (), False),         # channels padded to whole vectors
+    (60, 1, 20, 28, 28, 5, 1, 0, False, False, ("tanh",), False), # one channel; tanh in the pixel-order store
+    (60, 1, 20, 28, 28, 5, 1, 0, False, False, ("tanh",), True),  # the same kept channel-last: 20 channels per pixel
+    (2, 37, 50, 20, 20, 5, 1, 2, True, True, (), True),          # padded channels, channel-last result that is no multiple of eight
+    (12, 3, 64, 64, 62, 7, 2, 3, False, True, (), False),         # three channels, even tile
+    (70, 3, 18, 57, 57, 1, 2, 0, False, False, (), False),       # one tap, K of three channels, many tiles
+    (2, 104, 264, 28, 28, 3, 1, 1, True, True, ("sigmoid", "neg"), False),
+    (64, 104, 192, 28, 28, 3, 1, 1, False, True, (), False),     # 128-wide tiles
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", TAPS_CASES, ids=[f"taps{i}" for i in range(len(TAPS_CASES))])
+def test_convolution_with_ragged_channels(dtype, case):
+    b, ci, co, h, w, k, s, p, res, relu, acts, tail = case
+    spec, data = W.conv_group(b, ci, co, h, w, k, s, p, dtype, residual=res, relu=relu, acts=acts, tail=tail)
+    assert not any("_gather" in x for x in steps_of(spec) if x.startswith("igemm")), steps_of(spec)
+    check(spec, data, dtype, f"taps {case} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dims", [(10, 1446, 128, 45), (150, 867, 20, 100), (300, 235, 57, 33), (1, 1627, 450, 5), (513, 1001, 391, 77), (40, 112, 130, 70)])
+def test_dense_with_ragged_features(dtype, dims):
+    spec, data = W.mlp(*dims, dtype=dtype)
+    check(spec, data, dtype, f"ragged mlp {dims} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_input_gradient_with_ragged_channels(dtype):
+    for kind, dims, stride, pad in (("dense_grad_x", (167, 391, 720), 1, 0), ("conv2d_grad_x", (3, 93, 19, 19, 45, 5), 1, 2), ("conv2d_grad_x", (6, 40, 26, 26, 30, 3), 1, 1)):
+        spec, data = W.grad_case(kind, dims, dtype, stride, pad)
+        check(spec, data, dtype, f"ragged {kind} {dims} {dtype}")
