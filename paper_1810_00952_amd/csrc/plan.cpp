@@ -210,6 +210,15 @@ struct Planner {
         int xH = 0, xW = 0;
     };
 
+    // Shader cycles per K tile of the direct-load kernel on the fullest of 256 CUs: `alone` where a CU holds one workgroup, `share`
+    // per workgroup where it holds several (measured; f32 is the MFMA's own 1024 / 2048 / 4096 and a few percent)
+    static double tile_cost(int tile, int dtype, int64_t workgroups)
+    {
+        static const double alone[2][3] = {{4400, 2300, 1450}, {1400, 900, 680}}, share[2][3] = {{4400, 2100, 1100}, {1200, 600, 390}};
+        const int d = dtype == RL_BF16;
+        return std::max(alone[d][tile], share[d][tile] * (double)((workgroups + 255) / 256));
+    }
+
     // Whether a contraction whose channels (features) are no multiple of the 16-byte vector gets zero-padded rows, written by a
     // step of its own, for the vector-load kernels.  The element gather it takes otherwise needs no extra launch and is level
     // at a few K tiles on few workgroups (f32 dense 2 x 90 -> 8: 9 us either way; 10 x 1446 -> 128: 87 us against 16).
@@ -477,14 +486,12 @@ struct Planner {
             p.h_dtype = T(g.ops[ops.back()].out[1]).dtype;
         } else if (!il.avec) {
             il.tile = TILE_64x64;
-        } else if (il.taps) {
-            // by the padding of the last tiles and how the grid fills 256 CUs, in cycles per K tile: `alone` where a CU holds one
-            // workgroup, `share` per workgroup where it holds several
-            static const int tb[3][2] = {{128, 128}, {128, 64}, {64, 64}};
-            static const double alone[2][3] = {{4400, 2300, 1450}, {1400, 900, 680}}, share[2][3] = {{4400, 2100, 1100}, {1200, 600, 390}};
+        } else if (il.taps || (il.dma && in_dt == RL_F32)) {
+            // by the padding of the last tiles and how the grid fills 256 CUs (tile_cost); the f32 MFMA takes so long that small
+            // tiles cost nothing where they fill the chip better (16x128x28x28 -> 128 3x3: 128x64 67.8 us, 64x64 47.7)
             double best = 1e30;
-            for (int i = 0; i < 3; ++i) {
-                const double c = std::max(alone[in_dt == RL_BF16][i], share[in_dt == RL_BF16][i] * (double)((nblk(tb[i][0], tb[i][1]) + 255) / 256));
+            for (int i = TILE_128x128; i <= TILE_64x64; ++i) {
+                const double c = tile_cost(i, in_dt, nblk(i == TILE_64x64 ? 64 : 128, i == TILE_128x128 ? 128 : 64));
                 if (c < best) { best = c; il.tile = i; }
             }
         } else if (il.lp && p.N > 64 && nblk(256, 128) >= 190 && !plan.opts.no_lp_256) {
@@ -540,7 +547,16 @@ struct Planner {
             const int nk = (p.K + 8 * KV - 1) / (8 * KV);
             // from 8 K tiles on (fewer: the adding launch costs more than the serial K loop); slices of at least two K tiles
             int want = (int)std::min<int64_t>(std::min<int64_t>(16, 256 / std::max<int64_t>(tiles, 1)), nk / 2);
-            if (tiles <= 64 && nk >= 8 && want >= 2 && (int64_t)want * p.M * p.N * 4 < (int64_t)1 << 28) {
+            if (tiles > 64 && tiles < 512 && nk >= 8) {
+                // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
+                // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22)
+                double best = 1e30;
+                for (int sp = 1; sp <= std::min(16, nk / 2); ++sp) {
+                    const double c = (double)((nk + sp - 1) / sp) * tile_cost(il.tile, in_dt, tiles * sp) + (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
+                    if (c < best * 0.95) { best = c; want = sp; }
+                }
+            }
+            if (tiles < 512 && nk >= 8 && want >= 2 && (int64_t)want * p.M * p.N * 4 < (int64_t)1 << 28) {
                 const int per = (nk + want - 1) / want;
                 il.splits = (nk + per - 1) / per;
                 p.splits = il.splits; p.split_tiles = per;

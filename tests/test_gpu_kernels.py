@@ -108,3 +108,11 @@ def test_input_gradient_with_ragged_channels(dtype):
     for kind, dims, stride, pad in (("dense_grad_x", (167, 391, 720), 1, 0), ("conv2d_grad_x", (3, 93, 19, 19, 45, 5), 1, 2), ("conv2d_grad_x", (6, 40, 26, 26, 30, 3), 1, 1)):
         spec, data = W.grad_case(kind, dims, dtype, stride, pad)
         check(spec, data, dtype, f"ragged {kind} {dims} {dtype}")
+
+
+# ---- f32 tiles and K slices chosen by how the grid fills the chip ----------------------------------------------------------
+@pytest.mark.parametrize("case", [(8, 256, 256, 14, 14, 3, 1, 1), (4, 64, 128, 28, 28, 3, 2, 1), (9, 72, 200, 14, 14, 3, 1, 1)])
+def test_f32_half_filled_grids_split_k(case):
+    spec, data = W.conv_group(*case, dtype="f32", residual=True)
+    assert any(x.endswith("_splitk") for x in steps_of(spec)), steps_of(spec)
+    check(spec, data, "f32", f"half-filled {case}")
