@@ -465,6 +465,7 @@ rl_status rl_plan_run_recurrent(const rl_plan *cell, int32_t steps, const rl_rec
                     if (g.N % 8 == 0 && (b256 >= 190 || b128 >= 192) && !p.opts.no_lp) {
                         l.lp = 1;
                         l.tile = b256 >= 190 ? TILE_256x128 : TILE_128x128;
+                        l.big = l.tile == TILE_256x128 && igemm_big_better(g.M, g.N, g.K);
                         g.seg_stride = 64; g.ts_h = 0; g.ts_w = 0; g.tap_rep = 1;
                     }
                     hipError_t er = launch_igemm(g, l, (hipStream_t)stream);

@@ -391,6 +391,7 @@ hipError_t launch_igemm(const IgemmParams &p, const IgemmLaunch &l, hipStream_t 
     if (l.lp && l.c64) return launch_conv3x3_c64(p, s);
     if (l.lp && l.run) return launch_conv3x3_run(p, l, s);
     if (l.lp && l.ws) return launch_igemm_ws(p, s);
+    if (l.lp && l.big) return launch_igemm_big(p, s);
     if (l.lp) return launch_igemm_lp(p, l, s);
     if (l.avec && l.dma) return launch_igemm_dma(p, l, s);
     if (l.avec) return launch_igemm_fast(p, l, s);

@@ -518,7 +518,7 @@ static int lp_variant(const IgemmParams &p, const IgemmLaunch &l)
 bool igemm_lp_can_pair(const IgemmParams &a, const IgemmLaunch &la, const IgemmParams &b, const IgemmLaunch &lb)
 {
     return la.lp && lb.lp && !la.ws && !lb.ws && !la.c64 && !lb.c64 && !la.run && !lb.run && !la.gates && !lb.gates && !a.x2 && !b.x2 &&
-           !la.anyact && !lb.anyact &&
+           !la.anyact && !lb.anyact && !la.big && !lb.big &&
            a.in_dtype == DT_BF16 && b.in_dtype == DT_BF16 && a.y_dtype == DT_BF16 && b.y_dtype == DT_BF16 && lp_variant(a, la) == lp_variant(b, lb);
 }
 

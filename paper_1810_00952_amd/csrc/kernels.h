@@ -112,6 +112,7 @@ struct IgemmLaunch {
                         // 2: its 128x64 form with K split over the waves (C a multiple of 128)
     int32_t splits;     // > 1 (with dma, no lp, no gates): K split over that many workgroups per tile (IgemmParams::splits)
     int32_t s2pair;     // 1 (first step of a pair): the pair runs as one stride-2 contraction with two accumulator sets (conv3x3s2.hip)
+    int32_t big;        // 1 (with lp, tile 256x128): 256x256 tiles of a one-tap contraction (igemm_big.hip)
     int32_t anyact;     // 1 (with lp, no ws / c64 / run / pair): operand-free steps other than one ReLU behind bias and residual
 };
 hipError_t launch_igemm(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
@@ -142,6 +143,8 @@ hipError_t launch_igemm_lp_pair(const IgemmParams &a, const IgemmLaunch &la, con
 // accumulator sets (conv3x3s2.hip); the planner asks conv3x3s2_pair_ok before any pointer is bound
 bool conv3x3s2_pair_ok(const IgemmParams &a, const IgemmLaunch &la, const IgemmParams &b, const IgemmLaunch &lb);
 hipError_t launch_conv3x3s2_pair(const IgemmParams &a, const IgemmLaunch &la, const IgemmParams &b, const IgemmLaunch &lb, hipStream_t s);
+bool igemm_big_better(int64_t M, int64_t N, int64_t K);     // 256x256 tiles pay off (igemm_big.hip)
+hipError_t launch_igemm_big(const IgemmParams &p, hipStream_t s);
 hipError_t launch_conv3x3_c64(const IgemmParams &p, hipStream_t s);
 hipError_t launch_conv3x3_run(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
 

@@ -504,6 +504,10 @@ struct Planner {
             il.tile = TILE_64x64;
         }
 
+        // a dense, or a 1x1 convolution at stride 1, large enough for 256x256 tiles
+        il.big = il.lp && !il.anyact && !il.ws && !stem && il.tile == TILE_256x128 && p.KH * p.KW == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0 &&
+                 igemm_big_better(p.M, p.N, p.K);
+
         // 3x3 / stride 1 / pad 1 on short image rows with whole 64-channel slices: the nine taps of a slice are read
         // from one copy of the input rows (needs one of the larger tiles)
         il.run = il.lp && !il.anyact && !il.c64 && !il.ws && !stem && akind == RL_OP_CONV2D && p.KH == 3 && p.KW == 3 && p.sh == 1 && p.sw == 1 && p.ph == 1 &&
@@ -566,7 +570,7 @@ struct Planner {
         }
         static const char *tile_names[] = {"128x128", "128x64", "64x64", "256x128"};
         std::string kname = (ov ? std::string("igemm_") + op_name(an.kind) + "_" : std::string(akind == RL_OP_CONV2D ? "igemm_conv2d_" : "igemm_dense_")) + (in_dt == RL_BF16 ? "bf16_" : "f32_") +
-                            (il.c64 ? "3x3_c64" : il.ws ? "128x64_ws" : tile_names[il.tile]) + (il.c64 || il.ws ? "" : il.run ? "_run" : il.lp ? "_lp" : il.avec ? (il.dma ? (il.taps ? "_dma_taps" : "_dma") : "") : "_gather") + (gates ? "_gates" : "") +
+                            (il.c64 ? "3x3_c64" : il.ws ? "128x64_ws" : il.big ? "256x256" : tile_names[il.tile]) + (il.c64 || il.ws ? "" : il.run ? "_run" : il.lp ? "_lp" : il.avec ? (il.dma ? (il.taps ? "_dma_taps" : "_dma") : "") : "_gather") + (gates ? "_gates" : "") +
                             (il.splits > 1 ? "_splitk" : "");
         Step &s = add_step(S_IGEMM, std::string(op_name(an.kind)) + "#" + std::to_string(ops[ai]), kname);
         s.group = gi;

@@ -116,3 +116,24 @@ def test_f32_half_filled_grids_split_k(case):
     spec, data = W.conv_group(*case, dtype="f32", residual=True)
     assert any(x.endswith("_splitk") for x in steps_of(spec)), steps_of(spec)
     check(spec, data, "f32", f"half-filled {case}")
+
+
+# ---- 256 x 256 tiles (igemm_big.hip) -----------------------------------------------------------------------------------------
+@pytest.mark.parametrize("m,n,k,res", [(4096, 4096, 64, False), (3841, 4000, 192, False), (4100, 3336, 128, True)])
+def test_dense_at_matrix_multiplication_scale(m, n, k, res):
+    # ragged last tiles both ways, the shortest K and one that ends between two rounds of the stages, with and without a residual
+    import numpy as np
+    rng = np.random.default_rng(3)
+    g = W.GraphSpec("dense_big")
+    x = g.input("x", "bf16", (m, k)); w = g.param("w", "bf16", (n, k)); b = g.param("b", "f32", (n,))
+    t = ("bf16", (m, n))
+    data = {"x": W.as_dtype(rng.standard_normal((m, k)), "bf16"), "w": W.as_dtype(rng.standard_normal((n, k)) / k ** 0.5, "bf16"), "b": W.as_dtype(rng.uniform(-1, 1, n), "f32")}
+    o0, (y,) = g.op("dense", [x, w], [t]); ops = [o0]
+    o1, (y,) = g.op("bias_add", [y, b], [t], axis=1); ops.append(o1)
+    if res:
+        r = g.input("r", "bf16", (m, n)); data["r"] = W.as_dtype(rng.standard_normal((m, n)), "bf16")
+        o2, (y,) = g.op("add", [y, r], [t]); ops.append(o2)
+    o3, (y,) = g.op("relu", [y], [t]); ops.append(o3)
+    g.group(ops); g.output(y)
+    assert any("256x256" in s for s in steps_of(g)), steps_of(g)
+    check(g, data, "bf16", f"dense {m}x{n}x{k}")
