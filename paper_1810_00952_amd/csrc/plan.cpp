@@ -441,6 +441,11 @@ struct Planner {
                         bytes_of(vout) < lim;
             il.lp = stem || (il.avec && in_dt == RL_BF16 && p.C % bke == 0 && p.K % bke == 0 && p.KH * p.KW <= 32 && x2 < 0 && !gates &&
                              x_extent + halo < lim && epi_any && y_ok && !plan.opts.no_lp);
+            // A very long K on few tiles (late layers at small batches): the pixel-on-lane kernels do not cut K, the direct-load
+            // kernel does.  From 64 K tiles on, on 2 to 64 tiles of 64x64, that is worth its adding launch (98 x 512 x 4608: 24 us
+            // against 15.5; 36 K tiles are level, 15 us either way).
+            const int64_t lp_tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
+            if (il.lp && !stem && il.dma && p.K / bke >= 64 && lp_tiles >= 2 && lp_tiles <= 64 && !plan.opts.no_splitk) il.lp = 0;
             // everything else whose chunks are whole: K tiles that span taps (or a dense of less than two)
             if (!il.dma && !il.lp && il.avec && !stem && !gates && x2 < 0 && x_extent + halo < lim && pack.bytes < lim && !plan.opts.no_dma) {
                 il.dma = il.taps = 1;

@@ -137,3 +137,12 @@ def test_dense_at_matrix_multiplication_scale(m, n, k, res):
     g.group(ops); g.output(y)
     assert any("256x256" in s for s in steps_of(g)), steps_of(g)
     check(g, data, "bf16", f"dense {m}x{n}x{k}")
+
+
+# ---- bf16, a very long K on few tiles: cut along K by the direct-load kernel -------------------------------------------------
+@pytest.mark.parametrize("case", [(2, 512, 512, 7, 7, 3, 1, 1, True, True), (1, 512, 136, 9, 8, 3, 2, 1, True, False)])
+def test_bf16_long_k_on_few_tiles(case):
+    b, ci, co, h, w, k, s, p, res, tail = case
+    spec, data = W.conv_group(b, ci, co, h, w, k, s, p, "bf16", residual=res, tail=tail)
+    assert any(x.endswith("_dma_splitk") for x in steps_of(spec)), steps_of(spec)
+    check(spec, data, "bf16", f"long K {case}")
