@@ -209,6 +209,9 @@ typedef struct rl_plan_opts {
     int32_t no_dense_chain; /* a split dense contraction followed by a small dense layer on its result alone: keep them two
                                steps (contraction, adding launch, small layer) instead of letting the adding launch run
                                the small layer too */
+    int32_t no_seq;         /* rl_plan_run_recurrent, hoisted form: 1: one launch per step, never one for the whole sequence; 2: the
+                               one-launch form with every workgroup on its own (what it falls back to where its workgroups are
+                               not all resident at once) */
 } rl_plan_opts;
 
 /* rl_plan_create re-checks the whole graph (Type-Call on every call, group legality, outputs reachable), picks

@@ -470,6 +470,24 @@ rl_status rl_plan_run_recurrent(const rl_plan *cell, int32_t steps, const rl_rec
                     }
                     hipError_t er = launch_igemm(g, l, (hipStream_t)stream);
                     if (er != hipSuccess) return fail(err, RL_ERR_HIP, std::string("launch of the hoisted input projection failed: ") + hipGetErrorString(er));
+                    // the recurrent part of the chunk as one launch that keeps the weights in registers; not while the stream is being
+                    // captured (a graph's replays need not run cooperative launches one at a time)
+                    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+                    if (p.opts.no_seq != 1 && lstm_seq_ok(B, H, tc) && (!bias || bias_dt == DT_F32) && ptrs[hs->slot[SL_CIN]] == ptrs[hs->slot[SL_COUT]] &&
+                        hipStreamIsCapturing((hipStream_t)stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+                        LstmSeqParams q{};
+                        q.h0 = t0 == 0 ? io->h0_dev : (const void *)((const char *)io->h_seq_dev + (size_t)(t0 - 1) * io->h_step_bytes);
+                        q.h_seq = (char *)io->h_seq_dev + (size_t)t0 * io->h_step_bytes; q.h_step_bytes = io->h_step_bytes;
+                        q.w = g.w; q.w_bytes = (uint32_t)((uint64_t)g0.N * g0.Kp * 2);
+                        q.zx = zx; q.bias = (const float *)bias; q.c = (float *)ptrs[hs->slot[SL_COUT]];
+                        q.ctl = (uint32_t *)(zx + (size_t)(tc - 1) * B * g.N);
+                        q.save = (uint32_t *)((char *)q.h_seq + (size_t)(tc - 1) * io->h_step_bytes);
+                        q.B = (int32_t)B; q.H = (int32_t)H; q.Kp = g0.Kp; q.k_off = (int32_t)I; q.T = (int32_t)tc;
+                        q.spins = p.opts.no_seq == 2 ? 0 : 20000;
+                        er = launch_lstm_seq(q, (hipStream_t)stream);
+                        if (er == hipSuccess) continue;
+                        if (er != hipErrorNotSupported) return fail(err, RL_ERR_HIP, std::string("launch of lstm_seq failed: ") + hipGetErrorString(er));
+                    }
                     for (int64_t t = t0; t < t0 + tc; ++t) {
                         LstmStepParams q{};
                         q.h_prev = t == 0 ? io->h0_dev : (const void *)((const char *)io->h_seq_dev + (size_t)(t - 1) * io->h_step_bytes);

@@ -215,6 +215,19 @@ struct LstmStepParams {
 };
 hipError_t launch_lstm_step(const LstmStepParams &p, hipStream_t s);
 
+// ---- a whole LSTM sequence on precomputed input projections, one cooperative launch (lstm_seq.hip) ------
+struct LstmSeqParams {
+    const void *h0; void *h_seq; size_t h_step_bytes;   // [B, H] bf16 before the first step; step t's result at h_seq + t * h_step_bytes
+    const void *w; uint32_t w_bytes;    // packed cell weights, as in LstmStepParams
+    const float *zx;                    // [T][B][4H] f32
+    const float *bias;                  // [4H] f32 in declaration order, or null
+    float *c;                           // [B, H] f32, updated in place
+    uint32_t *ctl, *save;               // control words (at zx of step T-1) and where what they displace is kept (at h of step T-1)
+    int32_t B, H, Kp, k_off, T, spins;  // spins: polls for the other workgroups before a workgroup goes on alone
+};
+bool lstm_seq_ok(int64_t B, int64_t H, int64_t T);
+hipError_t launch_lstm_seq(const LstmSeqParams &p, hipStream_t s);
+
 // ---- purely elementwise fused group ---------------------------------------
 struct EltwiseParams {
     const void *x; int32_t x_dtype;     // first operand: initial running value

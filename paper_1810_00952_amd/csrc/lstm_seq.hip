@@ -1,0 +1,282 @@
+// A whole LSTM sequence in one launch, input projections already done (zx of every step, packed column order):
+//
+//   z_t = zx_t + h_{t-1} . Wh^T + bias;  c_t, h_t by the gates (see lstm_step.hip)
+//
+// What bounds the one-launch-per-step form is not its arithmetic: 6.3 us per step, of which about 3 pass between dependent
+// launches and the rest fetching 128 KB per CU again (64 KB of weights that never change).  Here every CU keeps its weights in
+// registers for the whole sequence and a step costs one exchange of h between the CUs that need it, 1.9 us.
+//
+// Split: batch rows over the eight XCDs (8 of 64), hidden units over the CUs of an XCD (32 each at H = 1024), 8 units per wave:
+// its 32 gate columns x H are 256 registers per lane.  A step's h is then written and read inside one XCD, through its L2: the
+// stores go there (the vector L1 writes through), the loads bypass the L1 (device
+// scope; the narrower scopes may hit it).  No cache is flushed, which is what made a
+// grid-wide barrier cost more than a launch.  A workgroup publishes step t by writing t + 1 into its flag word after its stores
+// were acknowledged; the members of its group poll the flags of all of them.
+// MFMA 16x16x32, weights as the row operand with row 4u + gate: a lane's four result registers are the four gates of one
+// (unit, batch row), so the gates, c (in registers throughout) and h need no exchange between lanes.
+//
+// Waiting for other workgroups is safe only if all of them are resident.  The kernel is launched cooperatively, and it checks:
+// every workgroup registers (device-scope atomics); the last one finds `members` workgroups on every XCD and says "go", or says
+// "alone"; so does anyone whose bounded wait for the others runs out.  Alone, a workgroup takes sixteen batch rows through the
+// whole sequence by itself (weights fetched every step: slow, but it waits for nobody).
+// The control words live where step T-1's projections of batch row 0 begin (scratch); what they displace was saved at the start
+// of h_{T-1} by the launch before and is fetched into LDS before registering.
+#include "device_utils.h"
+
+namespace rl {
+
+namespace {
+
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+#define RL_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, untyped dwords
+}
+
+__device__ __forceinline__ void wg_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+constexpr int N_XCD = 8, DEV = 16;              // DEV: cache policy (sc1, device scope) of a load that bypasses the vector L1
+constexpr int CTL_TOTAL = N_XCD, CTL_STATE = N_XCD + 1, CTL_FLAGS = 32;
+enum { ST_WAIT = 0, ST_GO = 1, ST_ALONE = 2 };
+constexpr int UNITS = 32;                       // hidden units of a workgroup
+constexpr int MAX_POLLS = 1 << 20;              // of a resident workgroup for its group: never reached; ends the wait, with NaN in c, all the same
+
+}  // namespace
+
+int lstm_seq_ctl_words(int H) { return CTL_FLAGS + N_XCD * (H / UNITS); }
+
+// saves the words the control block displaces and clears it, or puts them back
+__global__ void lstm_seq_prepare_kernel(uint32_t *ctl, uint32_t *save, int words, int back)
+{
+    for (int i = threadIdx.x; i < words; i += blockDim.x) {
+        if (back) ctl[i] = save[i];
+        else { save[i] = ctl[i]; ctl[i] = 0u; }
+    }
+}
+
+template <int KS>                               // H / 32
+__global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
+    constexpr int H = KS * 32, MEMBERS = H / UNITS, ROWB = H * 2;
+    __shared__ __attribute__((aligned(1024))) unsigned char hbuf[2][16 * ROWB];
+    __shared__ uint32_t saved[CTL_FLAGS + N_XCD * MEMBERS];
+    __shared__ int s_state, s_slot;
+
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int l16 = lane & 15, q4 = lane >> 4;
+    uint32_t *ctl = p.ctl;
+    const int words = CTL_FLAGS + N_XCD * MEMBERS;
+    for (int i = t; i < words; i += 256) saved[i] = p.save[i];
+    uint32_t xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    xcc &= N_XCD - 1;
+    __syncthreads();                             // the saved words are fetched before anyone can pass the registration
+
+    if (t == 0) {
+        s_slot = (int)__hip_atomic_fetch_add(ctl + xcc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t before = __hip_atomic_fetch_add(ctl + CTL_TOTAL, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == gridDim.x - 1) {
+            bool even = true;
+            for (int i = 0; i < N_XCD; ++i) even &= __hip_atomic_load(ctl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)MEMBERS;
+            uint32_t want = ST_WAIT;
+            __hip_atomic_compare_exchange_strong(ctl + CTL_STATE, &want, even ? ST_GO : ST_ALONE, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        uint32_t st = ST_WAIT;
+        for (int i = 0; i < p.spins && st == ST_WAIT; ++i) st = __hip_atomic_load(ctl + CTL_STATE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (st == ST_WAIT) {
+            uint32_t want = ST_WAIT;
+            if (__hip_atomic_compare_exchange_strong(ctl + CTL_STATE, &want, (uint32_t)ST_ALONE, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) st = ST_ALONE;
+            else st = want;
+        }
+        s_state = (int)st;
+    }
+    __syncthreads();
+    const bool go = __builtin_amdgcn_readfirstlane(s_state) == ST_GO;
+    const int member = __builtin_amdgcn_readfirstlane(s_slot);
+
+    // ---- rows and units of this workgroup
+    const int R = go ? (p.B + N_XCD - 1) / N_XCD : 16;           // at most 16 (checked by the launcher)
+    const int r0 = (go ? (int)xcc : (int)blockIdx.x) * R;
+    const int rows = min(R, p.B - r0);
+    if (rows <= 0 || (go && member >= MEMBERS)) return;
+    const bool live = l16 < rows;
+    const int row = r0 + min(l16, rows - 1);                     // the lane's batch row
+    const int N = 4 * H;
+    const rsrc_t rw = make_rsrc(p.w, p.w_bytes);
+    // packed weight row (= packed column of zx) of (unit, gate)
+    auto packed = [](int unit, int gate) { return (unit >> 4) * 64 + gate * 16 + (unit & 15); };
+    auto zx_at = [&](int tt, int unit, int gate) -> float {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.zx + (size_t)tt * p.B * N, (uint32_t)p.B * N * 4u), (uint32_t)(row * N + packed(unit, gate)) * 4u, 0, 0));
+    };
+    auto zx_true = [&](float z, int tt, int unit, int gate) -> float {       // ... unless the control words stand there
+        const int col = packed(unit, gate);
+        return tt == p.T - 1 && row == 0 && col < words ? __uint_as_float(saved[col]) : z;
+    };
+    // h_{tt-1} of the workgroup's rows into buffer tt & 1; 16-byte chunk c of row r at position c ^ 4 (r & 3)
+    auto fetch_h = [&](int tt) {
+        const char *src = tt == 0 ? (const char *)p.h0 : (const char *)p.h_seq + (size_t)(tt - 1) * p.h_step_bytes;
+        const rsrc_t rh = make_rsrc(src + (size_t)r0 * ROWB, (uint32_t)rows * ROWB);
+        constexpr int PER = (ROWB + 1023) / 1024;                // direct loads per row, 1 KB each (the last may be half used)
+        for (int i = wave; i < rows * PER; i += 4) {
+            const int r = i / PER, part = i - r * PER, at = part * 64 + lane;
+            if (at < ROWB / 16)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, RL_LDS_PTR(hbuf[tt & 1] + r * ROWB + part * 1024), 16, (uint32_t)(r * ROWB + (at ^ ((r & 3) << 2)) * 16), 0, 0, DEV);
+        }
+        asm volatile("" ::: "memory");                           // what is requested next stays behind these in the counter
+    };
+    const int hrow = min(l16, rows - 1);
+    const int h_key = (hrow & 3) << 2;
+    auto h_frag = [&](int tt, int ks) -> bf16x8 {
+        return __builtin_bit_cast(bf16x8, *(const u32x4 *)(hbuf[tt & 1] + hrow * ROWB + (((ks * 4 + q4) ^ h_key) << 4)));
+    };
+    auto bias_at = [&](int unit, int gate) { return p.bias ? p.bias[gate * H + unit] : 0.0f; };
+
+    if (go) {
+        const int unit0 = member * UNITS + wave * 8;
+        u32x4 fw[2][KS];                                          // row l16 = 4 unit + gate of tile ct, contraction indices 32 ks + 8 q4 ..
+        float bias_r[2][4], c_r[2];
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+            const uint32_t wrow = (uint32_t)packed(unit0 + ct * 4 + (l16 >> 2), l16 & 3) * (uint32_t)p.Kp * 2u + (uint32_t)p.k_off * 2u + (uint32_t)q4 * 16u;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) fw[ct][ks] = __builtin_amdgcn_raw_buffer_load_b128(rw, wrow + ks * 64, 0, 0);
+            const int unit = unit0 + ct * 4 + q4;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) bias_r[ct][g] = bias_at(unit, g);
+            c_r[ct] = p.c[(size_t)row * H + unit];
+        }
+        float z_r[2][2][4];                                       // projections of step t and t + 1 (set t & 1)
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) z_r[0][ct][g] = zx_at(0, unit0 + ct * 4 + q4, g);
+        uint32_t *flags = ctl + CTL_FLAGS + xcc * MEMBERS;
+        const rsrc_t rf = make_rsrc(flags, MEMBERS * 4);
+        bool lost = false;
+        auto step = [&](int tt, float (&zc)[2][4], float (&zn)[2][4]) {
+            if (tt > 0) {
+                // every member's flag says its h_{tt-1} is in the L2 (lanes past the members read zero and do not count)
+                int i = 0;
+                for (; i < MAX_POLLS; ++i) {
+                    const uint32_t f = __builtin_amdgcn_raw_buffer_load_b32(rf, (uint32_t)lane * 4u, 0, DEV);
+                    if (__all(lane >= MEMBERS || f >= (uint32_t)tt)) break;
+                    asm volatile("" ::: "memory");
+                }
+                lost |= i == MAX_POLLS;
+            }
+            fetch_h(tt);
+            const int tn = min(tt + 1, p.T - 1);
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) zn[ct][g] = zx_at(tn, unit0 + ct * 4 + q4, g);
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");     // h has landed; the eight projections of the next step may still fly
+            wg_barrier();
+            f32x4 acc[2][2];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) acc[a >> 1][a & 1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const bf16x8 hf = h_frag(tt, ks);
+#pragma unroll
+                for (int ct = 0; ct < 2; ++ct)
+                    acc[ct][ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ct][ks]), hf, acc[ct][ks & 1], 0, 0, 0);
+            }
+            uint16_t *out = (uint16_t *)((char *)p.h_seq + (size_t)tt * p.h_step_bytes) + (size_t)row * H;
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) {
+                float z[4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) z[g] = ((acc[ct][0][g] + acc[ct][1][g]) + zx_true(zc[ct][g], tt, unit0 + ct * 4 + q4, g)) + bias_r[ct][g];
+                c_r[ct] = sigmoidf_(z[1]) * c_r[ct] + sigmoidf_(z[0]) * tanhf_(z[2]);
+                const float hn = sigmoidf_(z[3]) * tanhf_(c_r[ct]);
+                if (live) out[unit0 + ct * 4 + q4] = (uint16_t)f32_to_bf16_bits(hn);
+            }
+            // this wave's h is in the L2; after the barrier every wave's is (and every wave has read this step's buffer)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            wg_barrier();
+            if (t == 0) __hip_atomic_store(flags + member, (uint32_t)(tt + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+#pragma unroll 1
+        for (int tt = 0; tt < p.T; tt += 2) {
+            step(tt, z_r[0], z_r[1]);
+            if (tt + 1 < p.T) step(tt + 1, z_r[1], z_r[0]);
+            if (lost) break;
+        }
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+            if (live) p.c[(size_t)row * H + unit0 + ct * 4 + q4] = lost ? __uint_as_float(0x7fc00000u) : c_r[ct];
+        return;
+    }
+
+    // ---- alone: sixteen rows, every unit; the wave's units are 4 wave, 4 wave + 16, ...
+#pragma unroll 1
+    for (int tt = 0; tt < p.T; ++tt) {
+        if (tt == 0) {
+            fetch_h(0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        __syncthreads();
+        uint16_t *out = (uint16_t *)((char *)p.h_seq + (size_t)tt * p.h_step_bytes) + (size_t)row * H;
+#pragma unroll 1
+        for (int u0 = wave * 4; u0 < H; u0 += 16) {
+            f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+            const uint32_t wrow = (uint32_t)packed(u0 + (l16 >> 2), l16 & 3) * (uint32_t)p.Kp * 2u + (uint32_t)p.k_off * 2u + (uint32_t)q4 * 16u;
+#pragma unroll 8
+            for (int ks = 0; ks < KS; ++ks)
+                acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, wrow + ks * 64, 0, 0)), h_frag(tt, ks), acc[ks & 1], 0, 0, 0);
+            const int unit = u0 + q4;
+            float z[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) z[g] = ((acc[0][g] + acc[1][g]) + zx_true(zx_at(tt, unit, g), tt, unit, g)) + bias_at(unit, g);
+            if (live) {
+                float *cp = p.c + (size_t)row * H + unit;
+                const float cn = sigmoidf_(z[1]) * *cp + sigmoidf_(z[0]) * tanhf_(z[2]);
+                const uint16_t hb = (uint16_t)f32_to_bf16_bits(sigmoidf_(z[3]) * tanhf_(cn));
+                *cp = cn;
+                out[unit] = hb;
+                *(uint16_t *)(hbuf[(tt + 1) & 1] + l16 * ROWB + (((unit >> 3) ^ ((l16 & 3) << 2)) << 4) + (unit & 7) * 2) = hb;
+            }
+        }
+    }
+#endif
+}
+
+template __global__ void lstm_seq_kernel<8>(const LstmSeqParams);
+template __global__ void lstm_seq_kernel<16>(const LstmSeqParams);
+template __global__ void lstm_seq_kernel<24>(const LstmSeqParams);
+template __global__ void lstm_seq_kernel<32>(const LstmSeqParams);
+
+bool lstm_seq_ok(int64_t B, int64_t H, int64_t T) { return B >= 1 && B <= 16 * N_XCD && H >= 256 && H <= 1024 && H % 256 == 0 && T >= 8; }
+
+hipError_t launch_lstm_seq(const LstmSeqParams &p0, hipStream_t s)
+{
+    LstmSeqParams p = p0;
+    if (!lstm_seq_ok(p.B, p.H, p.T) || !p.h0 || !p.h_seq || !p.w || !p.zx || !p.c || !p.ctl || !p.save || p.spins < 0 || p.Kp < p.k_off + p.H || p.k_off < 0 || p.k_off % 8 != 0 ||
+        p.Kp % 8 != 0 || (uint64_t)4 * p.H * p.Kp * 2 != p.w_bytes || p.w_bytes >= 0x7fffffffu || p.h_step_bytes < (size_t)p.B * p.H * 2 ||
+        ((uintptr_t)p.ctl & 255) || ((uintptr_t)p.save & 3))
+        return hipErrorInvalidValue;
+    const void *kern = p.H == 256 ? (const void *)lstm_seq_kernel<8> : p.H == 512 ? (const void *)lstm_seq_kernel<16> : p.H == 768 ? (const void *)lstm_seq_kernel<24> : (const void *)lstm_seq_kernel<32>;
+    hipLaunchKernelGGL(lstm_seq_prepare_kernel, dim3(1), dim3(256), 0, s, p.ctl, p.save, lstm_seq_ctl_words(p.H), 0);
+    hipError_t er = hipGetLastError();
+    if (er != hipSuccess) return er;
+    void *args[] = {&p};
+    er = hipLaunchCooperativeKernel(kern, dim3((unsigned)(N_XCD * (p.H / UNITS))), dim3(256), args, 0, s);
+    if (er == hipSuccess) return er;
+    // this device cannot hold the grid (or has no cooperative launches): the projections as they were, for the caller's other form
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(lstm_seq_prepare_kernel, dim3(1), dim3(256), 0, s, p.ctl, p.save, lstm_seq_ctl_words(p.H), 1);
+    (void)hipGetLastError();
+    return hipErrorNotSupported;
+}
+
+}  // namespace rl

@@ -3,6 +3,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+import oracle as O
 import workloads as W
 from oracle import graph as OG
 from helpers import assert_close, error_budget, run_hip
@@ -146,3 +147,69 @@ def test_bf16_long_k_on_few_tiles(case):
     spec, data = W.conv_group(b, ci, co, h, w, k, s, p, "bf16", residual=res, tail=tail)
     assert any(x.endswith("_dma_splitk") for x in steps_of(spec)), steps_of(spec)
     check(spec, data, "bf16", f"long K {case}")
+
+
+# ---- a whole sequence in one launch (lstm_seq.hip) ---------------------------------------------------------------------------
+def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None):
+    import torch
+    from paper_1810_00952_amd import harness
+    spec = W.lstm_cell_graph(B, I, H, "bf16", True)
+    s = harness.Session(spec, opts=opts)
+    s.load({"w": d["w"], "b": d["b"]})
+    x = harness.to_device(d["x"], "bf16")
+    h0 = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda:0") if h0 is None else harness.to_device(h0, "bf16")
+    c = torch.zeros((B, H), dtype=torch.float32, device="cuda:0") if c0 is None else harness.to_device(c0, "f32")
+    hs = torch.full((T, B, H), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    ws = torch.empty(max(256, s.plan.recurrent_workspace_bytes(room or T)), dtype=torch.uint8, device="cuda:0")
+    n = s.by_name
+    roles = {"x": n["x"], "h_in": n["h"], "c_in": n["c"], "c_out": spec.outputs[0], "h_out": spec.outputs[1]}
+    s.plan.run_recurrent(T, roles, x.data_ptr(), B * I * 2, h0.data_ptr(), c.data_ptr(), hs.data_ptr(), B * H * 2,
+                         {n["w"]: s.tensors[n["w"]].data_ptr(), n["b"]: s.tensors[n["b"]].data_ptr()}, ws.data_ptr(), ws.numel(), harness.stream_handle())
+    torch.cuda.synchronize()
+    return O.widen(harness.to_host(hs), "bf16"), O.widen(harness.to_host(c), "f32")
+
+
+# batches that leave XCDs without rows, with ragged last groups, and at the limit; every hidden size the kernel is built for; odd
+# and even step counts; the sequence whole and in chunks (the second starts from the first one's last h and c)
+SEQ_CASES = [(8, 5, 128, 256, None), (9, 70, 192, 512, None), (12, 33, 128, 768, None), (16, 64, 256, 1024, None), (11, 128, 128, 1024, None), (1 + 8 + 9, 1, 128, 1024, 9)]
+
+
+@pytest.mark.parametrize("case", SEQ_CASES, ids=[f"seq{i}" for i in range(len(SEQ_CASES))])
+def test_lstm_sequence_in_one_launch(case):
+    import numpy as np
+    T, B, I, H, room = case
+    d = W.lstm_data(T, B, I, H, "bf16")
+    rng = np.random.default_rng(11)
+    c0, h0 = W.as_dtype(rng.standard_normal((B, H)), "f32"), W.as_dtype(rng.uniform(-1, 1, (B, H)), "bf16")
+    ref_h, ref_c = O.lstm_sequence(O.widen(d["x"], "bf16"), O.widen(d["w"], "bf16"), O.widen(d["b"], "f32"), O.widen(h0, "bf16"), O.widen(c0, "f32"), h_dtype="bf16")
+    for opts in (None, {"no_seq": 2}, {"no_seq": 1}):
+        print(f"sequence {case} {opts}", flush=True)
+        h, c = run_sequence(T, B, I, H, d, opts, room, c0, h0)
+        assert_close(h, ref_h, "bf16", f"sequence h {case} {opts}")
+        assert_close(c, ref_c, "bf16", f"sequence c {case} {opts}")
+    first = run_sequence(T, B, I, H, d, None, room, c0, h0)
+    again = run_sequence(T, B, I, H, d, None, room, c0, h0)
+    np.testing.assert_array_equal(first[0], again[0])
+    np.testing.assert_array_equal(first[1], again[1])
+
+
+def test_lstm_sequences_on_two_streams_do_not_wait_for_each_other():
+    import numpy as np
+    import torch
+    T, B, I, H = 40, 64, 128, 1024
+    ds = [W.lstm_data(T, B, I, H, "bf16", config=5 + i) for i in (0, 20)]
+    alone = [run_sequence(T, B, I, H, d) for d in ds]
+    import threading
+    got = [None, None]
+
+    def work(i):
+        torch.cuda.set_device(0)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(3):
+                got[i] = run_sequence(T, B, I, H, ds[i])
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    for i in range(2):
+        np.testing.assert_array_equal(got[i][0], alone[i][0])
+        np.testing.assert_array_equal(got[i][1], alone[i][1])
