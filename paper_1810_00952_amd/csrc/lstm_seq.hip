@@ -4,14 +4,19 @@
 //
 // What bounds the one-launch-per-step form is not its arithmetic: 6.3 us per step, of which about 3 pass between dependent
 // launches and the rest fetching 128 KB per CU again (64 KB of weights that never change).  Here every CU keeps its weights in
-// registers for the whole sequence and a step costs one exchange of h between the CUs that need it, 1.9 us.
+// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 2.8 us at 64 rows of
+// 1024 units (128 steps with their projections: 814 us step by step, 446 us here).  What is left of a step is a chain of
+// latencies - the flags' poll, the L2 round trip for h, the meeting of the partial sums, the gates, the store's acknowledgement -
+// and not work: the MFMAs of a step take 0.3 us.
 //
-// Split: batch rows over the eight XCDs (8 of 64), hidden units over the CUs of an XCD (32 each at H = 1024), 8 units per wave:
-// its 32 gate columns x H are 256 registers per lane.  A step's h is then written and read inside one XCD, through its L2: the
-// stores go there (the vector L1 writes through), the loads bypass the L1 (device
-// scope; the narrower scopes may hit it).  No cache is flushed, which is what made a
-// grid-wide barrier cost more than a launch.  A workgroup publishes step t by writing t + 1 into its flag word after its stores
-// were acknowledged; the members of its group poll the flags of all of them.
+// Split: batch rows over the eight XCDs (8 of 64), hidden units over the CUs of an XCD (32 each at H = 1024).  Inside a CU each
+// of the four waves multiplies all 128 gate columns by its quarter of H (256 registers of weights per lane at H = 1024), so that
+// h is fetched once per CU, each wave its own part straight into registers; the four partial sums meet in LDS.  (Eight units
+// per wave over the whole of H, with h staged in LDS: 508 us instead of 498, before the gates were spread over idle lanes.)
+// A step's h is written and read inside one XCD, through its L2: the stores go there (the vector L1 writes through), the loads
+// bypass the L1 (device scope; the narrower scopes may hit it).  No cache is flushed, which is what made a grid-wide barrier
+// cost more than a launch.  A workgroup publishes step t by writing t + 1 into its flag word after its stores were acknowledged;
+// the members of its group poll the flags of all of them.
 // MFMA 16x16x32, weights as the row operand with row 4u + gate: a lane's four result registers are the four gates of one
 // (unit, batch row), so the gates, c (in registers throughout) and h need no exchange between lanes.
 //
@@ -61,12 +66,15 @@ __global__ void lstm_seq_prepare_kernel(uint32_t *ctl, uint32_t *save, int words
     }
 }
 
-template <int KS>                               // H / 32
+// KS: H / 32.  HALF: at most eight rows per XCD, so that half of the MFMA's sixteen columns are empty: the lanes of those take
+// every other unit in the gate arithmetic, which is a serial chain of exponentials (128 steps of 64 rows: 498 -> 446 us).
+template <int KS, bool HALF>
 __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
     constexpr int H = KS * 32, MEMBERS = H / UNITS, ROWB = H * 2;
     __shared__ __attribute__((aligned(1024))) unsigned char hbuf[2][16 * ROWB];
+    __shared__ f32x4 part[4][UNITS / 4][64];    // the waves' partial sums
     __shared__ uint32_t saved[CTL_FLAGS + N_XCD * MEMBERS];
     __shared__ int s_state, s_slot;
 
@@ -109,7 +117,7 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
     const int rows = min(R, p.B - r0);
     if (rows <= 0 || (go && member >= MEMBERS)) return;
     const bool live = l16 < rows;
-    const int row = r0 + min(l16, rows - 1);                     // the lane's batch row
+    int row = r0 + min(l16, rows - 1);                           // the lane's batch row
     const int N = 4 * H;
     const rsrc_t rw = make_rsrc(p.w, p.w_bytes);
     // packed weight row (= packed column of zx) of (unit, gate)
@@ -141,28 +149,42 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
     auto bias_at = [&](int unit, int gate) { return p.bias ? p.bias[gate * H + unit] : 0.0f; };
 
     if (go) {
+        // A wave multiplies all 128 gate columns by its quarter of H (its h fragments come straight from the L2 into registers), the
+        // quarters meet in LDS, and it finishes eight of the units.
+        constexpr int KW = KS / 4, CT = UNITS / 4;
         const int unit0 = member * UNITS + wave * 8;
-        u32x4 fw[2][KS];                                          // row l16 = 4 unit + gate of tile ct, contraction indices 32 ks + 8 q4 ..
-        float bias_r[2][4], c_r[2];
+        u32x4 fw[CT][KW];                                         // row l16 = 4 unit + gate of column tile ct, contraction indices 32 (wave KW + ks) + 8 q4 ..
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            const uint32_t wrow = (uint32_t)packed(unit0 + ct * 4 + (l16 >> 2), l16 & 3) * (uint32_t)p.Kp * 2u + (uint32_t)p.k_off * 2u + (uint32_t)q4 * 16u;
+        for (int ct = 0; ct < CT; ++ct) {
+            const uint32_t wrow = (uint32_t)packed(member * UNITS + ct * 4 + (l16 >> 2), l16 & 3) * (uint32_t)p.Kp * 2u + (uint32_t)p.k_off * 2u + (uint32_t)(wave * KW * 64 + q4 * 16);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) fw[ct][ks] = __builtin_amdgcn_raw_buffer_load_b128(rw, wrow + ks * 64, 0, 0);
-            const int unit = unit0 + ct * 4 + q4;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) bias_r[ct][g] = bias_at(unit, g);
-            c_r[ct] = p.c[(size_t)row * H + unit];
+            for (int ks = 0; ks < KW; ++ks) fw[ct][ks] = __builtin_amdgcn_raw_buffer_load_b128(rw, wrow + ks * 64, 0, 0);
         }
-        float z_r[2][2][4];                                       // projections of step t and t + 1 (set t & 1)
+        const uint32_t h_off = live ? (uint32_t)(l16 * ROWB + wave * KW * 64 + q4 * 16) : 0x80000000u;     // lanes past the rows read zeros
+        // what the lane finishes: unit tile 2 wave + ct_of(u) of its batch row
+        constexpr int NU = HALF ? 1 : 2;
+        const int grow = HALF ? l16 & 7 : l16;                    // row of the group, and the lane that holds its sums
+        const int src_lane = q4 * 16 + grow;
+        const bool glive = grow < rows;
+        row = r0 + min(grow, rows - 1);
+        auto ct_of = [&](int u) { return HALF ? l16 >> 3 : u; };
+        float bias_r[NU][4], c_r[NU];
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
+        for (int u = 0; u < NU; ++u) {
+            const int unit = unit0 + ct_of(u) * 4 + q4;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) z_r[0][ct][g] = zx_at(0, unit0 + ct * 4 + q4, g);
+            for (int g = 0; g < 4; ++g) bias_r[u][g] = bias_at(unit, g);
+            c_r[u] = p.c[(size_t)row * H + unit];
+        }
+        float z_r[2][NU][4];                                      // projections of step t and t + 1 (set t & 1)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) z_r[0][u][g] = zx_at(0, unit0 + ct_of(u) * 4 + q4, g);
         uint32_t *flags = ctl + CTL_FLAGS + xcc * MEMBERS;
         const rsrc_t rf = make_rsrc(flags, MEMBERS * 4);
         bool lost = false;
-        auto step = [&](int tt, float (&zc)[2][4], float (&zn)[2][4]) {
+        auto step = [&](int tt, float (&zc)[NU][4], float (&zn)[NU][4]) {
             if (tt > 0) {
                 // every member's flag says its h_{tt-1} is in the L2 (lanes past the members read zero and do not count)
                 int i = 0;
@@ -173,35 +195,51 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
                 }
                 lost |= i == MAX_POLLS;
             }
-            fetch_h(tt);
+            const char *src = tt == 0 ? (const char *)p.h0 : (const char *)p.h_seq + (size_t)(tt - 1) * p.h_step_bytes;
+            const rsrc_t rh = make_rsrc(src + (size_t)r0 * ROWB, (uint32_t)rows * ROWB);
+            u32x4 hf[KW];
+#pragma unroll
+            for (int ks = 0; ks < KW; ++ks) hf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rh, h_off + ks * 64, 0, DEV);
+            asm volatile("" ::: "memory");                       // the next step's projections are requested behind h
             const int tn = min(tt + 1, p.T - 1);
 #pragma unroll
-            for (int ct = 0; ct < 2; ++ct)
+            for (int u = 0; u < NU; ++u)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) zn[ct][g] = zx_at(tn, unit0 + ct * 4 + q4, g);
-            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");     // h has landed; the eight projections of the next step may still fly
+                for (int g = 0; g < 4; ++g) zn[u][g] = zx_at(tn, unit0 + ct_of(u) * 4 + q4, g);
+            f32x4 acc[CT];
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < KW; ++ks)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ct][ks]), __builtin_bit_cast(bf16x8, hf[ks]), acc[ct], 0, 0, 0);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) part[wave][ct][lane] = acc[ct];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             wg_barrier();
-            f32x4 acc[2][2];
+            f32x4 z[NU];
 #pragma unroll
-            for (int a = 0; a < 4; ++a) acc[a >> 1][a & 1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int u = 0; u < NU; ++u) {
+                const int at = wave * 2 + ct_of(u);
+                z[u] = (part[0][at][src_lane] + part[1][at][src_lane]) + (part[2][at][src_lane] + part[3][at][src_lane]);
+            }
+            if (tt == p.T - 1 && r0 == 0) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 hf = h_frag(tt, ks);
+                for (int u = 0; u < NU; ++u)
 #pragma unroll
-                for (int ct = 0; ct < 2; ++ct)
-                    acc[ct][ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ct][ks]), hf, acc[ct][ks & 1], 0, 0, 0);
+                    for (int g = 0; g < 4; ++g) zc[u][g] = zx_true(zc[u][g], tt, unit0 + ct_of(u) * 4 + q4, g);
             }
             uint16_t *out = (uint16_t *)((char *)p.h_seq + (size_t)tt * p.h_step_bytes) + (size_t)row * H;
 #pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-                float z[4];
+            for (int u = 0; u < NU; ++u) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) z[g] = ((acc[ct][0][g] + acc[ct][1][g]) + zx_true(zc[ct][g], tt, unit0 + ct * 4 + q4, g)) + bias_r[ct][g];
-                c_r[ct] = sigmoidf_(z[1]) * c_r[ct] + sigmoidf_(z[0]) * tanhf_(z[2]);
-                const float hn = sigmoidf_(z[3]) * tanhf_(c_r[ct]);
-                if (live) out[unit0 + ct * 4 + q4] = (uint16_t)f32_to_bf16_bits(hn);
+                for (int g = 0; g < 4; ++g) z[u][g] = (z[u][g] + zc[u][g]) + bias_r[u][g];
+                c_r[u] = sigmoidf_(z[u][1]) * c_r[u] + sigmoidf_(z[u][0]) * tanhf_(z[u][2]);
+                const float hn = sigmoidf_(z[u][3]) * tanhf_(c_r[u]);
+                if (glive) out[unit0 + ct_of(u) * 4 + q4] = (uint16_t)f32_to_bf16_bits(hn);
             }
-            // this wave's h is in the L2; after the barrier every wave's is (and every wave has read this step's buffer)
+            // this wave's h is in the L2; after the barrier every wave's is (and every wave has read the partial sums)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             wg_barrier();
             if (t == 0) __hip_atomic_store(flags + member, (uint32_t)(tt + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -213,8 +251,8 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
             if (lost) break;
         }
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-            if (live) p.c[(size_t)row * H + unit0 + ct * 4 + q4] = lost ? __uint_as_float(0x7fc00000u) : c_r[ct];
+        for (int u = 0; u < NU; ++u)
+            if (glive) p.c[(size_t)row * H + unit0 + ct_of(u) * 4 + q4] = lost ? __uint_as_float(0x7fc00000u) : c_r[u];
         return;
     }
 
@@ -251,10 +289,9 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 #endif
 }
 
-template __global__ void lstm_seq_kernel<8>(const LstmSeqParams);
-template __global__ void lstm_seq_kernel<16>(const LstmSeqParams);
-template __global__ void lstm_seq_kernel<24>(const LstmSeqParams);
-template __global__ void lstm_seq_kernel<32>(const LstmSeqParams);
+#define RL_INST(KS) template __global__ void lstm_seq_kernel<KS, false>(const LstmSeqParams); template __global__ void lstm_seq_kernel<KS, true>(const LstmSeqParams);
+RL_INST(8) RL_INST(16) RL_INST(24) RL_INST(32)
+#undef RL_INST
 
 bool lstm_seq_ok(int64_t B, int64_t H, int64_t T) { return B >= 1 && B <= 16 * N_XCD && H >= 256 && H <= 1024 && H % 256 == 0 && T >= 8; }
 
@@ -265,7 +302,9 @@ hipError_t launch_lstm_seq(const LstmSeqParams &p0, hipStream_t s)
         p.Kp % 8 != 0 || (uint64_t)4 * p.H * p.Kp * 2 != p.w_bytes || p.w_bytes >= 0x7fffffffu || p.h_step_bytes < (size_t)p.B * p.H * 2 ||
         ((uintptr_t)p.ctl & 255) || ((uintptr_t)p.save & 3))
         return hipErrorInvalidValue;
-    const void *kern = p.H == 256 ? (const void *)lstm_seq_kernel<8> : p.H == 512 ? (const void *)lstm_seq_kernel<16> : p.H == 768 ? (const void *)lstm_seq_kernel<24> : (const void *)lstm_seq_kernel<32>;
+    static const void *const kerns[4][2] = {{(const void *)lstm_seq_kernel<8, false>, (const void *)lstm_seq_kernel<8, true>}, {(const void *)lstm_seq_kernel<16, false>, (const void *)lstm_seq_kernel<16, true>},
+                                            {(const void *)lstm_seq_kernel<24, false>, (const void *)lstm_seq_kernel<24, true>}, {(const void *)lstm_seq_kernel<32, false>, (const void *)lstm_seq_kernel<32, true>}};
+    const void *kern = kerns[p.H / 256 - 1][p.B <= 8 * N_XCD];
     hipLaunchKernelGGL(lstm_seq_prepare_kernel, dim3(1), dim3(256), 0, s, p.ctl, p.save, lstm_seq_ctl_words(p.H), 0);
     hipError_t er = hipGetLastError();
     if (er != hipSuccess) return er;
