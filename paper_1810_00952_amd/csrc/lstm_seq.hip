@@ -4,15 +4,16 @@
 //
 // What bounds the one-launch-per-step form is not its arithmetic: 6.3 us per step, of which about 3 pass between dependent
 // launches and the rest fetching 128 KB per CU again (64 KB of weights that never change).  Here every CU keeps its weights in
-// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 2.8 us at 64 rows of
-// 1024 units (128 steps with their projections: 814 us step by step, 446 us here).  What is left of a step is a chain of
-// latencies - the flags' poll, the L2 round trip for h, the meeting of the partial sums, the gates, the store's acknowledgement -
-// and not work: the MFMAs of a step take 0.3 us.
+// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 2.7 us at 64 rows of
+// 1024 units (128 steps with their projections: 825 us step by step, 417 us here; 383 us if the 134 MB of projections still
+// stand in the last-level cache).  What is left of a step is a chain of latencies - the flags' poll, the L2 round trip for h,
+// the meeting of the partial sums, the gates, the store's acknowledgement - and not work: the MFMAs of a step take 0.3 us.
 //
 // Split: batch rows over the eight XCDs (8 of 64), hidden units over the CUs of an XCD (32 each at H = 1024).  Inside a CU each
 // of the four waves multiplies all 128 gate columns by its quarter of H (256 registers of weights per lane at H = 1024), so that
 // h is fetched once per CU, each wave its own part straight into registers; the four partial sums meet in LDS.  (Eight units
-// per wave over the whole of H, with h staged in LDS: 508 us instead of 498, before the gates were spread over idle lanes.)
+// per wave over the whole of H, with h staged in LDS: 520 us.  Quarters with the loads left to the compiler, which asks for h two
+// fragments at a time and for the projections only after the products: 548 us.)
 // A step's h is written and read inside one XCD, through its L2: the stores go there (the vector L1 writes through), the loads
 // bypass the L1 (device scope; the narrower scopes may hit it).  No cache is flushed, which is what made a grid-wide barrier
 // cost more than a launch.  A workgroup publishes step t by writing t + 1 into its flag word after its stores were acknowledged;
@@ -67,7 +68,7 @@ __global__ void lstm_seq_prepare_kernel(uint32_t *ctl, uint32_t *save, int words
 }
 
 // KS: H / 32.  HALF: at most eight rows per XCD, so that half of the MFMA's sixteen columns are empty: the lanes of those take
-// every other unit in the gate arithmetic, which is a serial chain of exponentials (128 steps of 64 rows: 498 -> 446 us).
+// every other unit in the gate arithmetic, which is a serial chain of exponentials (128 steps of 64 rows, projections in cache: 498 -> 446 us).
 template <int KS, bool HALF>
 __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 {
@@ -188,6 +189,7 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
             if (tt > 0) {
                 // every member's flag says its h_{tt-1} is in the L2 (lanes past the members read zero and do not count)
                 int i = 0;
+#pragma unroll 1
                 for (; i < MAX_POLLS; ++i) {
                     const uint32_t f = __builtin_amdgcn_raw_buffer_load_b32(rf, (uint32_t)lane * 4u, 0, DEV);
                     if (__all(lane >= MEMBERS || f >= (uint32_t)tt)) break;
@@ -200,12 +202,13 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
             u32x4 hf[KW];
 #pragma unroll
             for (int ks = 0; ks < KW; ++ks) hf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rh, h_off + ks * 64, 0, DEV);
-            asm volatile("" ::: "memory");                       // the next step's projections are requested behind h
+            __builtin_amdgcn_sched_barrier(0);                   // all of them in flight at once; left to itself the compiler asks for two at a time
             const int tn = min(tt + 1, p.T - 1);
 #pragma unroll
             for (int u = 0; u < NU; ++u)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) zn[u][g] = zx_at(tn, unit0 + ct_of(u) * 4 + q4, g);
+            __builtin_amdgcn_sched_barrier(0);                   // the next step's projections are requested here, behind h, and not after the products
             f32x4 acc[CT];
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
