@@ -411,16 +411,16 @@ def bench_lstm(args):
     flops = sum(st["flops"] for st in desc["steps"]) * T
     hoisted = ws.numel() > max(256, s.plan.workspace_bytes()) and not args.unfused
     if hoisted:
-        # input projection of all steps as one contraction (x, Wx read once, zx written once), then per step the
-        # recurrent weights, that step's zx, h in and out, c in and out
-        nbytes = (T * B * I * 2 + 4 * H * I * 2 + T * B * 4 * H * 4) + T * (4 * H * H * 2 + B * 4 * H * 4 + 2 * B * H * 2 + 2 * B * H * 4)
-        kernels, launches = "igemm_lp_f32out_kernel 256x128 (once) + lstm_step_kernel (per step)", T + 1
+        # input projection of all steps as one contraction (x, Wx read once, zx written once), then all steps in one launch: the
+        # recurrent weights and c in and out once, per step its zx, h in and out
+        nbytes = (T * B * I * 2 + 4 * H * I * 2 + T * B * 4 * H * 4) + 4 * H * H * 2 + 2 * B * H * 4 + T * (B * 4 * H * 4 + 2 * B * H * 2)
+        kernels, launches = "input projection (once) + lstm_seq_kernel (all steps)", 3
     else:
         nbytes = sum(st["bytes"] for st in desc["steps"]) * T
         kernels, launches = "+".join(st["kernel"] for st in desc["steps"]), T * len(desc["steps"])
     out = base_json("sequences/sec unrolled LSTM b64 1024x1024 T128 bf16", B / (ms * 1e-3), "sequences/s", args, ms, "bf16",
                     "unrolled LSTM, batch 64, input and hidden 1024, 128 steps, bf16 weights, fp32 accumulate, "
-                    + ("input projection hoisted, one recurrent kernel per step" if hoisted else
+                    + ("input projection hoisted, all steps in one recurrent kernel (replayed from a HIP graph: one kernel per step)" if hoisted else
                        "gate math fused into the GEMM epilogue" if not args.unfused else "GEMM group and gate group"))
     out["us_per_step_of_sequence"] = ms * 1e3 / T
     if ms_two is not None:
