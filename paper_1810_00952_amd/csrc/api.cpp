@@ -103,6 +103,21 @@ rl_status resolve(const Plan &p, const rl_binding *b, int32_t nb, void *ws, size
 
 }  // namespace
 
+rl_status rl::run_bound(const Plan &p, const rl_binding *bindings, int32_t n_bindings, void *ws, size_t ws_bytes, void *stream)
+{
+    auto &err = p.err;
+    return guarded(err, [&]() -> rl_status {
+        if (!bindings && n_bindings > 0) return fail(err, RL_ERR_NULL, "null bindings");
+        std::vector<void *> ptrs;
+        std::string msg;
+        rl_status st = resolve(p, bindings, n_bindings, ws, ws_bytes, ptrs, msg);
+        if (st != RL_OK) return fail(err, st, msg);
+        st = run_steps(p, ptrs.data(), (hipStream_t)stream, msg);
+        if (st != RL_OK) return fail(err, st, msg);
+        return RL_OK;
+    });
+}
+
 extern "C" {
 
 rl_status rl_ctx_create(rl_ctx **out)
@@ -267,6 +282,18 @@ rl_status rl_plan_create(rl_graph *g, const rl_plan_opts *opts, rl_plan **out)
             delete p;
             return fail(err, st, msg);
         }
+        // choices that trade workspace for time must not take rl_plan_run_static away from a graph
+        if (p->p.spent && p->p.workspace_bytes > (size_t)RL_STATIC_WORKSPACE_BYTES) {
+            std::unique_ptr<Plan> q(new Plan);
+            q->opts = p->p.opts;
+            q->lean = true;
+            if (build_plan(g->g, *q, msg) == RL_OK && q->workspace_bytes <= (size_t)RL_STATIC_WORKSPACE_BYTES) {
+                bool same = q->packs.size() == p->p.packs.size();      // both read every param either packed or as given
+                for (auto &k : q->packs) same &= p->p.packs.count(k.first) != 0;
+                if (same) p->small = std::move(q);
+                else p->p = std::move(*q);
+            }
+        }
         *out = p;
         return RL_OK;
     });
@@ -311,7 +338,7 @@ rl_status rl_plan_packed_bytes(const rl_plan *plan, int32_t v, size_t *bytes)
     if (v < 0 || v >= (int)plan->p.values.size() || plan->p.values[v].role != ROLE_PARAM)
         return fail(plan->p.err, RL_ERR_BINDING, "not a param value id");
     auto it = plan->p.packs.find(v);
-    *bytes = it == plan->p.packs.end() ? 0 : it->second.bytes;
+    *bytes = it == plan->p.packs.end() ? 0 : plan->small ? small_offset(it->second) + plan->small->packs.at(v).bytes : it->second.bytes;
     return RL_OK;
 }
 
@@ -324,11 +351,14 @@ rl_status rl_plan_prepack(const rl_plan *plan, int32_t v, const void *src, void 
         auto it = plan->p.packs.find(v);
         if (it == plan->p.packs.end()) return fail(err, RL_ERR_BINDING, "this value id needs no packing");
         if (((uintptr_t)src & 15) || ((uintptr_t)dst & 15)) return fail(err, RL_ERR_ALIGN, "device pointer is not 16-byte aligned");
-        const PackSpec &k = it->second;
-        hipError_t er = k.gather ? launch_pack_gather(src, dst, k.gp, (hipStream_t)stream)
-                      : k.stem == 2 ? launch_pack_weight_stem_direct(src, dst, k.O, k.C, k.KH, k.KW, k.pw, (hipStream_t)stream)
-                      : k.stem ? launch_pack_weight_stem(src, dst, k.O, k.C, k.KH, k.KW, k.Kp, (hipStream_t)stream)
-                               : launch_pack_weight(src, dst, k.dtype, k.O, k.C, k.T, k.Kp, k.perm_block, (hipStream_t)stream);
+        auto pack = [&](const PackSpec &k, void *to) {
+            return k.gather ? launch_pack_gather(src, to, k.gp, (hipStream_t)stream)
+                 : k.stem == 2 ? launch_pack_weight_stem_direct(src, to, k.O, k.C, k.KH, k.KW, k.pw, (hipStream_t)stream)
+                 : k.stem ? launch_pack_weight_stem(src, to, k.O, k.C, k.KH, k.KW, k.Kp, (hipStream_t)stream)
+                          : launch_pack_weight(src, to, k.dtype, k.O, k.C, k.T, k.Kp, k.perm_block, (hipStream_t)stream);
+        };
+        hipError_t er = pack(it->second, dst);
+        if (er == hipSuccess && plan->small) er = pack(plan->small->packs.at(v), (char *)dst + small_offset(it->second));
         if (er != hipSuccess) return fail(err, RL_ERR_HIP, std::string("pack_weight: ") + hipGetErrorString(er));
         return RL_OK;
     });
@@ -337,17 +367,7 @@ rl_status rl_plan_prepack(const rl_plan *plan, int32_t v, const void *src, void 
 rl_status rl_plan_run(const rl_plan *plan, const rl_binding *bindings, int32_t n_bindings, void *ws, size_t ws_bytes, void *stream)
 {
     if (!plan) return RL_ERR_NULL;
-    auto &err = plan->p.err;
-    return guarded(err, [&]() -> rl_status {
-        if (!bindings && n_bindings > 0) return fail(err, RL_ERR_NULL, "null bindings");
-        std::vector<void *> ptrs;
-        std::string msg;
-        rl_status st = resolve(plan->p, bindings, n_bindings, ws, ws_bytes, ptrs, msg);
-        if (st != RL_OK) return fail(err, st, msg);
-        st = run_steps(plan->p, ptrs.data(), (hipStream_t)stream, msg);
-        if (st != RL_OK) return fail(err, st, msg);
-        return RL_OK;
-    });
+    return run_bound(plan->p, bindings, n_bindings, ws, ws_bytes, stream);
 }
 
 rl_status rl_plan_profile(const rl_plan *plan, const rl_binding *bindings, int32_t n_bindings, void *ws, size_t ws_bytes, void *stream,

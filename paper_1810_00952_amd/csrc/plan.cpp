@@ -224,9 +224,11 @@ struct Planner {
     // at a few K tiles on few workgroups (f32 dense 2 x 90 -> 8: 9 us either way; 10 x 1446 -> 128: 87 us against 16).
     bool pad_k(int x, int wv, int C, int KV, int64_t M, int64_t N, int64_t K, bool concat, int64_t bytes_per_channel) const
     {
-        if (C % KV == 0 || concat || plan.opts.no_dma || g.values[x].role == ROLE_PARAM || consumers[wv].size() != 1) return false;
+        if (plan.lean || C % KV == 0 || concat || plan.opts.no_dma || g.values[x].role == ROLE_PARAM || consumers[wv].size() != 1) return false;
         const int64_t nk = (K + 8 * KV - 1) / (8 * KV), tiles = ((M + 63) / 64) * ((N + 63) / 64), ld = round_up(C, KV), lim = (int64_t)1 << 30;
-        return (nk >= 4 || tiles * nk >= 512) && bytes_per_channel * ld < lim && N * (K / C) * ld * 4 < lim && T(x).dims[0] <= 65535;
+        const bool pad = (nk >= 4 || tiles * nk >= 512) && bytes_per_channel * ld < lim && N * (K / C) * ld * 4 < lim && T(x).dims[0] <= 65535;
+        plan.spent |= pad;
+        return pad;
     }
     // the weight packing and the contraction's sizes with C filled up to ld
     void pad_gather(PackSpec &pack, IgemmParams &p, const AnchorView *ov, int ld, int KV) const
@@ -445,7 +447,7 @@ struct Planner {
             // kernel does.  From 64 K tiles on, on 2 to 64 tiles of 64x64, that is worth its adding launch (98 x 512 x 4608: 24 us
             // against 15.5; 36 K tiles are level, 15 us either way).
             const int64_t lp_tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
-            if (il.lp && !stem && il.dma && p.K / bke >= 64 && lp_tiles >= 2 && lp_tiles <= 64 && !plan.opts.no_splitk) il.lp = 0;
+            if (il.lp && !stem && il.dma && p.K / bke >= 64 && lp_tiles >= 2 && lp_tiles <= 64 && !plan.opts.no_splitk && !plan.lean) il.lp = 0;
             // everything else whose chunks are whole: K tiles that span taps (or a dense of less than two)
             if (!il.dma && !il.lp && il.avec && !stem && !gates && x2 < 0 && x_extent + halo < lim && pack.bytes < lim && !plan.opts.no_dma) {
                 il.dma = il.taps = 1;
@@ -556,7 +558,7 @@ struct Planner {
             const int nk = (p.K + 8 * KV - 1) / (8 * KV);
             // from 8 K tiles on (fewer: the adding launch costs more than the serial K loop); slices of at least two K tiles
             int want = (int)std::min<int64_t>(std::min<int64_t>(16, 256 / std::max<int64_t>(tiles, 1)), nk / 2);
-            if (tiles > 64 && tiles < 512 && nk >= 8) {
+            if (tiles > 64 && tiles < 512 && nk >= 8 && !plan.lean) {
                 // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
                 // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22)
                 double best = 1e30;
@@ -569,6 +571,7 @@ struct Planner {
                 const int per = (nk + want - 1) / want;
                 il.splits = (nk + per - 1) / per;
                 p.splits = il.splits; p.split_tiles = per;
+                plan.spent = true;
                 part_buf = new_ws((size_t)il.splits * p.M * p.N * 4);
                 bytes += 2.0 * il.splits * p.M * (double)p.N * 4;
             }
@@ -995,7 +998,7 @@ struct Planner {
     {
         const int va = o.in[0], vb = o.in[1];
         const rl_type &ta = T(va), &tb = T(vb);
-        if (plan.opts.no_wgrad || g.values[va].role == ROLE_PARAM || g.values[vb].role == ROLE_PARAM) return false;
+        if (plan.lean || plan.opts.no_wgrad || g.values[va].role == ROLE_PARAM || g.values[vb].role == ROLE_PARAM) return false;
         const bool conv = o.kind == RL_OP_CONV2D_GRAD_W;
         const int64_t P = conv ? ta.dims[0] * ta.dims[2] * ta.dims[3] : ta.dims[0], T_ = conv ? numel(T(o.out[0])) / (ta.dims[1] * tb.dims[1]) : 1;
         const double macs = (double)P * ta.dims[1] * tb.dims[1] * T_;
@@ -1008,6 +1011,7 @@ struct Planner {
 
     rl_status plan_tn(int gi, int oi)
     {
+        plan.spent = true;
         const OpNode &o = g.ops[oi];
         const int va = o.in[0], vb = o.in[1], vy = o.out[0];
         const rl_type &ta = T(va), &tb = T(vb), &ty = T(vy);

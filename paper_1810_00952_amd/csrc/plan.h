@@ -66,6 +66,8 @@ struct Plan {
     std::map<int, PackSpec> packs;       // param value id -> packing
     size_t workspace_bytes = 0;
     rl_plan_opts opts{};                 // the caller's plan-time switches, fixed at creation
+    bool lean = false;                   // set before build_plan: none of the choices that trade workspace for time
+    bool spent = false;                  // set by build_plan: at least one of them was made
 };
 
 rl_status build_plan(const Graph &g, Plan &plan, std::string &msg);

@@ -41,13 +41,14 @@ extern "C" rl_status rl_plan_run_static(const rl_plan *plan, const rl_binding *b
 {
     if (!plan) return RL_ERR_NULL;
     const std::shared_ptr<rl::ErrBox> &err = plan->p.err;
-    if (plan->p.workspace_bytes > (size_t)RL_STATIC_WORKSPACE_BYTES) {
-        if (err) err->set("plan needs a workspace of " + std::to_string(plan->p.workspace_bytes) + " bytes, the built-in one holds " +
+    const rl::Plan &p = plan->small ? *plan->small : plan->p;
+    if (p.workspace_bytes > (size_t)RL_STATIC_WORKSPACE_BYTES) {
+        if (err) err->set("plan needs a workspace of " + std::to_string(p.workspace_bytes) + " bytes, the built-in one holds " +
                           std::to_string((size_t)RL_STATIC_WORKSPACE_BYTES) + ": use rl_plan_run with a workspace of the caller's");
         return RL_ERR_WORKSPACE;
     }
     void *ws = nullptr;
-    if (plan->p.workspace_bytes > 0) {
+    if (p.workspace_bytes > 0) {
         const hipError_t er = scratch_address(&ws);
         if (er != hipSuccess) {
             if (err) err->set(std::string("address of the built-in workspace: ") + hipGetErrorString(er));
@@ -55,5 +56,18 @@ extern "C" rl_status rl_plan_run_static(const rl_plan *plan, const rl_binding *b
         }
     }
     // every byte of the workspace a step reads was written by an earlier step of the same run: nothing to clear
-    return rl_plan_run(plan, bindings, n_bindings, ws, ws ? (size_t)RL_STATIC_WORKSPACE_BYTES : 0, hip_stream);
+    try {
+        std::vector<rl_binding> own;
+        if (plan->small && bindings && n_bindings > 0) {
+            own.assign(bindings, bindings + n_bindings);
+            for (rl_binding &b : own) {
+                auto it = plan->p.packs.find(b.value_id);
+                if (it != plan->p.packs.end() && b.dev_ptr) b.dev_ptr = (char *)b.dev_ptr + rl::small_offset(it->second);
+            }
+            bindings = own.data();
+        }
+        return rl::run_bound(p, bindings, n_bindings, ws, ws ? (size_t)RL_STATIC_WORKSPACE_BYTES : 0, hip_stream);
+    } catch (const std::bad_alloc &) {
+        return RL_ERR_WORKSPACE;
+    }
 }

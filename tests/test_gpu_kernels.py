@@ -213,3 +213,30 @@ def test_lstm_sequences_on_two_streams_do_not_wait_for_each_other():
     for i in range(2):
         np.testing.assert_array_equal(got[i][0], alone[i][0])
         np.testing.assert_array_equal(got[i][1], alone[i][1])
+
+
+# plans whose quicker forms (padded rows, weight gradients over rows) need more than the built-in workspace: the allocation-free
+# entry point runs the form that fits, from its own packed weights behind the plan's
+@pytest.mark.parametrize("case", ["conv", "grad_w"])
+def test_built_in_workspace_holds_a_smaller_form(case):
+    import torch
+    from paper_1810_00952_amd import binding, harness
+    if case == "conv":
+        spec, data = W.conv_group(64, 53, 384, 53, 53, 1, 2, 0, "bf16")
+        dtype = "bf16"
+    else:
+        spec, data = W.grad_case("conv2d_grad_w", (32, 235, 36, 36, 24, 1), "f32", 1, 0, second_is_param=False)
+        dtype = "f32"
+    s = harness.Session(spec); s.load(data); s.alloc()
+    assert s.plan.workspace_bytes() > binding.STATIC_WORKSPACE_BYTES
+    ref = OG.run(spec, data)[spec.outputs[0]]
+    budget = (lambda: error_budget(spec, data)[spec.outputs[0]]) if dtype == "f32" else None
+    for static in (False, True):
+        print(case, static, flush=True)
+        s.output().zero_()
+        if static:
+            s.plan.run_static({vid: t.data_ptr() for vid, t in s.tensors.items()}, harness.stream_handle())
+        else:
+            s.run()
+        torch.cuda.synchronize()
+        assert_close(O.widen(harness.to_host(s.output()), dtype), ref, dtype, f"{case} static={static}", budget=budget)
