@@ -283,7 +283,8 @@ rl_status rl_calibrate_mfma_bf16(rl_ctx *ctx, void *scratch_dev, int32_t workgro
  * cell's x input is x_seq_dev + t*x_step_bytes, its h input is h0_dev (t = 0)
  * or the previous step's h output, its c input/output is c_dev (updated in
  * place; the caller initialises it), and its h output is written to
- * h_seq_dev + t*h_step_bytes.  `bindings` supplies the params.  The value ids
+ * h_seq_dev + t*h_step_bytes.  h0_dev may lie inside h_seq_dev, at any step's
+ * slot but the first (a sequence continued in the same buffer from its last state).  `bindings` supplies the params.  The value ids
  * name the cell graph's values playing each role. */
 typedef struct rl_recurrent {
     int32_t x_id, h_in_id, c_in_id, h_out_id, c_out_id;

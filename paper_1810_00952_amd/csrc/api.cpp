@@ -68,6 +68,21 @@ const Step *hoistable_cell(const Plan &p)
 size_t hoist_bytes_per_step(const Step &s) { return (size_t)s.ig.M * s.ig.N * sizeof(float); }
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
+// Where the sequence kernel keeps the projections that its control words displace: a step's slot of h_seq, which that step writes
+// at the end.  h0 may be one of the slots (a sequence continued from the last state of the one before, in the same buffer) and is
+// read at step 0.
+uint32_t *lstm_seq_save_slot(const LstmSeqParams &q)
+{
+    char *const last = (char *)q.h_seq + (size_t)(q.T - 1) * q.h_step_bytes;
+    return (uint32_t *)(q.h0 == last ? last - q.h_step_bytes : last);
+}
+// h0 apart from h_seq or one of its slots: the sequence kernel's workgroups keep step 0 and the later ones apart row by row only
+bool h0_keeps_rows(const rl_recurrent &io, int64_t steps, size_t bytes)
+{
+    const uintptr_t h0 = (uintptr_t)io.h0_dev, lo = (uintptr_t)io.h_seq_dev, hi = lo + (size_t)(steps - 1) * io.h_step_bytes + bytes;
+    return h0 + bytes <= lo || h0 >= hi || (h0 >= lo && (h0 - lo) % io.h_step_bytes == 0);
+}
+
 rl_status resolve(const Plan &p, const rl_binding *b, int32_t nb, void *ws, size_t ws_bytes, std::vector<void *> &ptrs, std::string &msg)
 {
     const int nv = (int)p.values.size();
@@ -493,7 +508,7 @@ rl_status rl_plan_run_recurrent(const rl_plan *cell, int32_t steps, const rl_rec
                     // the recurrent part of the chunk as one launch that keeps the weights in registers; not while the stream is being
                     // captured (a graph's replays need not run cooperative launches one at a time)
                     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-                    if (p.opts.no_seq != 1 && lstm_seq_ok(B, H, tc) && (!bias || bias_dt == DT_F32) && ptrs[hs->slot[SL_CIN]] == ptrs[hs->slot[SL_COUT]] &&
+                    if (p.opts.no_seq != 1 && lstm_seq_ok(B, H, tc) && h0_keeps_rows(*io, steps, (size_t)B * H * 2) && (!bias || bias_dt == DT_F32) && ptrs[hs->slot[SL_CIN]] == ptrs[hs->slot[SL_COUT]] &&
                         hipStreamIsCapturing((hipStream_t)stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
                         LstmSeqParams q{};
                         q.h0 = t0 == 0 ? io->h0_dev : (const void *)((const char *)io->h_seq_dev + (size_t)(t0 - 1) * io->h_step_bytes);
@@ -501,8 +516,8 @@ rl_status rl_plan_run_recurrent(const rl_plan *cell, int32_t steps, const rl_rec
                         q.w = g.w; q.w_bytes = (uint32_t)((uint64_t)g0.N * g0.Kp * 2);
                         q.zx = zx; q.bias = (const float *)bias; q.c = (float *)ptrs[hs->slot[SL_COUT]];
                         q.ctl = (uint32_t *)(zx + (size_t)(tc - 1) * B * g.N);
-                        q.save = (uint32_t *)((char *)q.h_seq + (size_t)(tc - 1) * io->h_step_bytes);
                         q.B = (int32_t)B; q.H = (int32_t)H; q.Kp = g0.Kp; q.k_off = (int32_t)I; q.T = (int32_t)tc;
+                        q.save = lstm_seq_save_slot(q);
                         q.spins = p.opts.no_seq == 2 ? 0 : 20000;
                         er = launch_lstm_seq(q, (hipStream_t)stream);
                         if (er == hipSuccess) continue;

@@ -222,7 +222,7 @@ struct LstmSeqParams {
     const float *zx;                    // [T][B][4H] f32
     const float *bias;                  // [4H] f32 in declaration order, or null
     float *c;                           // [B, H] f32, updated in place
-    uint32_t *ctl, *save;               // control words (at zx of step T-1) and where what they displace is kept (at h of step T-1)
+    uint32_t *ctl, *save;               // control words (at zx of step T-1) and where what they displace is kept (a slot of h_seq that is not h0)
     int32_t B, H, Kp, k_off, T, spins;  // spins: polls for the other workgroups before a workgroup goes on alone
 };
 bool lstm_seq_ok(int64_t B, int64_t H, int64_t T);

@@ -26,7 +26,7 @@
 // "alone"; so does anyone whose bounded wait for the others runs out.  Alone, a workgroup takes sixteen batch rows through the
 // whole sequence by itself (weights fetched every step: slow, but it waits for nobody).
 // The control words live where step T-1's projections of batch row 0 begin (scratch); what they displace was saved at the start
-// of h_{T-1} by the launch before and is fetched into LDS before registering.
+// of h_{T-1} (of h_{T-2} where h0 lies there) by the launch before and is fetched into LDS before registering.
 #include "device_utils.h"
 
 namespace rl {

@@ -150,7 +150,7 @@ def test_bf16_long_k_on_few_tiles(case):
 
 
 # ---- a whole sequence in one launch (lstm_seq.hip) ---------------------------------------------------------------------------
-def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None):
+def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None, h0_slot=None):
     import torch
     from paper_1810_00952_amd import harness
     spec = W.lstm_cell_graph(B, I, H, "bf16", True)
@@ -160,6 +160,9 @@ def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None):
     h0 = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda:0") if h0 is None else harness.to_device(h0, "bf16")
     c = torch.zeros((B, H), dtype=torch.float32, device="cuda:0") if c0 is None else harness.to_device(c0, "f32")
     hs = torch.full((T, B, H), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    if h0_slot is not None:
+        hs[h0_slot] = h0
+        h0 = hs[h0_slot]
     ws = torch.empty(max(256, s.plan.recurrent_workspace_bytes(room or T)), dtype=torch.uint8, device="cuda:0")
     n = s.by_name
     roles = {"x": n["x"], "h_in": n["h"], "c_in": n["c"], "c_out": spec.outputs[0], "h_out": spec.outputs[1]}
@@ -191,6 +194,21 @@ def test_lstm_sequence_in_one_launch(case):
     again = run_sequence(T, B, I, H, d, None, room, c0, h0)
     np.testing.assert_array_equal(first[0], again[0])
     np.testing.assert_array_equal(first[1], again[1])
+
+
+# a sequence continued from the last state of the one before, in the same buffer: h0 is the slot that the last step will write
+@pytest.mark.parametrize("room", [None, 16])
+def test_lstm_sequence_from_the_last_slot_of_its_own_results(room):
+    import numpy as np
+    T, B, I, H = 33, 9, 128, 1024
+    d = W.lstm_data(T, B, I, H, "bf16")
+    h0 = W.as_dtype(np.random.default_rng(12).uniform(-1, 1, (B, H)), "bf16")
+    ref_h, ref_c = O.lstm_sequence(O.widen(d["x"], "bf16"), O.widen(d["w"], "bf16"), O.widen(d["b"], "f32"), O.widen(h0, "bf16"), np.zeros((B, H)), h_dtype="bf16")
+    for at in (None, T - 1, 1):
+        print(f"sequence from slot {at}, room {room}", flush=True)
+        h, c = run_sequence(T, B, I, H, d, None, room, None, h0, at)
+        assert_close(h, ref_h, "bf16", f"sequence h, h0 in slot {at}")
+        assert_close(c, ref_c, "bf16", f"sequence c, h0 in slot {at}")
 
 
 def test_lstm_sequences_on_two_streams_do_not_wait_for_each_other():
