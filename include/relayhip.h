@@ -210,8 +210,8 @@ typedef struct rl_plan_opts {
                                steps (contraction, adding launch, small layer) instead of letting the adding launch run
                                the small layer too */
     int32_t no_seq;         /* rl_plan_run_recurrent, hoisted form: 1: one launch per step, never one for the whole sequence; 2: the
-                               one-launch form with every workgroup on its own (what it falls back to where its workgroups are
-                               not all resident at once) */
+                               one-launch form without waiting for all of its workgroups to be resident: those that are there
+                               share the work (what it falls back to); n > 2: on its first n workgroups.  All give the same bits */
 } rl_plan_opts;
 
 /* rl_plan_create re-checks the whole graph (Type-Call on every call, group legality, outputs reachable), picks
@@ -299,7 +299,9 @@ typedef struct rl_recurrent {
  * contraction up front and each step only runs the recurrent part (h_{t-1} . Wh^T and the gates).  With less
  * (but room for at least 8 steps' projections) the steps are processed in chunks; with only
  * rl_plan_workspace_bytes the cell plan is replayed once per step.  For every other cell the value equals
- * rl_plan_workspace_bytes.  Results of the forms agree to summation order.  Host call; errors: RL_ERR_NULL,
+ * rl_plan_workspace_bytes.  The per-step part of the hoisted form is one launch per step, or one for a whole chunk (bf16, hidden
+ * size 256, 512, 768 or 1024, at most 128 rows; not on a stream that is being captured or was given a part of the
+ * CUs): the same bits either way.  Hoisted and replayed results agree to summation order.  Host call; errors: RL_ERR_NULL,
  * RL_ERR_BINDING (negative steps). */
 rl_status rl_plan_recurrent_workspace_bytes(const rl_plan *cell, int32_t steps, size_t *bytes);
 rl_status rl_plan_run_recurrent(const rl_plan *cell, int32_t steps, const rl_recurrent *io,

@@ -85,6 +85,13 @@ __device__ __forceinline__ float tanhf_(float x)
     return copysignf(t, x);
 }
 
+// One LSTM unit: the gates' sums i, f, g, o and c, which becomes c'; returns h'.  Written out, so that every kernel rounds alike.
+__device__ __forceinline__ float lstm_cell_(const float (&z)[4], float &c)
+{
+    c = __builtin_fmaf(sigmoidf_(z[1]), c, sigmoidf_(z[0]) * tanhf_(z[2]));
+    return sigmoidf_(z[3]) * tanhf_(c);
+}
+
 // operand-free steps
 __device__ __forceinline__ float unary_step(int op, float v)
 {

@@ -210,9 +210,8 @@ __global__ __launch_bounds__(256) void lstm_step_kernel(const LstmStepParams p)
                 for (int w = 0; w < 4; ++w) a += ((const float *)(lds + w * NSTAGE * STAGE))[row * PSTRIDE + 8 * g + j];
                 z[g] = (a + zx_r[s][g]) + bias_r[s][g];
             }
-            const float cn = sigmoidf_(z[1]) * c_r[s] + sigmoidf_(z[0]) * tanhf_(z[2]);
-            const float hn = sigmoidf_(z[3]) * tanhf_(cn);
-            p.c_out[(int64_t)m * p.H + unit] = cn;
+            const float hn = lstm_cell_(z, c_r[s]);
+            p.c_out[(int64_t)m * p.H + unit] = c_r[s];
             store_from_f32(p.h_out, p.h_dtype, (int64_t)m * p.H + unit, hn);
         }
     }

@@ -150,7 +150,7 @@ def test_bf16_long_k_on_few_tiles(case):
 
 
 # ---- a whole sequence in one launch (lstm_seq.hip) ---------------------------------------------------------------------------
-def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None, h0_slot=None):
+def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None, h0_slot=None, capture=False):
     import torch
     from paper_1810_00952_amd import harness
     spec = W.lstm_cell_graph(B, I, H, "bf16", True)
@@ -166,8 +166,18 @@ def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None, h0_slot=
     ws = torch.empty(max(256, s.plan.recurrent_workspace_bytes(room or T)), dtype=torch.uint8, device="cuda:0")
     n = s.by_name
     roles = {"x": n["x"], "h_in": n["h"], "c_in": n["c"], "c_out": spec.outputs[0], "h_out": spec.outputs[1]}
-    s.plan.run_recurrent(T, roles, x.data_ptr(), B * I * 2, h0.data_ptr(), c.data_ptr(), hs.data_ptr(), B * H * 2,
-                         {n["w"]: s.tensors[n["w"]].data_ptr(), n["b"]: s.tensors[n["b"]].data_ptr()}, ws.data_ptr(), ws.numel(), harness.stream_handle())
+
+    def run():
+        s.plan.run_recurrent(T, roles, x.data_ptr(), B * I * 2, h0.data_ptr(), c.data_ptr(), hs.data_ptr(), B * H * 2,
+                             {n["w"]: s.tensors[n["w"]].data_ptr(), n["b"]: s.tensors[n["b"]].data_ptr()}, ws.data_ptr(), ws.numel(), harness.stream_handle())
+    if capture:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run()
+        graph.replay()
+    else:
+        run()
     torch.cuda.synchronize()
     return O.widen(harness.to_host(hs), "bf16"), O.widen(harness.to_host(c), "f32")
 
@@ -190,10 +200,23 @@ def test_lstm_sequence_in_one_launch(case):
         h, c = run_sequence(T, B, I, H, d, opts, room, c0, h0)
         assert_close(h, ref_h, "bf16", f"sequence h {case} {opts}")
         assert_close(c, ref_c, "bf16", f"sequence c {case} {opts}")
-    first = run_sequence(T, B, I, H, d, None, room, c0, h0)
-    again = run_sequence(T, B, I, H, d, None, room, c0, h0)
-    np.testing.assert_array_equal(first[0], again[0])
-    np.testing.assert_array_equal(first[1], again[1])
+    # one result whichever form runs it: a launch per step, and one launch whose workgroups are all there, whoever is there, or too
+    # few (one XCD a workgroup short, two blocks each, XCDs with none, three in all)
+    first = run_sequence(T, B, I, H, d, {"no_seq": 1}, room, c0, h0)
+    for no_seq in (0, 0, 2, H // 4 - 1, H // 8 + 3, 9, 3):
+        print(f"sequence {case} bits, no_seq {no_seq}", flush=True)
+        again = run_sequence(T, B, I, H, d, {"no_seq": no_seq}, room, c0, h0)
+        np.testing.assert_array_equal(first[0], again[0])
+        np.testing.assert_array_equal(first[1], again[1])
+
+
+def test_lstm_sequence_captured_and_eager_agree():
+    import numpy as np
+    T, B, I, H = 16, 64, 128, 1024
+    d = W.lstm_data(T, B, I, H, "bf16")
+    eager, captured = run_sequence(T, B, I, H, d), run_sequence(T, B, I, H, d, capture=True)
+    np.testing.assert_array_equal(eager[0], captured[0])
+    np.testing.assert_array_equal(eager[1], captured[1])
 
 
 # a sequence continued from the last state of the one before, in the same buffer: h0 is the slot that the last step will write
