@@ -300,7 +300,7 @@ typedef struct rl_recurrent {
  * (but room for at least 8 steps' projections) the steps are processed in chunks; with only
  * rl_plan_workspace_bytes the cell plan is replayed once per step.  For every other cell the value equals
  * rl_plan_workspace_bytes.  The per-step part of the hoisted form is one launch per step, or one for a whole chunk (bf16, hidden
- * size 256, 512, 768 or 1024, at most 128 rows; not on a stream that is being captured or was given a part of the
+ * size 256, 512, 768 or 1024, at most 128 rows, from 12 or 16 steps on; not on a stream that is being captured or was given a part of the
  * CUs): the same bits either way.  Hoisted and replayed results agree to summation order.  Host call; errors: RL_ERR_NULL,
  * RL_ERR_BINDING (negative steps). */
 rl_status rl_plan_recurrent_workspace_bytes(const rl_plan *cell, int32_t steps, size_t *bytes);

@@ -42,7 +42,6 @@ namespace rl {
 namespace {
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-#define RL_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
 __device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
 {
@@ -346,7 +345,14 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 RL_INST(8) RL_INST(16) RL_INST(24) RL_INST(32)
 #undef RL_INST
 
-bool lstm_seq_ok(int64_t B, int64_t H, int64_t T) { return B >= 1 && B <= 16 * N_XCD && H >= 256 && H <= 1024 && H % 256 == 0 && T >= 8; }
+// From 16 steps on, or 12 where a step's own launch (H / 8 x B / 32 workgroups) does not fit on the 256 CUs at once: entering and
+// fetching the weights take as long as 8 to 10 steps.  Step by step / in one launch, us with the projections: 16 steps of 1 x 1024
+// units 84 / 77, 64 x 1024 98 / 94, 64 x 256 76 / 58; 12 steps 65 / 73, 77 / 87, 58 / 54, of 128 x 768 103 / 90; 8 steps 45 / 66,
+// 57 / 76, 41 / 50, 72 / 78.
+bool lstm_seq_ok(int64_t B, int64_t H, int64_t T)
+{
+    return B >= 1 && B <= 16 * N_XCD && H >= 256 && H <= 1024 && H % 256 == 0 && T >= (H / 8 * ((B + 31) / 32) > 256 ? 12 : 16);
+}
 
 // A stream that was given a part of the CUs gets the launches of a step each: a cooperative launch goes out on a queue of its own,
 // which need not keep to that part.
