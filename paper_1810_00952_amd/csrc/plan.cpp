@@ -1055,12 +1055,13 @@ struct Planner {
             const double share = es == 2 ? (tl == 128 ? 1330 : 390) : (tl == 128 ? 4550 : 1100);
             for (int sp = 1; sp <= std::min(nk, 512); ++sp) {
                 const int per = (nk + sp - 1) / sp;
-                if ((nk + per - 1) / per != sp || (int64_t)sp * p.M * p.N >= (int64_t)1 << 27) continue;
+                if ((nk + per - 1) / per != sp || (sp > 1 && (int64_t)sp * p.M * p.N >= (int64_t)1 << 27)) continue;     // partial sums below 512 MB
                 const double cost = per * std::max(alone, share * (double)((tiles * sp + 255) / 256)) + 4000.0 +
                                     (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
                 if (cost < best) { best = cost; tile = tl; p.splits = sp; p.split_tiles = per; }
             }
         }
+        if (p.splits < 1) return fail(RL_ERR_UNSUPPORTED, "internal: no tile for the contraction over rows");
         const int part = p.splits > 1 ? new_ws((size_t)p.splits * p.M * p.N * 4) : -1;
         const int ybuf = out_buf(vy, L_NATIVE);
         p.y_dtype = ty.dtype;

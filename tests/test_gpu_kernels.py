@@ -37,6 +37,7 @@ ROWS_CASES = [
     ("conv2d_grad_w", (12, 128, 23, 21, 200, 1), 2, 0),   # the strided projection
     ("conv2d_grad_w", (1, 512, 7, 7, 512, 3), 1, 1),     # one K tile and a remainder, many tiles: no slices
     ("conv2d_grad_w", (40, 128, 36, 1, 72, 3), 1, 1),    # rows of one pixel
+    ("dense_grad_w", (4, 16384, 8192), 1, 0),            # as many results as partial sums may be: one slice
 ]
 
 
