@@ -567,11 +567,12 @@ struct Planner {
                     if (c < best * 0.95) { best = c; want = sp; }
                 }
             }
-            if (tiles < 512 && nk >= 8 && want >= 2 && (int64_t)want * p.M * p.N * 4 < (int64_t)1 << 28) {
+            // a lean plan splits up to 64 tiles only, as the smallest-workspace form always did
+            if (tiles < (plan.lean ? 65 : 512) && nk >= 8 && want >= 2 && (int64_t)want * p.M * p.N * 4 < (int64_t)1 << 28) {
                 const int per = (nk + want - 1) / want;
                 il.splits = (nk + per - 1) / per;
                 p.splits = il.splits; p.split_tiles = per;
-                plan.spent = true;
+                plan.spent |= tiles > 64;
                 part_buf = new_ws((size_t)il.splits * p.M * p.N * 4);
                 bytes += 2.0 * il.splits * p.M * (double)p.N * 4;
             }

@@ -215,6 +215,16 @@ def test_static_entry_point_refuses_plans_beyond_its_workspace():
     assert B.lib().rl_plan_run_static(None, None, 0, None) == -1
 
 
+def test_static_entry_point_takes_plans_that_fit_without_splits():
+    # the second layer's 96 tiles are cut along K where the caller pays for the partial sums (23.6 MB with them, 15.7 without)
+    spec = W.mlp(6144, 64, 640, 64, dtype="f32")[0]
+    plan = B.Plan(B.graph_from_spec(B.Context(), spec))
+    assert plan.workspace_bytes() > B.STATIC_WORKSPACE_BYTES
+    with pytest.raises(B.RelayError) as ei:
+        plan.run_static({0: 0x1000}, 0)               # no GPU, or not every value bound: refused, but not for the workspace
+    assert ei.value.category != "workspace", ei.value
+
+
 def test_recurrent_call_rejects_mismatched_roles_on_the_host():
     fake = 0x10000
     ctx = B.Context()
