@@ -67,11 +67,12 @@ __device__ __forceinline__ void mma_chunk(f32x16 &acc, const u32x4 &a, const u32
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
 
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
-// vmcnt = bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
-template <int N> __device__ __forceinline__ void wait_vmcnt()
+// The wave's direct loads but the last N have landed and its own LDS reads are done, then the workgroup barrier.  Without the
+// second wait the compiler leaves the reads of the tile just multiplied in flight across the barrier, and the loads requested
+// behind it go into that tile's stage: an out-of-range one (zeros, no memory latency) can overtake them.
+template <int N> __device__ __forceinline__ void wait_barrier()
 {
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
 __device__ __forceinline__ void wg_barrier()
@@ -280,12 +281,11 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
 
     // ---- K loop, three stages, unrolled by three so that every stage use names its array.
     // Tile kt lives in stage kt % 3.  Body: wait until my DMAs of tile kt have landed (the LPT
-    // issued after them, for tile kt+1, may still fly), barrier, issue tile kt+2 into the stage
+    // issued after them, for tile kt+1, may still fly) and my reads of tile kt-1 are done, barrier, issue tile kt+2 into the stage
     // tile kt-1 just left, MFMAs on tile kt.
 #define RL_BODY(CUR, NXT)     \
     {                         \
-        wait_vmcnt<LPT>();    \
-        wg_barrier();         \
+        wait_barrier<LPT>();  \
         RL_ISSUE(NXT)         \
         RL_COMPUTE(CUR)       \
     }
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
         RL_BODY(st0, st2)
         if (kt + 1 < nk) RL_BODY(st1, st0)
     }
-    wait_vmcnt<0>();           // the trailing out-of-range issues
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");           // the trailing out-of-range issues, the last tile's reads
 #undef RL_BODY
 #undef RL_COMPUTE
 #undef RL_ISSUE
