@@ -253,8 +253,12 @@ rl_status rl_plan_run(const rl_plan *plan, const rl_binding *bindings, int32_t n
 /* rl_plan_run without a workspace argument, for callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the intermediates live in an array of
  * RL_STATIC_WORKSPACE_BYTES that is part of the library's code object (each GPU the library runs on holds one copy
- * until the process ends).  Plans with rl_plan_workspace_bytes above that return RL_ERR_WORKSPACE.  The call
- * allocates nothing on the device and otherwise behaves like rl_plan_run (same kernels, same results, same errors).
+ * until the process ends).  A plan whose rl_plan_workspace_bytes are more than that holds, where one fits, a second form
+ * made without the choices that trade workspace for time (padded rows, contractions cut along K on larger grids, weight
+ * gradients over rows); this call then runs that form: other kernels, results equal to summation order.  rl_plan_describe
+ * and rl_plan_workspace_bytes speak of the first form, rl_plan_packed_bytes counts a param that the second reads laid out
+ * otherwise in both layouts.  Where no form fits the call returns RL_ERR_WORKSPACE.  It allocates nothing on the device
+ * and otherwise behaves like rl_plan_run (for plans that fit: same kernels, same results; same errors).
  * All calls on one GPU share the array: two calls that may overlap in time (different streams or threads) race;
  * serialise them or use rl_plan_run with workspaces of the caller's. */
 #define RL_STATIC_WORKSPACE_BYTES (16u << 20)

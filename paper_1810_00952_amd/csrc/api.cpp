@@ -303,10 +303,10 @@ rl_status rl_plan_create(rl_graph *g, const rl_plan_opts *opts, rl_plan **out)
             q->opts = p->p.opts;
             q->lean = true;
             if (build_plan(g->g, *q, msg) == RL_OK && q->workspace_bytes <= (size_t)RL_STATIC_WORKSPACE_BYTES) {
-                bool same = q->packs.size() == p->p.packs.size();      // both read every param either packed or as given
+                // which params are read packed does not depend on those choices, only how; were it otherwise there would be no second form
+                bool same = q->packs.size() == p->p.packs.size();
                 for (auto &k : q->packs) same &= p->p.packs.count(k.first) != 0;
                 if (same) p->small = std::move(q);
-                else p->p = std::move(*q);
             }
         }
         *out = p;
@@ -353,7 +353,8 @@ rl_status rl_plan_packed_bytes(const rl_plan *plan, int32_t v, size_t *bytes)
     if (v < 0 || v >= (int)plan->p.values.size() || plan->p.values[v].role != ROLE_PARAM)
         return fail(plan->p.err, RL_ERR_BINDING, "not a param value id");
     auto it = plan->p.packs.find(v);
-    *bytes = it == plan->p.packs.end() ? 0 : plan->small ? small_offset(it->second) + plan->small->packs.at(v).bytes : it->second.bytes;
+    const PackSpec *second = second_pack(*plan, v);
+    *bytes = it == plan->p.packs.end() ? 0 : second ? small_offset(it->second) + second->bytes : it->second.bytes;
     return RL_OK;
 }
 
@@ -373,7 +374,8 @@ rl_status rl_plan_prepack(const rl_plan *plan, int32_t v, const void *src, void 
                           : launch_pack_weight(src, to, k.dtype, k.O, k.C, k.T, k.Kp, k.perm_block, (hipStream_t)stream);
         };
         hipError_t er = pack(it->second, dst);
-        if (er == hipSuccess && plan->small) er = pack(plan->small->packs.at(v), (char *)dst + small_offset(it->second));
+        const PackSpec *second = second_pack(*plan, v);
+        if (er == hipSuccess && second) er = pack(*second, (char *)dst + small_offset(it->second));
         if (er != hipSuccess) return fail(err, RL_ERR_HIP, std::string("pack_weight: ") + hipGetErrorString(er));
         return RL_OK;
     });

@@ -3,6 +3,7 @@
 #pragma once
 #include <map>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "graph.h"
@@ -54,6 +55,14 @@ struct PackSpec {
     int pw = 0;                         // stem = 2: the convolution's left padding (its parity shifts the filter inside the 8-pixel window)
     int gather = 0; GatherPack gp{};   // gather = 1: launch_pack_gather (operands of the gradient operators)
     size_t bytes = 0;
+    bool operator==(const PackSpec &o) const
+    {
+        auto all = [](const PackSpec &k) {
+            return std::make_tuple(k.dtype, k.O, k.C, k.T, k.Kp, k.perm_block, k.stem, k.KH, k.KW, k.pw, k.gather, k.bytes, k.gp.dtype, k.gp.R, k.gp.Kp,
+                                   k.gp.T, k.gp.Cq, k.gp.TW, k.gp.base, k.gp.s_row, k.gp.s_c, k.gp.s_ti, k.gp.s_tj, k.gp.Creal);
+        };
+        return all(*this) == all(o);
+    }
 };
 
 struct Plan {

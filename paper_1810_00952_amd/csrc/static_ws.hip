@@ -61,8 +61,7 @@ extern "C" rl_status rl_plan_run_static(const rl_plan *plan, const rl_binding *b
         if (plan->small && bindings && n_bindings > 0) {
             own.assign(bindings, bindings + n_bindings);
             for (rl_binding &b : own) {
-                auto it = plan->p.packs.find(b.value_id);
-                if (it != plan->p.packs.end() && b.dev_ptr) b.dev_ptr = (char *)b.dev_ptr + rl::small_offset(it->second);
+                if (b.dev_ptr && rl::second_pack(*plan, b.value_id)) b.dev_ptr = (char *)b.dev_ptr + rl::small_offset(plan->p.packs.at(b.value_id));
             }
             bindings = own.data();
         }

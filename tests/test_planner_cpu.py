@@ -225,6 +225,22 @@ def test_static_entry_point_takes_plans_that_fit_without_splits():
     assert ei.value.category != "workspace", ei.value
 
 
+def test_params_are_packed_twice_only_where_the_built_in_workspace_needs_another_layout():
+    # a layer of 53 channels, padded to 56 in the plan and as it is in the form that fits the built-in workspace, then one that both
+    # read alike
+    g = W.GraphSpec("two_layers")
+    x, w1, w2 = g.input("x", "bf16", (64, 53, 53, 53)), g.param("w1", "bf16", (64, 53, 3, 3)), g.param("w2", "bf16", (24, 64, 3, 3))
+    at = dict(stride=(2, 2), pad=(1, 1))
+    o, (y,) = g.op("conv2d", [x, w1], [("bf16", (64, 64, 27, 27))], **at); g.group([o])
+    o, (y,) = g.op("conv2d", [y, w2], [("bf16", (64, 24, 14, 14))], **at); g.group([o])
+    g.output(y)
+    plan = B.Plan(B.graph_from_spec(B.Context(), g))
+    assert plan.workspace_bytes() > B.STATIC_WORKSPACE_BYTES
+    assert plan.packed_bytes(w2) == 24 * 64 * 9 * 2
+    own = 64 * 56 * 9 * 2
+    assert own <= plan.packed_bytes(w1) <= own + 255 + 64 * 480 * 2
+
+
 def test_recurrent_call_rejects_mismatched_roles_on_the_host():
     fake = 0x10000
     ctx = B.Context()
