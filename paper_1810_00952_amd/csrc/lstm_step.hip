@@ -192,9 +192,7 @@ __global__ __launch_bounds__(256) void lstm_step_kernel(const LstmStepParams p)
             for (int k = 0; k < 4; ++k) v[k] = acc[i][4 * g + k];
             *(f32x4 *)(park + (32 * i + frow) * PSTRIDE + 8 * g + 4 * fhalf) = v;
         }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the parked tile is there before anyone reads it
 
     // ---- gate arithmetic: gate g of unit j sits in gate column 8g + j of every wave's partial tile
 #pragma unroll

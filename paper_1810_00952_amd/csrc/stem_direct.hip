@@ -44,11 +44,10 @@ __device__ __forceinline__ void dma4(const u32x4 &desc, uint32_t lds_addr, uint3
 
 #define RL_WAIT_VM(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
 
+// The wave's own LDS operations are done (what it wrote is there for the others, what it read may be overwritten), then the barrier.
 __device__ __forceinline__ void wg_barrier()
 {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 __device__ __forceinline__ uint32_t lds_addr_of(const void *p)
