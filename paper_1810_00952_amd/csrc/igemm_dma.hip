@@ -266,17 +266,20 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) f_off[ks] = frow * 128 + (((2 * ks + fhalf) ^ ((frow >> 1) & 7)) << 4);
 
+    // All of a tile's reads before its first MFMA: they are done while the MFMAs run, and the wait before the next barrier costs nothing.
 #define RL_COMPUTE(ST)                                                                                                \
     {                                                                                                                 \
+        u32x4 fa[4][TM], fb[4][TN];                                                                                   \
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                                            \
-            u32x4 fa[TM], fb[TN];                                                                                     \
             _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                            \
-                fa[i] = *(const u32x4 *)(ST + (wm * WTM + i * 32) * 128 + f_off[ks]);                                 \
+                fa[ks][i] = *(const u32x4 *)(ST + (wm * WTM + i * 32) * 128 + f_off[ks]);                             \
             _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                            \
-                fb[j] = *(const u32x4 *)(ST + A_BYTES + (wn * WTN + j * 32) * 128 + f_off[ks]);                       \
-            _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                            \
-                _Pragma("unroll") for (int j = 0; j < TN; ++j) mma_chunk(acc[i][j], fa[i], fb[j], T());               \
+                fb[ks][j] = *(const u32x4 *)(ST + A_BYTES + (wn * WTN + j * 32) * 128 + f_off[ks]);                   \
         }                                                                                                             \
+        __builtin_amdgcn_sched_barrier(0);                                                                            \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                              \
+            _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                            \
+                _Pragma("unroll") for (int j = 0; j < TN; ++j) mma_chunk(acc[i][j], fa[ks][i], fb[ks][j], T());       \
     }
 
     // ---- K loop, three stages, unrolled by three so that every stage use names its array.
