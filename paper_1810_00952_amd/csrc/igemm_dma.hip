@@ -115,6 +115,10 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform by construction; keep it in an SGPR
     const int wm = wave >> 1, wn = wave & 1;
 
+    // The kernel arguments that the first request hangs on, fetched together; left to itself the compiler asks for some of them
+    // behind the arithmetic on others (dense 1000 x 1000 x 784 bf16 8.94 -> 8.62 us, two-layer classifier f32 12.52 -> 12.43).
+    asm volatile("" :: "s"(p.nblk_m), "s"(p.nblk_n), "s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kp), "s"(p.K1), "s"(p.C), "s"(p.H), "s"(p.W), "s"(p.KH), "s"(p.KW),
+                 "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw), "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.splits), "s"(p.split_tiles));
     // consecutive workgroup ids go to different XCDs; give each XCD a contiguous run of tiles
     const int nblk = p.nblk_m * p.nblk_n;
     int bid = blockIdx.x;

@@ -82,7 +82,6 @@ struct IgemmParams {
     uint32_t seg_stride;                   // bytes between the two 64-byte halves of an A row's K tile (64: contiguous)
     int64_t ts_h, ts_w;                    // element strides of one filter-tap step (xs_h, xs_w unless the taps are regrouped)
     uint32_t div_ohw_mul, div_ohw_sh, div_ow_mul, div_ow_sh;   // m / OHW and pix / OW by multiply-high (make_fast_div)
-    uint32_t div_c_mul, div_c_sh, div_kw_mul, div_kw_sh;       // k / C and tap / KW (direct-load variant, K tiles that span taps)
     uint32_t tap_rep;                      // bit kh*KW set for every kh < KH (KH*KW <= 32)
     // K split over `splits` workgroups per tile (direct-load variant only; 0 or 1: no split): workgroup (tile, z)
     // multiplies K tiles [z*per, (z+1)*per) and writes its fp32 sums to partial[z][M][N]; a second kernel adds the
@@ -94,6 +93,7 @@ struct IgemmParams {
     int32_t splits, split_tiles;           // split_tiles: K tiles per slice
     float *partial;
     int32_t skip_reduce;                   // direct-load variant, splits > 1: the slices are added by the caller's next launch
+    uint32_t div_c_mul, div_c_sh, div_kw_mul, div_kw_sh;       // k / C and tap / KW (direct-load variant, K tiles that span taps)
 };
 // q = n / d for n < 2^31:  d == 1 ? n : (mulhi(n, mul) >> sh)
 void make_fast_div(uint32_t d, uint32_t &mul, uint32_t &sh);
