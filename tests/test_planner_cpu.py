@@ -438,6 +438,16 @@ def test_layout_transform_kernel_choice():
 
 
 # ---------------------------------------------------------------- K split over workgroups (host logic only)
+def test_channels_are_padded_only_where_the_copy_pays():
+    # the copy is written whole, whatever the layer reads of it: not for a 1x1 layer at stride 2, nor for one channel of f32
+    for args, padded in (((32, 467, 9, 50, 50, 1, 2, 0, "f32"), False), ((64, 1, 20, 28, 28, 5, 1, 0, "f32"), False),
+                         ((17, 93, 136, 29, 29, 3, 1, 1, "f32"), True), ((17, 93, 136, 29, 29, 3, 1, 1, "bf16"), True), ((64, 3, 64, 56, 56, 3, 1, 1, "bf16"), True)):
+        spec = W.conv_group(*args, make_x=False)[0]
+        assert any("padded" in kernel for _, kernel in _plan_steps(spec)) == padded, (args, _plan_steps(spec))
+        if not padded:
+            assert B.Plan(B.graph_from_spec(B.Context(), spec)).workspace_bytes() == 0
+
+
 def test_large_weight_gradients_are_planned_in_one_slice():
     # results of 2^27 elements and more: too large for partial sums, so one slice; bf16 on the larger tile (a plan without any
     # slice kept the smaller one, which f32 takes here in any case)
