@@ -568,12 +568,16 @@ struct Planner {
             int want = (int)std::min<int64_t>(std::min<int64_t>(16, 256 / std::max<int64_t>(tiles, 1)), nk / 2);
             if (tiles > 64 && tiles < 512 && nk >= 8 && !plan.lean) {
                 // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
-                // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22)
-                double best = 1e30;
+                // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22).  The
+                // estimate is good to a fifth: over 700 layers, split where it promised less than that, 89 were slower than whole by
+                // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 9; few channels need a third
+                double whole = 0.0, best = 1e30;
                 for (int sp = 1; sp <= std::min(16, nk / 2); ++sp) {
                     const double c = (double)((nk + sp - 1) / sp) * tile_cost(il.tile, in_dt, tiles * sp) + (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
+                    if (sp == 1) whole = c;
                     if (c < best * 0.95) { best = c; want = sp; }
                 }
+                if (best > whole * (p.N < 16 ? 0.7 : 0.83)) want = 1;
             }
             // a lean plan splits up to 64 tiles only, as the smallest-workspace form always did
             if (tiles < (plan.lean ? 65 : 512) && nk >= 8 && want >= 2 && (int64_t)want * p.M * p.N * 4 < (int64_t)1 << 28) {
