@@ -146,6 +146,12 @@ struct TileEpilogue {
         const Epilogue &e = p.epi;
         const bool tload = e.t_op >= 0;
         const bool chan_fast = p.ys_c == 1;
+        const bool even_rows = p.ys_n == (int64_t)p.OHW * p.ys_p;        // images follow one another like pixels
+        auto row_off = [&](int m) -> int64_t {
+            if (even_rows) return (int64_t)m * p.ys_p;
+            const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+            return (int64_t)img * p.ys_n + (int64_t)(m - img * p.OHW) * p.ys_p;
+        };
         if (e.simple && chan_fast && p.N - n0 >= BN) {
             // channels fastest, N no multiple of eight, a whole tile of channels: a thread keeps its channel, four rows at a time
             constexpr int RS = 256 / BN;
@@ -158,8 +164,7 @@ struct TileEpilogue {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int m = mq + r0 + RS * i;
-                    const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
-                    off[i] = (int64_t)img * p.ys_n + (int64_t)(m - img * p.OHW) * p.ys_p + n;
+                    off[i] = row_off(m) + n;
                     v[i] = sC[(r0 + RS * i) * ldc + col];
                     bias[i] = b;
                     tt[i] = tload && m < p.M ? load_as_f32(e.t_ptr, e.t_dtype, off[i]) : 0.0f;
@@ -186,8 +191,7 @@ struct TileEpilogue {
                     const int idx = i0 + 256 * i, row = (int)(((uint32_t)idx * inv) >> 20), col = idx - row * cols;
                     const int m = mq + row, n = n0 + col;
                     const bool live = idx < total && m < p.M;
-                    const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
-                    off[i] = live ? (int64_t)img * p.ys_n + (int64_t)(m - img * p.OHW) * p.ys_p + n : -1;
+                    off[i] = live ? row_off(m) + n : -1;
                     v[i] = live ? sC[row * ldc + col] : 0.0f;
                     bias[i] = live && e.has_bias ? load_as_f32(e.bias_ptr, e.bias_dtype, n) : 0.0f;
                     tt[i] = live && tload ? load_as_f32(e.t_ptr, e.t_dtype, off[i]) : 0.0f;

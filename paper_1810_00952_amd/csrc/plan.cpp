@@ -569,8 +569,8 @@ struct Planner {
             if (tiles > 64 && tiles < 512 && nk >= 8 && !plan.lean) {
                 // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
                 // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22).  The
-                // estimate is good to a fifth: over 700 layers, split where it promised less than that, 89 were slower than whole by
-                // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 9; few channels need a third
+                // estimate is good to a sixth: over 700 layers, split where it promised less than that, 89 were slower than whole by
+                // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 17; few channels need a third
                 double whole = 0.0, best = 1e30;
                 for (int sp = 1; sp <= std::min(16, nk / 2); ++sp) {
                     const double c = (double)((nk + sp - 1) / sp) * tile_cost(il.tile, in_dt, tiles * sp) + (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
