@@ -456,8 +456,11 @@ struct Planner {
             // against 15.5; 36 K tiles are level, 15 us either way).
             const int64_t lp_tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
             if (il.lp && !stem && il.dma && p.K / bke >= 64 && lp_tiles >= 2 && lp_tiles <= 64 && !plan.opts.no_splitk && !plan.lean) il.lp = 0;
-            // everything else whose chunks are whole: K tiles that span taps (or a dense of less than two)
-            if (!il.dma && !il.lp && il.avec && !stem && !gates && x2 < 0 && x_extent + halo < lim && pack.bytes < lim && !plan.opts.no_dma) {
+            // everything else whose chunks are whole: K tiles that span taps (or a dense of less than two).  Not for bf16 results in whole
+            // rows of channels on 300 tiles of 128x128 and more: the register-staged kernel runs two such workgroups per CU (64x200x28x28
+            // -> 128 3x3: 74 us against 83, 128 such layers 1.05 on average; fewer tiles or channel-first results 0.72 to 0.94)
+            const bool many_rows = in_dt == RL_BF16 && p.ys_c == 1 && p.N > 64 && p.N % 8 == 0 && (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) >= 300;
+            if (!il.dma && !il.lp && il.avec && !stem && !gates && x2 < 0 && !many_rows && x_extent + halo < lim && pack.bytes < lim && !plan.opts.no_dma) {
                 il.dma = il.taps = 1;
                 make_fast_div((uint32_t)p.C, p.div_c_mul, p.div_c_sh);
                 make_fast_div((uint32_t)p.KW, p.div_kw_mul, p.div_kw_sh);
@@ -504,8 +507,9 @@ struct Planner {
         } else if (il.taps || (il.dma && in_dt == RL_F32)) {
             // by the padding of the last tiles and how the grid fills 256 CUs (tile_cost); the f32 MFMA takes so long that small
             // tiles cost nothing where they fill the chip better (16x128x28x28 -> 128 3x3: 128x64 67.8 us, 64x64 47.7)
+            // (bf16 across taps: never 128x128, one workgroup per CU; 48 layers that took it ran in 0.87 of its time on 128x64)
             double best = 1e30;
-            for (int i = TILE_128x128; i <= TILE_64x64; ++i) {
+            for (int i = il.taps && in_dt == RL_BF16 ? TILE_128x64 : TILE_128x128; i <= TILE_64x64; ++i) {
                 const double c = tile_cost(i, in_dt, nblk(i == TILE_64x64 ? 64 : 128, i == TILE_128x128 ? 128 : 64));
                 if (c < best) { best = c; il.tile = i; }
             }
