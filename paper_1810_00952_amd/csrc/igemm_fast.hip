@@ -260,14 +260,18 @@ __global__ __launch_bounds__(256) void igemm_fast_kernel(const IgemmParams p)
         TE::load_bias(p, t, n0, bias8);
         TE::prefetch(p, t, m0, n0, cur);
     }
+    if (!GATES && !vec_ok) {
 #pragma unroll 1
+        for (int q = 0; q < BM / 32; ++q) TE::store_pass_scalar(p, sC + q * 32 * ldc, ldc, t, m0 + q * 32, n0);      // rolled: inlined BM / 32 times it costs registers
+        return;
+    }
+#pragma unroll
     for (int q = 0; q < BM / 32; ++q) {
         if (pre && q + 1 < BM / 32) TE::prefetch(p, t, m0 + (q + 1) * 32, n0, nxt);
         const int mq = m0 + q * 32;
-        const float *sq = sC + q * 32 * ldc;
+        const float *sq = sC + q * 32 * LDC;
         if (GATES) TE::gates_pass(p, sq, LDC, t, mq, bn);
-        else if (vec_ok) TE::store_pass(p, sq, LDC, t, mq, n0, bias8, cur);
-        else TE::store_pass_scalar(p, sq, ldc, t, mq, n0);
+        else TE::store_pass(p, sq, LDC, t, mq, n0, bias8, cur);
         cur = nxt;
     }
 }
