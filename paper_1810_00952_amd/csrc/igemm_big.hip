@@ -254,7 +254,7 @@ hipError_t launch_igemm_big(const IgemmParams &p0, hipStream_t s)
     p.nblk_n = (p.N + 255) / 256;
     if (p.OHW == 1) p.xs_w = p.xs_n;             // elements from one row of A to the next: images of a dense, pixels of a convolution
     const int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
-    // rows of whole 16-byte chunks one after the other, an even number of K tiles, [f32 bias] [+ bf16 residual] [relu]
+    // rows of whole 16-byte chunks one after the other, whole K tiles, [f32 bias] [+ bf16 residual] [relu]
     if (p.in_dtype != DT_BF16 || p.x2 || p.KH * p.KW != 1 || p.sh != 1 || p.sw != 1 || p.ph || p.pw || p.K % 64 != 0 || p.K < 64 || p.K1 != p.K || p.xs_w % 8 || p.Kp % 8 ||
         p.N % 8 || p.ys_c != 1 || p.ys_n != (int64_t)p.OHW * p.ys_p || p.ys_p % 8 || (p.epi.rest_n > 0 && !p.epi.relu_last) ||
         (p.epi.t_op >= 0 && (p.epi.t_op != E_ADD || p.epi.t_dtype != DT_BF16 || p.y_dtype != DT_BF16)) || nblk <= 0 || nblk > 0x7fffffff ||
