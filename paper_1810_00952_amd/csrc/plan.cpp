@@ -223,16 +223,16 @@ struct Planner {
     // step of its own, for the vector-load kernels.  The element gather it takes otherwise needs no extra launch and is level
     // at a few K tiles on few workgroups (f32 dense 2 x 90 -> 8: 9 us either way; 10 x 1446 -> 128: 87 us against 16).  From
     // there on the copy, read and written whole at 3 MB per us, must cost less than the K tiles save: us per 64x64 tile and CU,
-    // less where the result's rows of channels are stored one element at a time; fitted to 2500 layers of 1 to 467 channels,
+    // less where the result's rows of channels are stored one element at a time; fitted to 3000 layers of 1 to 467 channels,
     // 1x1 to 7x7, stride 1 and 2, both source and both result layouts (LeNet's one-channel first layer 21 + 7 us padded, 22 as it
-    // is; 32 x 467 x 55 x 55 -> 64 1x1 at stride 2 267 against 194).  Over those the layers that padding slows down by more than
-    // 3 % went from 90 (by up to 1.7) to 14 (one by 1.19); it wins 1.7x f32 and 1.9x bf16 on the whole.
+    // is; 32 x 467 x 55 x 55 -> 64 1x1 at stride 2 267 against 194).  Of those the K tiles alone would have padded 85 that lose by
+    // more than 3 % (up to 1.7x), the copy's cost leaves 7 (up to 1.14x) and gives up 18; it wins 1.7x f32 and 2.0x bf16 on the whole.
     bool pad_k(int x, int wv, int C, int KV, int64_t M, int64_t N, int64_t K, bool concat, int64_t bytes_per_channel, bool slow_store) const
     {
         if (plan.lean || C % KV == 0 || concat || plan.opts.no_dma || g.values[x].role == ROLE_PARAM || consumers[wv].size() != 1) return false;
         const int64_t nk = (K + 8 * KV - 1) / (8 * KV), tiles = ((M + 63) / 64) * ((N + 63) / 64), ld = round_up(C, KV), lim = (int64_t)1 << 30;
         const int64_t nkp = (K / C * ld + 8 * KV - 1) / (8 * KV);
-        const double per_tile = KV == 4 ? 2.4 * nk - 0.6 * nkp - (slow_store ? 2.0 : 1.0) : 2.8 * K / 64.0 - 0.3 * nkp + (slow_store ? 0.0 : 1.0);
+        const double per_tile = KV == 4 ? 2.4 * nk - 0.6 * nkp - (slow_store ? 2.0 : 1.0) : 2.4 * (K / 64 + std::min(1.0, (double)(K % 64) / 8.0)) - 0.3 * nkp + (slow_store ? -1.0 : 0.5);
         const bool pays = (double)bytes_per_channel * (C + ld) / 3e6 < per_tile * (double)std::max<int64_t>(tiles, 256) / 256.0;
         const bool pad = (nk >= 4 || tiles * nk >= 512) && pays && bytes_per_channel * ld < lim && N * (K / C) * ld * 4 < lim && T(x).dims[0] <= 65535;
         plan.spent |= pad;
