@@ -4,8 +4,8 @@
 //
 // What bounds the one-launch-per-step form is not its arithmetic: 6.3 us per step, of which about 3 pass between dependent
 // launches and the rest fetching 128 KB per CU again (64 KB of weights that never change).  Here every CU keeps its weights in
-// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 2.7 us at 64 rows of
-// 1024 units (128 steps with their projections: 825 us step by step, 417 us here; 383 us if the 134 MB of projections still
+// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 2.3 us at 64 rows of
+// 1024 units (128 steps with their projections: 814 us step by step, 412 us here; 387 us if the 134 MB of projections still
 // stand in the last-level cache).  What is left of a step is a chain of latencies - the flags' poll, the L2 round trip for h,
 // the meeting of the partial sums, the gates, the store's acknowledgement - and not work: the MFMAs of a step take 0.3 us.
 //
