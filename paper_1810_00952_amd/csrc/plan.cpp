@@ -507,10 +507,11 @@ struct Planner {
         } else if (il.taps || (il.dma && in_dt == RL_F32)) {
             // by the padding of the last tiles and how the grid fills 256 CUs (tile_cost); the f32 MFMA takes so long that small
             // tiles cost nothing where they fill the chip better (16x128x28x28 -> 128 3x3: 128x64 67.8 us, 64x64 47.7)
-            // (bf16 across taps: never 128x128, one workgroup per CU; 48 layers that took it ran in 0.87 of its time on 128x64)
+            // (never 128x128: f32 has no gain from it, and bf16 across taps holds one such workgroup per CU; 48 layers that took it ran
+            // in 0.87 of its time on 128x64)
             double best = 1e30;
-            for (int i = il.taps && in_dt == RL_BF16 ? TILE_128x64 : TILE_128x128; i <= TILE_64x64; ++i) {
-                const double c = tile_cost(i, in_dt, nblk(i == TILE_64x64 ? 64 : 128, i == TILE_128x128 ? 128 : 64));
+            for (int i = TILE_128x64; i <= TILE_64x64; ++i) {
+                const double c = tile_cost(i, in_dt, nblk(i == TILE_64x64 ? 64 : 128, 64));
                 if (c < best) { best = c; il.tile = i; }
             }
         } else if (il.lp && p.N > 64 && nblk(256, 128) >= 190 && !plan.opts.no_lp_256) {
