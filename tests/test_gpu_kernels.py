@@ -191,8 +191,9 @@ def run_sequence(T, B, I, H, d, opts=None, room=None, c0=None, h0=None, h0_slot=
     c = torch.zeros((B, H), dtype=torch.float32, device="cuda:0") if c0 is None else harness.to_device(c0, "f32")
     hs = torch.full((T, B, H), float("nan"), dtype=torch.bfloat16, device="cuda:0")
     if h0_slot is not None:
-        hs[h0_slot] = h0
-        h0 = hs[h0_slot]
+        at = int(h0_slot * B * H)                         # a fraction: across two slots
+        hs.view(-1)[at:at + B * H] = h0.view(-1)
+        h0 = hs.view(-1)[at:at + B * H]
     ws = torch.empty(max(256, s.plan.recurrent_workspace_bytes(room or T)), dtype=torch.uint8, device="cuda:0")
     n = s.by_name
     roles = {"x": n["x"], "h_in": n["h"], "c_in": n["c"], "c_out": spec.outputs[0], "h_out": spec.outputs[1]}
@@ -257,7 +258,7 @@ def test_lstm_sequence_from_the_last_slot_of_its_own_results(room):
     d = W.lstm_data(T, B, I, H, "bf16")
     h0 = W.as_dtype(np.random.default_rng(12).uniform(-1, 1, (B, H)), "bf16")
     ref_h, ref_c = O.lstm_sequence(O.widen(d["x"], "bf16"), O.widen(d["w"], "bf16"), O.widen(d["b"], "f32"), O.widen(h0, "bf16"), np.zeros((B, H)), h_dtype="bf16")
-    for at in (None, T - 1, 1):
+    for at in (None, T - 1, 1, T - 1.5):
         print(f"sequence from slot {at}, room {room}", flush=True)
         h, c = run_sequence(T, B, I, H, d, None, room, None, h0, at)
         assert_close(h, ref_h, "bf16", f"sequence h, h0 in slot {at}")
