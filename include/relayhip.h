@@ -212,6 +212,8 @@ typedef struct rl_plan_opts {
     int32_t no_seq;         /* rl_plan_run_recurrent, hoisted form: 1: one launch per step, never one for the whole sequence; 2: the
                                one-launch form without waiting for all of its workgroups to be resident: those that are there
                                share the work (what it falls back to); n > 2: on its first n workgroups.  All give the same bits */
+    int32_t no_direct;      /* never the contraction kernel that loads its operands straight into registers */
+    int32_t direct_all;     /* that kernel wherever it can run, for tests and measurements */
 } rl_plan_opts;
 
 /* rl_plan_create re-checks the whole graph (Type-Call on every call, group legality, outputs reachable), picks

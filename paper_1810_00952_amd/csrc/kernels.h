@@ -94,6 +94,9 @@ struct IgemmParams {
     float *partial;
     int32_t skip_reduce;                   // direct-load variant, splits > 1: the slices are added by the caller's next launch
     uint32_t div_c_mul, div_c_sh, div_kw_mul, div_kw_sh;       // k / C and tap / KW (direct-load variant, K tiles that span taps)
+    // igemm_direct.hip: 1: the result is the 2x2 / stride 2 max-pool of the contraction's; OW, OHW, ys_* then are of pooled
+    // pixels, M counts the four pixels of each
+    int32_t pool;
 };
 // q = n / d for n < 2^31:  d == 1 ? n : (mulhi(n, mul) >> sh)
 void make_fast_div(uint32_t d, uint32_t &mul, uint32_t &sh);
@@ -113,9 +116,13 @@ struct IgemmLaunch {
     int32_t splits;     // > 1 (with dma, no lp, no gates): K split over that many workgroups per tile (IgemmParams::splits)
     int32_t s2pair;     // 1 (first step of a pair): the pair runs as one stride-2 contraction with two accumulator sets (conv3x3s2.hip)
     int32_t big;        // 1 (with lp, tile 256x128): 256x256 tiles of a one-tap contraction (igemm_big.hip)
+    int32_t direct;     // > 0: operands straight into registers, K over a workgroup's waves (igemm_direct.hip), 1 + how A is read
+    int32_t direct_tile, direct_slices;     // ... its tile (32 or 16, square) and K slices (1, 2, 4, 8; 8 at tile 16)
     int32_t anyact;     // 1 (with lp, no ws / c64 / run / pair): operand-free steps other than one ReLU behind bias and residual
 };
 hipError_t launch_igemm(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
+enum { DIRECT_ROWS = 0, DIRECT_PLANES = 1, DIRECT_ANY = 2 };
+hipError_t launch_igemm_direct(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
 
 // The adding launch of a split dense contraction, and the small dense layer behind it, in one kernel: row m of
 //   h = epi1(partial[0][m][:] + partial[1][m][:] + ...)         (slices in order; rounded to h_dtype as the tensor between

@@ -234,9 +234,7 @@ struct Planner {
         const int64_t nkp = (K / C * ld + 8 * KV - 1) / (8 * KV);
         const double per_tile = KV == 4 ? 2.4 * nk - 0.6 * nkp - (slow_store ? 2.0 : 1.0) : 2.4 * (K / 64 + std::min(1.0, (double)(K % 64) / 8.0)) - 0.3 * nkp + (slow_store ? -1.0 : 0.5);
         const bool pays = (double)bytes_per_channel * (C + ld) / 3e6 < per_tile * (double)std::max<int64_t>(tiles, 256) / 256.0;
-        const bool pad = (nk >= 4 || tiles * nk >= 512) && pays && bytes_per_channel * ld < lim && N * (K / C) * ld * 4 < lim && T(x).dims[0] <= 65535;
-        plan.spent |= pad;
-        return pad;
+        return (nk >= 4 || tiles * nk >= 512) && pays && bytes_per_channel * ld < lim && N * (K / C) * ld * 4 < lim && T(x).dims[0] <= 65535;
     }
     // the weight packing and the contraction's sizes with C filled up to ld
     void pad_gather(PackSpec &pack, IgemmParams &p, const AnchorView *ov, int ld, int KV) const
@@ -248,6 +246,62 @@ struct Planner {
         pack.gp.dtype = p.in_dtype;
         pack.gp.Cq = ld; pack.gp.Creal = p.C;
         p.C = ld; p.K = p.K1 = ld * T_; p.Kp = (int)round_up(p.K, KV);
+    }
+
+    // Whether a contraction runs on the kernel without LDS tiles (igemm_direct.hip), with which tile and K slices (tile 0: no).
+    // By two estimates of the call in us, each fitted to 900 conv and dense layers of 1 to 50000 rows (rms 8 to 20 %): launches and
+    // latencies, the K steps of the fullest CU, and per workgroup what it starts and ends with.  `other` is the planner's next choice.
+    // Taken where it promises a seventh.  Over 1200 drawn graphs (no_direct / as planned): conv f32 0.76 of the time (half of the layers
+    // move, to 0.60), bf16 0.88, dense 0.77 and 0.88, LeNet's shape 0.58 and 0.66; of 424 that moved one lost more than 3 % (1.7x: 5x5
+    // at stride 2 from 240 channels, since then the `lines` below).
+    struct Direct { int tile = 0, slices = 0; };
+    enum OtherKind { OTHER_DMA = 0, OTHER_TAPS = 1, OTHER_GATHER = 2 };
+    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided) const
+    {
+        Direct best;
+        if (plan.opts.no_direct || M * N >= (int64_t)1 << 31) return best;
+        const bool bf16 = dtype == RL_BF16;
+        const int KV = kv_of(dtype), BKE = 8 * KV;
+        auto cd = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+        // start, per K step alone, per K step of 256 workgroups, per 256 workgroups, and per tile of theirs
+        static const double cost32[2][3][5] = {{{5.4, 0.17, 0.40, 0.0, 1.42}, {6.0, 0.13, 0.475, 0.2, 0.86}, {5.0, 0.53, 0.742, 0.37, 0.6}},
+                                               {{4.7, 0.31, 0.35, 0.27, 1.03}, {6.0, 0.60, 0.50, 0.39, 0.66}, {4.7, 0.81, 1.2, 0.0, 0.58}}};
+        static const double cost16[2][3][4] = {{{3.9, 0.17, 0.42, 1.0}, {5.1, 0.39, 0.40, 1.0}, {4.5, 0.64, 0.59, 0.85}},
+                                               {{3.8, 0.18, 0.40, 0.87}, {5.1, 0.73, 0.51, 0.5}, {5.3, 1.0, 1.3, 0.05}}};
+        double us = 1e30;
+        for (int form = 0; form < 5; ++form) {
+            const int tile = form < 4 ? 32 : 16, slices = form < 4 ? 1 << form : 8, wt = 8 / slices;
+            if (plan.opts.no_splitk && slices > 1) continue;
+            if (plan.opts.direct_all > 1 && (tile != plan.opts.direct_all / 16 || slices != plan.opts.direct_all % 16)) continue;
+            const double steps = (double)cd(cd(K, KV * (64 / tile)), slices), rounds = (double)(cd(M, tile * wt) * cd(N, tile)) / 256.0;
+            const double *c = tile == 32 ? cost32[bf16][mode] : cost16[bf16][mode];
+            // the chunk's tap; at a stride a tap's pixels fill half of their cache lines, and the next tap comes back for the rest too late
+            const double per = c[2] + (mode == DIRECT_ROWS && taps > 1 ? 0.1 : 0.0), lines = strided && mode != DIRECT_ROWS ? 1.0 + 0.02 * taps : 1.0;
+            const double t = c[0] + lines * std::max(c[1] * steps, per * steps * std::max(rounds, 1.0)) + (c[3] + (tile == 32 ? c[4] * wt : 0.0)) * rounds;
+            if (t < us) { us = t; best.tile = tile; best.slices = slices; }
+        }
+        if (plan.opts.direct_all) return best;
+        // the tiles and slices the other kernels would take (see below), in us of the fullest CU
+        const int64_t nk = cd(K, BKE), t128 = cd(M, 128) * cd(N, 64), t64 = cd(M, 64) * cd(N, 64);
+        const bool wide = tile_cost(TILE_128x64, dtype, t128) < tile_cost(TILE_64x64, dtype, t64);
+        const int tile = wide ? TILE_128x64 : TILE_64x64;
+        const int64_t tiles = wide ? t128 : t64;
+        double cyc = (double)nk * tile_cost(tile, dtype, tiles);
+        bool split = false;
+        if (nk >= 8 && !plan.opts.no_splitk && tiles < (plan.lean ? 65 : 512)) {
+            const double whole = cyc;
+            for (int64_t sp = 2; sp <= std::min<int64_t>(tiles <= 64 ? std::min<int64_t>(16, 256 / tiles) : 16, nk / 2); ++sp) {
+                const double t = (double)cd(nk, sp) * tile_cost(tile, dtype, tiles * sp) + (tiles > 64 ? 6500.0 : 0.0) + 8.0 * sp * M * (double)N / 2200.0;
+                if (t < cyc * 0.95 && (tiles <= 64 || t < whole * 0.83)) { cyc = t; split = true; }
+            }
+        }
+        static const double otherc[2][3][6] = {{{4.5, 1.04, 3.2, 2.8, 0.48, 0.63}, {5.0, 1.15, 3.5, 2.8, 0.35, 0.69}, {11.0, 2.3, 3.0, 0.0, 0.0, 1.09}},
+                                               {{3.9, 0.95, 4.3, 3.7, 0.95, 1.64}, {6.1, 1.11, 3.1, 2.1, 0.67, 1.52}, {15.5, 4.4, 5.0, 0.0, 0.0, 0.84}}};
+        const double *c = otherc[bf16][other];
+        const double theirs = c[0] + c[1] * cyc / 2100.0 + (split ? c[2] : 0.0) + (copies_x ? c[3] + c[4] * x_mbytes : 0.0) +
+                              c[5] * M * (double)N * dtype_size(dtype) / 1e6 - (rides && split ? 3.0 : 0.0);
+        // (few slices: short K on many tiles, where the stores decide and the estimates are at their worst)
+        return us < (best.slices < 4 && other != OTHER_GATHER ? 0.7 : 0.85) * theirs ? best : Direct();
     }
 
     rl_status plan_anchor(int gi, const std::vector<int> &ops, const AnchorView *ov = nullptr)
@@ -302,6 +356,8 @@ struct Planner {
         const bool relu_form = cls.rest_n == 0 || cls.relu_last;     // at most one ReLU behind them: every pixel-on-lane kernel; anything else: the general one
         const bool epi_lp = epi_any && relu_form;
         bool stem = false;
+        Direct direct;
+        int direct_mode = 0;
         const size_t lim = (size_t)1 << 31;
 
         if (akind == RL_OP_CONV2D) {
@@ -320,6 +376,16 @@ struct Planner {
             p.Kp = (int)round_up(p.K, KV);
             out_layout = (vout >= 0 && out_set.count(vout)) ? L_NATIVE : L_NHWC;
             flops = 2.0 * p.M * (double)p.N * p.K;
+            const int64_t bytes_per_channel = xt.dims[0] * (int64_t)p.H * p.W * dtype_size(in_dt);
+            const bool pad = !xov && pad_k(x, wv, p.C, KV, p.M, p.N, p.K, x2 >= 0, bytes_per_channel, out_layout == L_NHWC && p.N % 8 != 0);
+            if (vout >= 0 && x2 < 0 && !gates && x_own < lim && (size_t)p.N * p.Kp * dtype_size(in_dt) < lim) {
+                const bool last = xov || phys[L_NHWC][x] >= 0, vec = p.C % KV == 0;
+                direct_mode = !vec ? DIRECT_ANY : last ? DIRECT_ROWS : DIRECT_PLANES;
+                // bf16 channels in whole K tiles stay with the kernels that are made for them
+                if (in_dt == RL_F32 || p.C % 64 != 0 || plan.opts.direct_all)
+                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, !vec && !pad ? OTHER_GATHER : p.C % (8 * KV) == 0 ? OTHER_DMA : OTHER_TAPS,
+                                         (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1);
+            }
             // A bf16 result that is a graph output (Shape order): only the slower direct-load kernel stores in that order
             // itself.  From 0.4 GFLOP on, the pixel-on-lane kernels writing channel-last into the workspace plus a
             // transposition (one launch more, and one more for a channel-first residual) are faster: 64x128x28x28 through
@@ -340,6 +406,7 @@ struct Planner {
             stem = in_dt == RL_BF16 && p.C <= 4 && p.KW <= 8 && p.sw % 2 == 0 && KH2 <= 32 && epi_lp && vout >= 0 && T(vout).dtype == RL_BF16 &&
                    out_layout == L_NHWC && p.N % 8 == 0 && bytes_of(vout) < lim && frame < lim && phys[L_NATIVE][x] >= 0 && !plan.opts.no_stem && !ov;
             if (stem) {
+                direct = Direct();
                 int xnat;
                 st = need(x, L_NATIVE, xnat);
                 if (st != RL_OK) return st;
@@ -359,9 +426,10 @@ struct Planner {
                 il.avec = 1;
                 need_pack = true;
                 x_extent = frame;
-            } else if (!xov && pad_k(x, wv, p.C, KV, p.M, p.N, p.K, x2 >= 0, xt.dims[0] * (int64_t)p.H * p.W * dtype_size(in_dt), out_layout == L_NHWC && p.N % 8 != 0)) {
+            } else if (pad && !direct.tile) {
                 // a channel count that is no multiple of the vector: rows padded with zeros, weights likewise
                 int ld;
+                plan.spent = true;
                 st = need_rows(gi, x, xbuf, ld);
                 if (st != RL_OK) return st;
                 pad_gather(pack, p, ov, ld, KV);
@@ -374,7 +442,8 @@ struct Planner {
             } else {
                 il.avec = (p.C % KV == 0);
                 int xl;
-                if (il.avec || xov) xl = L_NHWC;
+                if (direct.tile) xl = xov || phys[L_NHWC][x] >= 0 ? L_NHWC : L_NATIVE;
+                else if (il.avec || xov) xl = L_NHWC;
                 else xl = phys[L_NATIVE][x] >= 0 ? L_NATIVE : L_NHWC;
                 if (xov) xbuf = ov->xbuf;
                 else st = need(x, xl, xbuf);
@@ -397,8 +466,22 @@ struct Planner {
             il.avec = (p.K1 % KV == 0) && (K2 % KV == 0);
             // a layer of at most 64 outputs behind another layer keeps its own rows: it may ride on that layer's adding launch
             const bool may_chain = p.N <= REDUCE_DENSE_MAX_N2 && g.values[x].producer >= 0;
-            if (!il.avec && !gates && !may_chain && pad_k(x, wv, p.K, KV, p.M, p.N, p.K, x2 >= 0, (int64_t)p.M * dtype_size(in_dt), false)) {
+            const bool pad = !il.avec && !gates && !may_chain && pad_k(x, wv, p.K, KV, p.M, p.N, p.K, x2 >= 0, (int64_t)p.M * dtype_size(in_dt), false);
+            if (vout >= 0 && x2 < 0 && !gates && bytes_of(x) < lim && (size_t)p.N * round_up(p.K, 8 * KV) * dtype_size(in_dt) < lim) {
+                // a split layer whose adding launch also runs the small layer behind it (chain_small_dense) is one launch for two already
+                const int next = !out_set.count(vout) && consumers[vout].size() == 1 ? consumers[vout][0] : -1;
+                const bool rides = next >= 0 && p.N <= REDUCE_DENSE_MAX_N1 && g.ops[next].kind == RL_OP_DENSE && T(g.ops[next].out[0]).dims[1] <= REDUCE_DENSE_MAX_N2 &&
+                                   !plan.opts.no_splitk;
+                const int64_t nk = (K + 8 * KV - 1) / (8 * KV);
+                direct_mode = il.avec ? DIRECT_ROWS : DIRECT_ANY;
+                // with up to 4 (bf16: 8) K tiles, more than 256 tiles of 32 x 32, or bf16 K in whole tiles, the kernels with LDS tiles are level or ahead
+                const bool lds = il.avec && (rides || nk <= (in_dt == RL_F32 ? 4 : 8) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256);
+                if (plan.opts.direct_all || (!lds && (in_dt == RL_F32 || p.K % 64 != 0)))
+                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false);
+            }
+            if (pad && !direct.tile) {
                 int ld;
+                plan.spent = true;
                 flops = 2.0 * p.M * (double)p.N * p.K;
                 st = need_rows(gi, x, xbuf, ld);
                 if (st != RL_OK) return st;
@@ -491,6 +574,15 @@ struct Planner {
             plan.packs[wv] = pack;
         } else if (plan.packs.count(wv)) {
             return fail(RL_ERR_UNSUPPORTED, "one param needs two different kernel-native layouts");
+        }
+
+        // (whether and how the weights are packed does not depend on this choice)
+        if (direct.tile) {
+            il = IgemmLaunch{};
+            il.direct = 1 + direct_mode;
+            il.direct_tile = direct.tile; il.direct_slices = direct.slices;
+            make_fast_div((uint32_t)p.C, p.div_c_mul, p.div_c_sh);
+            make_fast_div((uint32_t)p.KW, p.div_kw_mul, p.div_kw_sh);
         }
 
         // tile: the largest that still yields enough workgroups for 256 CUs
@@ -598,6 +690,11 @@ struct Planner {
         std::string kname = (ov ? std::string("igemm_") + op_name(an.kind) + "_" : std::string(akind == RL_OP_CONV2D ? "igemm_conv2d_" : "igemm_dense_")) + (in_dt == RL_BF16 ? "bf16_" : "f32_") +
                             (il.c64 ? "3x3_c64" : il.ws ? "128x64_ws" : il.big ? "256x256" : tile_names[il.tile]) + (il.c64 || il.ws ? "" : il.run ? "_run" : il.lp ? "_lp" : il.avec ? (il.dma ? (il.taps ? "_dma_taps" : "_dma") : "") : "_gather") + (gates ? "_gates" : "") +
                             (il.splits > 1 ? "_splitk" : "");
+        if (il.direct) {
+            const char *reads[] = {"", "_planes", in_dt == RL_F32 && p.C == 1 ? "_gather" : "_any"};
+            const std::string tl = std::to_string(il.direct_tile);
+            kname = kname.substr(0, kname.find(tile_names[il.tile])) + tl + "x" + tl + "_direct" + reads[il.direct - 1] + (il.direct_slices > 1 ? "_splitk" : "");
+        }
         Step &s = add_step(S_IGEMM, std::string(op_name(an.kind)) + "#" + std::to_string(ops[ai]), kname);
         s.group = gi;
         s.ig = p; s.il = il;
@@ -1268,6 +1365,7 @@ struct Planner {
             }
         }
         fuse_stem_pool();
+        fuse_direct_store();
         pair_contractions();
         chain_small_dense();
         assign_workspace();
@@ -1338,6 +1436,52 @@ struct Planner {
             if (direct) {
                 plan.steps.erase(plan.steps.begin() + (long)si - 1);
                 --si;
+            }
+        }
+    }
+
+    // A contraction on the kernel of igemm_direct.hip, which stores through any strides: a 2x2 / stride 2 max-pool of its result
+    // alone is taken over the finished values (same bits: max commutes with the rounding), and the change of layout that only
+    // moves its result becomes the way it stores.
+    void fuse_direct_store()
+    {
+        for (size_t si = 0; si + 1 < plan.steps.size(); ++si) {
+            Step &c = plan.steps[si];
+            if (c.kind != S_IGEMM || !c.il.direct) continue;
+            Epilogue e = c.ig.epi;
+            finalize_epilogue(e);
+            bool elementwise_only = true;                       // no operand of the result's shape (it would have the result's layout)
+            for (int i = 0; i < e.n_ops; ++i) elementwise_only &= epi_host_op(e, i) < E_ADD || epi_host_op(e, i) > E_RDIV;
+            if (!elementwise_only) continue;
+            while (si + 1 < plan.steps.size()) {
+                const Step &m = plan.steps[si + 1];
+                const int mid = c.slot[SL_Y];
+                if (mid < 0 || m.slot[SL_X] != mid || plan.bufs[mid].bound_value >= 0) break;
+                bool other_use = false;
+                for (size_t sj = 0; sj < plan.steps.size(); ++sj)
+                    if (sj != si && sj != si + 1)
+                        for (int b : plan.steps[sj].slot) other_use |= (b == mid);
+                if (other_use) break;
+                IgemmParams &p = c.ig;
+                const PoolParams &po = m.po;
+                if (m.kind == S_MAXPOOL && !p.pool && e.simple && p.ys_c == 1 && po.KH == 2 && po.KW == 2 && po.sh == 2 && po.sw == 2 && po.ph == 0 && po.pw == 0 &&
+                    po.H == p.OH && po.W == p.OW && po.C == p.N && po.dtype == p.y_dtype) {
+                    p.pool = 1;
+                    p.OH = po.OH; p.OW = po.OW; p.OHW = po.OH * po.OW;
+                    p.M = 4 * po.N * p.OHW;                      // the last row and column of an odd image are not computed
+                    p.ys_n = (int64_t)p.OHW * p.N;
+                    make_fast_div((uint32_t)p.OHW, p.div_ohw_mul, p.div_ohw_sh);
+                    make_fast_div((uint32_t)p.OW, p.div_ow_mul, p.div_ow_sh);
+                    c.kernel += "_maxpool";
+                } else if (m.kind == S_TO_NCHW && p.ys_c == 1 && p.ys_p == p.N) {
+                    p.ys_n = (int64_t)p.N * p.OHW; p.ys_p = 1; p.ys_c = p.OHW;
+                } else {
+                    break;
+                }
+                c.bytes += (double)plan.bufs[m.slot[SL_Y]].bytes - (double)plan.bufs[mid].bytes;
+                c.slot[SL_Y] = m.slot[SL_Y];
+                c.name += "+" + m.name;
+                plan.steps.erase(plan.steps.begin() + (long)si + 1);
             }
         }
     }

@@ -315,3 +315,93 @@ def test_built_in_workspace_holds_a_smaller_form(case):
             s.run()
         torch.cuda.synchronize()
         assert_close(O.widen(harness.to_host(s.output()), dtype), ref, dtype, f"{case} static={static}", budget=budget)
+
+
+# ---- operands straight into registers, K over the waves of a workgroup (igemm_direct.hip) ------------------------------------
+DIRECT_CASES = [
+    # batch cin cout h  w  k s p residual relu acts tail
+    (1, 64, 64, 56, 56, 3, 1, 1, False, True, (), False),      # planes read and written as they are
+    (3, 8, 33, 9, 11, 3, 1, 1, True, True, (), False),         # one channel past a tile; images of 99 pixels
+    (2, 72, 31, 13, 7, 5, 2, 2, True, False, ("tanh", "neg"), True),     # stride 2, channel-last result of odd rows
+    (1, 20, 50, 12, 12, 5, 1, 0, False, True, (), True),       # f32 vectors, bf16 element by element
+    (5, 7, 40, 10, 9, 3, 1, 1, True, True, ("sigmoid",), False),    # every element decoded, padding
+    (2, 1, 20, 28, 28, 5, 1, 0, False, False, ("tanh",), False),    # one channel
+    (4, 24, 16, 1, 1, 1, 1, 0, False, True, (), False),        # one pixel per image, fewer K steps than slices
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form", [32 * 16 + 1, 32 * 16 + 2, 32 * 16 + 4, 32 * 16 + 8, 16 * 16 + 8])
+def test_contractions_without_lds_tiles(dtype, form):
+    for case in DIRECT_CASES:
+        b, ci, co, h, w, k, s, p, res, relu, acts, tail = case
+        spec, data = W.conv_group(b, ci, co, h, w, k, s, p, dtype, residual=res, relu=relu, acts=acts, tail=tail)
+        assert any("_direct" in x for x in steps_of(spec, {"direct_all": form})), steps_of(spec, {"direct_all": form})
+        check(spec, data, dtype, f"direct {case} {dtype} {form}", {"direct_all": form})
+    for dims in ((1, 4, 8, 8), (33, 784, 130, 31), (70, 515, 17, 5), (129, 30, 64, 3)):
+        spec, data = W.mlp(*dims, dtype=dtype)
+        check(spec, data, dtype, f"direct mlp {dims} {dtype} {form}", {"direct_all": form})
+    # channel-last input, two layers (the second reads what the first wrote, channels fastest), channel-last output
+    spec, data = W.channel_last_block(2, 24, 9, 7, dtype)
+    check(spec, data, dtype, f"direct channel-last block {dtype} {form}", {"direct_all": form})
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("b,c,h,w,k,pool,tail", [(3, 12, 12, 14, 3, 2, False), (2, 33, 9, 11, 3, 2, True), (5, 6, 7, 7, 5, 2, False), (2, 8, 9, 9, 3, 3, False)])
+def test_max_pool_over_a_contraction_without_lds_tiles(dtype, b, c, h, w, k, pool, tail):
+    # odd images (their last row and column are in no window), values of both signs, the pooled result in Shape order and
+    # channel-last; 3x3 windows stay a kernel of their own.  The two-kernel form gives the same bits
+    import numpy as np
+    rng = np.random.default_rng(b * c)
+    g = W.GraphSpec("conv_pool")
+    oh, ow = h - k + 1, w - k + 1
+    shapes = dict(x=(b, 5, h, w), w=(c, 5, k, k))
+    data = {n: W.as_dtype(rng.standard_normal(s), dtype) for n, s in shapes.items()}
+    data["b"] = W.as_dtype(rng.uniform(-1, 1, c), "f32")
+    x, wv, bv = g.input("x", dtype, shapes["x"]), g.param("w", dtype, shapes["w"]), g.param("b", "f32", (c,))
+    o0, (y,) = g.op("conv2d", [x, wv], [(dtype, (b, c, oh, ow))])
+    o1, (y,) = g.op("bias_add", [y, bv], [(dtype, (b, c, oh, ow))], axis=1)
+    g.group([o0, o1])
+    q = (dtype, (b, c, (oh - pool) // pool + 1, (ow - pool) // pool + 1))
+    o, (y,) = g.op("maxpool2d", [y], [q], kernel=(pool, pool), stride=(pool, pool)); g.group([o])
+    if tail:
+        o, (y,) = g.op("neg", [y], [q]); g.group([o])
+    g.output(y)
+    opts = {"direct_all": 1}
+    assert any(s.endswith("_maxpool") for s in steps_of(g, opts)) == (pool == 2), steps_of(g, opts)
+    check(g, data, dtype, f"direct pool {dtype} {(b, c, h, w, k, pool)}", opts)
+    if pool == 2:
+        got, _ = run_hip(g, data, opts=opts)
+        # the contraction's result as an output too: the pool then is a kernel of its own
+        o_mid = g.ops[1].outputs[0]
+        g.output(o_mid)
+        assert not any(s.endswith("_maxpool") for s in steps_of(g, opts)), steps_of(g, opts)
+        apart, _ = run_hip(g, data, opts=opts)
+        np.testing.assert_array_equal(got[g.outputs[0]], apart[g.outputs[0]])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_contraction_with_k_split_over_workgroups_where_another_kernel_is_planned(dtype):
+    # the adding launch at the sizes the kernel without LDS tiles has taken over
+    for b, ci, co, h, w, k, s, p, res, tail in ((1, 256, 256, 14, 14, 3, 1, 1, True, False), (2, 64, 72, 9, 11, 3, 1, 1, True, False), (64, 20, 50, 12, 12, 5, 1, 0, False, False),
+                                                (3, 36, 24, 9, 7, 3, 2, 1, True, False), (2, 40, 40, 8, 8, 5, 1, 2, False, True)):
+        if dtype == "bf16" and ci % 8:
+            continue
+        spec, data = W.conv_group(b, ci, co, h, w, k, s, p, dtype, residual=res, tail=tail)
+        opts = {"no_direct": 1}
+        assert any(x.endswith("_splitk") for x in steps_of(spec, opts)) and not any("_direct" in x for x in steps_of(spec, opts)), steps_of(spec, opts)
+        check(spec, data, dtype, f"split-K {(b, ci, co, h, w)} {dtype}", opts)
+
+
+def test_one_param_read_by_layers_of_different_batches():
+    # one layer small enough for the kernel without LDS tiles, one not: both read the same packed weights
+    import numpy as np
+    rng = np.random.default_rng(4)
+    for k in (200, 203, 256):
+        g = W.GraphSpec("shared")
+        xs = [g.input("xa", "f32", (9, k)), g.input("xb", "f32", (3000, k))]
+        w = g.param("w", "f32", (500, k))
+        data = {"xa": W.as_dtype(rng.standard_normal((9, k)), "f32"), "xb": W.as_dtype(rng.standard_normal((3000, k)), "f32"), "w": W.as_dtype(rng.standard_normal((500, k)), "f32")}
+        for x, m in zip(xs, (9, 3000)):
+            o, (y,) = g.op("dense", [x, w], [("f32", (m, 500))]); g.group([o]); g.output(y)
+        check(g, data, "f32", f"shared param {k}")
