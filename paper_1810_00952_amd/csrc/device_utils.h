@@ -23,6 +23,19 @@ __device__ __forceinline__ void wave_lds_exchange()
 #endif
 }
 
+// One word of each cache line of a kernel's arguments (640 bytes at most), asked for together: the segment lies in memory that the host
+// wrote, and left to itself the compiler asks for an argument where it is used, one line after the other.
+template <typename P> __device__ __forceinline__ void touch_args(const P &p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(sizeof(P) > 256 && sizeof(P) <= 640, "lines to touch");
+    const uint32_t *w = (const uint32_t *)&p;
+    constexpr int last = (int)sizeof(P) / 4 - 1;
+    auto at = [&](int i) { return w[i < last ? i : last]; };
+    asm volatile("" :: "s"(at(0)), "s"(at(16)), "s"(at(32)), "s"(at(48)), "s"(at(64)), "s"(at(80)), "s"(at(96)), "s"(at(112)), "s"(at(128)), "s"(at(144)));
+#endif
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
 // round to nearest, ties to even; finite inputs (NaN maps to a quiet NaN)

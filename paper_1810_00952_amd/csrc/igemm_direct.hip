@@ -6,8 +6,8 @@
 // What bounds these calls is launches and latencies, not work: cut over workgroups the sums meet in a scratch tensor that a second
 // launch adds up, and a channel-first operand is copied first.  Here the whole call is one launch: a wave has eight K steps of both
 // operands in flight, the slices meet behind one barrier, and the operands of the epilogue are requested ahead of the products.
-// One image of 64x56x56 through 3x3 to 64 channels, f32: 17.5 us (copy, split contraction, adding launch) -> 9.7; LeNet's shape,
-// batch 64, 62 -> 34 (its max-pools and a change of layout ride along).
+// One image of 64x56x56 through 3x3 to 64 channels, f32: 17.5 us (copy, split contraction, adding launch) -> 8.8; LeNet's shape,
+// batch 64, 62 -> 28 (its max-pools and a change of layout ride along).
 // No LDS tile: a lane of an MFMA operand needs 16 bytes of its own row, and neighbouring lanes' rows lie apart, so that a load of 1 KB
 // occupies the vector L1 for about 50 cycles (8 waves' step 780 cycles on a CU, its f32 MFMAs 512).  That is what sends
 // larger contractions to the kernels with LDS tiles; Planner::direct_form has the line.
@@ -75,6 +75,10 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     constexpr int EPT = PER < 1 ? 1 : PER;
     __shared__ float part[WAVES][TS * LD];
 
+    touch_args(p);
+    // what the first request hangs on
+    asm volatile("" :: "s"(p.nblk_m), "s"(p.nblk_n), "s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kp), "s"(p.C), "s"(p.H), "s"(p.W), "s"(p.KH), "s"(p.KW), "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw),
+                 "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_c), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.pool));
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int slice = wave % KS, tw = wave / KS;
@@ -133,12 +137,12 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     };
     auto fetch = [&](int slot, int step) {
         const int k = (step * G + g) * KV;
-        fb[slot] = __builtin_amdgcn_raw_buffer_load_b128(rw, n_live && k < p.Kp && step < s1 ? b_off + (uint32_t)(k * ES) : OOB, 0, 0);
+        fb[slot] = __builtin_amdgcn_raw_buffer_load_b128(rw, n_live && k < p.Kp ? b_off + (uint32_t)(k * ES) : OOB, 0, 0);
         if constexpr (MODE == DIRECT_ANY) {
 #pragma unroll
-            for (int e = 0; e < KV; ++e) fa[slot][e] = load1(step < s1 ? a_at(k + e) : OOB);
+            for (int e = 0; e < KV; ++e) fa[slot][e] = load1(a_at(k + e));
         } else {
-            const uint32_t off = step < s1 ? a_at(k) : OOB;
+            const uint32_t off = a_at(k);
             if constexpr (MODE == DIRECT_ROWS) {
                 const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0);
 #pragma unroll
@@ -161,7 +165,8 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
         return v;
     };
 #pragma unroll
-    for (int i = 0; i < DEPTH; ++i) fetch(i, s0 + i);
+    for (int i = 0; i < DEPTH; ++i)
+        if (s0 + i < s1) fetch(i, s0 + i);           // (the wave's last steps take their chunks' addresses for nothing otherwise: most of a short K's time)
     __builtin_amdgcn_sched_barrier(0);               // all of them in flight before the first is used
 
     // ---- the results this thread finishes: lanes along the result's fastest axis, and along the other one a fixed step apart, so
@@ -208,7 +213,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
         for (int i = 0; i < DEPTH; ++i) {
             if (b + i >= steps) break;
             mma<T, TS>(acc, chunk_a(i), fb[i]);
-            fetch(i, s0 + b + i + DEPTH);
+            if (b + i + DEPTH < steps) fetch(i, s0 + b + i + DEPTH);
         }
     }
 #pragma unroll
