@@ -28,7 +28,7 @@ __device__ __forceinline__ void wave_lds_exchange()
 template <typename P> __device__ __forceinline__ void touch_args(const P &p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    static_assert(sizeof(P) > 256 && sizeof(P) <= 640, "lines to touch");
+    static_assert(sizeof(P) <= 640, "lines to touch");
     const uint32_t *w = (const uint32_t *)&p;
     constexpr int last = (int)sizeof(P) / 4 - 1;
     auto at = [&](int i) { return w[i < last ? i : last]; };

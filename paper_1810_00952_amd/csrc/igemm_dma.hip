@@ -95,6 +95,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
 {
     constexpr bool GATES = MODE == STORE_GATES;
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
+    touch_args(p);
     constexpr int KV = Elem<T>::KV;
     constexpr int ES = (int)sizeof(T);
     constexpr int BKE = 8 * KV;               // K elements per tile (128 bytes per row)
@@ -116,7 +117,8 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
     const int wm = wave >> 1, wn = wave & 1;
 
     // The kernel arguments that the first request hangs on, fetched together; left to itself the compiler asks for some of them
-    // behind the arithmetic on others (dense 1000 x 1000 x 784 bf16 8.94 -> 8.62 us, two-layer classifier f32 12.52 -> 12.43).
+    // behind the arithmetic on others (dense 1000 x 1000 x 784 bf16 8.94 -> 8.62 us, two-layer classifier f32 12.52 -> 12.43); the lines
+    // of all others above (8.54 -> 8.15; dense gradients 15.48 -> 15.11).  The longer kernels do not gain by it.
     asm volatile("" :: "s"(p.nblk_m), "s"(p.nblk_n), "s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kp), "s"(p.K1), "s"(p.C), "s"(p.H), "s"(p.W), "s"(p.KH), "s"(p.KW),
                  "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw), "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.splits), "s"(p.split_tiles));
     // consecutive workgroup ids go to different XCDs; give each XCD a contiguous run of tiles
@@ -404,6 +406,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
 // per thread, slices added in order (so the result does not depend on timing), any output strides.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const IgemmParams p)
 {
+    touch_args(p);
     const Epilogue &e = p.epi;
     const uint32_t total = (uint32_t)p.M * (uint32_t)p.N;            // below 2^31 (checked by the launcher): 32-bit index arithmetic
     for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
