@@ -118,6 +118,7 @@ struct IgemmLaunch {
     int32_t big;        // 1 (with lp, tile 256x128): 256x256 tiles of a one-tap contraction (igemm_big.hip)
     int32_t direct;     // > 0: operands straight into registers, K over a workgroup's waves (igemm_direct.hip), 1 + how A is read
     int32_t direct_tile, direct_slices;     // ... its tile (32 or 16, square) and K slices (1, 2, 4, 8; 8 at tile 16)
+    int32_t direct_units;                   // ... with gates: hidden units per workgroup (4 or 8)
     int32_t anyact;     // 1 (with lp, no ws / c64 / run / pair): operand-free steps other than one ReLU behind bias and residual
 };
 hipError_t launch_igemm(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);

@@ -594,6 +594,24 @@ struct Planner {
             if (Hd % 16 != 0) return fail(RL_ERR_UNSUPPORTED, "fused gate epilogue needs hidden size divisible by 16");
             p.hidden = (int)Hd;
             p.h_dtype = T(g.ops[ops.back()].out[1]).dtype;
+            const int64_t K2 = p.K - p.K1;
+            // the step without LDS tiles (igemm_direct.hip), except for bf16 cells that rl_plan_run_recurrent may hoist, and where the
+            // direct-load kernel is ahead, which fetches its fragments once per 64 rows (2048 x 256 units from 256, f32: 27 us against 52; 512:
+            // 17.3 against 16.2; bf16 9.6 and 10.3).  Estimates in us: 50 cycles a load on either side of 16 rows and 4 units, a K tile per tile_cost.
+            const int64_t rows16 = ((int64_t)p.M + 15) / 16;
+            const int units = rows16 * (Hd / 16) < 64 ? 4 : 8;       // measured 4 / 8 / 16 at 32 to 63 blocks of 16 x 16: 0.18 / 0.22 / 0.33 of the gather's time, at 64 to 127 0.32 / 0.28 / 0.42
+            const double direct_us = 3.6 + (double)(rows16 * Hd / 8) / 256.0 * (double)(p.K / (4 * KV)) * 200.0 / 2100.0;
+            const double dma_us = 5.5 + (double)(p.K / (8 * KV)) * tile_cost(TILE_64x64, in_dt, (p.M + 63) / 64 * (Hd / 16)) / 2100.0;
+            const bool keep = il.dma && (in_dt == RL_BF16 ? p.K1 >= 128 || dma_us < direct_us : dma_us < direct_us);
+            if (x2 >= 0 && p.K1 % KV == 0 && K2 % KV == 0 && x_extent < lim && bytes_of(x2) < lim && pack.bytes < lim && chain.epi.n_ops <= 1 && p.M <= 65535 * 16 && !plan.opts.no_direct &&
+                (!keep || plan.opts.direct_all)) {
+                il = IgemmLaunch{};
+                il.tile = TILE_64x64;
+                il.gates = il.direct = 1;
+                il.direct_tile = 16; il.direct_slices = 8;
+                il.direct_units = plan.opts.direct_all > 1 ? (plan.opts.direct_all % 16 == 4 ? 4 : 8) : units;
+                p.w_bytes = (uint32_t)pack.bytes;
+            }
         } else if (!il.avec) {
             il.tile = TILE_64x64;
         } else if (il.taps || (il.dma && in_dt == RL_F32)) {
@@ -693,7 +711,7 @@ struct Planner {
         if (il.direct) {
             const char *reads[] = {"", "_planes", in_dt == RL_F32 && p.C == 1 ? "_gather" : "_any"};
             const std::string tl = std::to_string(il.direct_tile);
-            kname = kname.substr(0, kname.find(tile_names[il.tile])) + tl + "x" + tl + "_direct" + reads[il.direct - 1] + (il.direct_slices > 1 ? "_splitk" : "");
+            kname = kname.substr(0, kname.find(tile_names[il.tile])) + tl + "x" + (gates ? std::to_string(4 * il.direct_units) : tl) + "_direct" + reads[il.direct - 1] + (gates ? "_gates" : il.direct_slices > 1 ? "_splitk" : "");
         }
         Step &s = add_step(S_IGEMM, std::string(op_name(an.kind)) + "#" + std::to_string(ops[ai]), kname);
         s.group = gi;

@@ -405,3 +405,22 @@ def test_one_param_read_by_layers_of_different_batches():
         for x, m in zip(xs, (9, 3000)):
             o, (y,) = g.op("dense", [x, w], [("f32", (m, 500))]); g.group([o]); g.output(y)
         check(g, data, "f32", f"shared param {k}")
+
+
+# ---- the recurrent cell without LDS tiles ---------------------------------------------------------------------------------------
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,I,H,opts", [(1, 8, 16, {}), (17, 96, 48, {}), (5, 656, 80, {}), (33, 24, 272, {}), (70, 104, 336, {}), (129, 40, 144, {}), (9, 128, 64, {"direct_all": 1}),
+                                        (48, 16, 32, {"direct_all": 4}), (16, 200, 64, {"direct_all": 8})])
+def test_recurrent_cell_without_lds_tiles(dtype, B, I, H, opts):
+    # a step whose x and h end inside a K tile, one unit block and many, rows past a tile of 16, both widths of a workgroup
+    import numpy as np
+    spec = W.lstm_cell_graph(B, I, H, dtype, True)
+    assert steps_of(spec, opts)[0].endswith("_direct_gates"), steps_of(spec, opts)
+    rng = np.random.default_rng(B + H)
+    data = {"x": W.as_dtype(rng.standard_normal((B, I)), dtype), "h": W.as_dtype(rng.standard_normal((B, H)) / 2, dtype), "c": W.as_dtype(rng.standard_normal((B, H)), "f32"),
+            "w": W.as_dtype(rng.uniform(-1, 1, (4 * H, I + H)) * H ** -0.5, dtype), "b": W.as_dtype(rng.uniform(-1, 1, 4 * H) * H ** -0.5, "f32")}
+    print(f"cell {dtype} {B} {I} {H}", flush=True)
+    ref = OG.run(spec, data)
+    got, _ = run_hip(spec, data, opts=opts)
+    for v in spec.outputs:
+        assert_close(got[v], ref[v], spec.values[v].type.dtype, f"cell {dtype} {(B, I, H)}")
