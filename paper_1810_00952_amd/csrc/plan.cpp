@@ -256,7 +256,7 @@ struct Planner {
     // at stride 2 from 240 channels, since then the `lines` below).
     struct Direct { int tile = 0, slices = 0; };
     enum OtherKind { OTHER_DMA = 0, OTHER_TAPS = 1, OTHER_GATHER = 2 };
-    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided) const
+    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided, bool paired) const
     {
         Direct best;
         if (plan.opts.no_direct || M * N >= (int64_t)1 << 31) return best;
@@ -299,9 +299,18 @@ struct Planner {
                                                {{3.9, 0.95, 4.3, 3.7, 0.95, 1.64}, {6.1, 1.11, 3.1, 2.1, 0.67, 1.52}, {15.5, 4.4, 5.0, 0.0, 0.0, 0.84}}};
         const double *c = otherc[bf16][other];
         const double theirs = c[0] + c[1] * cyc / 2100.0 + (split ? c[2] : 0.0) + (copies_x ? c[3] + c[4] * x_mbytes : 0.0) +
-                              c[5] * M * (double)N * dtype_size(dtype) / 1e6 - (rides && split ? 3.0 : 0.0);
+                              c[5] * M * (double)N * dtype_size(dtype) / 1e6 - (rides && split ? 3.0 : 0.0) - (paired ? 3.5 : 0.0);
         // (few slices: short K on many tiles, where the stores decide and the estimates are at their worst)
         return us < (best.slices < 4 && other != OTHER_GATHER ? 0.7 : 0.85) * theirs ? best : Direct();
+    }
+
+    // the gradient with respect to the input may go out with the one with respect to the weights (pair_gradients)
+    bool beside_weights_gradient(int dy) const
+    {
+        if (plan.opts.no_pair || plan.lean) return false;
+        for (int c : consumers[dy])
+            if ((g.ops[c].kind == RL_OP_DENSE_GRAD_W || g.ops[c].kind == RL_OP_CONV2D_GRAD_W) && g.ops[c].in[0] == dy && tn_ok(g.ops[c])) return true;
+        return false;
     }
 
     rl_status plan_anchor(int gi, const std::vector<int> &ops, const AnchorView *ov = nullptr)
@@ -384,7 +393,7 @@ struct Planner {
                 // bf16 channels in whole K tiles stay with the kernels that are made for them
                 if (in_dt == RL_F32 || p.C % 64 != 0 || plan.opts.direct_all)
                     direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, !vec && !pad ? OTHER_GATHER : p.C % (8 * KV) == 0 ? OTHER_DMA : OTHER_TAPS,
-                                         (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1);
+                                         (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1, ov && beside_weights_gradient(x));
             }
             // A bf16 result that is a graph output (Shape order): only the slower direct-load kernel stores in that order
             // itself.  From 0.4 GFLOP on, the pixel-on-lane kernels writing channel-last into the workspace plus a
@@ -477,7 +486,7 @@ struct Planner {
                 // with up to 4 (bf16: 8) K tiles, more than 256 tiles of 32 x 32, or bf16 K in whole tiles, the kernels with LDS tiles are level or ahead
                 const bool lds = il.avec && (rides || nk <= (in_dt == RL_F32 ? 4 : 8) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256);
                 if (plan.opts.direct_all || (!lds && (in_dt == RL_F32 || p.K % 64 != 0)))
-                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false);
+                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false, ov && beside_weights_gradient(x));
             }
             if (pad && !direct.tile) {
                 int ld;
@@ -1385,6 +1394,7 @@ struct Planner {
         fuse_stem_pool();
         fuse_direct_store();
         pair_contractions();
+        pair_gradients();
         chain_small_dense();
         assign_workspace();
         return RL_OK;
@@ -1535,6 +1545,74 @@ struct Planner {
             a.name += " | " + b.name;
             b.kernel = "(launched with the step before)";
             ++si;
+        }
+    }
+
+    // K slices of the contraction over rows where it shares its launch: alone it is cut until it fills the chip, here the other one
+    // fills a part of it, and slices that end in one round with it cost less (32x64x28x28 -> 64 3x3 f32: 392 tiles beside 765 workgroups of
+    // 85 slices 61 us the layer, beside 41 slices' 369 50).  In shader cycles: three workgroups share a CU, what is left over runs half of a workgroup's
+    // time longer, and the adding launch as in plan_tn.
+    void reslice_beside(const Step &ig, Step &tn)
+    {
+        TnParams &p = tn.tn;
+        const int dt = tn.t_dtype, part = tn.slot[SL_PART];
+        if (p.splits < 2 || part < 0) return;
+        const int BK = 128 / (int)dtype_size(dt);
+        const int64_t na = (int64_t)((ig.ig.M + 63) / 64) * ((ig.ig.N + 63) / 64) * std::max(ig.il.splits, 1), nka = ig.il.splits > 1 ? ig.ig.split_tiles : (ig.ig.K + BK - 1) / BK;
+        const int64_t tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), nk = (p.P + BK - 1) / BK;
+        const double share = tile_cost(TILE_64x64, dt, 1 << 20) / (double)((1 << 20) / 256), alone = tile_cost(TILE_64x64, dt, 1);
+        double best = 1e30;
+        int splits = p.splits, tiles_each = p.split_tiles;
+        for (int64_t sp = 2; sp <= p.splits; ++sp) {
+            const int64_t per = (nk + sp - 1) / sp, w = na + tiles * sp;
+            if ((nk + per - 1) / per != sp) continue;
+            const double work = (double)(na * nka + tiles * nk);
+            double t = share * std::max(work / 256.0, w <= 768 ? (double)((w + 255) / 256) * work / (double)w : work / 256.0 + 1.5 * (double)std::min(per, nka));
+            const double longest = (double)std::max(per, nka);
+            t = std::max(t, std::max(alone * longest, share * (double)std::min<int64_t>(3, (w + 255) / 256) * longest)) + 8.0 * sp * p.M * (double)p.N / 2200.0;
+            if (t < best) { best = t; splits = (int)sp; tiles_each = (int)per; }
+        }
+        p.splits = splits; p.split_tiles = tiles_each;
+        plan.bufs[part].bytes = (size_t)round_up((int64_t)splits * p.M * p.N * 4, 256);
+    }
+
+    // A layer's two gradients (a direct-load contraction and one over rows, on 64x64 tiles) in one launch, if nothing between them
+    // but layout changes: the earlier one then waits until the other's operands are there too.
+    void pair_gradients()
+    {
+        if (plan.opts.no_pair || plan.lean) return;
+        auto moves_only = [](const Step &s) { return s.kind == S_TO_NHWC || s.kind == S_TO_NCHW || s.kind == S_PAD_NHWC || s.kind == S_PACK; };
+        auto writes = [](const Step &s, int b) { return b >= 0 && (s.slot[SL_Y] == b || s.slot[SL_PART] == b); };
+        auto touches = [](const Step &s, int b) {
+            for (int q : s.slot)
+                if (q == b) return true;
+            return false;
+        };
+        // whether step b may run beside, or before, step a
+        auto independent = [&](const Step &a, const Step &b) {
+            for (int q : a.slot)
+                if (q >= 0 && (writes(b, q) || (writes(a, q) && touches(b, q)))) return false;
+            return true;
+        };
+        for (size_t si = 0; si < plan.steps.size(); ++si) {
+            if ((plan.steps[si].kind != S_IGEMM && plan.steps[si].kind != S_TN) || plan.steps[si].pair) continue;
+            size_t sj = si + 1;
+            while (sj < plan.steps.size() && moves_only(plan.steps[sj]) && independent(plan.steps[si], plan.steps[sj])) ++sj;
+            if (sj == plan.steps.size()) continue;
+            const Step &a = plan.steps[si], &b = plan.steps[sj];
+            if (a.kind + b.kind != S_IGEMM + S_TN || a.kind == b.kind || b.pair || !independent(a, b)) continue;
+            const Step &ig = a.kind == S_IGEMM ? a : b, &tn = a.kind == S_TN ? a : b;
+            if (ig.chain || ig.stem || !igemm_grads_ok(ig.ig, ig.il, tn.tn, tn.t_dtype, tn.tn_tile)) continue;
+            std::rotate(plan.steps.begin() + (long)si, plan.steps.begin() + (long)si + 1, plan.steps.begin() + (long)sj);
+            Step &first = plan.steps[sj - 1], &second = plan.steps[sj];
+            reslice_beside(first.kind == S_IGEMM ? first : second, first.kind == S_TN ? first : second);
+            first.pair = 3; second.pair = 2;
+            first.flops += second.flops; first.bytes += second.bytes;
+            second.flops = 0; second.bytes = 0;
+            first.name += " | " + second.name;
+            first.kernel += " | " + second.kernel;
+            second.kernel = "(launched with the step before)";
+            si = sj;
         }
     }
 
@@ -1694,6 +1772,20 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
 {
     size_t si = 0;
     auto P = [&](const Step &s, int slot) -> void * { return s.slot[slot] >= 0 ? ptrs[s.slot[slot]] : nullptr; };
+    auto params = [&](const Step &t) {
+        IgemmParams p = t.ig;
+        p.x = P(t, SL_X); p.x2 = P(t, SL_X2); p.w = P(t, SL_W); p.y = P(t, SL_Y);
+        for (int i = 0; i < RL_EPI_MAX_PTRS; ++i) p.epi.ptr[i] = P(t, SL_E0 + i);
+        finalize_epilogue(p.epi);
+        p.c_in = (const float *)P(t, SL_CIN); p.c_out = (float *)P(t, SL_COUT); p.h_out = P(t, SL_HOUT);
+        p.partial = (float *)P(t, SL_PART);
+        return p;
+    };
+    auto tn_params = [&](const Step &t) {
+        TnParams q = t.tn;
+        q.a = P(t, SL_X); q.b = P(t, SL_X2); q.y = P(t, SL_Y); q.partial = (float *)P(t, SL_PART);
+        return q;
+    };
     for (const Step &s : plan.steps) {
         hipError_t er = hipSuccess;
         if (events) er = hipEventRecord(events[si], stream);
@@ -1701,15 +1793,10 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
         if (er == hipSuccess) switch (s.kind) {
         case S_IGEMM: {
             if (s.pair == 2 || s.chain == 2) break; // went out with the step before
-            auto params = [&](const Step &t) {
-                IgemmParams p = t.ig;
-                p.x = P(t, SL_X); p.x2 = P(t, SL_X2); p.w = P(t, SL_W); p.y = P(t, SL_Y);
-                for (int i = 0; i < RL_EPI_MAX_PTRS; ++i) p.epi.ptr[i] = P(t, SL_E0 + i);
-                finalize_epilogue(p.epi);
-                p.c_in = (const float *)P(t, SL_CIN); p.c_out = (float *)P(t, SL_COUT); p.h_out = P(t, SL_HOUT);
-                p.partial = (float *)P(t, SL_PART);
-                return p;
-            };
+            if (s.pair == 3) {
+                er = launch_igemm_grads(params(s), s.il, tn_params(plan.steps[si]), s.ig.in_dtype, stream);
+                break;
+            }
             if (s.chain == 1) {
                 const Step &t = plan.steps[si];     // si already counts this step: the next one
                 IgemmParams pa = params(s), pb = params(t);
@@ -1803,12 +1890,15 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
             er = launch_conv_wgrad(q, stream);
             break;
         }
-        case S_TN: {
-            TnParams q = s.tn;
-            q.a = P(s, SL_X); q.b = P(s, SL_X2); q.y = P(s, SL_Y); q.partial = (float *)P(s, SL_PART);
-            er = launch_igemm_tn(q, s.t_dtype, s.tn_tile, stream);
+        case S_TN:
+            if (s.pair == 2) break;
+            if (s.pair == 3) {
+                const Step &t = plan.steps[si];     // si already counts this step: the next one
+                er = launch_igemm_grads(params(t), t.il, tn_params(s), s.t_dtype, stream);
+                break;
+            }
+            er = launch_igemm_tn(tn_params(s), s.t_dtype, s.tn_tile, stream);
             break;
-        }
         case S_PAD_NHWC:
             er = launch_transpose_pad(P(s, SL_X), P(s, SL_Y), s.t_dtype, s.t_N, s.t_C, s.t_P, s.st_W, stream);
             break;

@@ -424,3 +424,59 @@ def test_recurrent_cell_without_lds_tiles(dtype, B, I, H, opts):
     got, _ = run_hip(spec, data, opts=opts)
     for v in spec.outputs:
         assert_close(got[v], ref[v], spec.values[v].type.dtype, f"cell {dtype} {(B, I, H)}")
+
+
+# ---- both gradients of a layer in one launch (igemm_grads.hip) ------------------------------------------------------------------
+def layer_backward(kind, dims, dtype, stride=1, pad=1, weights_first=False, inner=False):
+    import numpy as np
+    rng = np.random.default_rng(sum(dims))
+    g = W.GraphSpec("layer_backward")
+    if kind == "dense":
+        m, n, k = dims
+        sdy, sx, sw, at, dx, dw = (m, n), (m, k), (n, k), {}, "dense_grad_x", "dense_grad_w"
+    else:
+        b, c, h, w, o, k = dims
+        oh, ow = (h + 2 * pad - k) // stride + 1, (w + 2 * pad - k) // stride + 1
+        sdy, sx, sw, at, dx, dw = (b, o, oh, ow), (b, c, h, w), (o, c, k, k), dict(stride=(stride, stride), pad=(pad, pad)), "conv2d_grad_x", "conv2d_grad_w"
+    dy, wv, x = g.input("dy", dtype, sdy), g.param("w", dtype, sw), g.input("x", dtype, sx)
+    data = {"dy": W.as_dtype(rng.standard_normal(sdy), dtype), "x": W.as_dtype(rng.standard_normal(sx), dtype), "w": W.as_dtype(rng.standard_normal(sw) / np.prod(sw[1:]) ** 0.5, dtype)}
+    out = []
+    for which in ((dw, dx) if weights_first else (dx, dw)):
+        o_, (y,) = g.op(which, [dy, wv] if which == dx else [dy, x], [(dtype, sx)] if which == dx else [("f32", sw)], **(at if which == dx else dict(at, out_dtype="f32")))
+        g.group([o_])
+        out.append(y)
+    if inner:                                           # dx goes on to a group of its own: stored channel-last
+        at_dx = 1 if weights_first else 0
+        o_, (out[at_dx],) = g.op("neg", [out[at_dx]], [(dtype, sx)]); g.group([o_])
+    for y in out:
+        g.output(y)
+    return g, data
+
+
+PAIR_CASES = [
+    # kind   dims                      stride pad weights_first inner
+    ("dense", (512, 1000, 784), 1, 0, False, False),      # one slice; f32: the other contraction cut along K as well
+    ("dense", (2050, 136, 72), 1, 0, True, False),        # slices; the other order
+    ("conv", (8, 64, 20, 19, 64, 3), 1, 1, False, False),     # taps inside a K tile, result in Shape order
+    ("conv", (9, 40, 17, 21, 72, 3), 1, 1, False, True),      # K tiles across taps, result kept channel-last
+    ("conv", (24, 64, 14, 14, 128, 1), 1, 0, True, False),    # one tap: rows as they lie
+    ("conv", (6, 40, 33, 29, 64, 3), 2, 1, False, False),     # stride 2: dy spread out beside dy as it is
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", PAIR_CASES, ids=[f"pair{i}" for i in range(len(PAIR_CASES))])
+def test_both_gradients_of_a_layer_in_one_launch(dtype, case):
+    import numpy as np
+    kind, dims, stride, pad, weights_first, inner = case
+    spec, data = layer_backward(kind, dims, dtype, stride, pad, weights_first, inner)
+    opts = {"no_direct": 1, "no_lp": 1}                # bf16 too on the direct-load kernel
+    ks = steps_of(spec, opts)
+    together = [k for k in ks if " | " in k and "_rows" in k and "_dma" in k]
+    assert len(together) == 1 and "(launched with the step before)" in ks, ks
+    check(spec, data, dtype, f"both gradients {case} {dtype}", opts)
+    first, _ = run_hip(spec, data, opts=opts)
+    again, _ = run_hip(spec, data, opts=opts)
+    for v in spec.outputs:
+        np.testing.assert_array_equal(first[v], again[v])
+    assert not any(" | " in k for k in steps_of(spec, dict(opts, no_pair=1)))

@@ -486,3 +486,24 @@ def test_split_k_is_planned_for_few_tiles_and_long_k():
     d = B.Plan(B.graph_from_spec(B.Context(), W.mlp(32, 784, 128, 10, "f32")[0])).describe()
     assert [s["kernel"] for s in d["steps"]] == ["igemm_dense_f32_64x64_dma_splitk+dense", "(launched with the step before)"]
     assert d["steps"][1]["flops"] == 0 and d["steps"][0]["flops"] == 2.0 * 32 * (784 * 128 + 128 * 10)
+
+
+def test_both_gradients_of_a_layer_share_no_workspace():
+    # the two run at once: whatever either reads or writes is apart from what the other writes
+    for dtype, (b, c, h, o) in (("f32", (32, 64, 28, 64)), ("bf16", (16, 40, 20, 72))):
+        g = W.GraphSpec("layer_backward")
+        dy, w, x = g.input("dy", dtype, (b, o, h, h)), g.param("w", dtype, (o, c, 3, 3)), g.input("x", dtype, (b, c, h, h))
+        at = dict(stride=(1, 1), pad=(1, 1))
+        o0, (dx,) = g.op("conv2d_grad_x", [dy, w], [(dtype, (b, c, h, h))], **at); g.group([o0])
+        o1, (dw,) = g.op("conv2d_grad_w", [dy, x], [("f32", (o, c, 3, 3))], out_dtype="f32", **at); g.group([o1])
+        o2, (y,) = g.op("neg", [dx], [(dtype, (b, c, h, h))]); g.group([o2])
+        g.output(y); g.output(dw)
+        plan = B.Plan(B.graph_from_spec(B.Context(), g), {"no_direct": 1, "no_lp": 1})
+        d = plan.describe()
+        at_pair = [i for i, s in enumerate(d["steps"]) if " | " in s["kernel"]]
+        assert len(at_pair) == 1, [s["kernel"] for s in d["steps"]]
+        i = at_pair[0]
+        live = [q for q in d["buffers"] if q["first"] <= i + 1 and q["last"] >= i]
+        for k, p in enumerate(live):
+            for q in live[k + 1:]:
+                assert p["offset"] + p["bytes"] <= q["offset"] or q["offset"] + q["bytes"] <= p["offset"], (p, q)
