@@ -226,6 +226,15 @@ __device__ __forceinline__ void igemm_dma_body(const IgemmParams &p, int bid, co
                 _Pragma("unroll") for (int j = 0; j < TN; ++j) mma_chunk(acc[i][j], fa[ks][i], fb[ks][j], T());       \
     }
 
+    // Results in Shape order: the epilogue's operands of a thread's pixels, requested ahead of the K loop (they arrive under it; asked for
+    // where they are needed, pass by pass, they were most of a short contraction's time).
+    // 17x96x29x29 -> 136 3x3 bf16 with a residual 25.5 -> 21.6 us; 130 bf16 layers 0.93 (128x64) and 0.98, f32 on 128x64 0.97, on 64x64
+    // level and left as it was.  (128x128: too many registers.)
+    constexpr bool AHEAD = MODE == STORE_ANY && BM * BN <= 128 * 64 && (ES == 2 || BM == 128);
+    PixelEpilogue<AHEAD ? BM : 32, AHEAD ? BN : 32> pe;
+    pe.form = PE_NONE;
+    if constexpr (AHEAD) pe.request(p, t, m0, n0);
+
     // ---- K loop, three stages, unrolled by three so that every stage use names its array.
     // Tile kt lives in stage kt % 3.  Body: wait until my DMAs of tile kt have landed (the LPT
     // issued after them, for tile kt+1, may still fly) and my reads of tile kt-1 are done, barrier, issue tile kt+2 into the stage
@@ -286,6 +295,34 @@ __device__ __forceinline__ void igemm_dma_body(const IgemmParams &p, int bid, co
         return;
     }
     if constexpr (MODE == STORE_ANY) {
+        if constexpr (AHEAD) if (pe.form != PE_NONE) {
+            // two passes of 32 rows at a time, one in stage 0's array and one in stage 1's
+            static_assert(32 * (BN + 1) * 4 <= STAGE, "a pass must fit in one stage");
+            float *sD = (float *)st1;
+#pragma unroll
+            for (int q = 0; q < BM / 32; q += 2) {
+                wg_barrier();                       // previous passes read out / last K tile consumed
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int own = wm * TM + i;
+                    if (own >> 1 == q >> 1) {
+                        float *dst = own & 1 ? sD : sC;
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                int row = 8 * (r >> 2) + 4 * fhalf + (r & 3);
+                                int col = wn * WTN + j * 32 + frow;
+                                dst[row * (BN + 1) + col] = acc[i][j][r];
+                            }
+                    }
+                }
+                __syncthreads();
+                pe.store(p, sC, t, m0, n0, q);
+                pe.store(p, sD, t, m0, n0, q + 1);
+            }
+            return;
+        }
         // the loop stays rolled (its pass inlined BM / 32 times costs the registers of a second workgroup per CU), rows BN + 1
         // floats apart for the reads down a column
 #pragma unroll 1

@@ -298,4 +298,115 @@ struct TileEpilogue {
     }
 };
 
+// Results in Shape order (pixels fastest) behind a simple chain: a thread's pixels and channels, fixed for the whole tile, so that
+// what the chain reads of them can be requested long before they are finished.
+//   PE_VEC    four pixels of one channel (whole groups of four per image): 8 groups of pixels x 32 channels per pass of 32 rows
+//   PE_PIXEL  one pixel: 32 pixels x 8 channels
+enum { PE_NONE = 0, PE_VEC, PE_PIXEL };
+template <int BM, int BN>
+struct PixelEpilogue {
+    static constexpr int NQ = BM / 32, NV = BN / 32, NP = BN / 8;      // passes; channels per thread and pass of either form
+    int form;
+    uint32_t raw[NQ * NP];                 // PE_VEC: 4 words per (pass, channel) or 2 in bf16; PE_PIXEL: one
+    float bias[NP];
+
+    static __device__ __forceinline__ int64_t base(const IgemmParams &p, int m)
+    {
+        const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+        return (int64_t)img * p.ys_n + (m - img * p.OHW);
+    }
+
+    __device__ __forceinline__ void request(const IgemmParams &p, int t, int m0, int n0)
+    {
+        const Epilogue &e = p.epi;
+        form = PE_NONE;
+        // a bias or a residual, and half a tile of channels at least (without either the rolled passes are up to 1.1x ahead, and on few channels)
+        if (!e.simple || (e.t_op < 0 && !e.has_bias) || p.N - n0 < BN / 2 || p.ys_p != 1 || p.ys_c == 1 || p.splits > 1) return;
+        const bool vec = (p.OHW & 3) == 0 && (p.ys_c & 3) == 0 && (p.ys_n & 3) == 0 && (((uintptr_t)p.y | (uintptr_t)e.t_ptr) & 15) == 0;
+        form = vec ? PE_VEC : PE_PIXEL;
+        const int row = vec ? (t & 7) * 4 : t & 31, c0 = vec ? t >> 3 : t >> 5, step = vec ? 32 : 8;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int n = n0 + c0 + step * j;
+            bias[j] = e.has_bias && c0 + step * j < BN && n < p.N ? load_as_f32(e.bias_ptr, e.bias_dtype, n) : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < NQ * NP; ++i) raw[i] = 0u;
+        if (e.t_op < 0) return;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int m = m0 + q * 32 + row;
+            const int64_t b = base(p, m);
+            if (vec) {
+#pragma unroll
+                for (int j = 0; j < NV; ++j) {
+                    const int n = n0 + c0 + 32 * j;
+                    if (m >= p.M || n >= p.N) continue;
+                    const int64_t off = b + (int64_t)n * p.ys_c;
+                    if (e.t_dtype == DT_F32) {
+                        const u32x4 f = *(const u32x4 *)((const float *)e.t_ptr + off);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) raw[q * NP + 4 * j + k] = f[k];
+                    } else {
+                        const u32x2 h = *(const u32x2 *)((const uint16_t *)e.t_ptr + off);
+                        raw[q * NP + 4 * j] = h[0];
+                        raw[q * NP + 4 * j + 1] = h[1];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    const int n = n0 + c0 + 8 * j;
+                    if (m >= p.M || n >= p.N) continue;
+                    const int64_t off = b + (int64_t)n * p.ys_c;
+                    raw[q * NP + j] = e.t_dtype == DT_F32 ? ((const uint32_t *)e.t_ptr)[off] : (uint32_t)((const uint16_t *)e.t_ptr)[off];
+                }
+            }
+        }
+    }
+
+    // the pass's 32 rows from sC, BN + 1 floats apart
+    __device__ __forceinline__ void store(const IgemmParams &p, const float *sC, int t, int m0, int n0, int q)
+    {
+        const Epilogue &e = p.epi;
+        const bool vec = form == PE_VEC, f32 = e.t_dtype == DT_F32;
+        const int row = vec ? (t & 7) * 4 : t & 31, c0 = vec ? t >> 3 : t >> 5;
+        const int m = m0 + q * 32 + row;
+        if (m >= p.M) return;
+        const int64_t b = base(p, m);
+        if (vec) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const int c = c0 + 32 * j, n = n0 + c;
+                if (n >= p.N) continue;
+                float v[4], bs[4], tt[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    v[k] = sC[(row + k) * (BN + 1) + c];
+                    bs[k] = bias[j];
+                    const uint32_t w = raw[q * NP + 4 * j + (k >> 1)];
+                    tt[k] = f32 ? __uint_as_float(raw[q * NP + 4 * j + k]) : __uint_as_float(k & 1 ? w & 0xffff0000u : w << 16);
+                }
+                TileEpilogue<64>::template finish<4>(e, v, bs, tt);
+                const int64_t off = b + (int64_t)n * p.ys_c;
+                if (p.y_dtype == DT_F32) *(f32x4 *)((float *)p.y + off) = f32x4{v[0], v[1], v[2], v[3]};
+                else *(u32x2 *)((uint16_t *)p.y + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+            }
+            return;
+        }
+        float v[NP], tt[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            v[j] = sC[row * (BN + 1) + c0 + 8 * j];
+            tt[j] = __uint_as_float(f32 ? raw[q * NP + j] : raw[q * NP + j] << 16);
+        }
+        TileEpilogue<64>::template finish<NP>(e, v, bias, tt);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int n = n0 + c0 + 8 * j;
+            if (n < p.N) store_from_f32(p.y, p.y_dtype, b + (int64_t)n * p.ys_c, v[j]);
+        }
+    }
+};
+
 }  // namespace rl
