@@ -272,10 +272,11 @@ hipError_t launch_gavgpool_nhwc(const PoolParams &p, hipStream_t s);   // y: [N,
 
 // ---- layout change and weight packing -------------------------------------
 // dst[n, p, c] (pixel-major, channel-last) <-> src[n, c, p]
-hipError_t launch_nchw_to_nhwc(const void *src, void *dst, int32_t dtype, int32_t N, int32_t C, int32_t P, hipStream_t s);
-hipError_t launch_nhwc_to_nchw(const void *src, void *dst, int32_t dtype, int32_t N, int32_t C, int32_t P, hipStream_t s);
-// src[n][r][q] -> dst[n][q][Rp], elements R .. Rp-1 of a row zero; Rp a multiple of the 16-byte vector
-hipError_t launch_transpose_pad(const void *src, void *dst, int32_t dtype, int32_t N, int32_t R, int32_t Q, int32_t Rp, hipStream_t s);
+// as src[n][r][q] -> dst[n][q][r] with rows of R elements (Rp = 0), or of Rp, a multiple of the 16-byte vector, R .. Rp-1 zero;
+// and two of them, neither of which touches what the other writes, in one launch
+struct MoveParams { const void *src; void *dst; int32_t dtype, N, R, Q, Rp; };
+hipError_t launch_move(const MoveParams &p, hipStream_t s);
+hipError_t launch_move_pair(const MoveParams &a, const MoveParams &b, hipStream_t s);
 // any permutation of up to six axes (element gather): y[i0..] = x[sum_k i_k * xstride[k]], i over ydims
 struct PermuteParams {
     const void *x; void *y; int32_t dtype; int32_t rank;

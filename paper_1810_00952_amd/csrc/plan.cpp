@@ -1395,6 +1395,7 @@ struct Planner {
         fuse_direct_store();
         pair_contractions();
         pair_gradients();
+        pair_moves();
         chain_small_dense();
         assign_workspace();
         return RL_OK;
@@ -1616,6 +1617,21 @@ struct Planner {
         }
     }
 
+    // Two changes of layout that follow one another, neither of which touches what the other writes, in one launch: a layer's dy and x, a
+    // convolution's input and its residual, one gradient's way out and the other operand's way in.
+    void pair_moves()
+    {
+        if (plan.opts.no_pair || plan.lean) return;
+        auto moves = [](const Step &s) { return s.kind == S_TO_NHWC || s.kind == S_TO_NCHW || s.kind == S_PAD_NHWC; };
+        for (size_t si = 0; si + 1 < plan.steps.size(); ++si) {
+            Step &a = plan.steps[si], &b = plan.steps[si + 1];
+            if (!moves(a) || !moves(b) || a.t_dtype != b.t_dtype || a.slot[SL_Y] == b.slot[SL_Y] || a.slot[SL_Y] == b.slot[SL_X] || a.slot[SL_X] == b.slot[SL_Y]) continue;
+            a.pair = 1; b.pair = 2;
+            plan.spent = true;                           // the second one's result is there a step earlier
+            ++si;
+        }
+    }
+
     // A dense contraction whose K is split over workgroups ends in a launch that adds the slices.  When its result feeds
     // nothing but a small dense layer right behind it (an MLP's output layer), that launch computes the small layer as
     // well, a row per workgroup, and the tensor between the two groups never leaves LDS: a launch fewer on graphs
@@ -1786,6 +1802,11 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
         q.a = P(t, SL_X); q.b = P(t, SL_X2); q.y = P(t, SL_Y); q.partial = (float *)P(t, SL_PART);
         return q;
     };
+    auto move = [&](const Step &t) {
+        MoveParams m{P(t, SL_X), P(t, SL_Y), t.t_dtype, t.t_N, t.t_C, t.t_P, t.kind == S_PAD_NHWC ? t.st_W : 0};
+        if (t.kind == S_TO_NCHW) std::swap(m.R, m.Q);
+        return m;
+    };
     for (const Step &s : plan.steps) {
         hipError_t er = hipSuccess;
         if (events) er = hipEventRecord(events[si], stream);
@@ -1839,11 +1860,9 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
             er = s.kind == S_MAXPOOL ? launch_maxpool_nhwc(p, stream) : launch_gavgpool_nhwc(p, stream);
             break;
         }
-        case S_TO_NHWC:
-            er = launch_nchw_to_nhwc(P(s, SL_X), P(s, SL_Y), s.t_dtype, s.t_N, s.t_C, s.t_P, stream);
-            break;
-        case S_TO_NCHW:
-            er = launch_nhwc_to_nchw(P(s, SL_X), P(s, SL_Y), s.t_dtype, s.t_N, s.t_C, s.t_P, stream);
+        case S_TO_NHWC: case S_TO_NCHW: case S_PAD_NHWC:
+            if (s.pair == 2) break;                 // went out with the step before
+            er = s.pair == 1 ? launch_move_pair(move(s), move(plan.steps[si]), stream) : launch_move(move(s), stream);
             break;
         case S_STEM_POOL: {
             if (s.stem_direct) {
@@ -1898,9 +1917,6 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
                 break;
             }
             er = launch_igemm_tn(tn_params(s), s.t_dtype, s.tn_tile, stream);
-            break;
-        case S_PAD_NHWC:
-            er = launch_transpose_pad(P(s, SL_X), P(s, SL_Y), s.t_dtype, s.t_N, s.t_C, s.t_P, s.st_W, stream);
             break;
         case S_DILATE:
             er = launch_dilate_nhwc(P(s, SL_X), P(s, SL_Y), s.t_N, s.st_H, s.st_W, s.st_Hp, s.st_Wp, s.t_C, s.st_ph, stream);

@@ -480,3 +480,23 @@ def test_both_gradients_of_a_layer_in_one_launch(dtype, case):
     for v in spec.outputs:
         np.testing.assert_array_equal(first[v], again[v])
     assert not any(" | " in k for k in steps_of(spec, dict(opts, no_pair=1)))
+
+
+# ---- two changes of layout in one launch -------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shapes", [((3, 40, 16, 24), (2, 64, 56, 8)), ((1, 8, 4, 2), (5, 33, 7, 9)), ((2, 31, 29, 3), (1, 1000, 1, 72)), ((9, 24, 28, 28), (70, 3, 5, 5))])
+def test_two_changes_of_layout_in_one_launch(dtype, shapes):
+    # whole vectors and ragged tiles, either first, sizes far apart: every element, bit for bit
+    import numpy as np
+    rng = np.random.default_rng(8)
+    g = W.GraphSpec("moves")
+    data, want = {}, []
+    for i, shape in enumerate(shapes):
+        data[f"x{i}"] = W.as_dtype(rng.standard_normal(shape), dtype)
+        o, (y,) = g.op("layout_transform", [g.input(f"x{i}", dtype, shape)], [(dtype, (shape[0], shape[2], shape[3], shape[1]))], perm=(0, 2, 3, 1))
+        g.group([o]); g.output(y)
+    assert steps_of(g) == ["transpose_tiled"] * 2, steps_of(g)
+    got, _ = run_hip(g, data)
+    ref = OG.run(g, data)
+    for v in g.outputs:
+        np.testing.assert_array_equal(got[v], ref[v])
