@@ -214,6 +214,8 @@ typedef struct rl_plan_opts {
                                share the work (what it falls back to); n > 2: on its first n workgroups.  All give the same bits */
     int32_t no_direct;      /* never the contraction kernel that loads its operands straight into registers */
     int32_t direct_all;     /* that kernel wherever it can run, for tests and measurements */
+    int32_t tn_run;         /* 3x3 bf16 weight gradients with the taps of a filter row from one copy of the rows: 1: wherever
+                               that kernel can run (n > 1: K cut into up to n slices), -1: never */
 } rl_plan_opts;
 
 /* rl_plan_create re-checks the whole graph (Type-Call on every call, group legality, outputs reachable), picks

@@ -209,6 +209,8 @@ struct TnParams {
     int32_t nblk_m, nblk_n;                 // filled by the launcher
 };
 hipError_t launch_igemm_tn(const TnParams &p, int32_t dtype, int32_t tile, hipStream_t s);     // tile: 128 or 64 (square)
+bool igemm_tn_run_ok(const TnParams &p, int32_t dtype);                                         // 3x3, stride 1, pad 1 in bf16: igemm_tn_run.hip
+hipError_t launch_igemm_tn_run(const TnParams &p, int32_t dtype, hipStream_t s);
 // a direct-load contraction and one over rows, neither of which reads what the other writes, in one launch (igemm_grads.hip)
 bool igemm_grads_ok(const IgemmParams &a, const IgemmLaunch &la, const TnParams &b, int32_t tn_dtype, int32_t tn_tile);
 hipError_t launch_igemm_grads(const IgemmParams &a, const IgemmLaunch &la, const TnParams &b, int32_t dtype, hipStream_t s);

@@ -1210,7 +1210,7 @@ struct Planner {
         Step &s = add_step(S_TN, std::string(op_name(o.kind)) + "#" + std::to_string(oi), std::string("igemm_") + op_name(o.kind) + (dt == RL_BF16 ? "_bf16_" : "_f32_") +
                            (tile == 128 ? "128x128" : "64x64") + "_rows" + (p.splits > 1 ? "_splitk" : ""));
         s.group = gi;
-        s.tn = p; s.tn_tile = tile; s.t_dtype = dt;
+        s.tn = p; s.tn_tile = tile; s.t_dtype = dt; s.tn_cost = best;
         s.slot[SL_X] = abuf; s.slot[SL_X2] = bbuf; s.slot[SL_Y] = ybuf; s.slot[SL_PART] = part;
         s.flops = 2.0 * p.P * (double)p.Mout * p.Cout * p.T;
         s.bytes = (double)bytes_of(va) + (double)bytes_of(vb) + (double)bytes_of(vy);
@@ -1395,6 +1395,7 @@ struct Planner {
         fuse_direct_store();
         pair_contractions();
         pair_gradients();
+        run_weight_gradients();
         pair_moves();
         chain_small_dense();
         assign_workspace();
@@ -1614,6 +1615,35 @@ struct Planner {
             first.kernel += " | " + second.kernel;
             second.kernel = "(launched with the step before)";
             si = sj;
+        }
+    }
+
+    // A 3x3 weight gradient that has a launch of its own takes the kernel that reads the three taps of a filter row from one copy of the
+    // rows, where it is ahead.  Its cost in shader cycles beside that of the square tiles (plan_tn): a K tile of one workgroup, of which a CU
+    // holds one, 600, to start and end 15500, and the same adding launch.  Of 20 layers of 16 to 64 images the nine it takes run at 0.86 to 0.97 of
+    // their time, those it leaves would at 0.98 to 1.08 (64x512x14x14 -> 64 57.1 against 59.2 us, 64x192x14x14 -> 192 55.9 and 55.0).
+    void run_weight_gradients()
+    {
+        if (plan.opts.tn_run < 0) return;
+        for (size_t si = 0; si < plan.steps.size(); ++si) {
+            Step &s = plan.steps[si];
+            if (s.kind != S_TN || s.pair || !igemm_tn_run_ok(s.tn, s.t_dtype)) continue;
+            TnParams &p = s.tn;
+            const int64_t nk = ((int64_t)p.P + 63) / 64, tiles = (int64_t)((p.M + 63) / 64) * ((p.C + 63) / 64) * 3;
+            double best = plan.opts.tn_run ? 1e30 : s.tn_cost;
+            int splits = 0, per_best = 0;
+            for (int64_t sp = 1; sp <= std::min<int64_t>(nk, plan.opts.tn_run > 1 ? plan.opts.tn_run : 512); ++sp) {
+                const int64_t per = (nk + sp - 1) / sp;
+                if ((nk + per - 1) / per != sp || (sp > 1 && sp * p.M * p.N >= (int64_t)1 << 27)) continue;
+                if (sp > 1 && s.slot[SL_PART] < 0) break;                          // (one slice of the square tiles: the results alone fill the chip)
+                const double cost = (double)((tiles * sp + 255) / 256) * ((double)per * 600.0 + 15500.0) + (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
+                if (cost < best || (plan.opts.tn_run > 1 && sp > splits)) { best = cost; splits = (int)sp; per_best = (int)per; }
+            }
+            if (!splits) continue;
+            p.splits = splits; p.split_tiles = per_best;
+            if (s.slot[SL_PART] >= 0) plan.bufs[s.slot[SL_PART]].bytes = (size_t)round_up(splits > 1 ? (int64_t)splits * p.M * p.N * 4 : 256, 256);
+            s.tn_tile = 0;
+            s.kernel = std::string("igemm_conv2d_grad_w_bf16_64x64x3_rows_run") + (splits > 1 ? "_splitk" : "");
         }
     }
 
@@ -1916,7 +1946,7 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
                 er = launch_igemm_grads(params(t), t.il, tn_params(s), s.t_dtype, stream);
                 break;
             }
-            er = launch_igemm_tn(tn_params(s), s.t_dtype, s.tn_tile, stream);
+            er = s.tn_tile ? launch_igemm_tn(tn_params(s), s.t_dtype, s.tn_tile, stream) : launch_igemm_tn_run(tn_params(s), s.t_dtype, stream);
             break;
         case S_DILATE:
             er = launch_dilate_nhwc(P(s, SL_X), P(s, SL_Y), s.t_N, s.st_H, s.st_W, s.st_Hp, s.st_Wp, s.t_C, s.st_ph, stream);

@@ -32,7 +32,8 @@ struct Step {
     PoolParams po{};
     PermuteParams pe{};
     WgradParams wg{};                   // S_WGRAD (and the counts S_WGRAD_REDUCE adds up)
-    TnParams tn{}; int tn_tile = 0;     // S_TN
+    TnParams tn{}; int tn_tile = 0;     // S_TN (tile 0: igemm_tn_run.hip)
+    double tn_cost = 0;                 // ... estimate of the square tile's time, shader cycles
     GatherPack gp{};                    // S_PACK: an activation gathered into the K-contiguous rows a contraction reads
     int t_dtype = 0, t_N = 0, t_C = 0, t_P = 0;
     int st_H = 0, st_W = 0, st_Hp = 0, st_Wp = 0, st_ph = 0, st_pw = 0;   // S_STEM_PAD geometry (t_N, t_C: batch, channels)

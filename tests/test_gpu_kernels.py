@@ -500,3 +500,32 @@ def test_two_changes_of_layout_in_one_launch(dtype, shapes):
     ref = OG.run(g, data)
     for v in g.outputs:
         np.testing.assert_array_equal(got[v], ref[v])
+
+
+# ---- 3x3 weight gradients with the taps of a filter row from one copy of the rows (igemm_tn_run.hip) ---------------------------------
+TN_RUN_CASES = [
+    # n  c    h   w   o
+    (4, 64, 16, 16, 64),        # every size whole: one tile of channels, whole K tiles
+    (5, 40, 17, 19, 72),        # channels past the tile on both sides, a last K tile of 15 pixels, images that end inside a K tile
+    (40, 64, 33, 1, 64),        # one column: kw = 1 alone is inside the image
+    (5, 136, 2, 131, 64),       # rows longer than two K tiles, every line at an edge
+    (1, 24, 40, 35, 200),       # one image
+    (70, 72, 5, 6, 40),         # lines and images shorter than a wave's pixels
+]
+
+
+@pytest.mark.parametrize("case", TN_RUN_CASES, ids=[f"tn_run{i}" for i in range(len(TN_RUN_CASES))])
+def test_weight_gradient_with_a_filter_rows_taps_from_one_copy(case):
+    import numpy as np
+    n, c, h, w, o = case
+    for slices in (2, 5, 512):                          # one or many K tiles a slice: shorter and longer than the ring of stages
+        for out_dtype in ("f32", None):
+            spec, data = W.grad_case("conv2d_grad_w", (n, c, h, w, o, 3), "bf16", 1, 1, second_is_param=False, out_dtype=out_dtype)
+            opts = {"tn_run": slices}
+            assert any("64x64x3_rows_run" in k for k in steps_of(spec, opts)), steps_of(spec, opts)
+            check(spec, data, "bf16", f"tn_run {case} {slices} {out_dtype}", opts)
+            if out_dtype == "f32":
+                first, _ = run_hip(spec, data, opts=opts)
+                again, _ = run_hip(spec, data, opts=opts)
+                for v in spec.outputs:
+                    np.testing.assert_array_equal(first[v], again[v])
