@@ -39,7 +39,7 @@
 // 3x3 / stride 1 / pad 1, C a multiple of 64, W <= 30, dense channel-last
 // activations, output rows contiguous in n with N a multiple of 8, tensors
 // below 2 GiB.
-#include "device_utils.h"
+#include "lp_planes.h"
 
 namespace rl {
 
@@ -104,7 +104,8 @@ constexpr int PITCH = 144;                        // bytes per run pixel in LDS
 
 // NB: weight-tile stages.  Weight tile u + NB - 1 is requested while tile u is multiplied, and at the end of a tile
 // the requests of the last NB - 3 tiles may still be in flight: more stages, more time for a request to return.
-template <int BM, int BN, int WGM, int WGN, int NB>
+// PLANES: the result in Shape order (lp_planes.h)
+template <int BM, int BN, int WGM, int WGN, int NB, bool PLANES>
 __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const IgemmParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
@@ -173,6 +174,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const Igemm
                 const int n = nb + j * 32 + 8 * g;
                 bias_r[j][g] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, n < p.N ? (uint32_t)n * 4u : OOB, 0, 0));
             }
+        if (!PLANES)
 #pragma unroll
         for (int q = 0; q < NPASS; ++q) {
             const int row = q * RPP + rr;
@@ -338,6 +340,12 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const Igemm
     constexpr int WBYTES = WTM * WTN * 4, ROWB = WTN * 4;
     static_assert(NW * WBYTES <= LDS_BYTES, "LDS must hold the waves' parked tiles");
     unsigned char *park = lds + wave * WBYTES;
+    const rsrc_t ry = make_rsrc(p.y, y_bytes);
+    const float lo = e.relu_last ? 0.0f : -INFINITY;
+    if constexpr (PLANES) {
+        store_planes<WTM, WTN>(p, park, acc, bias_r, m0 + wm * WTM, n0 + wn * WTN, lane, ry, lo);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -353,8 +361,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const Igemm
                 *(f32x4 *)(park + row * ROWB + pos * 16) = v;
             }
     wave_lds_exchange();
-    const rsrc_t ry = make_rsrc(p.y, y_bytes);
-    const float lo = e.relu_last ? 0.0f : -INFINITY;
 #pragma unroll
     for (int q = 0; q < NPASS; ++q) {
         const int row = q * RPP + rr;
@@ -643,14 +649,15 @@ __global__ __launch_bounds__(256) void conv3x3_run_ks_kernel(const IgemmParams p
 }
 
 template <int BM, int BN, int WGM, int WGN, int NB>
-static hipError_t launch_run(const IgemmParams &p0, hipStream_t s)
+static hipError_t launch_run(const IgemmParams &p0, bool planes, hipStream_t s)
 {
     IgemmParams p = p0;
     p.nblk_m = (p.M + BM - 1) / BM;
     p.nblk_n = (p.N + BN - 1) / BN;
     int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((conv3x3_run_kernel<BM, BN, WGM, WGN, NB>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
+    if (planes) hipLaunchKernelGGL((conv3x3_run_kernel<BM, BN, WGM, WGN, NB, true>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
+    else hipLaunchKernelGGL((conv3x3_run_kernel<BM, BN, WGM, WGN, NB, false>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
     return hipGetLastError();
 }
 
@@ -661,13 +668,13 @@ hipError_t launch_conv3x3_run(const IgemmParams &p, const IgemmLaunch &l, hipStr
     if (p.in_dtype != DT_BF16 || p.y_dtype != DT_BF16 || p.x2 || p.C < 64 || p.C % 64 != 0 || p.KH != 3 || p.KW != 3 || p.sh != 1 || p.sw != 1 ||
         p.ph != 1 || p.pw != 1 || p.OH != p.H || p.OW != p.W || p.W < 1 || p.W > RUN_W_MAX || p.K != 9 * p.C || p.Kp != p.K || p.N % 8 != 0 ||
         HW < 1 || p.M % HW != 0 || p.OHW != HW || p.xs_c != 1 || p.xs_w != p.C || p.xs_h != (int64_t)p.W * p.C || p.xs_n != HW * p.C ||
-        p.ys_c != 1 || p.ys_n != HW * p.ys_p || (uint64_t)p.M * p.C * 2 >= 0x7fffffffull || p.x_bytes != (uint32_t)((uint64_t)p.M * p.C * 2) ||
+        !(l.planes ? planes_ok(p) && l.run == 1 : p.ys_c == 1 && p.ys_n == HW * p.ys_p) || (uint64_t)p.M * p.C * 2 >= 0x7fffffffull || p.x_bytes != (uint32_t)((uint64_t)p.M * p.C * 2) ||
         p.w_bytes < (uint32_t)((uint64_t)p.N * p.Kp * 2) || !p.epi.simple || (p.epi.has_bias && p.epi.bias_dtype != DT_F32) ||
         (p.epi.t_op >= 0 && (p.epi.t_op != E_ADD || p.epi.t_dtype != DT_BF16)) || (p.epi.rest_n != 0 && !p.epi.relu_last))
         return hipErrorInvalidValue;
     switch (l.tile) {
-    case TILE_256x128: return launch_run<256, 128, 4, 2, 4>(p, s);      // 160 KB of LDS with four stages
-    case TILE_128x128: return launch_run<128, 128, 2, 4, 5>(p, s);
+    case TILE_256x128: return launch_run<256, 128, 4, 2, 4>(p, l.planes != 0, s);      // 160 KB of LDS with four stages
+    case TILE_128x128: return launch_run<128, 128, 2, 4, 5>(p, l.planes != 0, s);
     case TILE_128x64:
         if (l.run == 2) {
             if (p.C % 128 != 0) return hipErrorInvalidValue;      // each of the four waves takes whole k-steps of a 128-channel pair of slices
@@ -677,7 +684,7 @@ hipError_t launch_conv3x3_run(const IgemmParams &p, const IgemmLaunch &l, hipStr
             hipLaunchKernelGGL((conv3x3_run_ks_kernel<128, 64, 6>), dim3((unsigned)(q.nblk_m * q.nblk_n)), dim3(256), 0, s, q);
             return hipGetLastError();
         }
-        return launch_run<128, 64, 4, 2, 6>(p, s);
+        return launch_run<128, 64, 4, 2, 6>(p, l.planes != 0, s);
     default: return hipErrorInvalidValue;
     }
 }

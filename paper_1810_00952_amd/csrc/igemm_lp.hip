@@ -52,7 +52,7 @@
 // filter tap; K a multiple of 64; KH*KW <= 32; output rows contiguous in n with
 // N a multiple of 8; epilogue of the form [f32 bias] [+ bf16 residual] [relu];
 // every tensor below 2 GiB.
-#include "device_utils.h"
+#include "lp_planes.h"
 
 namespace rl {
 
@@ -93,8 +93,9 @@ constexpr uint32_t OOB = 0x80000000u;
 }  // namespace
 
 // The workgroup's work: tile number bid_in of the contraction p.  YF32: the output is fp32 (no residual then).
+// PLANES: the result in Shape order (lp_planes.h; bf16, no residual).
 // ANYACT: the operand-free steps behind bias and residual are any (up to eight, codes in the epilogue), not just one ReLU.
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool YF32 = false, bool ANYACT = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool YF32 = false, bool ANYACT = false, bool PLANES = false>
 __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bid_in)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
@@ -272,7 +273,7 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
     constexpr int LPR = WTN / 8;                   // lanes per output row of the wave tile (16 bytes of bf16 each)
     constexpr int RPP = 64 / LPR;                  // rows per row-wise pass
     constexpr int NPASS = WTM / RPP;
-    constexpr int NEPI = TN * 4 + NPASS;           // vector-memory operations RL_EPI_LOADS issues
+    constexpr int NEPI = TN * 4 + (PLANES ? 0 : NPASS);   // vector-memory operations RL_EPI_LOADS issues
     constexpr int POSN = WTN / 4;                  // 16-byte fp32 positions per parked row
     constexpr int RP = 16 / POSN > 0 ? 16 / POSN : 1;   // parked rows per 256 bytes (all 64 banks)
     const int rr = lane / LPR, pp = lane % LPR;
@@ -293,7 +294,7 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
                 const int n = nb + j * 32 + 8 * g;                                                                    \
                 bias_r[j][g] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, n < p.N ? (uint32_t)n * 4u : OOB, 0, 0)); \
             }                                                                                                         \
-        _Pragma("unroll") for (int q = 0; q < NPASS; ++q) {                                                           \
+        if (!PLANES) _Pragma("unroll") for (int q = 0; q < NPASS; ++q) {                                              \
             const int row = q * RPP + rr;                                                                             \
             const int key = (row / RP) & (POSN - 1);                                                                  \
             pA[q] = 2 * pp + (key & 1);                                                                               \
@@ -389,6 +390,12 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
     static_assert((NW + STAGES - 1) / STAGES * WBYTES <= STAGE, "a stage must hold its waves' parked tiles");
     const int wsel = wave % STAGES;
     unsigned char *park = (wsel == 0 ? st0 : wsel == 1 ? st1 : wsel == 2 ? st2 : st3) + (wave / STAGES) * WBYTES;
+    const rsrc_t ry = make_rsrc(p.y, y_bytes);
+    const float lo = (!ANYACT && e.relu_last) ? 0.0f : -INFINITY;
+    if constexpr (PLANES) {
+        store_planes<WTM, WTN>(p, park, acc, bias_r, m0 + wm * WTM, n0 + wn * WTN, lane, ry, lo);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -404,8 +411,6 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
                 *(f32x4 *)(park + row * ROWB + pos * 16) = v;
             }
     wave_lds_exchange();
-    const rsrc_t ry = make_rsrc(p.y, y_bytes);
-    const float lo = (!ANYACT && e.relu_last) ? 0.0f : -INFINITY;
 #pragma unroll
     for (int q = 0; q < NPASS; ++q) {
         const int row = q * RPP + rr;
@@ -457,6 +462,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) void igemm_lp_anyact_kernel(const I
     igemm_lp_body<BM, BN, WGM, WGN, STAGES, false, true>(p, (int)blockIdx.x);
 }
 
+// the result in Shape order
+template <int BM, int BN, int WGM, int WGN, int STAGES>
+__global__ __launch_bounds__(WGM * WGN * 64) void igemm_lp_planes_kernel(const IgemmParams p)
+{
+    igemm_lp_body<BM, BN, WGM, WGN, STAGES, false, false, true>(p, (int)blockIdx.x);
+}
+
 // fp32 output (a projection whose result feeds further fp32 arithmetic: the recurrent executor's hoisted x . Wx^T)
 template <int BM, int BN, int WGM, int WGN, int STAGES>
 __global__ __launch_bounds__(WGM * WGN * 64) void igemm_lp_f32out_kernel(const IgemmParams p)
@@ -480,14 +492,15 @@ RL_INST(128, 128, 2, 4, 4) RL_INST(256, 128, 4, 2, 3) RL_INST(128, 64, 4, 1, 3) 
 #undef RL_INST
 
 template <int BM, int BN, int WGM, int WGN, int STAGES>
-static hipError_t launch_lp(const IgemmParams &p0, hipStream_t s, bool anyact)
+static hipError_t launch_lp(const IgemmParams &p0, hipStream_t s, bool anyact, bool planes)
 {
     IgemmParams p = p0;
     p.nblk_m = (p.M + BM - 1) / BM;
     p.nblk_n = (p.N + BN - 1) / BN;
     int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
-    if (anyact) hipLaunchKernelGGL((igemm_lp_anyact_kernel<BM, BN, WGM, WGN, STAGES>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
+    if (planes) hipLaunchKernelGGL((igemm_lp_planes_kernel<BM, BN, WGM, WGN, STAGES>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
+    else if (anyact) hipLaunchKernelGGL((igemm_lp_anyact_kernel<BM, BN, WGM, WGN, STAGES>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
     else hipLaunchKernelGGL((igemm_lp_kernel<BM, BN, WGM, WGN, STAGES>), dim3((unsigned)nblk), dim3(WGM * WGN * 64), 0, s, p);
     return hipGetLastError();
 }
@@ -518,7 +531,7 @@ static int lp_variant(const IgemmParams &p, const IgemmLaunch &l)
 bool igemm_lp_can_pair(const IgemmParams &a, const IgemmLaunch &la, const IgemmParams &b, const IgemmLaunch &lb)
 {
     return la.lp && lb.lp && !la.ws && !lb.ws && !la.c64 && !lb.c64 && !la.run && !lb.run && !la.gates && !lb.gates && !a.x2 && !b.x2 &&
-           !la.anyact && !lb.anyact && !la.big && !lb.big &&
+           !la.anyact && !lb.anyact && !la.big && !lb.big && !la.planes && !lb.planes &&
            a.in_dtype == DT_BF16 && b.in_dtype == DT_BF16 && a.y_dtype == DT_BF16 && b.y_dtype == DT_BF16 && lp_variant(a, la) == lp_variant(b, lb);
 }
 
@@ -563,20 +576,21 @@ hipError_t launch_igemm_lp(const IgemmParams &p, const IgemmLaunch &l, hipStream
     // the planner's flag and the chain must agree: one ReLU at most without it, other operand-free steps with it
     const bool anyact = l.anyact != 0;
     if (anyact != (p.epi.rest_n > 0 && !p.epi.relu_last)) return hipErrorInvalidValue;
+    if (l.planes && (anyact || !planes_ok(p))) return hipErrorInvalidValue;
     switch (l.tile) {
     case TILE_128x128:
         // eight waves of 64 pixels x 32 channels, two per SIMD: one wave's fragment reads and request stalls are
         // covered by the other's MFMAs (measured 4% faster than four waves of 64 x 64 on the ResNet shapes)
-        return launch_lp<128, 128, 2, 4, 4>(p, s, anyact);
+        return launch_lp<128, 128, 2, 4, 4>(p, s, anyact, l.planes != 0);
     case TILE_256x128:
         // eight waves of 64 x 64, two per SIMD, three stages of 48 KB
-        return launch_lp<256, 128, 4, 2, 3>(p, s, anyact);
+        return launch_lp<256, 128, 4, 2, 3>(p, s, anyact, l.planes != 0);
     case TILE_128x64:
         // few workgroups (at most one per CU anyway): four stages, so fragments are prefetched across the barrier;
         // many: three stages, so two workgroups share a CU and cover each other's barriers and epilogues
-        if ((int64_t)((p.M + 127) / 128) * ((p.N + 63) / 64) <= 320) return launch_lp<128, 64, 4, 1, 4>(p, s, anyact);
-        return launch_lp<128, 64, 4, 1, 3>(p, s, anyact);
-    default: return launch_lp<64, 64, 2, 2, 4>(p, s, anyact);
+        if ((int64_t)((p.M + 127) / 128) * ((p.N + 63) / 64) <= 320) return launch_lp<128, 64, 4, 1, 4>(p, s, anyact, l.planes != 0);
+        return launch_lp<128, 64, 4, 1, 3>(p, s, anyact, l.planes != 0);
+    default: return launch_lp<64, 64, 2, 2, 4>(p, s, anyact, l.planes != 0);
     }
 }
 

@@ -119,9 +119,12 @@ struct IgemmLaunch {
     int32_t direct;     // > 0: operands straight into registers, K over a workgroup's waves (igemm_direct.hip), 1 + how A is read
     int32_t direct_tile, direct_slices;     // ... its tile (32 or 16, square) and K slices (1, 2, 4, 8; 8 at tile 16)
     int32_t direct_units;                   // ... with gates: hidden units per workgroup (4 or 8)
+    int32_t planes;     // 1 (with lp or run = 1, none of the others): the result in Shape order (lp_planes.h)
     int32_t anyact;     // 1 (with lp, no ws / c64 / run / pair): operand-free steps other than one ReLU behind bias and residual
 };
 hipError_t launch_igemm(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
+// whether the pixel-on-lane kernels may store this result in Shape order (lp_planes.h)
+inline bool planes_ok(const IgemmParams &p) { return p.OHW % 4 == 0 && p.ys_p == 1 && p.ys_c == p.OHW && p.ys_n == (int64_t)p.N * p.OHW && p.epi.t_op < 0 && p.y_dtype == DT_BF16; }
 enum { DIRECT_ROWS = 0, DIRECT_PLANES = 1, DIRECT_ANY = 2 };
 hipError_t launch_igemm_direct(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
 

@@ -1396,6 +1396,7 @@ struct Planner {
         pair_contractions();
         pair_gradients();
         run_weight_gradients();
+        fuse_planes_store();
         pair_moves();
         chain_small_dense();
         assign_workspace();
@@ -1513,6 +1514,38 @@ struct Planner {
                 c.name += "+" + m.name;
                 plan.steps.erase(plan.steps.begin() + (long)si + 1);
             }
+        }
+    }
+
+    // A result of the pixel-on-lane kernels that nothing but the change of layout into Shape order reads is stored in that order at once.
+    void fuse_planes_store()
+    {
+        if (plan.opts.no_pair || plan.lean) return;
+        for (size_t si = 0; si < plan.steps.size(); ++si) {
+            Step &c = plan.steps[si];
+            if (c.kind != S_IGEMM || c.pair || c.chain || c.stem || !c.il.lp || c.il.ws || c.il.c64 || c.il.big || c.il.s2pair || c.il.anyact || c.il.run > 1) continue;
+            IgemmParams p = c.ig;
+            const int mid = c.slot[SL_Y];
+            if (p.in_dtype != RL_BF16 || mid < 0 || plan.bufs[mid].bound_value >= 0 || p.ys_c != 1 || p.ys_p != p.N || p.ys_n != (int64_t)p.OHW * p.N) continue;
+            size_t sj = 0;
+            int users = 0;
+            for (size_t k = 0; k < plan.steps.size(); ++k)
+                if (k != si)
+                    for (int b : plan.steps[k].slot)
+                        if (b == mid) { ++users; sj = k; }
+            if (users != 1 || sj < si || plan.steps[sj].kind != S_TO_NCHW || plan.steps[sj].slot[SL_X] != mid || plan.steps[sj].t_C != p.N || plan.steps[sj].t_P != p.OHW) continue;
+            const int y = plan.steps[sj].slot[SL_Y];
+            bool other_use = false;                          // the result is there earlier
+            for (size_t k = 0; k < sj; ++k)
+                for (int b : plan.steps[k].slot) other_use |= b == y;
+            p.ys_n = (int64_t)p.N * p.OHW; p.ys_p = 1; p.ys_c = p.OHW;
+            finalize_epilogue(p.epi);
+            if (other_use || !p.epi.simple || !planes_ok(p)) continue;
+            c.ig.ys_n = p.ys_n; c.ig.ys_p = p.ys_p; c.ig.ys_c = p.ys_c;
+            c.il.planes = 1;
+            c.slot[SL_Y] = y;
+            c.kernel += "_planes";
+            plan.steps.erase(plan.steps.begin() + (long)sj);
         }
     }
 

@@ -529,3 +529,49 @@ def test_weight_gradient_with_a_filter_rows_taps_from_one_copy(case):
                 again, _ = run_hip(spec, data, opts=opts)
                 for v in spec.outputs:
                     np.testing.assert_array_equal(first[v], again[v])
+
+
+# ---- results of the pixel-on-lane kernels stored in Shape order (lp_planes.h) --------------------------------------------------------
+PLANES_CASES = [
+    # n   c    h   w   o    k  s  p  options
+    (16, 64, 28, 28, 128, 3, 1, 1, {}),                 # nine taps from one copy of the rows, whole tiles
+    (25, 320, 20, 20, 40, 3, 1, 1, {}),
+    (9, 64, 22, 26, 200, 3, 1, 1, {}),                  # images that end inside a wave's pixels, channels past the tile, a ragged last tile
+    (50, 256, 14, 14, 264, 3, 1, 1, {}),                # 196 pixels: four at a time and no more
+    (64, 128, 28, 28, 128, 3, 1, 1, {}),
+    (5, 64, 36, 33, 72, 3, 1, 1, {}),                   # rows too long for one copy
+    (33, 192, 30, 30, 136, 1, 1, 0, {}),
+    (17, 128, 31, 29, 256, 3, 2, 1, {}),                # 16 x 15
+    (16, 128, 28, 28, 128, 3, 1, 1, {"no_run": 1}),
+    (301, 256, 2, 2, 512, 3, 1, 1, {"no_run": 1}),      # images of four pixels
+    (301, 256, 2, 2, 512, 3, 1, 1, {}),
+]
+
+
+@pytest.mark.parametrize("steps", ["none", "bias", "bias_relu"])
+@pytest.mark.parametrize("case", PLANES_CASES, ids=[f"planes{i}" for i in range(len(PLANES_CASES))])
+def test_result_stored_in_shape_order(case, steps):
+    import numpy as np
+    n, c, h, w, o, k, s, p, opts = case
+    oh, ow = (h + 2 * p - k) // s + 1, (w + 2 * p - k) // s + 1
+    rng = np.random.default_rng(n + o)
+    g = W.GraphSpec("conv")
+    x, wv, b = g.input("x", "bf16", (n, c, h, w)), g.param("w", "bf16", (o, c, k, k)), g.param("b", "f32", (o,))
+    t = [("bf16", (n, o, oh, ow))]
+    ops = [g.op("conv2d", [x, wv], t, stride=(s, s), pad=(p, p))]
+    if steps != "none":
+        ops.append(g.op("bias_add", [ops[-1][1][0], b], t, axis=1))
+    if steps == "bias_relu":
+        ops.append(g.op("relu", [ops[-1][1][0]], t))
+    g.group([q[0] for q in ops])
+    g.output(ops[-1][1][0])
+    data = {"x": W.as_dtype(rng.standard_normal((n, c, h, w)), "bf16"), "w": W.as_dtype(rng.standard_normal((o, c, k, k)) / (c * k * k) ** 0.5, "bf16"),
+            "b": rng.standard_normal(o).astype(np.float32)}
+    assert any("_planes" in q and "direct" not in q for q in steps_of(g, opts)), steps_of(g, opts)
+    assert "nhwc_to_nchw" in steps_of(g, dict(opts, no_pair=1)), steps_of(g, dict(opts, no_pair=1))
+    print(case, steps_of(g, opts), flush=True)
+    got, _ = run_hip(g, data, opts=opts)
+    rows, _ = run_hip(g, data, opts=dict(opts, no_pair=1))       # rows of channels, then the transposition: the same sums and rounding
+    np.testing.assert_array_equal(got[g.outputs[0]], rows[g.outputs[0]])
+    if n * c * h * w * o < 2e8:
+        check(g, data, "bf16", f"planes {case} {steps}", opts)
