@@ -1518,12 +1518,15 @@ struct Planner {
     }
 
     // A result of the pixel-on-lane kernels that nothing but the change of layout into Shape order reads is stored in that order at once.
+    // The two forms that only store rows of channels give way to their neighbours that can: 256x256 tiles (64x64x56x56 -> 256 1x1 85.0 -> 55.7 us,
+    // 32x2048x14x14 -> 1024 67.0 -> 53.8) and K split over the waves, there below 512 channels (64x128x8x8 -> 512 16.9 -> 12.8, 8x256x28x28 -> 256
+    // 19.4 -> 17.1; 64x512x8x8 -> 512 28.2 against 28.8).
     void fuse_planes_store()
     {
         if (plan.opts.no_pair || plan.lean) return;
         for (size_t si = 0; si < plan.steps.size(); ++si) {
             Step &c = plan.steps[si];
-            if (c.kind != S_IGEMM || c.pair || c.chain || c.stem || !c.il.lp || c.il.ws || c.il.c64 || c.il.big || c.il.s2pair || c.il.anyact || c.il.run > 1) continue;
+            if (c.kind != S_IGEMM || c.pair || c.chain || c.stem || !c.il.lp || c.il.ws || c.il.c64 || c.il.s2pair || c.il.anyact || (c.il.run > 1 && c.ig.C >= 512)) continue;
             IgemmParams p = c.ig;
             const int mid = c.slot[SL_Y];
             if (p.in_dtype != RL_BF16 || mid < 0 || plan.bufs[mid].bound_value >= 0 || p.ys_c != 1 || p.ys_p != p.N || p.ys_n != (int64_t)p.OHW * p.N) continue;
@@ -1543,9 +1546,14 @@ struct Planner {
             if (other_use || !p.epi.simple || !planes_ok(p)) continue;
             c.ig.ys_n = p.ys_n; c.ig.ys_p = p.ys_p; c.ig.ys_c = p.ys_c;
             c.il.planes = 1;
+            if (c.il.run > 1) c.il.run = 1;
+            if (c.il.big) { c.il.big = 0; c.kernel.replace(c.kernel.find("256x256"), 7, "256x128"); }
             c.slot[SL_Y] = y;
-            c.kernel += "_planes";
-            plan.steps.erase(plan.steps.begin() + (long)sj);
+            // the change of layout stays in the list, as part of the step that stores
+            Step &m = plan.steps[sj];
+            m.slot[SL_X] = -1;
+            m.pair = 2;
+            m.bytes = 0;
         }
     }
 
@@ -1688,7 +1696,7 @@ struct Planner {
         auto moves = [](const Step &s) { return s.kind == S_TO_NHWC || s.kind == S_TO_NCHW || s.kind == S_PAD_NHWC; };
         for (size_t si = 0; si + 1 < plan.steps.size(); ++si) {
             Step &a = plan.steps[si], &b = plan.steps[si + 1];
-            if (!moves(a) || !moves(b) || a.t_dtype != b.t_dtype || a.slot[SL_Y] == b.slot[SL_Y] || a.slot[SL_Y] == b.slot[SL_X] || a.slot[SL_X] == b.slot[SL_Y]) continue;
+            if (!moves(a) || !moves(b) || a.pair || b.pair || a.t_dtype != b.t_dtype || a.slot[SL_Y] == b.slot[SL_Y] || a.slot[SL_Y] == b.slot[SL_X] || a.slot[SL_X] == b.slot[SL_Y]) continue;
             a.pair = 1; b.pair = 2;
             plan.spent = true;                           // the second one's result is there a step earlier
             ++si;
@@ -1788,7 +1796,7 @@ std::string describe_plan(const Plan &p)
           << ", \"flops\": " << (long long)s.flops << ", \"bytes\": " << (long long)s.bytes;
         if (s.kind == S_IGEMM)
             o << ", \"M\": " << s.ig.M << ", \"N\": " << s.ig.N << ", \"K\": " << s.ig.K << ", \"epilogue_ops\": " << s.ig.epi.n_ops
-              << ", \"k_split_waves\": " << (s.il.run == 2 ? 1 : 0) << ", \"channel_tile_major\": " << s.ig.nmajor << ", \"k_split_workgroups\": " << (s.il.splits > 1 ? s.il.splits : 1);
+              << ", \"k_split_waves\": " << (s.il.run == 2 ? 1 : 0) << ", \"channel_tile_major\": " << s.ig.nmajor << ", \"shape_order\": " << s.il.planes << ", \"k_split_workgroups\": " << (s.il.splits > 1 ? s.il.splits : 1);
         if (s.kind == S_ELTWISE) o << ", \"n\": " << (long long)s.el.n << ", \"chain_ops\": " << s.el.epi.n_ops;
         o << "}";
     }

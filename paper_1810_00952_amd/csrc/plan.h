@@ -43,7 +43,8 @@ struct Step {
     int stem_direct = 0, stem_kw = 0;   // S_STEM_POOL reading the channel-first input itself (st_* and t_C: its geometry; stem_kw: filter width)
     int pair = 0;                       // S_IGEMM: 1: launched together with the next step (an independent contraction of the
                                         // same tile shape); 2: that next step, which launches nothing itself.  S_IGEMM and S_TN, in
-                                        // either order: 3 and 2 likewise (both gradients of a layer).  Changes of layout: 1 and 2 likewise
+                                        // either order: 3 and 2 likewise (both gradients of a layer).  Changes of layout: 1 and 2 likewise,
+                                        // or 2: an earlier contraction stores in that order (il.planes)
     int chain = 0;                      // S_IGEMM: 1: a split dense contraction whose adding launch also runs the next step (a
                                         // small dense layer on its result); 2: that next step, which launches nothing itself
     int slot[SL_COUNT];

@@ -536,6 +536,8 @@ PLANES_CASES = [
     # n   c    h   w   o    k  s  p  options
     (16, 64, 28, 28, 128, 3, 1, 1, {}),                 # nine taps from one copy of the rows, whole tiles
     (25, 320, 20, 20, 40, 3, 1, 1, {}),
+    (16, 128, 28, 28, 128, 3, 1, 1, {}),                # in place of K split over the waves
+    (70, 64, 30, 58, 512, 1, 1, 0, {}),                 # in place of 256x256 tiles
     (9, 64, 22, 26, 200, 3, 1, 1, {}),                  # images that end inside a wave's pixels, channels past the tile, a ragged last tile
     (50, 256, 14, 14, 264, 3, 1, 1, {}),                # 196 pixels: four at a time and no more
     (64, 128, 28, 28, 128, 3, 1, 1, {}),
@@ -567,11 +569,15 @@ def test_result_stored_in_shape_order(case, steps):
     g.output(ops[-1][1][0])
     data = {"x": W.as_dtype(rng.standard_normal((n, c, h, w)), "bf16"), "w": W.as_dtype(rng.standard_normal((o, c, k, k)) / (c * k * k) ** 0.5, "bf16"),
             "b": rng.standard_normal(o).astype(np.float32)}
-    assert any("_planes" in q and "direct" not in q for q in steps_of(g, opts)), steps_of(g, opts)
-    assert "nhwc_to_nchw" in steps_of(g, dict(opts, no_pair=1)), steps_of(g, dict(opts, no_pair=1))
+    from paper_1810_00952_amd import binding
+    order = lambda o: [q.get("shape_order", 0) for q in binding.Plan(binding.graph_from_spec(binding.Context(), g), o).describe()["steps"]]
+    assert 1 in order(opts) and 1 not in order(dict(opts, no_pair=1)), steps_of(g, opts)
     print(case, steps_of(g, opts), flush=True)
     got, _ = run_hip(g, data, opts=opts)
-    rows, _ = run_hip(g, data, opts=dict(opts, no_pair=1))       # rows of channels, then the transposition: the same sums and rounding
-    np.testing.assert_array_equal(got[g.outputs[0]], rows[g.outputs[0]])
-    if n * c * h * w * o < 2e8:
+    # rows of channels, then the transposition: the same sums and rounding, K not split over the waves, and the same tiles
+    rows, _ = run_hip(g, data, opts=dict(opts, no_pair=1, no_run_ks=1))
+    other_tiles = any("256x256" in q for q in steps_of(g, dict(opts, no_pair=1)))
+    if not other_tiles:
+        np.testing.assert_array_equal(got[g.outputs[0]], rows[g.outputs[0]])
+    if n * c * h * w * o < 2e8 or (other_tiles and steps == "bias_relu"):
         check(g, data, "bf16", f"planes {case} {steps}", opts)
