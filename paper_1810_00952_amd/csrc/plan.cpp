@@ -395,8 +395,8 @@ struct Planner {
                     direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, !vec && !pad ? OTHER_GATHER : p.C % (8 * KV) == 0 ? OTHER_DMA : OTHER_TAPS,
                                          (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1, ov && beside_weights_gradient(x));
             }
-            // A bf16 result that is a graph output (Shape order): only the slower direct-load kernel stores in that order
-            // itself.  From 0.4 GFLOP on, the pixel-on-lane kernels writing channel-last into the workspace plus a
+            // A bf16 result that is a graph output (Shape order): the slower direct-load kernel stores in that order
+            // itself, the pixel-on-lane kernels only where fuse_planes_store lets them.  From 0.4 GFLOP on, the pixel-on-lane kernels writing channel-last into the workspace plus a
             // transposition (one launch more, and one more for a channel-first residual) are faster: 64x128x28x28 through
             // 3x3 20 + 9 us against 56, with a residual 43 against 166; at 0.46 GFLOP 14.3 against 16.9; below, the
             // direct-load kernel with its K split is level or ahead (0.23 GFLOP: 16.4 against 14.6).
