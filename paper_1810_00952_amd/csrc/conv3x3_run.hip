@@ -161,6 +161,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const Igemm
     uint32_t y_off[NPASS];                         // byte offset of the lane's 8 channels in pass q, or out of range
     int pA[NPASS];                                 // parked position read first in pass q
     const uint32_t y_bytes = p.y_bytes;
+    PlanesTile<WTM, WTN> planes;
     {
         const bool has_res = e.t_op >= 0;
         // absent operands get an empty descriptor: every load then returns zeros without touching memory
@@ -174,7 +175,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const Igemm
                 const int n = nb + j * 32 + 8 * g;
                 bias_r[j][g] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, n < p.N ? (uint32_t)n * 4u : OOB, 0, 0));
             }
-        if (!PLANES)
+        if (PLANES) planes.request(p, m0 + wm * WTM, n0 + wn * WTN, lane, rres);
+        else
 #pragma unroll
         for (int q = 0; q < NPASS; ++q) {
             const int row = q * RPP + rr;
@@ -343,7 +345,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv3x3_run_kernel(const Igemm
     const rsrc_t ry = make_rsrc(p.y, y_bytes);
     const float lo = e.relu_last ? 0.0f : -INFINITY;
     if constexpr (PLANES) {
-        store_planes<WTM, WTN>(p, park, acc, bias_r, m0 + wm * WTM, n0 + wn * WTN, lane, ry, lo);
+        planes.store(p, park, acc, bias_r, n0 + wn * WTN, lane, ry, lo);
         return;
     }
 #pragma unroll

@@ -93,7 +93,7 @@ constexpr uint32_t OOB = 0x80000000u;
 }  // namespace
 
 // The workgroup's work: tile number bid_in of the contraction p.  YF32: the output is fp32 (no residual then).
-// PLANES: the result in Shape order (lp_planes.h; bf16, no residual).
+// PLANES: the result in Shape order (lp_planes.h; bf16).
 // ANYACT: the operand-free steps behind bias and residual are any (up to eight, codes in the epilogue), not just one ReLU.
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool YF32 = false, bool ANYACT = false, bool PLANES = false>
 __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bid_in)
@@ -273,7 +273,8 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
     constexpr int LPR = WTN / 8;                   // lanes per output row of the wave tile (16 bytes of bf16 each)
     constexpr int RPP = 64 / LPR;                  // rows per row-wise pass
     constexpr int NPASS = WTM / RPP;
-    constexpr int NEPI = TN * 4 + (PLANES ? 0 : NPASS);   // vector-memory operations RL_EPI_LOADS issues
+    PlanesTile<WTM, WTN> planes;
+    constexpr int NEPI = TN * 4 + (PLANES ? PlanesTile<WTM, WTN>::NQ : NPASS);   // vector-memory operations RL_EPI_LOADS issues
     constexpr int POSN = WTN / 4;                  // 16-byte fp32 positions per parked row
     constexpr int RP = 16 / POSN > 0 ? 16 / POSN : 1;   // parked rows per 256 bytes (all 64 banks)
     const int rr = lane / LPR, pp = lane % LPR;
@@ -294,7 +295,8 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
                 const int n = nb + j * 32 + 8 * g;                                                                    \
                 bias_r[j][g] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, n < p.N ? (uint32_t)n * 4u : OOB, 0, 0)); \
             }                                                                                                         \
-        if (!PLANES) _Pragma("unroll") for (int q = 0; q < NPASS; ++q) {                                              \
+        if (PLANES) planes.request(p, m0 + wm * WTM, n0 + wn * WTN, lane, rres);                                      \
+        else _Pragma("unroll") for (int q = 0; q < NPASS; ++q) {                                                      \
             const int row = q * RPP + rr;                                                                             \
             const int key = (row / RP) & (POSN - 1);                                                                  \
             pA[q] = 2 * pp + (key & 1);                                                                               \
@@ -393,7 +395,7 @@ __device__ __forceinline__ void igemm_lp_body(const IgemmParams &p, const int bi
     const rsrc_t ry = make_rsrc(p.y, y_bytes);
     const float lo = (!ANYACT && e.relu_last) ? 0.0f : -INFINITY;
     if constexpr (PLANES) {
-        store_planes<WTM, WTN>(p, park, acc, bias_r, m0 + wm * WTM, n0 + wn * WTN, lane, ry, lo);
+        planes.store(p, park, acc, bias_r, n0 + wn * WTN, lane, ry, lo);
         return;
     }
 #pragma unroll

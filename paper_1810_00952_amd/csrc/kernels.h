@@ -124,7 +124,7 @@ struct IgemmLaunch {
 };
 hipError_t launch_igemm(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
 // whether the pixel-on-lane kernels may store this result in Shape order (lp_planes.h)
-inline bool planes_ok(const IgemmParams &p) { return p.OHW % 4 == 0 && p.ys_p == 1 && p.ys_c == p.OHW && p.ys_n == (int64_t)p.N * p.OHW && p.epi.t_op < 0 && p.y_dtype == DT_BF16; }
+inline bool planes_ok(const IgemmParams &p) { return p.OHW % 4 == 0 && p.ys_p == 1 && p.ys_c == p.OHW && p.ys_n == (int64_t)p.N * p.OHW && p.y_dtype == DT_BF16 && (p.epi.t_op < 0 || (p.epi.t_op == E_ADD && p.epi.t_dtype == DT_BF16)); }
 enum { DIRECT_ROWS = 0, DIRECT_PLANES = 1, DIRECT_ANY = 2 };
 hipError_t launch_igemm_direct(const IgemmParams &p, const IgemmLaunch &l, hipStream_t s);
 

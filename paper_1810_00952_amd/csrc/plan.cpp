@@ -1544,6 +1544,26 @@ struct Planner {
             p.ys_n = (int64_t)p.N * p.OHW; p.ys_p = 1; p.ys_c = p.OHW;
             finalize_epilogue(p.epi);
             if (other_use || !p.epi.simple || !planes_ok(p)) continue;
+            if (p.epi.t_op >= 0) {
+                // the residual in the order the caller or a step before gave it, if its change of layout is all that stands between
+                int &r = c.slot[SL_E0 + epi_host_arg(p.epi, p.epi.has_bias ? 1 : 0)];
+                size_t sk = plan.steps.size();
+                int readers = 0;
+                for (size_t k = 0; k < plan.steps.size(); ++k)
+                    for (int q = 0; q < SL_COUNT; ++q)
+                        if (plan.steps[k].slot[q] == r) {
+                            if (q == SL_Y) sk = k;
+                            else ++readers;
+                        }
+                if (sk >= si || plan.steps[sk].kind != S_TO_NHWC || plan.steps[sk].pair || plan.steps[sk].t_C != p.N || plan.steps[sk].t_P != p.OHW || plan.bufs[r].bound_value >= 0) continue;
+                Step &k = plan.steps[sk];
+                r = k.slot[SL_X];
+                if (readers == 1) {
+                    k.slot[SL_X] = k.slot[SL_Y] = -1;
+                    k.pair = 2;
+                    k.bytes = 0;
+                }
+            }
             c.ig.ys_n = p.ys_n; c.ig.ys_p = p.ys_p; c.ig.ys_c = p.ys_c;
             c.il.planes = 1;
             if (c.il.run > 1) c.il.run = 1;

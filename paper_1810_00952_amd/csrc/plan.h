@@ -44,7 +44,7 @@ struct Step {
     int pair = 0;                       // S_IGEMM: 1: launched together with the next step (an independent contraction of the
                                         // same tile shape); 2: that next step, which launches nothing itself.  S_IGEMM and S_TN, in
                                         // either order: 3 and 2 likewise (both gradients of a layer).  Changes of layout: 1 and 2 likewise,
-                                        // or 2: an earlier contraction stores in that order (il.planes)
+                                        // or 2: an earlier contraction stores, or a later one reads its residual, in that order (il.planes)
     int chain = 0;                      // S_IGEMM: 1: a split dense contraction whose adding launch also runs the next step (a
                                         // small dense layer on its result); 2: that next step, which launches nothing itself
     int slot[SL_COUNT];

@@ -550,7 +550,7 @@ PLANES_CASES = [
 ]
 
 
-@pytest.mark.parametrize("steps", ["none", "bias", "bias_relu"])
+@pytest.mark.parametrize("steps", ["none", "bias", "bias_relu", "bias_residual_relu", "residual"])
 @pytest.mark.parametrize("case", PLANES_CASES, ids=[f"planes{i}" for i in range(len(PLANES_CASES))])
 def test_result_stored_in_shape_order(case, steps):
     import numpy as np
@@ -561,14 +561,17 @@ def test_result_stored_in_shape_order(case, steps):
     x, wv, b = g.input("x", "bf16", (n, c, h, w)), g.param("w", "bf16", (o, c, k, k)), g.param("b", "f32", (o,))
     t = [("bf16", (n, o, oh, ow))]
     ops = [g.op("conv2d", [x, wv], t, stride=(s, s), pad=(p, p))]
-    if steps != "none":
+    if "bias" in steps:
         ops.append(g.op("bias_add", [ops[-1][1][0], b], t, axis=1))
-    if steps == "bias_relu":
+    if "residual" in steps:
+        ops.append(g.op("add", [ops[-1][1][0], g.input("r", "bf16", (n, o, oh, ow))], t))
+    if "relu" in steps:
         ops.append(g.op("relu", [ops[-1][1][0]], t))
     g.group([q[0] for q in ops])
     g.output(ops[-1][1][0])
     data = {"x": W.as_dtype(rng.standard_normal((n, c, h, w)), "bf16"), "w": W.as_dtype(rng.standard_normal((o, c, k, k)) / (c * k * k) ** 0.5, "bf16"),
-            "b": rng.standard_normal(o).astype(np.float32)}
+            "b": rng.standard_normal(o).astype(np.float32), "r": W.as_dtype(rng.standard_normal((n, o, oh, ow)), "bf16")}
+    data = {q: data[q] for q in data if q != "r" or "residual" in steps}
     from paper_1810_00952_amd import binding
     order = lambda o: [q.get("shape_order", 0) for q in binding.Plan(binding.graph_from_spec(binding.Context(), g), o).describe()["steps"]]
     assert 1 in order(opts) and 1 not in order(dict(opts, no_pair=1)), steps_of(g, opts)
