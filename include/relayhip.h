@@ -192,7 +192,9 @@ typedef struct rl_plan_opts {
     int32_t no_c64;         /* no weights-in-registers kernel for 3x3 64->64 convolutions */
     int32_t no_run;         /* no nine-taps-from-one-copy kernel for 3x3 stride-1 convolutions on short rows */
     int32_t no_run_ks;      /* in that kernel's 128x64 form: do not split K over the waves */
-    int32_t no_pair;        /* a stride-2 convolution and the 1x1 projection beside it go out as two launches */
+    int32_t no_pair;        /* no two steps share a launch: a stride-2 convolution and the 1x1 projection beside it, the two
+                               gradients of a layer (whose K slices, and the kernel of the one with respect to the input, are
+                               chosen for the shared launch where there is one), two changes of layout */
     int32_t s2_pair;        /* opt in: such a pair as ONE contraction whose centre tap carries the projection (second
                                accumulators) with the input rows shared in LDS -- correct and tested, but its 64-pixel tiles
                                lose to the two-contractions-in-one-grid form on every shape measured so far */
@@ -213,9 +215,13 @@ typedef struct rl_plan_opts {
                                one-launch form without waiting for all of its workgroups to be resident: those that are there
                                share the work (what it falls back to); n > 2: on its first n workgroups.  All give the same bits */
     int32_t no_direct;      /* never the contraction kernel that loads its operands straight into registers */
-    int32_t direct_all;     /* that kernel wherever it can run, for tests and measurements */
+    int32_t direct_all;     /* that kernel wherever it can run, for tests and measurements: 1: with the tile and K slices the
+                               planner would take; 16 * tile + slices: with those (tile 32: 1, 2, 4 or 8 slices; tile 16: 8).  Of a
+                               recurrent cell the last four bits are the hidden units per workgroup (4, else 8) */
     int32_t tn_run;         /* 3x3 bf16 weight gradients with the taps of a filter row from one copy of the rows: 1: wherever
                                that kernel can run (n > 1: K cut into up to n slices), -1: never */
+    int32_t no_shape_order; /* a large bf16 convolution whose result is a graph output: the pixel-on-lane kernels store channel-last
+                               and a transposition turns the result (and one its residual), never in Shape order at once */
 } rl_plan_opts;
 
 /* rl_plan_create re-checks the whole graph (Type-Call on every call, group legality, outputs reachable), picks

@@ -1523,7 +1523,7 @@ struct Planner {
     // 19.4 -> 17.1; 64x512x8x8 -> 512 28.2 against 28.8).
     void fuse_planes_store()
     {
-        if (plan.opts.no_pair || plan.lean) return;
+        if (plan.opts.no_shape_order || plan.lean) return;
         for (size_t si = 0; si < plan.steps.size(); ++si) {
             Step &c = plan.steps[si];
             if (c.kind != S_IGEMM || c.pair || c.chain || c.stem || !c.il.lp || c.il.ws || c.il.c64 || c.il.s2pair || c.il.anyact || (c.il.run > 1 && c.ig.C >= 512)) continue;

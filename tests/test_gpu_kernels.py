@@ -574,12 +574,12 @@ def test_result_stored_in_shape_order(case, steps):
     data = {q: data[q] for q in data if q != "r" or "residual" in steps}
     from paper_1810_00952_amd import binding
     order = lambda o: [q.get("shape_order", 0) for q in binding.Plan(binding.graph_from_spec(binding.Context(), g), o).describe()["steps"]]
-    assert 1 in order(opts) and 1 not in order(dict(opts, no_pair=1)), steps_of(g, opts)
+    assert 1 in order(opts) and 1 in order(dict(opts, no_pair=1)) and 1 not in order(dict(opts, no_shape_order=1)), steps_of(g, opts)
     print(case, steps_of(g, opts), flush=True)
     got, _ = run_hip(g, data, opts=opts)
     # rows of channels, then the transposition: the same sums and rounding, K not split over the waves, and the same tiles
-    rows, _ = run_hip(g, data, opts=dict(opts, no_pair=1, no_run_ks=1))
-    other_tiles = any("256x256" in q for q in steps_of(g, dict(opts, no_pair=1)))
+    rows, _ = run_hip(g, data, opts=dict(opts, no_shape_order=1, no_run_ks=1))
+    other_tiles = any("256x256" in q for q in steps_of(g, dict(opts, no_shape_order=1)))
     if not other_tiles:
         np.testing.assert_array_equal(got[g.outputs[0]], rows[g.outputs[0]])
     if n * c * h * w * o < 2e8 or (other_tiles and steps == "bias_relu"):

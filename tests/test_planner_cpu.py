@@ -488,6 +488,26 @@ def test_split_k_is_planned_for_few_tiles_and_long_k():
     assert d["steps"][1]["flops"] == 0 and d["steps"][0]["flops"] == 2.0 * 32 * (784 * 128 + 128 * 10)
 
 
+def _steps(spec, opts=None):
+    return B.Plan(B.graph_from_spec(B.Context(), spec), opts).describe()["steps"]
+
+
+def test_shared_launches_and_results_in_shape_order_have_an_option_each():
+    spec = W.conv_group(16, 64, 128, 28, 28, 3, 1, 1, "bf16", residual=True)[0]
+    order = lambda opts: [s["shape_order"] for s in _steps(spec, opts) if "shape_order" in s]
+    assert order({}) == [1] and order({"no_pair": 1}) == [1] and order({"no_shape_order": 1}) == [0]
+    # a caller built before the option was there gets the planner's choice
+    g = B.graph_from_spec(B.Context(), spec)
+    o, h = B.rl_plan_opts(), ctypes.c_void_p()
+    o.no_shape_order = 1
+    o.struct_size = B.rl_plan_opts.no_shape_order.offset
+    assert B.lib().rl_plan_create(g._h, ctypes.byref(o), ctypes.byref(h)) == 0
+    need = ctypes.c_size_t()
+    buf = ctypes.create_string_buffer(1 << 16)
+    assert B.lib().rl_plan_describe(h, buf, len(buf), ctypes.byref(need)) == 0 and b'"shape_order": 1' in buf.value
+    B.lib().rl_plan_destroy(h)
+
+
 def test_both_gradients_of_a_layer_share_no_workspace():
     # the two run at once: whatever either reads or writes is apart from what the other writes
     for dtype, (b, c, h, o) in (("f32", (32, 64, 28, 64)), ("bf16", (16, 40, 20, 72))):
