@@ -1562,18 +1562,21 @@ struct Planner {
                     k.slot[SL_X] = k.slot[SL_Y] = -1;
                     k.pair = 2;
                     k.bytes = 0;
+                    k.kernel = "(read by the contraction as it is)";
                 }
             }
             c.ig.ys_n = p.ys_n; c.ig.ys_p = p.ys_p; c.ig.ys_c = p.ys_c;
             c.il.planes = 1;
             if (c.il.run > 1) c.il.run = 1;
             if (c.il.big) { c.il.big = 0; c.kernel.replace(c.kernel.find("256x256"), 7, "256x128"); }
+            c.kernel += "_shape_order";
             c.slot[SL_Y] = y;
-            // the change of layout stays in the list, as part of the step that stores
+            // the change of layout stays in the list, as one that launches nothing
             Step &m = plan.steps[sj];
             m.slot[SL_X] = -1;
             m.pair = 2;
             m.bytes = 0;
+            m.kernel = "(stored by the contraction)";
         }
     }
 

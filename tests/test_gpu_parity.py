@@ -135,7 +135,7 @@ LP_CASES = [
 
 @pytest.mark.parametrize("case", LP_CASES, ids=[f"lp{i}" for i in range(len(LP_CASES))])
 def test_conv_group_internal_layout_bf16(case):
-    opts = {"no_c64": 1, "no_run": 1}                # the general kernel also on the shapes that have one of their own
+    opts = {"no_c64": 1, "no_run": 1, "no_shape_order": 1}      # the general kernel also on the shapes that have one of their own; rows of channels stored
     b, ci, co, h, w, k, s, p, res, relu = case
     spec, data = W.conv_group(b, ci, co, h, w, k, s, p, "bf16", residual=res, relu=relu, tail=True)
     from paper_1810_00952_amd import binding
@@ -274,13 +274,14 @@ def test_conv3x3_taps_from_one_copy_of_the_rows(case):
     b, ci, co, h, w, bias, res, relu, tile = case
     spec, data = W.conv_group(b, ci, co, h, w, 3, 1, 1, "bf16", residual=res, relu=relu, tail=True, bias=bias)
     from paper_1810_00952_amd import binding
-    desc = binding.Plan(binding.graph_from_spec(binding.Context(), spec)).describe()
+    rows = {"no_shape_order": 1}                     # rows of channels stored, then turned
+    desc = binding.Plan(binding.graph_from_spec(binding.Context(), spec), rows).describe()
     assert any(st["kernel"] == f"igemm_conv2d_bf16_{tile}_run" for st in desc["steps"]), [st["kernel"] for st in desc["steps"]]
     if ci == 512:
         st = [st for st in desc["steps"] if st["kernel"].endswith("_run")][0]
         assert st["k_split_waves"] == 1 and st["channel_tile_major"] == 1, st
     print(f"conv3x3 run case {case}", flush=True)
-    got, _ = check_graph(spec, data, f"conv3x3 run {case}")
+    got, _ = check_graph(spec, data, f"conv3x3 run {case}", opts=rows)
     # against the general kernel: same products, another summation order
     gen, _ = run_hip(spec, data, opts={"no_run": 1})
     for vid in spec.outputs:
@@ -929,12 +930,14 @@ OUT_ORDER_CASES = [
 
 @pytest.mark.parametrize("case", OUT_ORDER_CASES, ids=[f"oo{i}" for i in range(len(OUT_ORDER_CASES))])
 def test_convolution_result_as_channel_first_output(case):
-    # the fast kernels write channel-last into the workspace and a transposition fills the output; the plan option
-    # keeps the kernel that stores channel-first itself.  Both against the oracle.
+    # the fast kernels write channel-last into the workspace and a transposition fills the output, or store in Shape order
+    # themselves where they can; the other plan option keeps the kernel that always stores channel-first itself.  All against the oracle.
     b, ci, co, h, w, k, s, p, res, relu = case
     spec, data = W.conv_group(b, ci, co, h, w, k, s, p, "bf16", residual=res, relu=relu)
-    ks = [st["kernel"] for st in s_plan_steps(spec)]
+    rows = {"no_shape_order": 1, "no_pair": 1}
+    ks = [st["kernel"] for st in s_plan_steps(spec, rows)]
     assert ks[-1] == "nhwc_to_nchw" and not ks[-2].endswith("_dma") and ks.count("nchw_to_nhwc") == (2 if res else 1), ks
+    check_graph(spec, data, f"conv to channel-first output by a transposition {case}", opts=rows)
     ks1 = [st["kernel"] for st in s_plan_steps(spec, {"no_out_transpose": 1})]
     assert "_dma" in ks1[-1] and "nhwc_to_nchw" not in ks1, ks1
     check_graph(spec, data, f"conv to channel-first output {case}")

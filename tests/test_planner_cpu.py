@@ -155,16 +155,19 @@ def test_gradient_operators_plan_onto_the_fast_kernels():
     k = lambda spec, opts=None: [s["kernel"] for s in B.Plan(B.graph_from_spec(ctx, spec), opts).describe()["steps"]]
     # with respect to the input, through a param: the forward operator on re-ordered weights ...
     spec = W.grad_case("conv2d_grad_x", (64, 128, 28, 28, 128, 3), "bf16", 1, 1)[0]
-    # (its result, a graph output in Shape order, written channel-last by the nine-taps-from-one-copy kernel and transposed)
-    assert k(spec) == ["nchw_to_nhwc", "igemm_conv2d_grad_x_bf16_256x128_run", "nhwc_to_nchw"]
+    # (its result, a graph output in Shape order, stored in that order by the nine-taps-from-one-copy kernel, or channel-last and transposed)
+    assert k(spec) == ["nchw_to_nhwc", "igemm_conv2d_grad_x_bf16_256x128_run_shape_order", "(stored by the contraction)"]
+    rows = {"no_shape_order": 1}
+    assert k(spec, rows) == ["nchw_to_nhwc", "igemm_conv2d_grad_x_bf16_256x128_run", "nhwc_to_nchw"]
     assert k(spec, {"no_out_transpose": 1}) == ["nchw_to_nhwc", "igemm_conv2d_grad_x_bf16_128x128_dma"]
     assert k(spec, {"no_grad_fwd": 1}) == ["igemm_conv2d_grad_x_bf16_64x64_gather"]
     # ... inside a chain on the nine-taps-from-one-copy kernel, like the forward pass
-    assert k(W.grad_chain(64, 128, 28, 3, "bf16")[0]) == ["nchw_to_nhwc", "igemm_conv2d_grad_x_bf16_256x128_run", "igemm_conv2d_grad_x_bf16_256x128_run",
-                                                         "igemm_conv2d_grad_x_bf16_256x128_run", "nhwc_to_nchw"]
+    assert k(W.grad_chain(64, 128, 28, 3, "bf16")[0], rows) == ["nchw_to_nhwc", "igemm_conv2d_grad_x_bf16_256x128_run", "igemm_conv2d_grad_x_bf16_256x128_run",
+                                                               "igemm_conv2d_grad_x_bf16_256x128_run", "nhwc_to_nchw"]
     # ... at a stride on dy spread out with zeros
     spec = W.grad_case("conv2d_grad_x", (64, 64, 56, 56, 128, 3), "bf16", 2, 1)[0]
-    assert k(spec) == ["nchw_to_nhwc", "dilate_nhwc", "igemm_conv2d_grad_x_bf16_128x64_lp", "nhwc_to_nchw"]
+    assert k(spec, rows) == ["nchw_to_nhwc", "dilate_nhwc", "igemm_conv2d_grad_x_bf16_128x64_lp", "nhwc_to_nchw"]
+    assert k(spec) == ["nchw_to_nhwc", "dilate_nhwc", "igemm_conv2d_grad_x_bf16_128x64_lp_shape_order", "(stored by the contraction)"]
     assert k(spec, {"no_out_transpose": 1}) == ["nchw_to_nhwc", "dilate_nhwc", "igemm_conv2d_grad_x_bf16_128x64_dma"]
     # through weights that are an activation: the element gather, its operand gathered by a step of the plan
     spec = W.grad_case("conv2d_grad_x", (64, 64, 56, 56, 128, 3), "bf16", 2, 1, second_is_param=False)[0]
@@ -185,7 +188,8 @@ def test_plan_options_are_fixed_in_the_plan():
     g = B.graph_from_spec(ctx, spec)
     k = lambda opts: [s["kernel"] for s in B.Plan(g, opts).describe()["steps"] if s["kernel"].startswith("igemm")]
     assert k(None) == ["igemm_conv2d_bf16_3x3_c64"] == k({})
-    assert k({"no_c64": 1}) == ["igemm_conv2d_bf16_128x64_lp"]
+    assert k({"no_c64": 1}) == ["igemm_conv2d_bf16_128x64_lp_shape_order"]
+    assert k({"no_c64": 1, "no_shape_order": 1}) == ["igemm_conv2d_bf16_128x64_lp"]
     assert k({"no_c64": 1, "ws_all": 1}) == ["igemm_conv2d_bf16_128x64_ws"]
     assert k({"no_c64": 1, "no_lp": 1}) == ["igemm_conv2d_bf16_128x64_dma"]
     assert k(None) == ["igemm_conv2d_bf16_3x3_c64"]
@@ -490,6 +494,16 @@ def test_split_k_is_planned_for_few_tiles_and_long_k():
 
 def _steps(spec, opts=None):
     return B.Plan(B.graph_from_spec(B.Context(), spec), opts).describe()["steps"]
+
+
+# what a plan lists is what it launches: a step in brackets launches nothing and moves nothing
+@pytest.mark.parametrize("residual,want", [
+    (False, ["nchw_to_nhwc", "igemm_conv2d_bf16_128x64_run_shape_order", "(stored by the contraction)"]),
+    (True, ["nchw_to_nhwc", "(read by the contraction as it is)", "igemm_conv2d_bf16_128x64_run_shape_order", "(stored by the contraction)"])])
+def test_changes_of_layout_that_a_contraction_does_away_with_are_no_launches(residual, want):
+    steps = _steps(W.conv_group(16, 64, 128, 28, 28, 3, 1, 1, "bf16", residual=residual)[0])
+    assert [s["kernel"] for s in steps] == want
+    assert all((s["bytes"] == 0) == s["kernel"].startswith("(") for s in steps), steps
 
 
 def test_shared_launches_and_results_in_shape_order_have_an_option_each():
