@@ -1,5 +1,5 @@
-// The workgroup of the direct-load contraction kernel (igemm_dma.hip, where its design is described), for the kernels that run it
-// alone or beside another contraction (igemm_grads.hip).
+// The direct-load contraction kernel (igemm_dma.hip, where its design is described), alone in its grid or beside another contraction
+// (igemm_grads.hip).
 #pragma once
 #include "igemm_epilogue.h"
 #include "igemm_lds.h"
@@ -36,14 +36,34 @@ __device__ __forceinline__ void wg_barrier()
 // MODE of the result: rows of channels 16 bytes at a time, the LSTM gates, or any order
 enum { STORE_ROWS = 0, STORE_GATES = 1, STORE_ANY = 2 };
 
-// Tile `bid` (numbered for the XCDs) and K slice `split` by the 256 threads of a workgroup; st0 .. st2: its LDS
+// BESIDE: the workgroups of another contraction in the same grid (igemm_grads.hip).  Its take() does the work of those and returns false,
+// or returns true with the number of this contraction's workgroup.
+struct Alone {
+    static constexpr bool other = false;
+};
+
+// The body is the kernel's own text and no function that takes its arguments by reference: inlined from one, the compiler no longer holds
+// them for constant memory while it orders the code, and fetches those of the epilogue one by one, each where it is used (17 more scalar
+// loads; dense 1000 x 1000 x 784 bf16 8.2 us against 7.95, 17x96x29x29 -> 136 3x3 with a residual 21.9 against 21.4).
 template <int BM, int BN> constexpr int dma_stage_bytes() { return (BM + BN) * 128; }
-template <typename T, int BM, int BN, int MODE, bool TAPS>
-__device__ __forceinline__ void igemm_dma_body(const IgemmParams &p, int bid, const int split, unsigned char (&st0)[dma_stage_bytes<BM, BN>()], unsigned char (&st1)[dma_stage_bytes<BM, BN>()],
-                                               unsigned char (&st2)[dma_stage_bytes<BM, BN>()])
+template <typename T, int BM, int BN, int MODE, bool TAPS, typename BESIDE>
+__global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, const BESIDE beside)
 {
     constexpr bool GATES = MODE == STORE_GATES;
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
+    __shared__ __attribute__((aligned(1024))) unsigned char st0[dma_stage_bytes<BM, BN>()];
+    __shared__ __attribute__((aligned(1024))) unsigned char st1[dma_stage_bytes<BM, BN>()];
+    __shared__ __attribute__((aligned(1024))) unsigned char st2[dma_stage_bytes<BM, BN>()];
+    int bid = blockIdx.x, split = 0;
+    if constexpr (BESIDE::other) {
+        if (!beside.template take<T>(bid, st0, st1, st2)) return;
+        const int tiles = p.nblk_m * p.nblk_n;
+        if (bid >= tiles * max(p.splits, 1)) return;
+        split = p.splits > 1 ? bid / tiles : 0;
+        bid -= split * tiles;
+    } else {
+        split = p.splits > 1 ? (int)blockIdx.y : 0;
+    }
     touch_args(p);
     constexpr int KV = Elem<T>::KV;
     constexpr int ES = (int)sizeof(T);

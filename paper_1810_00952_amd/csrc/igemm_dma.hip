@@ -41,17 +41,6 @@
 
 namespace rl {
 
-template <typename T, int BM, int BN, int MODE, bool TAPS>
-__global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p)
-{
-#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
-    __shared__ __attribute__((aligned(1024))) unsigned char st0[dma_stage_bytes<BM, BN>()];
-    __shared__ __attribute__((aligned(1024))) unsigned char st1[dma_stage_bytes<BM, BN>()];
-    __shared__ __attribute__((aligned(1024))) unsigned char st2[dma_stage_bytes<BM, BN>()];
-    igemm_dma_body<T, BM, BN, MODE, TAPS>(p, blockIdx.x, p.splits > 1 ? (int)blockIdx.y : 0, st0, st1, st2);
-#endif
-}
-
 // The second kernel of a split contraction: y[m, n] = epilogue(partial[0][m][n] + partial[1][m][n] + ...), one element
 // per thread, slices added in order (so the result does not depend on timing), any output strides.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const IgemmParams p)
@@ -197,7 +186,7 @@ hipError_t launch_reduce_dense(const ReduceDenseParams &p, hipStream_t s)
 
 // explicit instantiations (the host-side launch stubs of a kernel template with function-local
 // __shared__ arrays are not emitted implicitly)
-#define RL_INST(T, BM, BN, MODE, TAPS) template __global__ void igemm_dma_kernel<T, BM, BN, MODE, TAPS>(const IgemmParams);
+#define RL_INST(T, BM, BN, MODE, TAPS) template __global__ void igemm_dma_kernel<T, BM, BN, MODE, TAPS, Alone>(const IgemmParams, const Alone);
 #define RL_INST4(T, BM, BN) RL_INST(T, BM, BN, STORE_ROWS, false) RL_INST(T, BM, BN, STORE_ANY, false) RL_INST(T, BM, BN, STORE_ROWS, true) RL_INST(T, BM, BN, STORE_ANY, true)
 RL_INST(uint16_t, 128, 128, STORE_ROWS, false) RL_INST(uint16_t, 128, 128, STORE_ANY, false) RL_INST4(uint16_t, 128, 64) RL_INST4(uint16_t, 64, 64) RL_INST(uint16_t, 64, 64, STORE_GATES, false)
 RL_INST4(float, 128, 64) RL_INST4(float, 64, 64) RL_INST(float, 64, 64, STORE_GATES, false)
@@ -236,15 +225,15 @@ static hipError_t launch_dma(const IgemmParams &p0, hipStream_t s)
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
     if (p.splits > 1) {
         if (GATES || !igemm_dma_splits_ok(p, TAPS, (int)sizeof(T))) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS>), dim3((unsigned)nblk, (unsigned)p.splits), dim3(256), 0, s, p);
+        hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS, Alone>), dim3((unsigned)nblk, (unsigned)p.splits), dim3(256), 0, s, p, Alone{});
         hipError_t er = hipGetLastError();
         if (er != hipSuccess || p.skip_reduce) return er;
         return launch_splitk_reduce(p, s);
     }
     const bool rows = p.ys_n == (int64_t)p.OHW * p.ys_p && p.ys_c == 1 && (p.N & 7) == 0 && (p.ys_p & 7) == 0;
-    if (GATES) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, STORE_GATES, false>), dim3((unsigned)nblk), dim3(256), 0, s, p);
-    else if (rows) hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS>), dim3((unsigned)nblk), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ANY, TAPS>), dim3((unsigned)nblk), dim3(256), 0, s, p);
+    if (GATES) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, STORE_GATES, false, Alone>), dim3((unsigned)nblk), dim3(256), 0, s, p, Alone{});
+    else if (rows) hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS, Alone>), dim3((unsigned)nblk), dim3(256), 0, s, p, Alone{});
+    else hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ANY, TAPS, Alone>), dim3((unsigned)nblk), dim3(256), 0, s, p, Alone{});
     return hipGetLastError();
 }
 

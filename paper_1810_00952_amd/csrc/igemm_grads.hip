@@ -12,33 +12,31 @@
 
 namespace rl {
 
-template <typename T, int MODE, bool TAPS, bool CONV>
-__global__ __launch_bounds__(256) void igemm_grads_kernel(const IgemmParams p, const TnParams q, const int n_first, const int tn_first)
-{
-#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
-    constexpr int STAGE = dma_stage_bytes<64, 64>();
-    static_assert(STAGE == tn_stage_bytes<64, 64>(), "one set of stages for either");
-    __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
-    __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
-    __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE];
-    // the second part starts at a multiple of the XCD count, so that a workgroup's XCD is that of its number in its own part
-    const int start = (n_first + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-    const bool first = (int)blockIdx.x < start;
-    const int bid = first ? (int)blockIdx.x : (int)blockIdx.x - start;
-    if (first == (tn_first != 0)) {
-        if (bid < q.nblk_m * q.nblk_n * q.splits) igemm_tn_body<T, 64, 64, CONV>(q, bid, st0, st1, st2);
-    } else {
-        const int tiles = p.nblk_m * p.nblk_n, split = p.splits > 1 ? bid / tiles : 0;
-        if (bid < tiles * max(p.splits, 1)) igemm_dma_body<T, 64, 64, MODE, TAPS>(p, bid - split * tiles, split, st0, st1, st2);
-    }
-#endif
-}
+// The contraction over rows, in the grid of the other one.  Its workgroups or the other's are the first n_first.
+template <bool CONV> struct BesideRows {
+    static constexpr bool other = true;
+    TnParams q;
+    int32_t n_first, rows_first;
 
-#define RL_INST(T, MODE) template __global__ void igemm_grads_kernel<T, MODE, false, false>(const IgemmParams, const TnParams, const int, const int); \
-    template __global__ void igemm_grads_kernel<T, MODE, false, true>(const IgemmParams, const TnParams, const int, const int);                      \
-    template __global__ void igemm_grads_kernel<T, MODE, true, true>(const IgemmParams, const TnParams, const int, const int);
+    template <typename T, int STAGE>
+    __device__ __forceinline__ bool take(int &bid, unsigned char (&st0)[STAGE], unsigned char (&st1)[STAGE], unsigned char (&st2)[STAGE]) const
+    {
+        static_assert(STAGE == tn_stage_bytes<64, 64>(), "one set of stages for either");
+        // the second part starts at a multiple of the XCD count, so that a workgroup's XCD is that of its number in its own part
+        const int start = (n_first + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
+        const bool first = bid < start;
+        if (!first) bid -= start;
+        if (first != (rows_first != 0)) return true;
+        if (bid < q.nblk_m * q.nblk_n * q.splits) igemm_tn_body<T, 64, 64, CONV>(q, bid, st0, st1, st2);
+        return false;
+    }
+};
+
+#define RL_ONE(T, MODE, TAPS, CONV) template __global__ void igemm_dma_kernel<T, 64, 64, MODE, TAPS, BesideRows<CONV>>(const IgemmParams, const BesideRows<CONV>);
+#define RL_INST(T, MODE) RL_ONE(T, MODE, false, false) RL_ONE(T, MODE, false, true) RL_ONE(T, MODE, true, true)
 RL_INST(float, STORE_ROWS) RL_INST(float, STORE_ANY) RL_INST(uint16_t, STORE_ROWS) RL_INST(uint16_t, STORE_ANY)
 #undef RL_INST
+#undef RL_ONE
 
 bool igemm_dma_takes(const IgemmParams &p, bool taps, int element_size);        // igemm_dma.hip
 bool igemm_dma_splits_ok(const IgemmParams &p, bool taps, int element_size);
@@ -52,10 +50,10 @@ static hipError_t launch_typed(const IgemmParams &p, const TnParams &q, bool tap
     const bool rows = p.splits > 1 || (p.ys_n == (int64_t)p.OHW * p.ys_p && p.ys_c == 1 && (p.N & 7) == 0 && (p.ys_p & 7) == 0);
     const int nk = (p.K + 128 / (int)sizeof(T) - 1) / (128 / (int)sizeof(T));
     const int64_t na = (int64_t)p.nblk_m * p.nblk_n * std::max(p.splits, 1), nb = (int64_t)q.nblk_m * q.nblk_n * q.splits;
-    const int tn_first = q.split_tiles > (p.splits > 1 ? p.split_tiles : nk);
-    const int64_t first = tn_first ? nb : na, grid = (first + NUM_XCD - 1) / NUM_XCD * NUM_XCD + (tn_first ? na : nb);
+    const int rows_first = q.split_tiles > (p.splits > 1 ? p.split_tiles : nk);
+    const int64_t first = rows_first ? nb : na, grid = (first + NUM_XCD - 1) / NUM_XCD * NUM_XCD + (rows_first ? na : nb);
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-#define RL_GO(MODE, TAPS, CONV) hipLaunchKernelGGL((igemm_grads_kernel<T, MODE, TAPS, CONV>), dim3((unsigned)grid), dim3(256), 0, s, p, q, (int)first, tn_first)
+#define RL_GO(MODE, TAPS, CONV) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, MODE, TAPS, BesideRows<CONV>>), dim3((unsigned)grid), dim3(256), 0, s, p, (BesideRows<CONV>{q, (int)first, rows_first}))
     if (taps && rows) RL_GO(STORE_ROWS, true, true);
     else if (taps) RL_GO(STORE_ANY, true, true);
     else if (q.conv && rows) RL_GO(STORE_ROWS, false, true);
