@@ -218,6 +218,50 @@ struct Planner {
         const int d = dtype == RL_BF16;
         return std::max(alone[d][tile], share[d][tile] * (double)((workgroups + 255) / 256));
     }
+    // 128x64 or 64x64 tiles, by the padding of the last ones and how the grid fills 256 CUs; the f32 MFMA takes so long that small
+    // tiles cost nothing where they fill the chip better (16x128x28x28 -> 128 3x3: 128x64 67.8 us, 64x64 47.7)
+    // (never 128x128: f32 has no gain from it, and bf16 across taps holds one such workgroup per CU; 48 layers that took it ran
+    // in 0.87 of its time on 128x64)
+    static int direct_load_tile(int dtype, int64_t M, int64_t N)
+    {
+        auto cost = [&](int tile, int64_t bm) { return tile_cost(tile, dtype, ((M + bm - 1) / bm) * ((N + 63) / 64)); };
+        return cost(TILE_64x64, 64) < cost(TILE_128x64, 128) ? TILE_64x64 : TILE_128x64;
+    }
+
+    // Few tiles and a long K (small batches, late stages): K is split over several workgroups per tile, whose fp32
+    // sums meet in a scratch tensor [splits][M][N] that a second kernel adds up in order before the epilogue.
+    // splits = 1: whole; per: K tiles of a slice; cycles: of the fullest CU, the adding launch's share included
+    struct KSlices { int splits = 1, per = 0; int64_t tiles = 0; double cycles = 0.0; };
+    KSlices k_slices(int tile, int dtype, int64_t M, int64_t N, int64_t K) const
+    {
+        static const int tbm[] = {128, 128, 64}, tbn[] = {128, 64, 64};
+        const int BK = 8 * kv_of(dtype), nk = (int)((K + BK - 1) / BK);
+        KSlices c;
+        c.tiles = ((M + tbm[tile] - 1) / tbm[tile]) * ((N + tbn[tile] - 1) / tbn[tile]);
+        c.per = nk;
+        c.cycles = (double)nk * tile_cost(tile, dtype, c.tiles);
+        // from 8 K tiles on (fewer: the adding launch costs more than the serial K loop); slices of at least two K tiles; a lean plan
+        // splits up to 64 tiles only, as the smallest-workspace form always did
+        if (plan.opts.no_splitk || nk < 8 || c.tiles >= (plan.lean ? 65 : 512)) return c;
+        auto cost = [&](int sp) { return (double)((nk + sp - 1) / sp) * tile_cost(tile, dtype, c.tiles * sp) + (c.tiles > 64 ? 6500.0 : 0.0) + 8.0 * sp * M * (double)N / 2200.0; };
+        int want = (int)std::min<int64_t>(std::min<int64_t>(16, 256 / std::max<int64_t>(c.tiles, 1)), nk / 2);
+        if (c.tiles > 64) {
+            // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
+            // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22).  The
+            // estimate is good to a sixth: over 700 layers, split where it promised less than that, 89 were slower than whole by
+            // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 17; few channels need a third
+            double best = c.cycles;
+            want = 1;
+            for (int sp = 2; sp <= std::min(16, nk / 2); ++sp)
+                if (cost(sp) < best * 0.95) { best = cost(sp); want = sp; }
+            if (best > c.cycles * (N < 16 ? 0.7 : 0.83)) want = 1;
+        }
+        if (want < 2 || want * M * N * 4 >= (int64_t)1 << 28) return c;
+        c.per = (nk + want - 1) / want;
+        c.splits = (nk + c.per - 1) / c.per;
+        c.cycles = cost(c.splits);
+        return c;
+    }
 
     // Whether a contraction whose channels (features) are no multiple of the 16-byte vector gets zero-padded rows, written by a
     // step of its own, for the vector-load kernels.  The element gather it takes otherwise needs no extra launch and is level
@@ -261,7 +305,7 @@ struct Planner {
         Direct best;
         if (plan.opts.no_direct || M * N >= (int64_t)1 << 31) return best;
         const bool bf16 = dtype == RL_BF16;
-        const int KV = kv_of(dtype), BKE = 8 * KV;
+        const int KV = kv_of(dtype);
         auto cd = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
         // start, per K step alone, per K step of 256 workgroups, per 256 workgroups, and per tile of theirs
         static const double cost32[2][3][5] = {{{5.4, 0.17, 0.40, 0.0, 1.42}, {6.0, 0.13, 0.475, 0.2, 0.86}, {5.0, 0.53, 0.742, 0.37, 0.6}},
@@ -281,24 +325,12 @@ struct Planner {
             if (t < us) { us = t; best.tile = tile; best.slices = slices; }
         }
         if (plan.opts.direct_all) return best;
-        // the tiles and slices the other kernels would take (see below), in us of the fullest CU
-        const int64_t nk = cd(K, BKE), t128 = cd(M, 128) * cd(N, 64), t64 = cd(M, 64) * cd(N, 64);
-        const bool wide = tile_cost(TILE_128x64, dtype, t128) < tile_cost(TILE_64x64, dtype, t64);
-        const int tile = wide ? TILE_128x64 : TILE_64x64;
-        const int64_t tiles = wide ? t128 : t64;
-        double cyc = (double)nk * tile_cost(tile, dtype, tiles);
-        bool split = false;
-        if (nk >= 8 && !plan.opts.no_splitk && tiles < (plan.lean ? 65 : 512)) {
-            const double whole = cyc;
-            for (int64_t sp = 2; sp <= std::min<int64_t>(tiles <= 64 ? std::min<int64_t>(16, 256 / tiles) : 16, nk / 2); ++sp) {
-                const double t = (double)cd(nk, sp) * tile_cost(tile, dtype, tiles * sp) + (tiles > 64 ? 6500.0 : 0.0) + 8.0 * sp * M * (double)N / 2200.0;
-                if (t < cyc * 0.95 && (tiles <= 64 || t < whole * 0.83)) { cyc = t; split = true; }
-            }
-        }
+        const KSlices lds = k_slices(direct_load_tile(dtype, M, N), dtype, M, N, K);
+        const bool split = lds.splits > 1;
         static const double otherc[2][3][6] = {{{4.5, 1.04, 3.2, 2.8, 0.48, 0.63}, {5.0, 1.15, 3.5, 2.8, 0.35, 0.69}, {11.0, 2.3, 3.0, 0.0, 0.0, 1.09}},
                                                {{3.9, 0.95, 4.3, 3.7, 0.95, 1.64}, {6.1, 1.11, 3.1, 2.1, 0.67, 1.52}, {15.5, 4.4, 5.0, 0.0, 0.0, 0.84}}};
         const double *c = otherc[bf16][other];
-        const double theirs = c[0] + c[1] * cyc / 2100.0 + (split ? c[2] : 0.0) + (copies_x ? c[3] + c[4] * x_mbytes : 0.0) +
+        const double theirs = c[0] + c[1] * lds.cycles / 2100.0 + (split ? c[2] : 0.0) + (copies_x ? c[3] + c[4] * x_mbytes : 0.0) +
                               c[5] * M * (double)N * dtype_size(dtype) / 1e6 - (rides && split ? 3.0 : 0.0) - (paired ? 3.5 : 0.0);
         // (few slices: short K on many tiles, where the stores decide and the estimates are at their worst)
         return us < (best.slices < 4 && other != OTHER_GATHER ? 0.7 : 0.85) * theirs ? best : Direct();
@@ -624,15 +656,7 @@ struct Planner {
         } else if (!il.avec) {
             il.tile = TILE_64x64;
         } else if (il.taps || (il.dma && in_dt == RL_F32)) {
-            // by the padding of the last tiles and how the grid fills 256 CUs (tile_cost); the f32 MFMA takes so long that small
-            // tiles cost nothing where they fill the chip better (16x128x28x28 -> 128 3x3: 128x64 67.8 us, 64x64 47.7)
-            // (never 128x128: f32 has no gain from it, and bf16 across taps holds one such workgroup per CU; 48 layers that took it ran
-            // in 0.87 of its time on 128x64)
-            double best = 1e30;
-            for (int i = TILE_128x64; i <= TILE_64x64; ++i) {
-                const double c = tile_cost(i, in_dt, nblk(i == TILE_64x64 ? 64 : 128, 64));
-                if (c < best) { best = c; il.tile = i; }
-            }
+            il.tile = direct_load_tile(in_dt, p.M, p.N);
         } else if (il.lp && p.N > 64 && nblk(256, 128) >= 190 && !plan.opts.no_lp_256) {
             il.tile = TILE_256x128;        // a quarter fewer operand bytes per MFMA than 128x128
         } else if (p.N > 64 && nblk(128, 128) >= 192) {
@@ -681,34 +705,13 @@ struct Planner {
             bytes += (double)bytes_of(vout);
         }
         p.epi = chain.epi;
-        // Few tiles and a long K (small batches, late stages): K is split over several workgroups per tile, whose fp32
-        // sums meet in a scratch tensor [splits][M][N] that a second kernel adds up in order before the epilogue.
         int part_buf = -1;
-        if (il.avec && !il.lp && !gates && x2 < 0 && !stem && !plan.opts.no_splitk) {
-            static const int tbm[] = {128, 128, 64, 256}, tbn[] = {128, 64, 64, 128};
-            const int64_t tiles = nblk(tbm[il.tile], tbn[il.tile]);
-            const int nk = (p.K + 8 * KV - 1) / (8 * KV);
-            // from 8 K tiles on (fewer: the adding launch costs more than the serial K loop); slices of at least two K tiles
-            int want = (int)std::min<int64_t>(std::min<int64_t>(16, 256 / std::max<int64_t>(tiles, 1)), nk / 2);
-            if (tiles > 64 && tiles < 512 && nk >= 8 && !plan.lean) {
-                // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
-                // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22).  The
-                // estimate is good to a sixth: over 700 layers, split where it promised less than that, 89 were slower than whole by
-                // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 17; few channels need a third
-                double whole = 0.0, best = 1e30;
-                for (int sp = 1; sp <= std::min(16, nk / 2); ++sp) {
-                    const double c = (double)((nk + sp - 1) / sp) * tile_cost(il.tile, in_dt, tiles * sp) + (sp > 1 ? 6500.0 + 8.0 * sp * p.M * (double)p.N / 2200.0 : 0.0);
-                    if (sp == 1) whole = c;
-                    if (c < best * 0.95) { best = c; want = sp; }
-                }
-                if (best > whole * (p.N < 16 ? 0.7 : 0.83)) want = 1;
-            }
-            // a lean plan splits up to 64 tiles only, as the smallest-workspace form always did
-            if (tiles < (plan.lean ? 65 : 512) && nk >= 8 && want >= 2 && (int64_t)want * p.M * p.N * 4 < (int64_t)1 << 28) {
-                const int per = (nk + want - 1) / want;
-                il.splits = (nk + per - 1) / per;
-                p.splits = il.splits; p.split_tiles = per;
-                plan.spent |= tiles > 64;
+        if (il.avec && !il.lp && !gates && x2 < 0 && !stem) {
+            const KSlices c = k_slices(il.tile, in_dt, p.M, p.N, p.K);
+            if (c.splits > 1) {
+                il.splits = c.splits;
+                p.splits = c.splits; p.split_tiles = c.per;
+                plan.spent |= c.tiles > 64;
                 part_buf = new_ws((size_t)il.splits * p.M * p.N * 4);
                 bytes += 2.0 * il.splits * p.M * (double)p.N * 4;
             }
