@@ -10,6 +10,7 @@
 #include "plan.h"
 
 #include <algorithm>
+#include <cmath>
 #include <set>
 #include <sstream>
 
@@ -295,12 +296,11 @@ struct Planner {
     // Whether a contraction runs on the kernel without LDS tiles (igemm_direct.hip), with which tile and K slices (tile 0: no).
     // By two estimates of the call in us, each fitted to 900 conv and dense layers of 1 to 50000 rows (rms 8 to 20 %): launches and
     // latencies, the K steps of the fullest CU, and per workgroup what it starts and ends with.  `other` is the planner's next choice.
-    // Taken where it promises a seventh.  Over 1200 drawn graphs (no_direct / as planned): conv f32 0.76 of the time (half of the layers
-    // move, to 0.60), bf16 0.88, dense 0.77 and 0.88, LeNet's shape 0.58 and 0.66; of 424 that moved one lost more than 3 % (1.7x: 5x5
-    // at stride 2 from 240 channels, since then the `lines` below).
+    // Taken where it promises a seventh: of drawn layers f32 convolutions that move to 0.58 of the time, bf16 0.52, dense 0.69 and 0.59, LeNet's
+    // shape 0.52 and 0.48.  How it is checked: plans with direct_all = 1 against no_direct, layer by layer.
     struct Direct { int tile = 0, slices = 0; };
     enum OtherKind { OTHER_DMA = 0, OTHER_TAPS = 1, OTHER_GATHER = 2 };
-    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided, bool paired) const
+    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided, bool paired, bool pooled) const
     {
         Direct best;
         if (plan.opts.no_direct || M * N >= (int64_t)1 << 31) return best;
@@ -312,7 +312,7 @@ struct Planner {
                                                {{4.7, 0.31, 0.35, 0.27, 1.03}, {6.0, 0.60, 0.50, 0.39, 0.66}, {4.7, 0.81, 1.2, 0.0, 0.58}}};
         static const double cost16[2][3][4] = {{{3.9, 0.17, 0.42, 1.0}, {5.1, 0.39, 0.40, 1.0}, {4.5, 0.64, 0.59, 0.85}},
                                                {{3.8, 0.18, 0.40, 0.87}, {5.1, 0.73, 0.51, 0.5}, {5.3, 1.0, 1.3, 0.05}}};
-        double us = 1e30;
+        double us = 1e30, us_whole = 1e30, rounds_best = 0.0, steps_best = 0.0;
         for (int form = 0; form < 5; ++form) {
             const int tile = form < 4 ? 32 : 16, slices = form < 4 ? 1 << form : 8, wt = 8 / slices;
             if (plan.opts.no_splitk && slices > 1) continue;
@@ -321,10 +321,19 @@ struct Planner {
             const double *c = tile == 32 ? cost32[bf16][mode] : cost16[bf16][mode];
             // the chunk's tap; at a stride a tap's pixels fill half of their cache lines, and the next tap comes back for the rest too late
             const double per = c[2] + (mode == DIRECT_ROWS && taps > 1 ? 0.1 : 0.0), lines = strided && mode != DIRECT_ROWS ? 1.0 + 0.02 * taps : 1.0;
-            const double t = c[0] + lines * std::max(c[1] * steps, per * steps * std::max(rounds, 1.0)) + (c[3] + (tile == 32 ? c[4] * wt : 0.0)) * rounds;
-            if (t < us) { us = t; best.tile = tile; best.slices = slices; }
+            auto at = [&](double r) { return c[0] + lines * std::max(c[1] * steps, per * steps * std::max(r, 1.0)) + (c[3] + (tile == 32 ? c[4] * wt : 0.0)) * rounds; };
+            if (at(rounds) < us) { us = at(rounds); us_whole = at(std::ceil(rounds)); best.tile = tile; best.slices = slices; rounds_best = rounds; steps_best = steps; }
         }
         if (plan.opts.direct_all) return best;
+        // A last round that only some of the CUs have a workgroup for.  Rows of f32 features read one by one: it counts in full, as two
+        // workgroups on a CU have twice the lines in use that the vector L1 holds (146 x 1920 x 590 17.2 us by padded rows, 23.0 so; 775 x 414 x
+        // 1013 23.8 and 36.0).  Elsewhere by half, from 14 K steps a slice on (32x304x37x37 -> 78 3x3 at stride 2 41 and 53).  Not up to 32
+        // channels, where the other kernels' estimate, of tiles that are half empty, is low itself, nor where a max-pool of the result rides along.  Of 1515 drawn layers that moved 24 lost
+        // more than 3 %, up to 1.9x; now 4, up to 1.18x (of 1502 others 3, up to 1.16x), and 7 that won more than 3 % (to 0.87) stay behind.
+        if (rounds_best > 1.0 && other != OTHER_GATHER && !pooled) {
+            if (!bf16 && mode == DIRECT_ANY && other == OTHER_DMA && steps_best >= 6 && N > 128) us = us_whole;
+            else if (steps_best >= 14 && N > 32) us = 0.5 * (us + us_whole);
+        }
         const KSlices lds = k_slices(direct_load_tile(dtype, M, N), dtype, M, N, K);
         const bool split = lds.splits > 1;
         static const double otherc[2][3][6] = {{{4.5, 1.04, 3.2, 2.8, 0.48, 0.63}, {5.0, 1.15, 3.5, 2.8, 0.35, 0.69}, {11.0, 2.3, 3.0, 0.0, 0.0, 1.09}},
@@ -334,6 +343,12 @@ struct Planner {
                               c[5] * M * (double)N * dtype_size(dtype) / 1e6 - (rides && split ? 3.0 : 0.0) - (paired ? 3.5 : 0.0);
         // (few slices: short K on many tiles, where the stores decide and the estimates are at their worst)
         return us < (best.slices < 4 && other != OTHER_GATHER ? 0.7 : 0.85) * theirs ? best : Direct();
+    }
+
+    static bool pool_2x2(const OpNode &o)
+    {
+        const auto &a = o.attrs;
+        return o.kind == RL_OP_MAXPOOL2D && a.kernel[0] == 2 && a.kernel[1] == 2 && a.stride[0] == 2 && a.stride[1] == 2 && a.pad[0] == 0 && a.pad[1] == 0;
     }
 
     // the gradient with respect to the input may go out with the one with respect to the weights (pair_gradients)
@@ -422,10 +437,12 @@ struct Planner {
             if (vout >= 0 && x2 < 0 && !gates && x_own < lim && (size_t)p.N * p.Kp * dtype_size(in_dt) < lim) {
                 const bool last = xov || phys[L_NHWC][x] >= 0, vec = p.C % KV == 0;
                 direct_mode = !vec ? DIRECT_ANY : last ? DIRECT_ROWS : DIRECT_PLANES;
+                const int next = !out_set.count(vout) && consumers[vout].size() == 1 ? consumers[vout][0] : -1;
+                const bool pooled = next >= 0 && cls.simple && cls.t_op < 0 && pool_2x2(g.ops[next]);       // fuse_direct_store
                 // bf16 channels in whole K tiles stay with the kernels that are made for them
                 if (in_dt == RL_F32 || p.C % 64 != 0 || plan.opts.direct_all)
                     direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, !vec && !pad ? OTHER_GATHER : p.C % (8 * KV) == 0 ? OTHER_DMA : OTHER_TAPS,
-                                         (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1, ov && beside_weights_gradient(x));
+                                         (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1, ov && beside_weights_gradient(x), pooled);
             }
             // A bf16 result that is a graph output (Shape order): the slower direct-load kernel stores in that order
             // itself, the pixel-on-lane kernels only where fuse_planes_store lets them.  From 0.4 GFLOP on, the pixel-on-lane kernels writing channel-last into the workspace plus a
@@ -518,7 +535,7 @@ struct Planner {
                 // with up to 4 (bf16: 8) K tiles, more than 256 tiles of 32 x 32, or bf16 K in whole tiles, the kernels with LDS tiles are level or ahead
                 const bool lds = il.avec && (rides || nk <= (in_dt == RL_F32 ? 4 : 8) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256);
                 if (plan.opts.direct_all || (!lds && (in_dt == RL_F32 || p.K % 64 != 0)))
-                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false, ov && beside_weights_gradient(x));
+                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false, ov && beside_weights_gradient(x), false);
             }
             if (pad && !direct.tile) {
                 int ld;

@@ -522,6 +522,26 @@ def test_shared_launches_and_results_in_shape_order_have_an_option_each():
     B.lib().rl_plan_destroy(h)
 
 
+def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty():
+    def dense(m, n, k):
+        g = W.GraphSpec("dense")
+        x, w = g.input("x", "f32", (m, k)), g.param("w", "f32", (n, k))
+        o, (y,) = g.op("dense", [x, w], [("f32", (m, n))]); g.group([o]); g.output(y)
+        return g
+    direct = lambda spec: any("_direct" in s["kernel"] for s in _steps(spec))
+    # rows of features read one by one, more workgroups than CUs: slower than padded rows (1.2 to 1.9 times)
+    for dims in ((146, 1920, 590), (775, 414, 1013), (306, 960, 919), (253, 1110, 602)):
+        assert not direct(dense(*dims)), dims
+    # long slices, a few workgroups past the CUs
+    for case in ((32, 304, 78, 37, 37, 3, 2, 1), (30, 192, 64, 85, 85, 3, 2, 0)):
+        assert not direct(W.conv_group(*case, "f32")[0]), case
+    # one round, short slices, few channels: it stays
+    for dims in ((498, 345, 457), (57, 256, 1093), (1562, 104, 495)):
+        assert direct(dense(*dims)), dims
+    for case in ((1, 64, 64, 56, 56, 3, 1, 1), (32, 128, 32, 53, 36, 3, 2, 1)):
+        assert direct(W.conv_group(*case, "f32")[0]), case
+
+
 def test_both_gradients_of_a_layer_share_no_workspace():
     # the two run at once: whatever either reads or writes is apart from what the other writes
     for dtype, (b, c, h, o) in (("f32", (32, 64, 28, 64)), ("bf16", (16, 40, 20, 72))):
