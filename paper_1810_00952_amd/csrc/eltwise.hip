@@ -662,11 +662,11 @@ __global__ __launch_bounds__(256) void move_pair_kernel(const Move a, const Move
     else transpose_pad(src, dst, m.R, m.Q, m.Rp, bx, by, n, tile.large);
 }
 
-// the grid the move would have alone; false: it is not paired
+// the grid the move would have alone (null pointers: that of aligned ones); false: it is not paired
 static bool prepare_move(const MoveParams &p, Move &m)
 {
     const int vec = p.dtype == DT_BF16 ? 8 : 4;
-    if (!p.src || !p.dst || p.N < 1 || p.R < 1 || p.Q < 1 || (int64_t)p.N * std::max(p.R, p.Rp) * p.Q * (p.dtype == DT_BF16 ? 2 : 4) >= (int64_t)1 << 28) return false;
+    if (p.N < 1 || p.R < 1 || p.Q < 1 || (int64_t)p.N * std::max(p.R, p.Rp) * p.Q * (p.dtype == DT_BF16 ? 2 : 4) >= (int64_t)1 << 28) return false;
     m = Move{p.src, p.dst, 0, p.R, p.Q, p.Rp, 0, 0, 0, 0};
     int ts;
     if (p.Rp) {
@@ -703,13 +703,27 @@ hipError_t launch_move(const MoveParams &p, hipStream_t s)
     return p.Rp ? launch_transpose_pad(p.src, p.dst, p.dtype, p.N, p.R, p.Q, p.Rp, s) : launch_transpose(p.src, p.dst, p.dtype, p.N, p.R, p.Q, s);
 }
 
+// A 32 x 32 tile of bf16, or of f32 with few rows or columns in it, is so little work that what the shared launch adds to it (the tile's
+// numbers by division, both moves' arguments) shows: of 450 drawn pairs in bf16 those of up to 2048 such tiles run at 0.62 to 0.64 of the
+// time of two launches, of 4096 to 8192 at 0.94, of 16384 to 32768 at 1.07, of more at 1.08 (64x297x48x48 and 64x64x44x47 61.4 us,
+// paired 71.4); f32 0.61 to 0.99 throughout, but 64x7x57x57 and 16x8x57x57 7.3 and 8.6.
+bool moves_pair_ok(const MoveParams &a, const MoveParams &b)
+{
+    Move m[2];
+    if (a.dtype != b.dtype || !prepare_move(a, m[0]) || !prepare_move(b, m[1])) return false;
+    int64_t tiles = 0, elements = 0;
+    for (int i = 0; i < 2; ++i)
+        if (m[i].form == 1) {
+            tiles += m[i].total;
+            elements += (int64_t)(i ? b.N : a.N) * m[i].R * m[i].Q;
+        }
+    return tiles <= 6144 || elements * (a.dtype == DT_BF16 ? 2 : 4) >= tiles * 3072;
+}
+
 hipError_t launch_move_pair(const MoveParams &a, const MoveParams &b, hipStream_t s)
 {
     Move ma, mb;
-    if (a.dtype != b.dtype || !prepare_move(a, ma) || !prepare_move(b, mb)) {
-        const hipError_t er = launch_move(a, s);
-        return er != hipSuccess ? er : launch_move(b, s);
-    }
+    if (!a.src || !a.dst || !b.src || !b.dst || a.dtype != b.dtype || !prepare_move(a, ma) || !prepare_move(b, mb)) return hipErrorInvalidValue;
     if (a.dtype == DT_BF16) hipLaunchKernelGGL(move_pair_kernel<uint16_t>, dim3((unsigned)(ma.blocks + mb.blocks)), dim3(256), 0, s, ma, mb);
     else hipLaunchKernelGGL(move_pair_kernel<float>, dim3((unsigned)(ma.blocks + mb.blocks)), dim3(256), 0, s, ma, mb);
     return hipGetLastError();

@@ -281,6 +281,7 @@ hipError_t launch_gavgpool_nhwc(const PoolParams &p, hipStream_t s);   // y: [N,
 // and two of them, neither of which touches what the other writes, in one launch
 struct MoveParams { const void *src; void *dst; int32_t dtype, N, R, Q, Rp; };
 hipError_t launch_move(const MoveParams &p, hipStream_t s);
+bool moves_pair_ok(const MoveParams &a, const MoveParams &b);         // by their sizes: whether that launch takes them, and pays
 hipError_t launch_move_pair(const MoveParams &a, const MoveParams &b, hipStream_t s);
 // any permutation of up to six axes (element gather): y[i0..] = x[sum_k i_k * xstride[k]], i over ydims
 struct PermuteParams {

@@ -23,6 +23,14 @@ enum { L_NATIVE = 0, L_NHWC = 1 };
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 inline int kv_of(int dtype) { return dtype == RL_BF16 ? 8 : 4; }
 
+// a change of layout without its pointers
+MoveParams move_params(const Step &t)
+{
+    MoveParams m{nullptr, nullptr, t.t_dtype, t.t_N, t.t_C, t.t_P, t.kind == S_PAD_NHWC ? t.st_W : 0};
+    if (t.kind == S_TO_NCHW) std::swap(m.R, m.Q);
+    return m;
+}
+
 struct Planner {
     const Graph &g;
     Plan &plan;
@@ -1739,9 +1747,15 @@ struct Planner {
         auto moves = [](const Step &s) { return s.kind == S_TO_NHWC || s.kind == S_TO_NCHW || s.kind == S_PAD_NHWC; };
         for (size_t si = 0; si + 1 < plan.steps.size(); ++si) {
             Step &a = plan.steps[si], &b = plan.steps[si + 1];
-            if (!moves(a) || !moves(b) || a.pair || b.pair || a.t_dtype != b.t_dtype || a.slot[SL_Y] == b.slot[SL_Y] || a.slot[SL_Y] == b.slot[SL_X] || a.slot[SL_X] == b.slot[SL_Y]) continue;
+            if (!moves(a) || !moves(b) || a.pair || b.pair || a.slot[SL_Y] == b.slot[SL_Y] || a.slot[SL_Y] == b.slot[SL_X] || a.slot[SL_X] == b.slot[SL_Y]) continue;
+            if (!moves_pair_ok(move_params(a), move_params(b))) continue;
             a.pair = 1; b.pair = 2;
             plan.spent = true;                           // the second one's result is there a step earlier
+            a.bytes += b.bytes;
+            b.bytes = 0;
+            a.name += " | " + b.name;
+            a.kernel += " | " + b.kernel;
+            b.kernel = "(launched with the step before)";
             ++si;
         }
     }
@@ -1917,8 +1931,8 @@ rl_status run_steps(const Plan &plan, void *const *ptrs, hipStream_t stream, std
         return q;
     };
     auto move = [&](const Step &t) {
-        MoveParams m{P(t, SL_X), P(t, SL_Y), t.t_dtype, t.t_N, t.t_C, t.t_P, t.kind == S_PAD_NHWC ? t.st_W : 0};
-        if (t.kind == S_TO_NCHW) std::swap(m.R, m.Q);
+        MoveParams m = move_params(t);
+        m.src = P(t, SL_X); m.dst = P(t, SL_Y);
         return m;
     };
     for (const Step &s : plan.steps) {

@@ -174,7 +174,8 @@ def test_gradient_operators_plan_onto_the_fast_kernels():
     assert k(spec) == ["pack_gather", "igemm_conv2d_grad_x_bf16_64x64_gather"]
     # with respect to the weights, bf16 batches of 64: images-last operands, contraction, ordered reduction
     spec = W.grad_case("conv2d_grad_w", (64, 128, 28, 28, 128, 3), "bf16", 1, 1, second_is_param=False)[0]
-    assert k(spec) == ["transpose_images_last", "transpose_images_last", "conv2d_grad_w_bf16_128x64_images_last", "wgrad_reduce"]
+    assert k(spec, {"no_pair": 1}) == ["transpose_images_last", "transpose_images_last", "conv2d_grad_w_bf16_128x64_images_last", "wgrad_reduce"]
+    assert k(spec) == ["transpose_images_last | transpose_images_last", "(launched with the step before)", "conv2d_grad_w_bf16_128x64_images_last", "wgrad_reduce"]
     assert k(spec, {"no_wgrad": 1}) == ["pack_gather", "igemm_conv2d_grad_w_bf16_64x64_gather_splitk"]
     for dims, dtype in (((32, 128, 28, 28, 128, 3), "bf16"), ((64, 128, 28, 28, 128, 3), "f32"), ((64, 96, 28, 28, 128, 3), "bf16"), ((64, 128, 28, 28, 128, 5), "bf16")):
         pad = dims[5] // 2
@@ -522,6 +523,39 @@ def test_shared_launches_and_results_in_shape_order_have_an_option_each():
     B.lib().rl_plan_destroy(h)
 
 
+def test_two_changes_of_layout_in_one_launch_are_one_step_and_share_no_workspace():
+    for dtype in ("f32", "bf16"):
+        # x and the residual both go channel-last, then the contraction reads either
+        spec = W.conv_group(16, 40, 136, 29, 29, 3, 1, 1, dtype, residual=True, tail=True)[0]
+        opts = {"no_direct": 1}
+        d = B.Plan(B.graph_from_spec(B.Context(), spec), opts).describe()
+        apart = _steps(spec, dict(opts, no_pair=1))
+        ks = [s["kernel"] for s in d["steps"]]
+        i = ks.index("nchw_to_nhwc | nchw_to_nhwc")
+        assert ks[i + 1] == "(launched with the step before)" and [s["kernel"] for s in apart][i:i + 2] == ["nchw_to_nhwc"] * 2, (ks, apart)
+        assert d["steps"][i]["bytes"] == apart[i]["bytes"] + apart[i + 1]["bytes"] and d["steps"][i + 1]["bytes"] == 0
+        live = [q for q in d["buffers"] if q["first"] <= i + 1 and q["last"] >= i]
+        assert len(live) >= 2
+        for k, p in enumerate(live):
+            for q in live[k + 1:]:
+                assert p["offset"] + p["bytes"] <= q["offset"] or q["offset"] + q["bytes"] <= p["offset"], (p, q)
+
+
+def test_many_small_tiles_are_turned_by_a_launch_each():
+    def moves(dtype, *shapes):
+        g = W.GraphSpec("moves")
+        for i, s in enumerate(shapes):
+            o, (y,) = g.op("layout_transform", [g.input(f"x{i}", dtype, s)], [(dtype, (s[0], s[2], s[3], s[1]))], perm=(0, 2, 3, 1))
+            g.group([o]); g.output(y)
+        return [s["kernel"] for s in _steps(g)]
+    together, apart = ["transpose_tiled | transpose_tiled", "(launched with the step before)"], ["transpose_tiled"] * 2
+    assert moves("bf16", (16, 64, 27, 27), (64, 4, 55, 55)) == apart         # 736 + 6080 tiles of 32 x 32
+    assert moves("bf16", (16, 64, 27, 27), (32, 4, 55, 55)) == together
+    assert moves("f32", (16, 64, 27, 27), (64, 30, 55, 55)) == together
+    assert moves("f32", (16, 64, 27, 27), (64, 3, 55, 55)) == apart
+    assert moves("bf16", (64, 64, 56, 56), (64, 64, 28, 28)) == together     # whole vectors
+
+
 def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty():
     def dense(m, n, k):
         g = W.GraphSpec("dense")
@@ -554,7 +588,7 @@ def test_both_gradients_of_a_layer_share_no_workspace():
         g.output(y); g.output(dw)
         plan = B.Plan(B.graph_from_spec(B.Context(), g), {"no_direct": 1, "no_lp": 1})
         d = plan.describe()
-        at_pair = [i for i, s in enumerate(d["steps"]) if " | " in s["kernel"]]
+        at_pair = [i for i, s in enumerate(d["steps"]) if " | " in s["kernel"] and "_rows" in s["kernel"]]
         assert len(at_pair) == 1, [s["kernel"] for s in d["steps"]]
         i = at_pair[0]
         live = [q for q in d["buffers"] if q["first"] <= i + 1 and q["last"] >= i]
