@@ -746,9 +746,9 @@ struct Planner {
                             (il.c64 ? "3x3_c64" : il.ws ? "128x64_ws" : il.big ? "256x256" : tile_names[il.tile]) + (il.c64 || il.ws ? "" : il.run ? "_run" : il.lp ? "_lp" : il.avec ? (il.dma ? (il.taps ? "_dma_taps" : "_dma") : "") : "_gather") + (gates ? "_gates" : "") +
                             (il.splits > 1 ? "_splitk" : "");
         if (il.direct) {
-            const char *reads[] = {"", "_planes", in_dt == RL_F32 && p.C == 1 ? "_gather" : "_any"};
+            const char *reads[] = {"", "_planes", "_any"};
             const std::string tl = std::to_string(il.direct_tile);
-            kname = kname.substr(0, kname.find(tile_names[il.tile])) + tl + "x" + (gates ? std::to_string(4 * il.direct_units) : tl) + "_direct" + reads[il.direct - 1] + (gates ? "_gates" : il.direct_slices > 1 ? "_splitk" : "");
+            kname = kname.substr(0, kname.find(tile_names[il.tile])) + tl + "x" + (gates ? std::to_string(4 * il.direct_units) : tl) + "_direct" + reads[il.direct - 1] + (gates ? "_gates" : il.direct_slices > 1 ? "_kwaves" : "");
         }
         Step &s = add_step(S_IGEMM, std::string(op_name(an.kind)) + "#" + std::to_string(ops[ai]), kname);
         s.group = gi;
@@ -1853,7 +1853,7 @@ std::string describe_plan(const Plan &p)
           << ", \"flops\": " << (long long)s.flops << ", \"bytes\": " << (long long)s.bytes;
         if (s.kind == S_IGEMM)
             o << ", \"M\": " << s.ig.M << ", \"N\": " << s.ig.N << ", \"K\": " << s.ig.K << ", \"epilogue_ops\": " << s.ig.epi.n_ops
-              << ", \"k_split_waves\": " << (s.il.run == 2 ? 1 : 0) << ", \"channel_tile_major\": " << s.ig.nmajor << ", \"shape_order\": " << s.il.planes << ", \"k_split_workgroups\": " << (s.il.splits > 1 ? s.il.splits : 1);
+              << ", \"k_split_waves\": " << (s.il.run == 2 || (s.il.direct && s.il.direct_slices > 1) ? 1 : 0) << ", \"channel_tile_major\": " << s.ig.nmajor << ", \"shape_order\": " << s.il.planes << ", \"k_split_workgroups\": " << (s.il.splits > 1 ? s.il.splits : 1);
         if (s.kind == S_ELTWISE) o << ", \"n\": " << (long long)s.el.n << ", \"chain_ops\": " << s.el.epi.n_ops;
         o << "}";
     }

@@ -14,12 +14,17 @@ pytestmark = pytest.mark.gpu
 def check_graph(spec, data, what, opts=None, rms_scaled=False):
     # fp32: the stated gate; an element outside it must lie within the first-order fp32 error budget of the graph
     # (computed only when needed); rms_scaled is for deep graphs, where that budget is vacuous
+    # where the plan has a contraction without LDS tiles, the kernels with them are held to the same
     ref = OG.run(spec, data)
-    got, _ = run_hip(spec, data, opts=opts)
-    for vid in spec.outputs:
-        dt = spec.values[vid].type.dtype
-        budget = None if (dt == "bf16" or rms_scaled) else (lambda vid=vid: error_budget(spec, data)[vid])
-        assert_close(got[vid], ref[vid], dt, f"{what} value {vid}", budget=budget, rms_scaled=rms_scaled)
+    got, session = run_hip(spec, data, opts=opts)
+    forms = [("", got)]
+    if not (opts or {}).get("no_direct") and any("_direct" in st["kernel"] and "stem" not in st["kernel"] for st in session.plan.describe()["steps"]):
+        forms.append((" with LDS tiles", run_hip(spec, data, opts=dict(opts or {}, no_direct=1, direct_all=0))[0]))
+    for form, out in forms:
+        for vid in spec.outputs:
+            dt = spec.values[vid].type.dtype
+            budget = None if (dt == "bf16" or rms_scaled) else (lambda vid=vid: error_budget(spec, data)[vid])
+            assert_close(out[vid], ref[vid], dt, f"{what} value {vid}{form}", budget=budget, rms_scaled=rms_scaled)
     return got, ref
 
 
@@ -627,7 +632,7 @@ def test_resnet_small_end_to_end_and_per_group(dtype):
                          budget=None if dtype == "bf16" else (lambda: error_budget(sub, sd)[vid]))
 
 
-@pytest.mark.parametrize("which", ["resnet_small_f32", "resnet_small_bf16", "conv_bf16", "mlp_f32", "splitk_f32", "channel_last_bf16", "grad_w_bf16", "grad_x_stride2_bf16",
+@pytest.mark.parametrize("which", ["resnet_small_f32", "resnet_small_bf16", "conv_bf16", "mlp_f32", "splitk_f32", "kwaves_f32", "channel_last_bf16", "grad_w_bf16", "grad_x_stride2_bf16",
                                    "stem_pool_bf16"])
 def test_plan_replays_from_a_hip_graph(which):
     # one rl_plan_run captured into a HIP graph, then replayed with fresh inputs, with eager work and
@@ -644,8 +649,12 @@ def test_plan_replays_from_a_hip_graph(which):
         s = harness.Session(spec); s.load(data)
     elif which == "splitk_f32":                     # two kernels per step and a scratch tensor in the workspace
         spec, data = W.conv_group(1, 256, 256, 14, 14, 3, 1, 1, "f32", residual=True, relu=True)
+        s = harness.Session(spec, opts={"no_direct": 1}); s.load(data)
+        assert any(st["kernel"].endswith("_splitk") for st in s.plan.describe()["steps"]) and s.plan.workspace_bytes() > 0
+    elif which == "kwaves_f32":                     # one kernel, nothing in the workspace
+        spec, data = W.conv_group(1, 256, 256, 14, 14, 3, 1, 1, "f32", residual=True, relu=True)
         s = harness.Session(spec); s.load(data)
-        assert any(st["kernel"].endswith("_splitk") for st in s.plan.describe()["steps"])
+        assert [st["kernel"] for st in s.plan.describe()["steps"]] == ["igemm_conv2d_f32_16x16_direct_planes_kwaves"] and s.plan.workspace_bytes() == 0
     elif which == "grad_w_bf16":                    # two transpositions, the contraction, the ordered reduction of its row segments
         spec, data = W.grad_case("conv2d_grad_w", (64, 64, 9, 8, 128, 3), "bf16", 2, 1, second_is_param=False)
         s = harness.Session(spec); s.load(data)
@@ -999,16 +1008,17 @@ def test_contraction_with_k_split_over_workgroups(case):
     from paper_1810_00952_amd import binding
     b, ci, co, h, w, k, s, p, res, relu, dtype, tail = case
     spec, data = W.conv_group(b, ci, co, h, w, k, s, p, dtype, residual=res, relu=relu, tail=tail)
-    desc = binding.Plan(binding.graph_from_spec(binding.Context(), spec)).describe()
+    opts = {"no_direct": 1}                         # some run without a split on the kernel that cuts K over a workgroup's waves
+    desc = binding.Plan(binding.graph_from_spec(binding.Context(), spec), opts).describe()
     assert any(st["kernel"].endswith("_splitk") for st in desc["steps"]), [st["kernel"] for st in desc["steps"]]
-    got, _ = run_hip(spec, data)
+    got, _ = run_hip(spec, data, opts=opts)
     ref = OG.run(spec, data)
     v = spec.outputs[0]
     bud = None if dtype == "bf16" else (lambda: error_budget(spec, data)[v])
     assert_close(got[v], ref[v], dtype, f"split-K {case}", budget=bud)
-    again, _ = run_hip(spec, data)
+    again, _ = run_hip(spec, data, opts=opts)
     np.testing.assert_array_equal(got[v], again[v])               # slices are added in a fixed order
-    whole, s1 = run_hip(spec, data, opts={"no_splitk": 1})
+    whole, s1 = run_hip(spec, data, opts=dict(opts, no_splitk=1))
     assert not any(st["kernel"].endswith("_splitk") for st in s1.plan.describe()["steps"])
     assert_close(whole[v], ref[v], dtype, f"unsplit {case}", budget=bud)
 

@@ -556,6 +556,16 @@ def test_many_small_tiles_are_turned_by_a_launch_each():
     assert moves("bf16", (64, 64, 56, 56), (64, 64, 28, 28)) == together     # whole vectors
 
 
+def test_k_over_the_waves_of_a_workgroup_is_not_called_a_split_over_workgroups():
+    spec = W.conv_group(1, 256, 256, 14, 14, 3, 1, 1, "f32")[0]
+    s, = _steps(spec)
+    assert s["kernel"] == "igemm_conv2d_f32_16x16_direct_planes_kwaves" and s["k_split_waves"] == 1 and s["k_split_workgroups"] == 1
+    s = _steps(spec, {"no_direct": 1})[-1]
+    assert s["kernel"] == "igemm_conv2d_f32_64x64_dma_splitk" and s["k_split_waves"] == 0 and s["k_split_workgroups"] > 1
+    # one channel is read element by element like any other count that is no whole vector
+    assert "_direct_any" in _steps(W.conv_group(3, 1, 20, 28, 28, 5, 1, 0, "f32")[0])[0]["kernel"]
+
+
 def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty():
     def dense(m, n, k):
         g = W.GraphSpec("dense")
