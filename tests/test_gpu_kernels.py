@@ -588,7 +588,9 @@ def test_result_stored_in_shape_order(case, steps):
     # rows of channels, then the transposition: the same sums and rounding, K not split over the waves, and the same tiles
     rows, _ = run_hip(g, data, opts=dict(opts, no_shape_order=1, no_run_ks=1))
     other_tiles = any("256x256" in q for q in steps_of(g, dict(opts, no_shape_order=1)))
-    if not other_tiles:
+    if other_tiles:
+        assert_close(got[g.outputs[0]], rows[g.outputs[0]], "bf16", f"planes against rows {case} {steps}")      # other sums
+    else:
         np.testing.assert_array_equal(got[g.outputs[0]], rows[g.outputs[0]])
-    if n * c * h * w * o < 2e8 or (other_tiles and steps == "bias_relu"):
+    if n * c * h * w * o < 2e8 or (other_tiles and steps in ("bias_relu", "bias_residual_relu")):
         check(g, data, "bf16", f"planes {case} {steps}", opts)
