@@ -44,27 +44,11 @@
 // Preconditions (checked by the launcher and the planner): bf16 throughout,
 // C = N = 64, 3x3, stride 1, pad 1, W <= 63, activations and output dense
 // channel-last, tensors below 2 GiB.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};   // raw buffer, untyped dwords
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff + soff] to LDS at lds_addr + lane*16
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff, uint32_t soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory");
-#endif
-}
 
 #define RL_WAIT_VM(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
 #define RL_WAIT_LGKM0 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
@@ -86,8 +70,6 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t mu
     return d == 1 ? n : (__umulhi(n, mul) >> sh);
 }
 
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int CH = 64, NTAP = 9;
 constexpr int C64_BM = 128;                       // pixels of a region
 constexpr int W_MAX = 63;                         // widest image row: a run is BM + 2W + 2 pixels
@@ -174,7 +156,6 @@ __global__ __launch_bounds__(256, 2) void conv3x3_c64_kernel(const IgemmParams p
     // bias and the zeros, in LDS for the whole kernel
     if (t < CH) *(float *)(lds + BIAS_OFF + t * 4) = bias_v;
     else if (t < CH + 32) *(uint32_t *)(lds + ZERO_OFF + (t - CH) * 4) = 0u;
-
 
     // the lane's two pixels within a region, and their fragment base addresses within a run buffer
     int pj[2];

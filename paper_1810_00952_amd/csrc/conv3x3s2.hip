@@ -27,34 +27,11 @@
 // contractions read the same dense channel-last tensor with even H and W and C a multiple of 64, have the same
 // number of output channels (a multiple of 8), dense channel-last outputs, tensors below 2 GiB, and the rows under a
 // tile fit the run buffer.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, untyped dwords
-}
-
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff + soff] to LDS at lds_addr + lane*16
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff, uint32_t soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory");
-#endif
-}
 
 #define RL_WAIT_LGKM0 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
 
@@ -82,8 +59,6 @@ template <int N> __device__ __forceinline__ void wait_vm()
     asm volatile("" ::: "memory");
 }
 
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int PITCH = 144;                        // bytes per pixel slot in LDS
 constexpr int S2_BM = 64, S2_BN = 128;
 constexpr int S2_RL_A = 14, S2_RL_B = 18;         // run loads per wave of the two instances (56 KB / 72 KB of run buffer)

@@ -23,27 +23,11 @@
 // The sums of the workgroups that share a block of dw (one per row segment) go to a scratch tensor
 // [segment][tap][O][C] in fp32 and are added in segment order by wgrad_reduce_kernel, which also writes dw in its
 // declared order [O][C][KH][KW] and dtype: results do not depend on timing.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};   // raw buffer, untyped dwords
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff + soff] to LDS at lds_addr + lane*16
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff, uint32_t soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory");
-#endif
-}
 
 #define RL_WAIT_VM(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
 

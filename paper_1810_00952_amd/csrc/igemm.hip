@@ -14,16 +14,12 @@
 // K tile).  LDS rows are padded by 16 bytes so that the 16-byte fragment reads
 // of 32 consecutive rows fall on distinct banks.  The accumulators stay in
 // registers (32x32 MFMA tiles, fp32) until the epilogue chain has been applied.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 constexpr int ROW_STRIDE = 144;   // 128 data bytes + 16 pad
 constexpr int CHUNKS = 8;         // 16-byte chunks per row per K tile
-
-template <typename T> struct Elem;
-template <> struct Elem<float> { static constexpr int KV = 4; };
-template <> struct Elem<uint16_t> { static constexpr int KV = 8; };
 
 __device__ __forceinline__ void mma_chunk(f32x16 &acc, const u32x4 &a, const u32x4 &b, float)
 {

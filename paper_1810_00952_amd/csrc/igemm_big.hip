@@ -13,19 +13,11 @@
 // Measured: 4096^3 146 -> 122 us on one box, 118 -> 103 on another, 8192 x 4096 x 1024 78 -> 66 us, 4096 x 4096 x 512 25.6 -> 21.3 us.
 // Eight waves (2 x 4), two per SIMD, 128 accumulator registers each.  Tile order, LDS swizzle, MFMA roles and the wave-private
 // epilogue (64 rows at a time through the stages) as in igemm_lp.hip.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-#define RL_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, untyped dwords
-}
 
 template <int N> __device__ __forceinline__ void wait_vmcnt()
 {
@@ -46,8 +38,6 @@ template <bool YF32>
 __global__ __launch_bounds__(512) void igemm_big_kernel(const IgemmParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
-    constexpr int NUM_XCD = 8;
-    constexpr uint32_t OOB = 0x80000000u;
     constexpr int BKE = 64, BM = 256, BN = 256, WTM = 128, WTN = 64, TM = 4, TN = 2;
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
     constexpr int LPT = 8;                          // direct loads per wave and tile: four of A, four of W

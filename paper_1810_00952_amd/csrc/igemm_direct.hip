@@ -15,25 +15,13 @@
 #include <algorithm>
 
 #include "igemm_epilogue.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
 
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, untyped dwords
-}
-
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;       // past every descriptor's extent (below 2^31): reads as zero, no memory traffic
 constexpr int WAVES = 8;
-
-template <typename T> struct Elem;
-template <> struct Elem<float> { static constexpr int KV = 4; };
-template <> struct Elem<uint16_t> { static constexpr int KV = 8; };
 
 template <int TS> struct Acc { f32x16 v; };
 template <> struct Acc<16> { f32x4 v; };
@@ -82,13 +70,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int slice = wave % KS, tw = wave / KS;
-    // consecutive workgroup ids go to different XCDs; give each XCD a contiguous run of tiles
-    const int nblk = p.nblk_m * p.nblk_n;
-    int bid = blockIdx.x;
-    {
-        const int per = nblk / NUM_XCD, main = per * NUM_XCD;
-        if (bid < main) bid = (bid % NUM_XCD) * per + bid / NUM_XCD;
-    }
+    const int bid = xcd_run(blockIdx.x, p.nblk_m * p.nblk_n);
     const int bm = bid / p.nblk_n, bn = bid - bm * p.nblk_n;
     const int m0 = bm * BM, n0 = bn * TS;
     const int l = lane % TS, g = lane / TS;

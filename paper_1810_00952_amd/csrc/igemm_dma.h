@@ -8,10 +8,6 @@ namespace rl {
 
 namespace {
 
-template <typename T> struct Elem;
-template <> struct Elem<float> { static constexpr int KV = 4; };
-template <> struct Elem<uint16_t> { static constexpr int KV = 8; };
-
 __device__ __forceinline__ void mma_chunk(f32x16 &acc, const u32x4 &a, const u32x4 &b, float)
 {
 #pragma unroll

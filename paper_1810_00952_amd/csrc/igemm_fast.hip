@@ -15,6 +15,7 @@
 // Workgroup ids are remapped so that the tiles sharing activation rows run on
 // one XCD (one L2).
 #include "igemm_epilogue.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
@@ -22,17 +23,6 @@ namespace {
 
 constexpr int ROW_STRIDE = 144;   // 128 data bytes + 16 pad
 constexpr int CHUNKS = 8;         // 16-byte chunks per row per K tile
-constexpr int NUM_XCD = 8;
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, 32-bit untyped data
-}
-
-template <typename T> struct Elem;
-template <> struct Elem<float> { static constexpr int KV = 4; };
-template <> struct Elem<uint16_t> { static constexpr int KV = 8; };
 
 __device__ __forceinline__ void mma_chunk(f32x16 &acc, const u32x4 &a, const u32x4 &b, float)
 {
@@ -80,7 +70,6 @@ __global__ __launch_bounds__(256) void igemm_fast_kernel(const IgemmParams p)
     // Buffer resources: a lane whose tap falls outside the image (or past K) is
     // given an offset beyond the range, which the hardware answers with zeros
     // without touching memory -- no branches and no zero-fill in the loop.
-    constexpr uint32_t OOB = 0x80000000u;
     constexpr int ES = (int)sizeof(T);
     const rsrc_t rx = make_rsrc(p.x, p.x_bytes);
     const rsrc_t rx2 = make_rsrc(p.x2 ? p.x2 : p.x, p.x2 ? p.x2_bytes : p.x_bytes);

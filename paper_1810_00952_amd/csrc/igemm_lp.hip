@@ -53,18 +53,11 @@
 // N a multiple of 8; epilogue of the form [f32 bias] [+ bf16 residual] [relu];
 // every tensor below 2 GiB.
 #include "lp_planes.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-#define RL_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, untyped dwords
-}
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
 // vmcnt = bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
@@ -86,9 +79,6 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t mu
 {
     return d == 1 ? n : (__umulhi(n, mul) >> sh);
 }
-
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;
 
 }  // namespace
 

@@ -33,22 +33,6 @@ constexpr int ST = 64 * 128;                      // bytes per stage of either o
 constexpr int RING = NB * ST, A_OFF = RING, Z_OFF = 2 * RING, LDS_BYTES = Z_OFF + 256;
 static_assert(4 * 96 * 64 * 4 <= Z_OFF && LDS_BYTES <= 160 * 1024, "LDS holds the sums of four waves");
 
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff] to LDS at lds_addr + lane*16.  Written out because the compiler would make
-// every read of the ring wait for all requests into it; they are counted by hand
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds_addr), "v"(voff), "s"(desc) : "memory");
-#endif
-}
-
 __device__ __forceinline__ int key(int row) { return ((row >> 1) & 1) << 2; }      // in 16-byte chunks of a row of eight
 
 }  // namespace

@@ -50,7 +50,7 @@
 //
 // Preconditions (checked by the planner): as for the pixel-on-lane kernel,
 // plus N <= 64 and K <= 576.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
@@ -68,23 +68,6 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t mu
     return d == 1 ? n : (__umulhi(n, mul) >> sh);
 }
 
-// raw buffer descriptor (untyped dwords, range-checked against `bytes`)
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff + soff] to LDS at lds_addr + lane*16
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff, uint32_t soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory");
-#endif
-}
-
 #define RL_WAIT_VM(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
 
 __device__ __forceinline__ uint32_t lds_addr_of(const void *p)
@@ -92,8 +75,6 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int WS_MAX_NK = 9;          // K tiles of stationary weights (9 x 8 KB)
 
 }  // namespace

@@ -35,18 +35,11 @@
 // Every result is computed by the same instructions in the same order whoever computes it.
 // The control words live where step T-1's projections of batch row 0 begin (scratch); what they displace was saved at the start
 // of h_{T-1} (of h_{T-2} where h0 lies there) by the launch before and is fetched into LDS before entering.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *ptr, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)ptr, 0, bytes, 0x00020000);   // raw buffer, untyped dwords
-}
 
 __device__ __forceinline__ void wg_barrier()
 {

@@ -34,27 +34,11 @@
 // the recurrent columns start at k_off; zx uses the same column order.
 // MFMA operand roles and LDS swizzle as in the contraction kernels (weights
 // are the row operand, a lane holds one batch row).
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};   // raw buffer, untyped dwords
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff + soff] to LDS at lds_addr + lane*16
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff, uint32_t soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory");
-#endif
-}
 
 #define RL_WAIT_VM(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
 #define RL_WAIT_LGKM0() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
@@ -64,7 +48,6 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int BM = 32, BNC = 32, UNITS = 8;       // batch rows, gate columns, hidden units per workgroup
 constexpr int STAGE = BM * 128, NSTAGE = 4;       // one h_prev tile; tiles per round
 constexpr int PSTRIDE = 36;                       // floats per parked row (32 + 4: spreads the banks)

@@ -20,18 +20,11 @@
 // kh & 1; 81 = 64 + 17 makes that the tile row 17 dy + dx plus a constant modulo the 64 banks, so the lanes of a wave
 // read consecutive banks whatever the row wrap, and the two filter rows of a k-step differ by the constant distance
 // between the areas.  Slots that hold nothing are requested out of range, which writes zeros.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};   // raw buffer, untyped dwords
-    return d;
-}
 
 // one direct load: 64 lanes x 4 bytes from desc[voff] to LDS at lds_addr + lane*4
 __device__ __forceinline__ void dma4(const u32x4 &desc, uint32_t lds_addr, uint32_t voff)
@@ -68,8 +61,6 @@ constexpr uint32_t LOWEST = 0x80008000u;          // below every mapped value
 // staging-tile row order, see stem_pool.hip
 __device__ __forceinline__ int stg_row(int m) { return (m & ~5) | ((m & 1) << 2) | ((m >> 2) & 1); }
 
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int TPH = 7, TPW = 8;                   // pooled pixels per region
 constexpr int RH = 2 * TPH + 1, RW = 2 * TPW + 1; // convolution outputs a region needs: 15 x 17
 constexpr int RPX = RH * RW;                      // 255 of the tile's 256 rows

@@ -46,27 +46,11 @@
 // of the pixel-on-lane path (4-channel padded frame, regrouped taps), exactly
 // four K tiles, convolution stride 2, N = 64, epilogue [f32 bias] [relu],
 // pool 3x3 / 2 / pad 1.
-#include "device_utils.h"
+#include "igemm_lds.h"
 
 namespace rl {
 
 namespace {
-
-__device__ __forceinline__ u32x4 make_desc(const void *ptr, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)ptr;
-    u32x4 d = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};   // raw buffer, untyped dwords
-    return d;
-}
-
-// one direct load: 64 lanes x 16 bytes from desc[voff + soff] to LDS at lds_addr + lane*16
-__device__ __forceinline__ void dma16(const u32x4 &desc, uint32_t lds_addr, uint32_t voff, uint32_t soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory");
-#endif
-}
 
 #define RL_WAIT_VM(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
 
@@ -100,8 +84,6 @@ constexpr uint32_t LOWEST = 0x80008000u;          // below every mapped value
 // in slot m; the 8-byte writes of the accumulator layout cost the same either way).
 __device__ __forceinline__ int stg_row(int m) { return (m & ~5) | ((m & 1) << 2) | ((m >> 2) & 1); }
 
-constexpr int NUM_XCD = 8;
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int TPH = 7, TPW = 8;                   // pooled pixels per region
 constexpr int RH = 2 * TPH + 1, RW = 2 * TPW + 1; // convolution outputs a region needs: 15 x 17
 constexpr int RPX = RH * RW;                      // 255 of the tile's 256 rows
@@ -346,7 +328,6 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolParams 
     }
 #endif
 }
-
 
 hipError_t launch_stem_pool(const StemPoolParams &q, hipStream_t s)
 {
