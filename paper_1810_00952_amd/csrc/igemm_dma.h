@@ -40,7 +40,7 @@ struct Alone {
 
 // The body is the kernel's own text and no function that takes its arguments by reference: inlined from one, the compiler no longer holds
 // them for constant memory while it orders the code, and fetches those of the epilogue one by one, each where it is used (17 more scalar
-// loads; dense 1000 x 1000 x 784 bf16 8.2 us against 7.95, 17x96x29x29 -> 136 3x3 with a residual 21.9 against 21.4).
+// loads; dense 1000 x 1000 x 784 bf16 8.2 us against 7.95, 17x96x29x29 -> 136 3x3 with a residual 21.8 against 21.4).
 template <int BM, int BN> constexpr int dma_stage_bytes() { return (BM + BN) * 128; }
 template <typename T, int BM, int BN, int MODE, bool TAPS, typename BESIDE>
 __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, const BESIDE beside)
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
 
     // The kernel arguments that the first request hangs on, fetched together; left to itself the compiler asks for some of them
     // behind the arithmetic on others (dense 1000 x 1000 x 784 bf16 8.94 -> 8.62 us, two-layer classifier f32 12.52 -> 12.43); the lines
-    // of all others above (8.54 -> 8.15; dense gradients 15.48 -> 15.11).  The longer kernels do not gain by it.
+    // of all others above (8.24 -> 7.97; dense gradients, each a launch, 15.48 -> 15.07).  The longer kernels do not gain by it.
     asm volatile("" :: "s"(p.nblk_m), "s"(p.nblk_n), "s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kp), "s"(p.K1), "s"(p.C), "s"(p.H), "s"(p.W), "s"(p.KH), "s"(p.KW),
                  "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw), "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.splits), "s"(p.split_tiles));
     bid = xcd_run(bid, p.nblk_m * p.nblk_n);
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
             if (!TAPS)
             for (int kh = 0; kh < p.KH; ++kh)
                 for (int kw = 0; kw < p.KW; ++kw)
-                    if ((unsigned)(ih0 + kh) < (unsigned)p.H && (unsigned)(iw0 + kw) < (unsigned)p.W) mask |= 1u << (kh * p.KW + kw);
+                    mask |= (uint32_t)(((unsigned)(ih0 + kh) < (unsigned)p.H) & ((unsigned)(iw0 + kw) < (unsigned)p.W)) << (kh * p.KW + kw);       // without a branch
             off = ((int64_t)img * p.xs_n + (int64_t)ih0 * p.xs_h + (int64_t)iw0 * p.xs_w) * ES;
         }
         if (m >= p.M) { t_ih[i] = -(1 << 24); t_iw[i] = 0; }
