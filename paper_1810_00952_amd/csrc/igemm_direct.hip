@@ -259,7 +259,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
 // A workgroup has 16 batch rows and UN units, all four gates of them; its waves take a slice of K each, so that every memory latency
 // of the step is paid once.  What bounds a step behind that and its launch is the vector L1's 50 cycles per load of a fragment, on
 // however many CUs take part: few units per workgroup where there are few rows.
-// 250 drawn sequences: f32 0.27 of the time, bf16 0.23 (us a step: f32 42 rows, 928 -> 544 units 34 -> 17; 12 rows, 96 -> 48, bf16 12.6 -> 3.6).
+// 160 drawn sequences: f32 0.25 of the time, bf16 0.22, none above 0.80 (us a step: f32 42 rows, 928 -> 544 units 34 -> 17; 12 rows, 96 -> 48, bf16 12.6 -> 3.6).
 // (The element gather, which ran wherever the width of x or h was no multiple of the K tile, read one element at a time on one workgroup
 // per 64 rows and block.)
 template <typename T, int UN>

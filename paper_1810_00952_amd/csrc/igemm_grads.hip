@@ -3,8 +3,9 @@
 //
 // Neither needs the other's result, and each alone ends in a last round that leaves CUs idle, then in the 3 to 4 us that pass between
 // dependent launches.  Together the workgroups of the one fill the rounds of the other.  The ones with the longer K loop come
-// first in the grid.  Dense 512 x 1000 x 784 bf16 15.1 -> 10.5 us; 32x64x28x28 -> 64 3x3 f32 60 -> 50, with the slices cut for the
-// shared launch (Planner::reslice_beside); of 600 drawn layers 128 go this way, to 0.76 (dense) to 0.88 of their time (conv f32).
+// first in the grid.  Dense 512 x 1000 x 784 bf16 15.1 -> 10.2 us; 32x64x28x28 -> 64 3x3 f32 60 -> 50, with the slices cut for the
+// shared launch (Planner::reslice_beside); of 900 drawn backward passes 355 go this way, at 0.81 (dense bf16), 0.84 (dense f32), 0.75 (conv
+// bf16) and 0.85 (conv f32) of the time without shared launches (no_pair; a convolution's layout changes share one too).
 #include <algorithm>
 
 #include "igemm_dma.h"

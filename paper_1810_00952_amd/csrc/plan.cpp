@@ -1548,7 +1548,8 @@ struct Planner {
     // A result of the pixel-on-lane kernels that nothing but the change of layout into Shape order reads is stored in that order at once.
     // The two forms that only store rows of channels give way to their neighbours that can: 256x256 tiles (64x64x56x56 -> 256 1x1 85.0 -> 55.7 us,
     // 32x2048x14x14 -> 1024 67.0 -> 53.8) and K split over the waves, there below 512 channels (64x128x8x8 -> 512 16.9 -> 12.8, 8x256x28x28 -> 256
-    // 19.4 -> 17.1; 64x512x8x8 -> 512 28.2 against 28.8).
+    // 19.4 -> 17.1; 512 channels, that split and the transposition against Shape order: 64x512x8x8 -> 512 28.0 and 29.7, with a residual
+    // 29.0 and 28.7, 4x512x28x28 -> 512 25.3 and 25.9, with a residual 26.3 and 25.9).
     void fuse_planes_store()
     {
         if (plan.opts.no_shape_order || plan.lean) return;
