@@ -82,10 +82,10 @@ hipError_t launch_splitk_reduce(const IgemmParams &p, hipStream_t s)
 // A chain of memory latencies and nothing else, so everything whose address is known is requested at the start: the slices, both
 // biases and the weights of a wave's first JP outputs (NI: shares of a row per lane).  32 rows, 128 -> 10: 6.1 us by the trace -> 5.4; 64 rows,
 // 500 -> 10: 9.6 -> 6.2 (one output of a wave after the other, its weights behind the barrier, on 256 threads).
-template <int NI>
-__global__ __launch_bounds__(512) void reduce_dense_kernel(const ReduceDenseParams p)
+constexpr int ADD_WAVES = 8;
+template <int NI, int JP>
+__global__ __launch_bounds__(64 * ADD_WAVES) void reduce_dense_kernel(const ReduceDenseParams p)
 {
-    constexpr int JP = NI >= 8 ? 2 : 16 / NI > 4 ? 4 : 16 / NI;
     __shared__ float hs[64 * NI];
     touch_args(p);
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -99,14 +99,14 @@ __global__ __launch_bounds__(512) void reduce_dense_kernel(const ReduceDensePara
     float w[JP][NI <= 8 ? NI : 1], b2[JP];
 #pragma unroll
     for (int q = 0; q < JP; ++q) {
-        const int j = wave + 8 * q;
+        const int j = wave + ADD_WAVES * q;
         b2[q] = p.epi2.simple && p.epi2.has_bias && j < p.N2 ? load_as_f32(p.epi2.bias_ptr, p.epi2.bias_dtype, j) : 0.0f;
         if constexpr (NI <= 8) {
 #pragma unroll
             for (int i = 0; i < NI; ++i) w[q][i] = weight(j, i);
         }
     }
-    for (int n = t; n < p.N1; n += 512) {
+    for (int n = t; n < p.N1; n += 64 * ADD_WAVES) {
         const float *src = p.partial + (int64_t)m * p.N1 + n;
         const float b1 = p.epi1.simple && p.epi1.has_bias ? load_as_f32(p.epi1.bias_ptr, p.epi1.bias_dtype, n) : 0.0f;
         float val = 0.0f;
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(512) void reduce_dense_kernel(const ReduceDensePara
         hs[n] = p.h_dtype == DT_BF16 ? round_bf16(val) : val;
     }
     __syncthreads();
-    for (int j0 = wave; j0 < p.N2; j0 += 8 * JP) {
+    for (int j0 = wave; j0 < p.N2; j0 += ADD_WAVES * JP) {
         float acc[JP];
 #pragma unroll
         for (int q = 0; q < JP; ++q) {
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(512) void reduce_dense_kernel(const ReduceDensePara
             if constexpr (NI <= 8) {
                 if (j0 != wave) {
 #pragma unroll
-                    for (int i = 0; i < NI; ++i) w[q][i] = weight(j0 + 8 * q, i);
+                    for (int i = 0; i < NI; ++i) w[q][i] = weight(j0 + ADD_WAVES * q, i);
                 }
             }
         }
@@ -147,8 +147,8 @@ __global__ __launch_bounds__(512) void reduce_dense_kernel(const ReduceDensePara
 #pragma unroll
                 for (int i = 0; i < NI; ++i)
                     if (lane + 64 * i < p.N1) acc[q] += hs[lane + 64 * i] * w[q][i];
-            } else if (j0 + 8 * q < p.N2) {
-                for (int n = lane; n < p.N1; n += 64) acc[q] += hs[n] * load_as_f32(p.w2, p.w_dtype, (int64_t)(j0 + 8 * q) * p.Kp2 + n);
+            } else if (j0 + ADD_WAVES * q < p.N2) {
+                for (int n = lane; n < p.N1; n += 64) acc[q] += hs[n] * load_as_f32(p.w2, p.w_dtype, (int64_t)(j0 + ADD_WAVES * q) * p.Kp2 + n);
             }
         }
 #pragma unroll
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(512) void reduce_dense_kernel(const ReduceDensePara
             for (int q = 0; q < JP; ++q) acc[q] += __shfl_xor(acc[q], d, 64);
 #pragma unroll
         for (int q = 0; q < JP; ++q) {
-            const int j = j0 + 8 * q;
+            const int j = j0 + ADD_WAVES * q;
             if (lane != q || j >= p.N2) continue;
             const int64_t off = (int64_t)m * p.ys_n + (int64_t)j * p.ys_c;
             float v = acc[q];
@@ -178,9 +178,18 @@ hipError_t launch_reduce_dense(const ReduceDenseParams &p, hipStream_t s)
     if (!p.partial || !p.w2 || !p.y || p.splits < 2 || p.splits > 64 || p.M < 1 || p.M > 65535 || p.N1 < 1 || p.N1 > REDUCE_DENSE_MAX_N1 ||
         p.N2 < 1 || p.N2 > REDUCE_DENSE_MAX_N2 || p.Kp2 < p.N1 || (int64_t)p.M * p.N1 * p.splits >= (int64_t)1 << 31)
         return hipErrorInvalidValue;
-    if (p.N1 <= 128) hipLaunchKernelGGL(reduce_dense_kernel<2>, dim3((unsigned)p.M), dim3(512), 0, s, p);
-    else if (p.N1 <= 512) hipLaunchKernelGGL(reduce_dense_kernel<8>, dim3((unsigned)p.M), dim3(512), 0, s, p);
-    else hipLaunchKernelGGL(reduce_dense_kernel<REDUCE_DENSE_MAX_N1 / 64>, dim3((unsigned)p.M), dim3(512), 0, s, p);
+#define RL_GO(NI, JP) hipLaunchKernelGGL((reduce_dense_kernel<NI, JP>), dim3((unsigned)p.M), dim3(64 * ADD_WAVES), 0, s, p)
+    // up to an output a wave: nothing is asked for ahead that is not there, and the row's shares fit closer (99 rows, 768 -> 128 -> 4 f32
+    // 10.7 us the two layers, now 9.9, 768 -> 256 -> 8 11.15 and 10.4; from 9 outputs on the other form, 768 -> 128 -> 24 11.4)
+    if (p.N2 <= 8) {
+        if (p.N1 <= 128) RL_GO(2, 1);
+        else if (p.N1 <= 256) RL_GO(4, 1);
+        else if (p.N1 <= 512) RL_GO(8, 1);
+        else RL_GO(REDUCE_DENSE_MAX_N1 / 64, 1);
+    } else if (p.N1 <= 128) RL_GO(2, 4);
+    else if (p.N1 <= 512) RL_GO(8, 2);
+    else RL_GO(REDUCE_DENSE_MAX_N1 / 64, 2);
+#undef RL_GO
     return hipGetLastError();
 }
 
@@ -192,9 +201,10 @@ RL_INST(uint16_t, 128, 128, STORE_ROWS, false) RL_INST(uint16_t, 128, 128, STORE
 RL_INST4(float, 128, 64) RL_INST4(float, 64, 64) RL_INST(float, 64, 64, STORE_GATES, false)
 #undef RL_INST4
 #undef RL_INST
-template __global__ void reduce_dense_kernel<2>(const ReduceDenseParams);
-template __global__ void reduce_dense_kernel<8>(const ReduceDenseParams);
-template __global__ void reduce_dense_kernel<REDUCE_DENSE_MAX_N1 / 64>(const ReduceDenseParams);
+#define RL_INST(NI, JP) template __global__ void reduce_dense_kernel<NI, JP>(const ReduceDenseParams);
+RL_INST(2, 4) RL_INST(8, 2) RL_INST(REDUCE_DENSE_MAX_N1 / 64, 2)
+RL_INST(2, 1) RL_INST(4, 1) RL_INST(8, 1) RL_INST(REDUCE_DENSE_MAX_N1 / 64, 1)
+#undef RL_INST
 
 // what the kernel's K loop assumes of the operands
 bool igemm_dma_takes(const IgemmParams &p, bool taps, int element_size)

@@ -39,7 +39,10 @@ def test_mlp(dtype, batch, d_in, d_hidden, d_out):
 
 
 DENSE_CHAIN_CASES = [(32, 784, 128, 10, "f32"), (32, 784, 128, 10, "bf16"), (1, 800, 500, 10, "f32"), (64, 800, 500, 10, "f32"), (7, 2048, 2048, 64, "f32"),
-                     (130, 1024, 136, 3, "f32"), (5, 516, 100, 1, "f32"), (33, 1000, 72, 24, "bf16")]
+                     (130, 1024, 136, 3, "f32"), (5, 516, 100, 1, "f32"), (33, 1000, 72, 24, "bf16"),
+                     # edges of the adding launch's forms: up to 128, 256, 512 hidden units, up to eight outputs
+                     (9, 768, 128, 8, "f32"), (3, 768, 129, 9, "f32"), (21, 768, 256, 8, "f32"), (6, 768, 257, 7, "f32"), (4, 1024, 512, 2, "f32"), (11, 768, 174, 4, "bf16"),
+                     (10, 1024, 516, 8, "f32")]
 
 
 @pytest.mark.parametrize("case", DENSE_CHAIN_CASES, ids=[f"b{c[0]}-{c[1]}-{c[2]}-{c[3]}-{c[4]}" for c in DENSE_CHAIN_CASES])
