@@ -265,7 +265,8 @@ rl_status rl_plan_run(const rl_plan *plan, const rl_binding *bindings, int32_t n
  * RL_STATIC_WORKSPACE_BYTES that is part of the library's code object (each GPU the library runs on holds one copy
  * until the process ends).  A plan whose rl_plan_workspace_bytes are more than that holds, where one fits, a second form
  * made without the choices that trade workspace for time (padded rows, contractions cut along K on larger grids, weight
- * gradients over rows); this call then runs that form: other kernels, results equal to summation order.  rl_plan_describe
+ * gradients over rows, launches that two gradients or two changes of layout share) and without results stored in Shape order
+ * at once; this call then runs that form: other kernels, results equal to summation order.  rl_plan_describe
  * and rl_plan_workspace_bytes speak of the first form, rl_plan_packed_bytes counts a param that the second reads laid out
  * otherwise in both layouts.  Where no form fits the call returns RL_ERR_WORKSPACE.  It allocates nothing on the device
  * and otherwise behaves like rl_plan_run (for plans that fit: same kernels, same results; same errors).
