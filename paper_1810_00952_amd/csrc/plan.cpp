@@ -239,7 +239,8 @@ struct Planner {
 
     // Few tiles and a long K (small batches, late stages): K is split over several workgroups per tile, whose fp32
     // sums meet in a scratch tensor [splits][M][N] that a second kernel adds up in order before the epilogue.
-    // splits = 1: whole; per: K tiles of a slice; cycles: of the fullest CU, the adding launch's share included
+    // splits = 1: whole; per: K tiles of a slice; cycles: of the fullest CU, the adding launch's share included (up to 64 tiles with the
+    // slices that each gain a twentieth; direct_form's constants are fitted to that)
     struct KSlices { int splits = 1, per = 0; int64_t tiles = 0; double cycles = 0.0; };
     KSlices k_slices(int tile, int dtype, int64_t M, int64_t N, int64_t K) const
     {
@@ -253,22 +254,21 @@ struct Planner {
         // splits up to 64 tiles only, as the smallest-workspace form always did
         if (plan.opts.no_splitk || nk < 8 || c.tiles >= (plan.lean ? 65 : 512)) return c;
         auto cost = [&](int sp) { return (double)((nk + sp - 1) / sp) * tile_cost(tile, dtype, c.tiles * sp) + (c.tiles > 64 ? 6500.0 : 0.0) + 8.0 * sp * M * (double)N / 2200.0; };
-        int want = (int)std::min<int64_t>(std::min<int64_t>(16, 256 / std::max<int64_t>(c.tiles, 1)), nk / 2);
-        if (c.tiles > 64) {
-            // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
-            // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22).  The
-            // estimate is good to a sixth: over 700 layers, split where it promised less than that, 89 were slower than whole by
-            // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 17; few channels need a third
-            double best = c.cycles;
-            want = 1;
-            for (int sp = 2; sp <= std::min(16, nk / 2); ++sp)
-                if (cost(sp) < best * 0.95) { best = cost(sp); want = sp; }
-            if (best > c.cycles * (N < 16 ? 0.7 : 0.83)) want = 1;
-        }
+        // half-filled grids: K tiles of the fullest CU against 6500 cycles for the adding launch and 2200 bytes per cycle of
+        // partial sums (f32 1568 x 256 x 2304: 100 tiles, whole 51 us, five slices 34; 500 x 700 x 1200 37 against 22).  The
+        // estimate is good to a sixth: over 700 layers, split where it promised less than that, 89 were slower than whole by
+        // more than 3 % (12544 x 6 x 864 in nine slices 36 us against 27), now 17; few channels need a third
+        const int most = (int)std::min<int64_t>(std::min<int64_t>(16, c.tiles > 64 ? 16 : 256 / std::max<int64_t>(c.tiles, 1)), nk / 2);
+        double best = c.cycles;
+        int want = 1;
+        for (int sp = 2; sp <= most; ++sp)
+            if (cost(sp) < best * 0.95) { best = cost(sp); want = sp; }
+        if (c.tiles <= 64) want = most;     // few tiles: as many slices as there are CUs for
+        else if (best > c.cycles * (N < 16 ? 0.7 : 0.83)) want = 1;
         if (want < 2 || want * M * N * 4 >= (int64_t)1 << 28) return c;
         c.per = (nk + want - 1) / want;
         c.splits = (nk + c.per - 1) / c.per;
-        c.cycles = cost(c.splits);
+        c.cycles = best;
         return c;
     }
 
@@ -334,13 +334,15 @@ struct Planner {
         }
         if (plan.opts.direct_all) return best;
         // A last round that only some of the CUs have a workgroup for.  Rows of f32 features read one by one: it counts in full, as two
-        // workgroups on a CU have twice the lines in use that the vector L1 holds (146 x 1920 x 590 17.2 us by padded rows, 23.0 so; 775 x 414 x
-        // 1013 23.8 and 36.0).  Elsewhere by half, from 14 K steps a slice on (32x304x37x37 -> 78 3x3 at stride 2 41 and 53).  Not up to 32
-        // channels, where the other kernels' estimate, of tiles that are half empty, is low itself, nor where a max-pool of the result rides along.  Of 1515 drawn layers that moved 24 lost
-        // more than 3 %, up to 1.9x; now 4, up to 1.18x (of 1502 others 3, up to 1.16x), and 7 that won more than 3 % (to 0.87) stay behind.
-        if (rounds_best > 1.0 && other != OTHER_GATHER && !pooled) {
-            if (!bf16 && mode == DIRECT_ANY && other == OTHER_DMA && steps_best >= 6 && N > 128) us = us_whole;
-            else if (steps_best >= 14 && N > 32) us = 0.5 * (us + us_whole);
+        // workgroups on a CU have twice the lines in use that the vector L1 holds (354 x 704 x 1066 19.2 us by padded rows, 33.2 so; 249 x 1172 x
+        // 1013 19.0 and 37.3); shorter rows still fit (1118 x 364 x 326 17.6 and 12.5).  Taps of channels in planes, a last round less than half full:
+        // it counts by half, from so many K steps a slice that the other kernels' longer start is made up for, earlier at a stride, where the lines
+        // fetched are half used (32x304x37x37 -> 78 3x3 at stride 2 41 and 53).  Not up to 32 channels, where the other kernels' estimate, of tiles
+        // that are half empty, is low itself, nor where a max-pool of the result rides along.  It takes 195 of 90000 drawn layers off
+        // this kernel, which then run in 0.84 of the time; 15 of them lose more than 3 %, up to 1.15x.
+        if (rounds_best > 1.0 && !pooled) {
+            if (!bf16 && mode == DIRECT_ANY && taps == 1 && other == OTHER_DMA && steps_best >= 10 && N > 128) us = us_whole;
+            else if (mode == DIRECT_PLANES && taps > 1 && steps_best >= (strided ? 16 : 32) && N > 32 && rounds_best - std::floor(rounds_best) < 0.5) us = 0.5 * (us + us_whole);
         }
         const KSlices lds = k_slices(direct_load_tile(dtype, M, N), dtype, M, N, K);
         const bool split = lds.splits > 1;

@@ -567,10 +567,10 @@ def test_k_over_the_waves_of_a_workgroup_is_not_called_a_split_over_workgroups()
 
 
 def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty():
-    def dense(m, n, k):
+    def dense(m, n, k, dtype="f32"):
         g = W.GraphSpec("dense")
-        x, w = g.input("x", "f32", (m, k)), g.param("w", "f32", (n, k))
-        o, (y,) = g.op("dense", [x, w], [("f32", (m, n))]); g.group([o]); g.output(y)
+        x, w = g.input("x", dtype, (m, k)), g.param("w", dtype, (n, k))
+        o, (y,) = g.op("dense", [x, w], [(dtype, (m, n))]); g.group([o]); g.output(y)
         return g
     direct = lambda spec: any("_direct" in s["kernel"] for s in _steps(spec))
     # rows of features read one by one, more workgroups than CUs: slower than padded rows (1.2 to 1.9 times)
@@ -579,11 +579,15 @@ def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty
     # long slices, a few workgroups past the CUs
     for case in ((32, 304, 78, 37, 37, 3, 2, 1), (30, 192, 64, 85, 85, 3, 2, 0)):
         assert not direct(W.conv_group(*case, "f32")[0]), case
-    # one round, short slices, few channels: it stays
-    for dims in ((498, 345, 457), (57, 256, 1093), (1562, 104, 495)):
+    # one round, short rows, few features: it stays
+    for dims in ((498, 345, 457), (57, 256, 1093), (1562, 104, 495), (1118, 364, 326), (1099, 242, 326), (695, 384, 387), (329, 230, 897)):
         assert direct(dense(*dims)), dims
-    for case in ((1, 64, 64, 56, 56, 3, 1, 1), (32, 128, 32, 53, 36, 3, 2, 1)):
+    # and so do one tap, short slices and a last round that is more than half full
+    for case in ((1, 64, 64, 56, 56, 3, 1, 1), (32, 128, 32, 53, 36, 3, 2, 1), (16, 212, 64, 9, 9, 3, 1, 1), (64, 448, 49, 29, 29, 1, 1, 0), (9, 64, 80, 36, 36, 5, 1, 0)):
         assert direct(W.conv_group(*case, "f32")[0]), case
+    # few tiles of the other kernel: their slices are priced as the constants were fitted
+    for m, n, k in ((485, 160, 2064), (366, 128, 2600)):
+        assert direct(dense(m, n, k, "bf16")), (m, n, k)
 
 
 def test_gradients_that_fill_their_rounds_apart_are_not_put_into_one_launch():
