@@ -1673,20 +1673,6 @@ struct Planner {
         plan.bufs[part].bytes = (size_t)round_up((int64_t)splits * p.M * p.N * 4, 256);
     }
 
-    // Whether the two, neither of them cut along K, are ahead in one launch: what three workgroups a CU leave over runs by itself, at half
-    // of a workgroup's time at least, and alone either might have filled its rounds (dense f32 1181 x 1272 x 1419, 437 and 460 tiles, 107.8 us
-    // shared and 99.1 apart; 1305 x 1552 x 1152 109.6 and 102.8).  In shader cycles; 6000 pass between two launches.
-    bool shared_launch_pays(const Step &ig, const Step &tn) const
-    {
-        const int dt = tn.t_dtype, BK = 128 / (int)dtype_size(dt);
-        if (tn.tn.splits > 1 || ig.il.splits > 1) return true;
-        const int64_t na = (int64_t)((ig.ig.M + 63) / 64) * ((ig.ig.N + 63) / 64), nka = (ig.ig.K + BK - 1) / BK;
-        const int64_t nb = (int64_t)((tn.tn.M + 63) / 64) * ((tn.tn.N + 63) / 64), nkb = (tn.tn.P + BK - 1) / BK;
-        const double share = tile_cost(TILE_64x64, dt, 1 << 20) / (double)((1 << 20) / 256), work = (double)(na * nka + nb * nkb) / 256.0;
-        const double shared = na + nb <= 768 ? 0.0 : share * (work + 1.5 * (double)std::min(nka, nkb));
-        return shared < (double)nka * tile_cost(TILE_64x64, dt, na) + (double)nkb * tile_cost(TILE_64x64, dt, nb) + 6000.0;
-    }
-
     // A layer's two gradients (a direct-load contraction and one over rows, on 64x64 tiles) in one launch, if nothing between them
     // but layout changes: the earlier one then waits until the other's operands are there too.
     void pair_gradients()
@@ -1714,7 +1700,6 @@ struct Planner {
             if (a.kind + b.kind != S_IGEMM + S_TN || a.kind == b.kind || b.pair || !independent(a, b)) continue;
             const Step &ig = a.kind == S_IGEMM ? a : b, &tn = a.kind == S_TN ? a : b;
             if (ig.chain || ig.stem || !igemm_grads_ok(ig.ig, ig.il, tn.tn, tn.t_dtype, tn.tn_tile)) continue;
-            if (!shared_launch_pays(ig, tn)) continue;
             std::rotate(plan.steps.begin() + (long)si, plan.steps.begin() + (long)si + 1, plan.steps.begin() + (long)sj);
             Step &first = plan.steps[sj - 1], &second = plan.steps[sj];
             reslice_beside(first.kind == S_IGEMM ? first : second, first.kind == S_TN ? first : second);

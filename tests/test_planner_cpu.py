@@ -590,19 +590,6 @@ def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty
         assert direct(dense(m, n, k, "bf16")), (m, n, k)
 
 
-def test_gradients_that_fill_their_rounds_apart_are_not_put_into_one_launch():
-    def together(m, n, k, dtype="f32"):
-        g = W.GraphSpec("layer_backward")
-        dy, w, x = g.input("dy", dtype, (m, n)), g.param("w", dtype, (n, k)), g.input("x", dtype, (m, k))
-        for kind, ins, t in (("dense_grad_x", [dy, w], (dtype, (m, k))), ("dense_grad_w", [dy, x], ("f32", (n, k)))):
-            o, (y,) = g.op(kind, ins, [t], **({"out_dtype": "f32"} if kind == "dense_grad_w" else {}))
-            g.group([o]); g.output(y)
-        return any(" | " in s["kernel"] and "_rows" in s["kernel"] for s in _steps(g))
-    # 437 and 460 workgroups, 378 and 450: two a CU each, but three and a bit together
-    assert not together(1181, 1272, 1419) and not together(1305, 1552, 1152)
-    assert together(512, 1000, 784) and together(512, 1000, 784, "bf16") and together(131, 1195, 1455) and together(2651, 535, 640)
-
-
 def test_both_gradients_of_a_layer_share_no_workspace():
     # the two run at once: whatever either reads or writes is apart from what the other writes
     for dtype, (b, c, h, o) in (("f32", (32, 64, 28, 64)), ("bf16", (16, 40, 20, 72))):
