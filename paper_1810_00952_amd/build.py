@@ -16,7 +16,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 # Per-source additions.  igemm_ws.hip: its accumulators live across a loop that also holds the epilogue's
 # VALU code; with the accumulators in AGPRs the compiler copies all of them to VGPRs and back on every
 # trip, so keep MFMA results in VGPRs there (the kernel fits in 256).
-EXTRA_FLAGS = {"igemm_ws.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# lstm_seq.hip: its sums go through lane moves to LDS every step, which from AGPRs takes a copy of each (128 steps of 64 x 1024: 314 -> 305 us).
+EXTRA_FLAGS = {"igemm_ws.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"], "lstm_seq.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc() -> str:

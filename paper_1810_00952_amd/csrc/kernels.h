@@ -235,7 +235,7 @@ hipError_t launch_lstm_step(const LstmStepParams &p, hipStream_t s);
 struct LstmSeqParams {
     const void *h0; void *h_seq; size_t h_step_bytes;   // [B, H] bf16 before the first step; step t's result at h_seq + t * h_step_bytes
     const void *w; uint32_t w_bytes;    // packed cell weights, as in LstmStepParams
-    const float *zx;                    // [T][B][4H] f32
+    const float *zx;                    // [T][B][4H] f32, scratch: step 0's become the exchange of h
     const float *bias;                  // [4H] f32 in declaration order, or null
     float *c;                           // [B, H] f32, updated in place
     uint32_t *ctl, *save;               // control words (at zx of step T-1) and where what they displace is kept (a slot of h_seq that is not h0)

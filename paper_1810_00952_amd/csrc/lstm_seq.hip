@@ -4,11 +4,11 @@
 //
 // What bounds the one-launch-per-step form is not its arithmetic: 6.3 us per step, of which about 3 pass between dependent
 // launches and the rest fetching 128 KB per CU again (64 KB of weights that never change).  Here every CU keeps its weights in
-// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 2.3 us at 64 rows of
-// 1024 units (128 steps with their projections: 814 us step by step, 412 us here; 387 us if the 134 MB of projections still
-// stand in the last-level cache).  What is left of a step is a chain of latencies - the flags' poll, the L2 round trip for h,
-// the meeting of the partial sums, the gates, the store's acknowledgement - and not work: the MFMAs of a step take 0.3 us.
-//
+// registers for the whole sequence and a step costs one exchange of h between the CUs that need it: about 1.6 us at 64 rows of
+// 1024 units (128 steps with their projections: 814 us step by step, 303 us here, 79 of them the projections).  What is left of a
+// step is a chain: the L2 round trip for h (900 cycles), the products (1050, half of the MFMA's columns empty), the partial sums
+// through LDS (350), the gates (600), the way of the result to the L2.
+
 // Split: batch rows over the eight XCDs (8 of 64), hidden units over the CUs of an XCD (32 each at H = 1024).  Inside a CU each
 // of the four waves multiplies all 128 gate columns by its quarter of H (256 registers of weights per lane at H = 1024), so that
 // h is fetched once per CU, each wave its own part straight into registers; the four partial sums meet in LDS.  Wave w's quarter
@@ -18,8 +18,17 @@
 // fragments at a time and for the projections only after the products: 548 us.)
 // A step's h is written and read inside one XCD, through its L2: the stores go there (the vector L1 writes through), the loads
 // bypass the L1 (device scope; the narrower scopes may hit it).  No cache is flushed, which is what made a grid-wide barrier
-// cost more than a launch.  A workgroup publishes step t by writing t + 1 into its flag word after its stores were acknowledged;
-// the members of its group poll the flags of all of them.
+// cost more than a launch.
+// The members of a group exchange h in a ring of four steps, in the order of the MFMA fragments, apart from the results: its lines
+// stay in the L2, a wave writes whole lines and reads 512 or 1024 bytes in a row.  (Read from the results themselves, a step's h took
+// 2700 cycles to come: 32 loads of scattered rows at 50 cycles each, of lines that the L2 had only parts of.)  The ring lies where
+// the group's projections of step 0 were.  Its words say themselves that they are there: every wave clears its words of the next
+// step to NOT_YET, which no h is, under the products, before it writes this step's, and a reader asks again until none is left; who
+// has seen all of step t - 1 knows everyone past step t - 2, so that nobody still reads the words that are cleared.  The first steps
+// go by flags: a workgroup publishes step t by writing t + 1 into its flag word after its stores were acknowledged, and the members
+// poll the flags of all of them (every step that way: 391 us with a row-major ring, 405 through the results).
+// What else the step's chain lost: stores of results and of cleared words, and the requests for projections, go out one at a time between the
+// products (all at once 306 us), the first steps are code of their own (327 -> 313), sums and lane moves stay out of AGPRs (-> 305).
 // MFMA 16x16x32, weights as the row operand with row 4u + gate: a lane's four result registers are the four gates of one
 // (unit, batch row), so the gates, c (in registers throughout) and h need no exchange between lanes.
 //
@@ -28,13 +37,15 @@
 // the workgroups that are there (3 us a step at full strength): they wait for no one else, whoever starts later returns at once.
 // The XCDs that have workgroups share the groups of rows, the workgroups of an XCD the units of a group.  An XCD with all of
 // its workgroups keeps the weights in registers; with fewer, each takes several blocks of 32 units a step, whose weights it
-// fetches every time, and c lives in memory: 128 steps of 64 rows of 1024 units take 0.39 ms with all 256, 2.8 ms with 255, 3.4
+// fetches every time, and c lives in memory: 128 steps of 64 rows of 1024 units take 0.30 ms with all 256, 2.8 ms with 255, 3.4
 // with 100, 34 with 9 (39 ms as soon as one was missing while each went on alone; a launch per step 0.77 ms).  Keeping one block's
 // weights in registers there too made that 1.4 ms with 255, and the normal case 6 % slower: half of its fragments then stand
 // where the MFMAs have to fetch them from.
 // Every result is computed by the same instructions in the same order whoever computes it.
 // The control words live where step T-1's projections of batch row 0 begin (scratch); what they displace was saved at the start
 // of h_{T-1} (of h_{T-2} where h0 lies there) by the launch before and is fetched into LDS before entering.
+#include <type_traits>
+
 #include "igemm_lds.h"
 
 namespace rl {
@@ -54,6 +65,12 @@ constexpr int N_XCD = 8, DEV = 16;              // DEV: cache policy (sc1, devic
 constexpr int CTL_ENTERED = N_XCD, CTL_PLACED = N_XCD + 1, CTL_READY = 32, CTL_FLAGS = 64;
 constexpr uint32_t CLOSED = 0x80000000u;
 constexpr int UNITS = 32;                       // hidden units of a block
+// Steps from this one on wait for the words of h themselves, cleared to NOT_YET (infinity and zero; |h| is 1 at most, or NaN) a step ahead;
+// the earlier ones for the flags (h0 may lie in any slot but the first, and is read until everyone has published step 0)
+constexpr int BY_WORD = 3;
+constexpr uint32_t NOT_YET = 0x7f800000u;
+constexpr int ROR8 = 0x128;                       // DPP: a row of sixteen lanes rotated by eight
+constexpr int RING = 4;                         // steps of h the exchange holds
 constexpr int MAX_POLLS = 1 << 20;              // of a resident workgroup for resident ones: never reached; ends the wait, with NaN in c, all the same
 
 #define RL_CTL_LOAD(i) __hip_atomic_load(ctl + (i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
@@ -73,13 +90,14 @@ __global__ void lstm_seq_prepare_kernel(uint32_t *ctl, uint32_t *save, int words
 }
 
 // KS: H / 32.  HALF: at most eight rows per XCD, so that half of the MFMA's sixteen columns are empty: the lanes of those take
-// every other unit in the gate arithmetic, which is a serial chain of exponentials (128 steps of 64 rows, projections in cache: 498 -> 446 us).
+// every other unit in the gate arithmetic, which is a serial chain of exponentials (128 steps of 64 rows, projections in cache: 498 -> 446 us),
+// and the odd one of two column tiles, or of two fragments of h.
 template <int KS, bool HALF>
 __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
     constexpr int H = KS * 32, MEMBERS = H / UNITS, ROWB = H * 2;
-    __shared__ f32x4 part[4][UNITS / 4][64];    // the waves' partial sums
+    __shared__ f32x4 part[2][4][UNITS / 4][64]; // the waves' partial sums; of even and odd steps where a step has one barrier
     __shared__ uint32_t saved[CTL_FLAGS + N_XCD * MEMBERS];
     __shared__ uint32_t s_slot;
     __shared__ int s_in;
@@ -161,7 +179,7 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
         lost |= i == MAX_POLLS;
     };
     auto publish = [&](uint32_t stamp) {
-        // this wave's h is in the L2; after the barrier every wave's is (and every wave has read the partial sums)
+        // this wave's h is in the L2; after the barrier every wave's is
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         wg_barrier();
         if (t == 0) __hip_atomic_store(flags + member, stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -169,19 +187,32 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
     auto sums = [&](int u) -> f32x4 {
         const int at = wave * 2 + ct_of(u);
         const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-        return (((zero + part[0][at][src_lane]) + part[1][at][src_lane]) + part[2][at][src_lane]) + part[3][at][src_lane];
+        return (((zero + part[0][0][at][src_lane]) + part[0][1][at][src_lane]) + part[0][2][at][src_lane]) + part[0][3][at][src_lane];
+    };
+    // The words of a row of h that a lane writes and clears, two units each: units 4 ct + (q4 & ~1) and the one behind it.  Sixteen rows
+    // a group: a lane has two units of its own (ct 0 and 1) and trades one with the lane 16 further; eight rows: the even q4 write.
+    const bool writes = !HALF || !(q4 & 1);
+    const int word_unit = wave * 8 + (HALF ? l16 >> 3 : q4 & 1) * 4 + (q4 & 2);
+    auto two_units = [&](const uint32_t (&h)[NU]) -> uint32_t {
+        const auto r = __builtin_amdgcn_permlane16_swap(h[0], h[NU - 1], false, false);      // odd rows of 16 lanes of the first against the even ones of the second
+        return r[0] | r[1] << 16;
     };
 
     uint32_t stamp = 0;                                          // of the last step published
     u32x4 fw[CT][KW];                                            // row l16 = 4 unit + gate of column tile ct, fragment ks of the wave's quarter
-    auto multiply = [&](f32x4 (&acc)[CT], const u32x4 (&hf)[KW]) {
+    auto multiply = [&](f32x4 (&acc)[CT], auto h_of, auto meanwhile) {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int ks = 0; ks < KW; ++ks)
+        for (int ks = 0; ks < KW; ++ks) {
+            const u32x4 h = h_of(ks);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
-                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ct][ks]), __builtin_bit_cast(bf16x8, hf[ks]), acc[ct], 0, 0, 0);
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ct][ks]), __builtin_bit_cast(bf16x8, h), acc[ct], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            meanwhile(ks);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
     const bool whole = members == MEMBERS;
     if (whole) {
@@ -226,23 +257,92 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
             for (int u = 0; u < NU; ++u)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) z_r[0][u][g] = zx_at(0, unit_of(member, u), g);
-            auto step = [&](int tt, float (&zc)[NU][4], float (&zn)[NU][4]) {
-                if (tt > 0) wait_for(stamp);
-                const rsrc_t rh = rsrc_h(tt);
-                u32x4 hf[KW];
+            // The members' exchange of h (steps from BY_WORD on): a few steps' worth where step 0's projections of the group's rows were, so
+            // that the lines stay in the L2, in the order of the fragments: [fragment = member][quarter = wave][row][8 units].
+            // A wave writes whole lines and reads a KB at a time.  With at most eight rows the lanes of the other eight columns fetch
+            // the fragment behind.
+            constexpr int NL = HALF ? KW / 2 : KW;
+            const uint32_t slot = (uint32_t)rows * ROWB;
+            const rsrc_t rr = make_rsrc(p.zx + (size_t)r0 * N, RING * slot);
+            auto ring = [&](int tt) { return (uint32_t)(tt % RING) * slot; };
+            const uint32_t word_at = writes && glive ? (uint32_t)(((member * 4 + wave) * rows + grow) * 16 + (word_unit & 7) * 2) : OOB;
+            const uint32_t out_at = writes && glive ? (uint32_t)(row * ROWB + (member * UNITS + word_unit) * 2) : OOB;
+            const uint32_t ring_at = glive ? (uint32_t)((((HALF ? l16 >> 3 : 0) * 4 + q4) * rows + grow) * 16) : OOB;
+            const uint32_t seq_at = glive ? (uint32_t)(grow * ROWB + (HALF ? l16 >> 3 : 0) * 64 + q4 * 16) : OOB;
+            uint32_t word = 0;                                   // what the lane writes of a step's h
+            auto write_out = [&](int tt) {
+                __builtin_amdgcn_raw_buffer_store_b32(word, make_rsrc((char *)p.h_seq + (size_t)tt * p.h_step_bytes, (uint32_t)p.B * ROWB), out_at, 0, 0);
+            };
+            auto step = [&](auto phase, int tt, float (&zc)[NU][4], float (&zn)[NU][4]) {
+                constexpr bool by_word = decltype(phase)::value;
+                if (tt > 0 && !by_word) wait_for(stamp);
+                u32x4 hl[NL];
+                const rsrc_t rh = by_word ? rr : rsrc_h(tt);
+                const uint32_t at = by_word ? ring_at : seq_at, base = by_word ? ring(tt - 1) : 0u, unit = by_word ? (uint32_t)rows * 128u : 128u;
+                auto fetch = [&]() {
 #pragma unroll
-                for (int ks = 0; ks < KW; ++ks) hf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rh, h_row + k_byte(ks), 0, DEV);
-                __builtin_amdgcn_sched_barrier(0);               // all of them in flight at once; left to itself the compiler asks for two at a time
-                const int tn = min(tt + 1, p.T - 1);
+                    for (int i = 0; i < NL; ++i) {
+                        const int ks = HALF ? 2 * i : i;         // slice (ks >> 1) * 4 + wave, two fragments
+                        hl[i] = __builtin_amdgcn_raw_buffer_load_b128(rh, at, base + (uint32_t)((ks >> 1) * 4 + wave) * unit + ((ks & 1) ? unit / 2 : 0u), DEV);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);           // all of them in flight at once; left to itself the compiler asks for two at a time
+                };
+                fetch();
+                if (by_word) {
+                    int i = 0;
+#pragma unroll 1
+                    for (; i < MAX_POLLS; ++i) {
+                        float top = -2.0f;                       // of the words as numbers; a NaN in a word does not count
 #pragma unroll
-                for (int u = 0; u < NU; ++u)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) zn[u][g] = zx_at(tn, unit_of(member, u), g);
-                __builtin_amdgcn_sched_barrier(0);               // the next step's projections are requested here, behind h, and not after the products
+                        for (int i = 0; i < NL; ++i) {
+                            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(top) : "v"(hl[i][0]), "v"(hl[i][1]));
+                            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(top) : "v"(hl[i][2]), "v"(hl[i][3]));
+                        }
+                        if (__all(top < 2.0f)) break;
+                        asm volatile("" ::: "memory");
+                        fetch();
+                    }
+                    lost |= i == MAX_POLLS;
+                }
                 f32x4 acc[CT];
-                multiply(acc, hf);
+                multiply(acc, [&](int ks) {
+                    if constexpr (!HALF) return hl[ks];
+                    u32x4 v = hl[ks >> 1];
+                    if (ks & 1) {
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) part[wave][ct][lane] = acc[ct];
+                        for (int e = 0; e < 4; ++e) v[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)v[e], ROR8, 0xf, 0xf, false);      // from eight lanes on in the row of sixteen
+                    }
+                    return v;
+                }, [&](int ks) {
+                    // under the products, a request at a time: the step before's h into the results, the words of the next one cleared, the
+                    // next step's projections
+                    constexpr int OPS = 2 + 4 * NU;
+#pragma unroll
+                    for (int i = ks * OPS / KW; i < (ks + 1) * OPS / KW; ++i) {
+                        if (i == 0) {
+                            if (by_word) write_out(tt - 1);
+                        } else if (i == 1) {
+                            if (by_word || tt >= BY_WORD - 2) __builtin_amdgcn_raw_buffer_store_b32(NOT_YET, rr, word_at, ring(tt + 1), 0);
+                        } else {
+                            zn[(i - 2) / 4][(i - 2) % 4] = zx_at(min(tt + 1, p.T - 1), unit_of(member, (i - 2) / 4), (i - 2) % 4);
+                        }
+                    }
+                });
+                f32x4 (&sums_of)[4][UNITS / 4][64] = part[tt & 1];
+                if constexpr (HALF) {
+                    // eight columns of a tile are empty: two tiles a register, the odd one in the upper eight lanes, where it is finished
+#pragma unroll
+                    for (int ct = 0; ct < CT; ct += 2) {
+                        f32x4 v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            v[e] = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(acc[ct][e]), __float_as_int(acc[ct + 1][e]), ROR8, 0xf, 0xc, false));
+                        sums_of[wave][ct >> 1][lane] = v;
+                    }
+                } else {
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) sums_of[wave][ct][lane] = acc[ct];
+                }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 wg_barrier();
                 if (tt == p.T - 1 && r0 == 0) {
@@ -251,24 +351,35 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 #pragma unroll
                         for (int g = 0; g < 4; ++g) zc[u][g] = zx_true(zc[u][g], tt, unit_of(member, u), g);
                 }
-                uint16_t *out = out_row(tt);
+                uint32_t hb[NU];
 #pragma unroll
                 for (int u = 0; u < NU; ++u) {
-                    const f32x4 a = sums(u);
+                    const int at = HALF ? wave : wave * 2 + u;
+                    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const f32x4 a = (((zero + sums_of[0][at][lane]) + sums_of[1][at][lane]) + sums_of[2][at][lane]) + sums_of[3][at][lane];
                     float z[4];
 #pragma unroll
                     for (int g = 0; g < 4; ++g) z[g] = (a[g] + zc[u][g]) + bias_r[u][g];
-                    const float hn = lstm_cell_(z, c_r[u]);
-                    if (glive) out[unit_of(member, u)] = (uint16_t)f32_to_bf16_bits(hn);
+                    const uint32_t h = __float_as_uint(lstm_cell_(z, c_r[u])), up = (h + 0x7fffu + (h >> 16 & 1u)) >> 16, nan = h >> 16 | 0x40u;      // f32_to_bf16_bits without a branch
+                    hb[u] = (h & 0x7fffffffu) > 0x7f800000u ? nan : up;
                 }
-                publish(++stamp);
+                word = two_units(hb);
+                // the next step's words are cleared before this step's are written
+                asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * NU) : "memory");
+                if (by_word || tt >= BY_WORD - 1) __builtin_amdgcn_raw_buffer_store_b32(word, rr, word_at, ring(tt), 0);
+                else write_out(tt);
+                if (!by_word && tt + 1 < BY_WORD) publish(++stamp);
             };
+            static_assert(BY_WORD == 3, "written out here");     // T is 12 at least
+            step(std::false_type{}, 0, z_r[0], z_r[1]);
+            step(std::false_type{}, 1, z_r[1], z_r[0]);
+            step(std::false_type{}, 2, z_r[0], z_r[1]);
 #pragma unroll 1
-            for (int tt = 0; tt < p.T; tt += 2) {
-                step(tt, z_r[0], z_r[1]);
-                if (tt + 1 < p.T) step(tt + 1, z_r[1], z_r[0]);
-                if (lost) break;
+            for (int tt = BY_WORD; tt < p.T && !lost; tt += 2) {
+                step(std::true_type{}, tt, z_r[1], z_r[0]);
+                if (tt + 1 < p.T) step(std::true_type{}, tt + 1, z_r[0], z_r[1]);
             }
+            write_out(p.T - 1);
 #pragma unroll
             for (int u = 0; u < NU; ++u)
                 if (glive) p.c[(size_t)row * H + unit_of(member, u)] = lost ? __uint_as_float(0x7fc00000u) : c_r[u];
@@ -304,7 +415,7 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
                     }
                     if (blk != member) wg_barrier();             // the block before is read out
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) part[wave][ct][lane] = acc[ct];
+                    for (int ct = 0; ct < CT; ++ct) part[0][wave][ct][lane] = acc[ct];
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     wg_barrier();
 #pragma unroll

@@ -248,6 +248,25 @@ def test_lstm_sequence_in_one_launch(case):
         np.testing.assert_array_equal(first[1], again[1])
 
 
+# what the waiting members must not take for a word that is still to come: NaN in a row's h and c from some step on, infinite c, h at
+# its largest (1 exactly in bf16), the sign of zero; rows beside them stay what they are
+@pytest.mark.parametrize("B", [5, 64, 70])
+def test_lstm_sequence_with_nan_and_extreme_rows(B):
+    import numpy as np
+    T, I, H = 19, 128, 512
+    d = dict(W.lstm_data(T, B, I, H, "bf16"))
+    c0 = np.zeros((B, H), np.float32)
+    c0[1], c0[2], c0[3, ::2] = np.inf, 1e30, -np.inf
+    x = O.widen(d["x"], "bf16").copy()
+    x[7, 0, :], x[4, 4, 3] = np.nan, np.inf
+    x[:, 2] *= 1e4                                       # saturated gates
+    d["x"] = W.as_dtype(x, "bf16")
+    first, again = (run_sequence(T, B, I, H, d, {"no_seq": n}, None, c0) for n in (1, 0))
+    assert np.isnan(first[0][7:, 0]).all() and np.abs(first[0][:, 2]).max() == 1.0
+    np.testing.assert_array_equal(first[0], again[0])
+    np.testing.assert_array_equal(first[1], again[1])
+
+
 def test_lstm_sequence_captured_and_eager_agree():
     import numpy as np
     T, B, I, H = 16, 64, 128, 1024
