@@ -32,6 +32,10 @@ __device__ __forceinline__ void wg_barrier()
 // MODE of the result: rows of channels 16 bytes at a time, the LSTM gates, or any order
 enum { STORE_ROWS = 0, STORE_GATES = 1, STORE_ANY = 2 };
 
+// TEAMS: 2: eight waves, of which each half takes two of the four steps of every K tile; the halves' sums meet at the end.  With one workgroup
+// on a CU a K tile is a serial chain per wave (four direct loads, eight fragment reads, the MFMAs, the barrier: 690 cycles, however
+// many tiles are requested ahead), which this halves.  Grids of at most 256 workgroups: dense 1000 x 1000 x 784 bf16 8.04 -> 7.76 us,
+// 4x96x29x29 -> 136 3x3 with a residual 17.9 -> 16.3; 17 images (672 workgroups, which cover each other's chains) 24.4 against 26.8.
 // BESIDE: the workgroups of another contraction in the same grid (igemm_grads.hip).  Its take() does the work of those and returns false,
 // or returns true with the number of this contraction's workgroup.
 struct Alone {
@@ -42,8 +46,8 @@ struct Alone {
 // them for constant memory while it orders the code, and fetches those of the epilogue one by one, each where it is used (17 more scalar
 // loads; dense 1000 x 1000 x 784 bf16 8.2 us against 7.95, 17x96x29x29 -> 136 3x3 with a residual 21.8 against 21.4).
 template <int BM, int BN> constexpr int dma_stage_bytes() { return (BM + BN) * 128; }
-template <typename T, int BM, int BN, int MODE, bool TAPS, typename BESIDE>
-__global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, const BESIDE beside)
+template <typename T, int BM, int BN, int MODE, bool TAPS, typename BESIDE, int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS) void igemm_dma_kernel(const IgemmParams p, const BESIDE beside)
 {
     constexpr bool GATES = MODE == STORE_GATES;
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
@@ -66,22 +70,23 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
     constexpr int BKE = 8 * KV;               // K elements per tile (128 bytes per row)
     constexpr int WTM = BM / 2, WTN = BN / 2; // wave tile
     constexpr int TM = WTM / 32, TN = WTN / 32;
-    constexpr int AG = BM / 32, BG = BN / 32; // 8-row DMA groups per wave
+    constexpr int AG = BM / 32 / TEAMS, BG = BN / 32 / TEAMS; // 8-row DMA groups per wave
+    constexpr int KS = 4 / TEAMS;             // of the four steps of a K tile, a team's own
     constexpr int LPT = AG + BG;              // DMA instructions per wave per tile
     constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, STAGE = A_BYTES + B_BYTES;
     constexpr int LDC = BN + 8;               // fp32 staging row (32 rows at a time)
     static_assert(32 * LDC * 4 <= STAGE, "epilogue staging must fit in one stage");
 
-    const int t = threadIdx.x;
+    const int t = threadIdx.x & 255;          // within the team
     const int lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform by construction; keep it in an SGPR
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);   // wave-uniform by construction; keep it in an SGPR
+    const int team = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
 
     // The kernel arguments that the first request hangs on, fetched together; left to itself the compiler asks for some of them
     // behind the arithmetic on others (dense 1000 x 1000 x 784 bf16 8.94 -> 8.62 us, two-layer classifier f32 12.52 -> 12.43); the lines
     // of all others above (8.24 -> 7.97; dense gradients, each a launch, 15.48 -> 15.07).  The longer kernels do not gain by it.
     asm volatile("" :: "s"(p.nblk_m), "s"(p.nblk_n), "s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kp), "s"(p.K1), "s"(p.C), "s"(p.H), "s"(p.W), "s"(p.KH), "s"(p.KW),
-                 "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw), "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.splits), "s"(p.split_tiles));
+                 "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw), "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.splits), "s"(p.split_tiles), "s"(p.div_ohw_mul), "s"(p.div_ohw_sh), "s"(p.div_ow_mul), "s"(p.div_ow_sh));
     bid = xcd_run(bid, p.nblk_m * p.nblk_n);
     const int bm = bid / p.nblk_n, bn = bid - bm * p.nblk_n;
     const int m0 = bm * BM, n0 = bn * BN;
@@ -98,7 +103,8 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
     uint32_t a_voff[AG], a_mask[AG], a2_voff[AG], b_voff[BG];
     int a_kc[AG];                       // first K element (within a tile) of the 16-byte chunk this lane fetches
     int t_ih[AG], t_iw[AG];             // TAPS: input coordinate of tap (0, 0)
-    static_assert(AG % 2 == 0 && BG % 2 == 0, "a lane's chunk depends on the parity of its row group only");
+    static_assert((AG % 2 == 0 && BG % 2 == 0) || (AG == 1 && BG == 1), "a lane's chunk depends on the parity of its row group only");
+    constexpr int PAR = AG == 1 ? 1 : 2;
 #pragma unroll
     for (int i = 0; i < AG; ++i) {
         const int row = wave * 8 * AG + 8 * i + r8;
@@ -107,10 +113,11 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
         uint32_t mask = 0;
         int64_t off = 0;
         if (m < p.M) {
-            int img = m / p.OHW;
-            int pix = m - img * p.OHW;
-            int oh = pix / p.OW;
-            int ow = pix - oh * p.OW;
+            // by multiply-high: dense 1000 x 1000 x 784 bf16 8.36 -> 8.04 us, LeNet's shape 28.0 -> 27.6
+            const int img = p.OHW == 1 ? m : (int)(__umulhi((uint32_t)m, p.div_ohw_mul) >> p.div_ohw_sh);
+            const int pix = m - img * p.OHW;
+            const int oh = p.OW == 1 ? pix : (int)(__umulhi((uint32_t)pix, p.div_ow_mul) >> p.div_ow_sh);
+            const int ow = pix - oh * p.OW;
             int ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw;
             t_ih[i] = ih0; t_iw[i] = iw0;
             if (!TAPS)
@@ -186,10 +193,10 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
 #define RL_ISSUE_TAPS(ST)                                                                                             \
     {                                                                                                                 \
         const bool live = f_kt < nk;                                                                                  \
-        uint32_t toff[2], koff[2];                                                                                    \
-        int tkh[2], tkw[2];                                                                                           \
-        bool oka[2], okb[2];                                                                                          \
-        _Pragma("unroll") for (int e = 0; e < 2; ++e) {                                                               \
+        uint32_t toff[PAR], koff[PAR];                                                                                \
+        int tkh[PAR], tkw[PAR];                                                                                       \
+        bool oka[PAR], okb[PAR];                                                                                      \
+        _Pragma("unroll") for (int e = 0; e < PAR; ++e) {                                                             \
             const uint32_t k = (uint32_t)(f_kt * BKE + a_kc[e]);                                                      \
             const uint32_t tap = (__umulhi(k, p.div_c_mul) + (k & one_c)) >> p.div_c_sh;                              \
             tkh[e] = (int)((__umulhi(tap, p.div_kw_mul) + (tap & one_kw)) >> p.div_kw_sh);                            \
@@ -222,22 +229,22 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
 
     // ---- fragment addresses: row frow of a 32-row MFMA tile, chunk 2*ks + fhalf, swizzled
     const int frow = lane & 31, fhalf = lane >> 5;
-    int f_off[4];
+    int f_off[KS];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) f_off[ks] = frow * 128 + (((2 * ks + fhalf) ^ ((frow >> 1) & 7)) << 4);
+    for (int ks = 0; ks < KS; ++ks) f_off[ks] = frow * 128 + (((2 * (team * KS + ks) + fhalf) ^ ((frow >> 1) & 7)) << 4);
 
     // All of a tile's reads before its first MFMA: they are done while the MFMAs run, and the wait before the next barrier costs nothing.
 #define RL_COMPUTE(ST)                                                                                                \
     {                                                                                                                 \
-        u32x4 fa[4][TM], fb[4][TN];                                                                                   \
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                                            \
+        u32x4 fa[KS][TM], fb[KS][TN];                                                                                 \
+        _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                                           \
             _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                            \
                 fa[ks][i] = *(const u32x4 *)(ST + (wm * WTM + i * 32) * 128 + f_off[ks]);                             \
             _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                            \
                 fb[ks][j] = *(const u32x4 *)(ST + A_BYTES + (wn * WTN + j * 32) * 128 + f_off[ks]);                   \
         }                                                                                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                            \
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                              \
+        _Pragma("unroll") for (int ks = 0; ks < KS; ++ks)                                                             \
             _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                            \
                 _Pragma("unroll") for (int j = 0; j < TN; ++j) mma_chunk(acc[i][j], fa[ks][i], fb[ks][j], T());       \
     }
@@ -249,7 +256,17 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
     constexpr bool AHEAD = MODE == STORE_ANY && BM * BN <= 128 * 64 && (ES == 2 || BM == 128);
     PixelEpilogue<AHEAD ? BM : 32, AHEAD ? BN : 32> pe;
     pe.form = PE_NONE;
-    if constexpr (AHEAD) pe.request(p, t, m0, n0);
+    if constexpr (AHEAD) if (team == 0) pe.request(p, t, m0, n0);
+    using TE = TileEpilogue<BN>;
+    const bool pre = !GATES && p.epi.simple;
+    float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    OperandRegs<TE::NV> cur = {}, nxt = {};
+    auto request_rows = [&]() {
+        if (!pre) return;
+        TE::load_bias(p, t, n0, bias8);
+        TE::prefetch(p, t, m0, n0, cur);
+    };
+    if constexpr (TEAMS > 1 && MODE == STORE_ROWS) if (team == 0 && p.splits <= 1) request_rows();
 
     // ---- K loop, three stages, unrolled by three so that every stage use names its array.
     // Tile kt lives in stage kt % 3.  Body: wait until my DMAs of tile kt have landed (the LPT
@@ -281,9 +298,27 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
 #undef RL_ISSUE_TAPS
 #undef RL_ISSUE_UNIFORM
 
+    if constexpr (TEAMS > 1) {
+        // the second team's sums into stage 1's array, and to the first team's
+        static_assert(TEAMS == 2 && TM == 1 && TN == 1 && STAGE == 4 * 64 * 64, "a stage holds a team's sums");
+        f32x4 *sums = (f32x4 *)st1 + (wave & 3) * 4 * 64 + lane;
+        wg_barrier();                               // every wave's direct loads and reads are done
+        if (team == 1) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sums[r * 64] = f32x4{acc[0][0][4 * r], acc[0][0][4 * r + 1], acc[0][0][4 * r + 2], acc[0][0][4 * r + 3]};
+        }
+        __syncthreads();
+        if (team == 1) return;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const f32x4 v = sums[r * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[0][0][4 * r + e] += v[e];
+        }
+    }
+
     // ---- epilogue: 32 rows at a time through LDS (stage 0's array), then 8 channels per thread;
     // the residual rows of the next pass are fetched while this pass is staged and stored
-    using TE = TileEpilogue<BN>;
     float *sC = (float *)st0;
     if (MODE == STORE_ROWS && p.splits > 1) {
         // a slice of K: the bare fp32 sums, row-major [M][N], into this slice's part of the scratch tensor
@@ -363,13 +398,7 @@ __global__ __launch_bounds__(256) void igemm_dma_kernel(const IgemmParams p, con
         }
         return;
     }
-    const bool pre = !GATES && p.epi.simple;
-    float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    OperandRegs<TE::NV> cur = {}, nxt = {};
-    if (pre) {
-        TE::load_bias(p, t, n0, bias8);
-        TE::prefetch(p, t, m0, n0, cur);
-    }
+    if constexpr (TEAMS == 1) request_rows();
 #pragma unroll
     for (int q = 0; q < BM / 32; ++q) {
         if (pre && q + 1 < BM / 32) TE::prefetch(p, t, m0 + (q + 1) * 32, n0, nxt);

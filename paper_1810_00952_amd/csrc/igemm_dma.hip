@@ -195,12 +195,17 @@ hipError_t launch_reduce_dense(const ReduceDenseParams &p, hipStream_t s)
 
 // explicit instantiations (the host-side launch stubs of a kernel template with function-local
 // __shared__ arrays are not emitted implicitly)
-#define RL_INST(T, BM, BN, MODE, TAPS) template __global__ void igemm_dma_kernel<T, BM, BN, MODE, TAPS, Alone>(const IgemmParams, const Alone);
+#define RL_ONE(T, BM, BN, MODE, TAPS, TEAMS) template __global__ void igemm_dma_kernel<T, BM, BN, MODE, TAPS, Alone, TEAMS>(const IgemmParams, const Alone);
+#define RL_INST(T, BM, BN, MODE, TAPS) RL_ONE(T, BM, BN, MODE, TAPS, 1)
+#define RL_TWO(T) RL_ONE(T, 64, 64, STORE_ROWS, false, 2) RL_ONE(T, 64, 64, STORE_ANY, false, 2) RL_ONE(T, 64, 64, STORE_ROWS, true, 2) RL_ONE(T, 64, 64, STORE_ANY, true, 2)
+RL_TWO(uint16_t) RL_TWO(float)
+#undef RL_TWO
 #define RL_INST4(T, BM, BN) RL_INST(T, BM, BN, STORE_ROWS, false) RL_INST(T, BM, BN, STORE_ANY, false) RL_INST(T, BM, BN, STORE_ROWS, true) RL_INST(T, BM, BN, STORE_ANY, true)
 RL_INST(uint16_t, 128, 128, STORE_ROWS, false) RL_INST(uint16_t, 128, 128, STORE_ANY, false) RL_INST4(uint16_t, 128, 64) RL_INST4(uint16_t, 64, 64) RL_INST(uint16_t, 64, 64, STORE_GATES, false)
 RL_INST4(float, 128, 64) RL_INST4(float, 64, 64) RL_INST(float, 64, 64, STORE_GATES, false)
 #undef RL_INST4
 #undef RL_INST
+#undef RL_ONE
 #define RL_INST(NI, JP) template __global__ void reduce_dense_kernel<NI, JP>(const ReduceDenseParams);
 RL_INST(2, 4) RL_INST(8, 2) RL_INST(REDUCE_DENSE_MAX_N1 / 64, 2)
 RL_INST(2, 1) RL_INST(4, 1) RL_INST(8, 1) RL_INST(REDUCE_DENSE_MAX_N1 / 64, 1)
@@ -224,6 +229,16 @@ bool igemm_dma_splits_ok(const IgemmParams &p, bool taps, int element_size)
            (int64_t)p.splits * p.split_tiles >= nk && (taps || p.C % BKE == 0 || p.KH * p.KW == 1) && p.K1 == p.K;
 }
 
+template <typename T, int BM, int BN, bool GATES, bool TAPS, int TEAMS>
+static void go_dma(const IgemmParams &p, unsigned nblk, hipStream_t s)
+{
+    const bool rows = p.splits > 1 || (p.ys_n == (int64_t)p.OHW * p.ys_p && p.ys_c == 1 && (p.N & 7) == 0 && (p.ys_p & 7) == 0);
+    const dim3 grid(nblk, (unsigned)std::max(p.splits, 1));
+    if constexpr (GATES) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, STORE_GATES, false, Alone, 1>), grid, dim3(256), 0, s, p, Alone{});
+    else if (rows) hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS, Alone, TEAMS>), grid, dim3(256 * TEAMS), 0, s, p, Alone{});
+    else hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ANY, TAPS, Alone, TEAMS>), grid, dim3(256 * TEAMS), 0, s, p, Alone{});
+}
+
 template <typename T, int BM, int BN, bool GATES, bool TAPS>
 static hipError_t launch_dma(const IgemmParams &p0, hipStream_t s)
 {
@@ -233,18 +248,15 @@ static hipError_t launch_dma(const IgemmParams &p0, hipStream_t s)
     p.nblk_n = (p.N + BN - 1) / BN;
     int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
-    if (p.splits > 1) {
-        if (GATES || !igemm_dma_splits_ok(p, TAPS, (int)sizeof(T))) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS, Alone>), dim3((unsigned)nblk, (unsigned)p.splits), dim3(256), 0, s, p, Alone{});
-        hipError_t er = hipGetLastError();
-        if (er != hipSuccess || p.skip_reduce) return er;
-        return launch_splitk_reduce(p, s);
-    }
-    const bool rows = p.ys_n == (int64_t)p.OHW * p.ys_p && p.ys_c == 1 && (p.N & 7) == 0 && (p.ys_p & 7) == 0;
-    if (GATES) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, STORE_GATES, false, Alone>), dim3((unsigned)nblk), dim3(256), 0, s, p, Alone{});
-    else if (rows) hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ROWS, TAPS, Alone>), dim3((unsigned)nblk), dim3(256), 0, s, p, Alone{});
-    else hipLaunchKernelGGL((igemm_dma_kernel<T, BM, BN, STORE_ANY, TAPS, Alone>), dim3((unsigned)nblk), dim3(256), 0, s, p, Alone{});
-    return hipGetLastError();
+    if (p.splits > 1 && (GATES || !igemm_dma_splits_ok(p, TAPS, (int)sizeof(T)))) return hipErrorInvalidValue;
+    const int64_t groups = nblk * std::max(p.splits, 1);
+    if constexpr (BM == 64 && BN == 64 && !GATES) {
+        if (groups <= 256) go_dma<T, 64, 64, false, TAPS, 2>(p, (unsigned)nblk, s);
+        else go_dma<T, 64, 64, false, TAPS, 1>(p, (unsigned)nblk, s);
+    } else go_dma<T, BM, BN, GATES, TAPS, 1>(p, (unsigned)nblk, s);
+    hipError_t er = hipGetLastError();
+    if (er != hipSuccess || p.splits <= 1 || p.skip_reduce) return er;
+    return launch_splitk_reduce(p, s);
 }
 
 template <typename T, bool TAPS>

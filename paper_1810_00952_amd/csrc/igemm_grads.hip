@@ -33,7 +33,7 @@ template <bool CONV> struct BesideRows {
     }
 };
 
-#define RL_ONE(T, MODE, TAPS, CONV) template __global__ void igemm_dma_kernel<T, 64, 64, MODE, TAPS, BesideRows<CONV>>(const IgemmParams, const BesideRows<CONV>);
+#define RL_ONE(T, MODE, TAPS, CONV) template __global__ void igemm_dma_kernel<T, 64, 64, MODE, TAPS, BesideRows<CONV>, 1>(const IgemmParams, const BesideRows<CONV>);
 #define RL_INST(T, MODE) RL_ONE(T, MODE, false, false) RL_ONE(T, MODE, false, true) RL_ONE(T, MODE, true, true)
 RL_INST(float, STORE_ROWS) RL_INST(float, STORE_ANY) RL_INST(uint16_t, STORE_ROWS) RL_INST(uint16_t, STORE_ANY)
 #undef RL_INST
@@ -54,7 +54,7 @@ static hipError_t launch_typed(const IgemmParams &p, const TnParams &q, bool tap
     const int rows_first = q.split_tiles > (p.splits > 1 ? p.split_tiles : nk);
     const int64_t first = rows_first ? nb : na, grid = (first + NUM_XCD - 1) / NUM_XCD * NUM_XCD + (rows_first ? na : nb);
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-#define RL_GO(MODE, TAPS, CONV) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, MODE, TAPS, BesideRows<CONV>>), dim3((unsigned)grid), dim3(256), 0, s, p, (BesideRows<CONV>{q, (int)first, rows_first}))
+#define RL_GO(MODE, TAPS, CONV) hipLaunchKernelGGL((igemm_dma_kernel<T, 64, 64, MODE, TAPS, BesideRows<CONV>, 1>), dim3((unsigned)grid), dim3(256), 0, s, p, (BesideRows<CONV>{q, (int)first, rows_first}))
     if (taps && rows) RL_GO(STORE_ROWS, true, true);
     else if (taps) RL_GO(STORE_ANY, true, true);
     else if (q.conv && rows) RL_GO(STORE_ROWS, false, true);

@@ -147,6 +147,24 @@ def test_input_gradient_with_ragged_channels(dtype):
         check(spec, data, dtype, f"ragged {kind} {dims} {dtype}")
 
 
+# ---- direct-load tiles of 64x64 with the steps of a K tile over two halves of the waves: grids of up to 256 workgroups, and one past it; the
+# fewest K tiles, a part-filled last one, one beyond a round of the stages; rows of channels, any order, K tiles across taps, K slices
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dims", [(1024, 136, 1024, 10), (1032, 136, 1024, 10), (1000, 200, 1001, 3), (70, 264, 72, 50), (65, 1000, 130, 9)])
+def test_dense_on_two_halves_of_the_waves(dtype, dims):
+    spec, data = W.mlp(*dims, dtype=dtype)
+    check(spec, data, dtype, f"two halves {dims} {dtype}", {"no_direct": 1})
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(4, 96, 136, 29, 29, 3, 1, 1, True), (2, 64, 72, 15, 13, 3, 1, 1, False), (5, 24, 65, 21, 21, 5, 2, 2, True), (9, 40, 130, 29, 28, 1, 1, 0, True)])
+def test_convolution_on_two_halves_of_the_waves(dtype, case):
+    b, ci, co, h, w, k, s, p, res = case
+    for tail in (False, True):
+        spec, data = W.conv_group(b, ci, co, h, w, k, s, p, dtype, residual=res, tail=tail)
+        check(spec, data, dtype, f"two halves {case} {dtype} {tail}", {"no_direct": 1})
+
+
 # ---- f32 tiles and K slices chosen by how the grid fills the chip ----------------------------------------------------------
 @pytest.mark.parametrize("case", [(8, 256, 256, 14, 14, 3, 1, 1), (4, 64, 128, 28, 28, 3, 2, 1), (9, 72, 200, 14, 14, 3, 1, 1)])
 def test_f32_half_filled_grids_split_k(case):
