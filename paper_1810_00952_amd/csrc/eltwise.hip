@@ -785,6 +785,22 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const T *__restrict__ 
     }
 }
 
+// [tile of rows][step][lane][16 bytes], a KB in a row for every load of igemm_direct.hip: lane g TS + l of a step has chunk g of row l
+template <typename T>
+__global__ __launch_bounds__(256) void pack_weight_direct_kernel(const T *__restrict__ src, T *__restrict__ dst, int O, int C, int Tt, int Kp, int TS)
+{
+    constexpr int KV = 16 / (int)sizeof(T);
+    const int G = 64 / TS, steps = Kp / (KV * G);
+    const int64_t total = (int64_t)((O + TS - 1) / TS) * TS * Kp;
+    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
+        const int e = (int)(idx % KV), lane = (int)(idx / KV % 64);
+        const int64_t block = idx / (KV * 64);
+        const int step = (int)(block % steps), o = (int)(block / steps) * TS + lane % TS, k = (step * G + lane / TS) * KV + e;
+        const int tap = k / C, c = k - tap * C;
+        dst[idx] = o < O && tap < Tt ? src[((int64_t)o * C + c) * Tt + tap] : (T)0;
+    }
+}
+
 // second copy of a 64 x (9 x 64) bf16 weight in the fragment order of the kernel that keeps it in registers
 __global__ __launch_bounds__(256) void pack_weight_frag64_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst)
 {
@@ -802,6 +818,14 @@ hipError_t launch_pack_weight(const void *src, void *dst, int32_t dtype, int32_t
         if (dtype != DT_BF16 || O != 64 || C != 64 || T != 9 || Kp != 576) return hipErrorInvalidValue;
         hipLaunchKernelGGL(pack_weight_kernel<uint16_t>, dim3(grid_for((int64_t)O * Kp)), dim3(256), 0, s, (const uint16_t *)src, (uint16_t *)dst, O, C, T, Kp, 0);
         hipLaunchKernelGGL(pack_weight_frag64_kernel, dim3(64 * 576 / 256), dim3(256), 0, s, (const uint16_t *)src, (uint16_t *)dst + 64 * 576);
+        return hipGetLastError();
+    }
+    if (perm_block == -16 || perm_block == -32) {
+        const int TS = -perm_block, step = (dtype == DT_BF16 ? 8 : 4) * (64 / TS);
+        if (Kp % step != 0 || Kp < C * T) return hipErrorInvalidValue;
+        const unsigned grid = grid_for((int64_t)((O + TS - 1) / TS) * TS * Kp);
+        if (dtype == DT_BF16) hipLaunchKernelGGL(pack_weight_direct_kernel<uint16_t>, dim3(grid), dim3(256), 0, s, (const uint16_t *)src, (uint16_t *)dst, O, C, T, Kp, TS);
+        else hipLaunchKernelGGL(pack_weight_direct_kernel<float>, dim3(grid), dim3(256), 0, s, (const float *)src, (float *)dst, O, C, T, Kp, TS);
         return hipGetLastError();
     }
     unsigned grid = grid_for((int64_t)O * Kp);

@@ -572,6 +572,14 @@ struct Planner {
         const bool dual = !ov && akind == RL_OP_CONV2D && !stem && in_dt == RL_BF16 && p.N == 64 && p.C == 64 && p.KH == 3 && p.KW == 3 && p.Kp == p.K;
         if (dual) pack.perm_block = -1;
         pack.bytes = (size_t)pack.O * pack.Kp * dtype_size(in_dt);
+        // a convolution's weights for the kernel without LDS tiles, used by it alone: packed in the order of its fragments (where they
+        // are packed in any case: which params are is the same in every form of a plan)
+        p.w_frag = akind == RL_OP_CONV2D && !ov && direct.tile && need_pack && pack.perm_block == 0 && !dual && consumers[wv].size() == 1 ? 1 : 0;
+        if (p.w_frag) {
+            pack.perm_block = -direct.tile;
+            p.Kp = pack.Kp = (int)round_up(p.K, KV * (64 / direct.tile));
+            pack.bytes = (size_t)round_up(pack.O, direct.tile) * pack.Kp * dtype_size(in_dt);
+        }
         // the vector-load kernel addresses its operands with 32-bit byte offsets and wants a K tile
         // (128 bytes per row) to lie inside one operand of a concatenation
         {

@@ -53,7 +53,7 @@ struct Step {
 };
 
 struct PackSpec {
-    int dtype = 0, O = 0, C = 0, T = 0, Kp = 0, perm_block = 0;   // perm_block -1: matrix, then the 64x64x3x3 fragment-order copy
+    int dtype = 0, O = 0, C = 0, T = 0, Kp = 0, perm_block = 0;   // perm_block -1: matrix, then the 64x64x3x3 fragment-order copy; -16, -32: fragments of igemm_direct.hip's tiles of so many rows
     int stem = 0, KH = 0, KW = 0;      // stem = 1: few-channel stem layout (launch_pack_weight_stem); 2: launch_pack_weight_stem_direct
     int pw = 0;                         // stem = 2: the convolution's left padding (its parity shifts the filter inside the 8-pixel window)
     int gather = 0; GatherPack gp{};   // gather = 1: launch_pack_gather (operands of the gradient operators)

@@ -147,6 +147,29 @@ def test_input_gradient_with_ragged_channels(dtype):
         check(spec, data, dtype, f"ragged {kind} {dims} {dtype}")
 
 
+# ---- weights in the order of the fragments: last tiles of few channels, K ending inside a step, every tile and slicing; a weight that two
+# convolutions read stays in rows
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form", [32 * 16 + 1, 32 * 16 + 8, 16 * 16 + 8])
+def test_convolution_weights_in_fragment_order(dtype, form):
+    for ci, co, k in ((8, 1, 3), (16, 33, 3), (12, 17, 5), (3, 40, 2), (24, 64, 3)):
+        spec, data = W.conv_group(2, ci, co, 9, 11, k, 1, 1, dtype, residual=True)
+        check(spec, data, dtype, f"fragments {ci} {co} {k} {form}", {"direct_all": form})
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_weight_of_two_convolutions_stays_in_rows(dtype):
+    import numpy as np
+    rng = np.random.default_rng(21)
+    spec, at = W.GraphSpec("shared"), dict(pad=(1, 1))
+    data = {"x": W.as_dtype(rng.standard_normal((1, 16, 10, 10)), dtype), "w": W.as_dtype(rng.standard_normal((16, 16, 3, 3)) / 12, dtype)}
+    y, w = spec.input("x", dtype, (1, 16, 10, 10)), spec.param("w", dtype, (16, 16, 3, 3))
+    for _ in range(2):
+        o, (y,) = spec.op("conv2d", [y, w], [(dtype, (1, 16, 10, 10))], **at); spec.group([o])
+    spec.output(y)
+    check(spec, data, dtype, f"shared weight {dtype}")
+
+
 # ---- direct-load tiles of 64x64 with the steps of a K tile over two halves of the waves: grids of up to 256 workgroups, and one past it; the
 # fewest K tiles, a part-filled last one, one beyond a round of the stages; rows of channels, any order, K tiles across taps, K slices
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
