@@ -51,7 +51,8 @@ template <typename T, int TS> __device__ __forceinline__ void mma(Acc<TS> &acc, 
 //   ROWS    channels fastest in memory and whole chunks of them: one 16-byte load
 //   PLANES  whole chunks of channels, any strides: one load per channel, neighbouring lanes neighbouring pixels
 //   ANY     every element decoded by itself
-template <typename T, int MODE, int TS, int KS>
+// FRAG: the weights lie in the order of the fragments
+template <typename T, int MODE, int TS, int KS, bool FRAG>
 __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     touch_args(p);
     // what the first request hangs on
     asm volatile("" :: "s"(p.nblk_m), "s"(p.nblk_n), "s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kp), "s"(p.C), "s"(p.H), "s"(p.W), "s"(p.KH), "s"(p.KW), "s"(p.OW), "s"(p.OHW), "s"(p.sh), "s"(p.sw),
-                 "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_c), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.pool), "s"(p.w_frag));
+                 "s"(p.ph), "s"(p.pw), "s"(p.xs_n), "s"(p.xs_c), "s"(p.xs_h), "s"(p.xs_w), "s"(p.x_bytes), "s"(p.w_bytes), "s"(p.pool));
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int slice = wave % KS, tw = wave / KS;
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     }
     const int n = n0 + l;
     const uint32_t b_off = (uint32_t)((int64_t)n * p.Kp * ES);
-    const bool n_live = n < p.N, frag = p.w_frag != 0;
+    const bool n_live = n < p.N;
     const bool row_live = (unsigned)ih0 < (unsigned)p.H && (unsigned)iw0 < (unsigned)p.W;
     const uint32_t xs_c = (uint32_t)(p.xs_c * ES), xs_h = (uint32_t)(p.xs_h * ES), xs_w = (uint32_t)(p.xs_w * ES);
 
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     };
     auto fetch = [&](int slot, int step) {
         const int k = (step * G + g) * KV;
-        fb[slot] = __builtin_amdgcn_raw_buffer_load_b128(rw, frag ? (uint32_t)lane * 16u : n_live && k < p.Kp ? b_off + (uint32_t)(k * ES) : OOB, frag ? (uint32_t)(bn * S + step) * 1024u : 0u, 0);
+        fb[slot] = __builtin_amdgcn_raw_buffer_load_b128(rw, FRAG ? (uint32_t)lane * 16u : n_live && k < p.Kp ? b_off + (uint32_t)(k * ES) : OOB, FRAG ? (uint32_t)(bn * S + step) * 1024u : 0u, 0);
         if constexpr (MODE == DIRECT_ANY) {
 #pragma unroll
             for (int e = 0; e < KV; ++e) fa[slot][e] = load1(a_at(k + e));
@@ -350,12 +351,11 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_cell_direct_kernel(const Igem
 RL_INST(4) RL_INST(8)
 #undef RL_INST
 
-#define RL_INST(T, MODE) \
-    template __global__ void igemm_direct_kernel<T, MODE, 32, 1>(const IgemmParams); template __global__ void igemm_direct_kernel<T, MODE, 32, 2>(const IgemmParams); \
-    template __global__ void igemm_direct_kernel<T, MODE, 32, 4>(const IgemmParams); template __global__ void igemm_direct_kernel<T, MODE, 32, 8>(const IgemmParams); \
-    template __global__ void igemm_direct_kernel<T, MODE, 16, 8>(const IgemmParams);
+#define RL_ONE(T, MODE, TS, KS) template __global__ void igemm_direct_kernel<T, MODE, TS, KS, false>(const IgemmParams); template __global__ void igemm_direct_kernel<T, MODE, TS, KS, true>(const IgemmParams);
+#define RL_INST(T, MODE) RL_ONE(T, MODE, 32, 1) RL_ONE(T, MODE, 32, 2) RL_ONE(T, MODE, 32, 4) RL_ONE(T, MODE, 32, 8) RL_ONE(T, MODE, 16, 8)
 RL_INST(float, DIRECT_ROWS) RL_INST(float, DIRECT_PLANES) RL_INST(float, DIRECT_ANY)
 RL_INST(uint16_t, DIRECT_ROWS) RL_INST(uint16_t, DIRECT_PLANES) RL_INST(uint16_t, DIRECT_ANY)
+#undef RL_ONE
 #undef RL_INST
 
 template <typename T, int MODE, int TS, int KS>
@@ -367,7 +367,8 @@ static hipError_t launch_one(const IgemmParams &p0, hipStream_t s)
     p.nblk_n = (p.N + TS - 1) / TS;
     const int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
+    if (p.w_frag) hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, true>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
+    else hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, false>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
     return hipGetLastError();
 }
 

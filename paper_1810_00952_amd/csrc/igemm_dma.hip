@@ -249,9 +249,8 @@ static hipError_t launch_dma(const IgemmParams &p0, hipStream_t s)
     int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
     if (p.splits > 1 && (GATES || !igemm_dma_splits_ok(p, TAPS, (int)sizeof(T)))) return hipErrorInvalidValue;
-    const int64_t groups = nblk * std::max(p.splits, 1);
     if constexpr (BM == 64 && BN == 64 && !GATES) {
-        if (groups <= 256) go_dma<T, 64, 64, false, TAPS, 2>(p, (unsigned)nblk, s);
+        if (p.splits <= 1 && nblk <= 256) go_dma<T, 64, 64, false, TAPS, 2>(p, (unsigned)nblk, s);
         else go_dma<T, 64, 64, false, TAPS, 1>(p, (unsigned)nblk, s);
     } else go_dma<T, BM, BN, GATES, TAPS, 1>(p, (unsigned)nblk, s);
     hipError_t er = hipGetLastError();
