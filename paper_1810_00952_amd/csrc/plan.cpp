@@ -308,7 +308,7 @@ struct Planner {
     // shape 0.52 and 0.48.  How it is checked: plans with direct_all = 1 against no_direct, layer by layer.
     struct Direct { int tile = 0, slices = 0; };
     enum OtherKind { OTHER_DMA = 0, OTHER_TAPS = 1, OTHER_GATHER = 2 };
-    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided, bool paired, bool pooled) const
+    Direct direct_form(int dtype, int64_t M, int64_t N, int64_t K, int mode, int other, bool copies_x, double x_mbytes, bool rides, int taps, bool strided, bool paired, bool pooled, double margin = 0.0, double *estimate = nullptr) const
     {
         Direct best;
         if (plan.opts.no_direct || M * N >= (int64_t)1 << 31) return best;
@@ -332,7 +332,8 @@ struct Planner {
             auto at = [&](double r) { return c[0] + lines * std::max(c[1] * steps, per * steps * std::max(r, 1.0)) + (c[3] + (tile == 32 ? c[4] * wt : 0.0)) * rounds; };
             if (at(rounds) < us) { us = at(rounds); us_whole = at(std::ceil(rounds)); best.tile = tile; best.slices = slices; rounds_best = rounds; steps_best = steps; }
         }
-        if (plan.opts.direct_all) return best;
+        if (estimate) *estimate = us;
+        if (plan.opts.direct_all || estimate) return best;      // the caller compares
         // A last round that only some of the CUs have a workgroup for.  Rows of f32 features read one by one: it counts in full, as two
         // workgroups on a CU have twice the lines in use that the vector L1 holds (354 x 704 x 1066 19.2 us by padded rows, 33.2 so; 249 x 1172 x
         // 1013 19.0 and 37.3); shorter rows still fit (1118 x 364 x 326 17.6 and 12.5).  Taps of channels in planes, a last round less than half full:
@@ -352,7 +353,21 @@ struct Planner {
         const double theirs = c[0] + c[1] * lds.cycles / 2100.0 + (split ? c[2] : 0.0) + (copies_x ? c[3] + c[4] * x_mbytes : 0.0) +
                               c[5] * M * (double)N * dtype_size(dtype) / 1e6 - (rides && split ? 3.0 : 0.0) - (paired ? 3.5 : 0.0);
         // (few slices: short K on many tiles, where the stores decide and the estimates are at their worst)
-        return us < (best.slices < 4 && other != OTHER_GATHER ? 0.7 : 0.85) * theirs ? best : Direct();
+        return us < (margin > 0.0 ? margin : best.slices < 4 && other != OTHER_GATHER ? 0.7 : 0.85) * theirs ? best : Direct();
+    }
+
+    // The same where the pixel-on-lane kernels would run, on 64x64 tiles: layers of a channel-last network at small batches.  They
+    // take 3.05 us and 0.244 a K tile, once more for every 256 tiles; this kernel 0.67 of the estimate above there, dense layers 0.8 (91 drawn convolutions of 64 to 512
+    // channels, rms 9 and 15 %).  Taken where it promises a seventh: 36 of them move, to 0.70 of their time, none loses
+    // (2x128x7x7 -> 128 3x3 6.6 -> 3.8 us; 4x192x14x14 10.7 -> 7.6; the residual network's shape, one image, 158 -> 124).
+    Direct direct_before_lp(int64_t M, int64_t N, int64_t K, int taps, bool strided, double of_estimate) const
+    {
+        auto cd = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+        if (cd(M, 128) * cd(N, 64) >= 192) return Direct();
+        double us = 0.0;
+        const Direct best = direct_form(RL_BF16, M, N, K, DIRECT_ROWS, OTHER_DMA, false, 0.0, false, taps, strided, false, false, 0.0, &us);
+        const double theirs = 3.05 + 0.244 * (double)cd(K, 64) * std::max(1.0, (double)(cd(M, 64) * cd(N, 64)) / 256.0);
+        return us > 0.0 && of_estimate * us < 0.85 * theirs ? best : Direct();
     }
 
     static bool pool_2x2(const OpNode &o)
@@ -449,8 +464,19 @@ struct Planner {
                 direct_mode = !vec ? DIRECT_ANY : last ? DIRECT_ROWS : DIRECT_PLANES;
                 const int next = !out_set.count(vout) && consumers[vout].size() == 1 ? consumers[vout][0] : -1;
                 const bool pooled = next >= 0 && cls.simple && cls.t_op < 0 && pool_2x2(g.ops[next]);       // fuse_direct_store
-                // bf16 channels in whole K tiles stay with the kernels that are made for them
-                if (in_dt == RL_F32 || p.C % 64 != 0 || plan.opts.direct_all)
+                // bf16 channels in whole K tiles: against the pixel-on-lane kernels where those would run (from channels in planes, which they
+                // get copied, never)
+                const bool lp_next = in_dt == RL_BF16 && p.C % 64 == 0 && p.N % 8 == 0 && p.KH * p.KW <= 32 && epi_any && T(vout).dtype == RL_BF16 && !plan.opts.no_lp &&
+                                     (out_layout == L_NHWC || (flops >= 4e8 && !plan.opts.no_out_transpose));
+                // 3x3 from 64 to 64 channels has a kernel and a packing of its own (conv3x3_c64.hip) and keeps them from planes too
+                const bool c64 = in_dt == RL_BF16 && p.C == 64 && p.N == 64 && p.KH == 3 && p.KW == 3 && !ov && !last;
+                // a strided convolution and the projection of the same input go out together (pair_contractions)
+                int strided = 0;
+                for (int c : consumers[x]) strided += g.ops[c].kind == RL_OP_CONV2D && g.ops[c].attrs.stride[0] > 1;
+                if (c64 && !plan.opts.direct_all) {}
+                else if (lp_next && !plan.opts.direct_all) {
+                    if (last && strided < 2 && !ov) direct = direct_before_lp(p.M, p.N, p.K, p.KH * p.KW, p.sw > 1, 0.67);
+                } else
                     direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, !vec && !pad ? OTHER_GATHER : p.C % (8 * KV) == 0 ? OTHER_DMA : OTHER_TAPS,
                                          (!last || pad) && consumers[x].size() == 1, (double)x_own / 1e6, false, p.KH * p.KW, p.sw > 1, ov && beside_weights_gradient(x), pooled);
             }
@@ -542,10 +568,21 @@ struct Planner {
                                    !plan.opts.no_splitk;
                 const int64_t nk = (K + 8 * KV - 1) / (8 * KV);
                 direct_mode = il.avec ? DIRECT_ROWS : DIRECT_ANY;
-                // with up to 4 (bf16: 8) K tiles, more than 256 tiles of 32 x 32, or bf16 K in whole tiles, the kernels with LDS tiles are level or ahead
-                const bool lds = il.avec && (rides || nk <= (in_dt == RL_F32 ? 4 : 8) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256);
-                if (plan.opts.direct_all || (!lds && (in_dt == RL_F32 || p.K % 64 != 0)))
-                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false, ov && beside_weights_gradient(x), false);
+                // with more than 256 tiles of 32 x 32 the kernels with LDS tiles are level or ahead.  With few K tiles, or bf16 K in whole ones, this
+                // kernel is ahead wherever its estimate is below theirs: of 124 drawn layers that went to LDS tiles before, 66 move, bf16 to 0.67
+                // of their time (28 x 446 x 320 8.2 -> 3.8 us, 48 x 980 x 1280 9.8 -> 5.4), f32 to 0.58, none loses; before the pixel-on-lane kernels
+                // (bf16, K in whole tiles, N in eights) 38 of 97 to 0.75, one loses 3 % (16 x 64 x 1024 6.1 -> 4.7)
+                // (not the gradients, which may go out in pairs, nor a layer that may ride on the adding launch of the one before)
+                const bool short_k = il.avec && (nk <= (in_dt == RL_F32 ? 4 : 8) || (in_dt == RL_BF16 && p.K % 64 == 0));
+                bool behind_split = false;
+                for (const Step &f : plan.steps) behind_split |= f.kind == S_IGEMM && f.slot[SL_Y] >= 0 && f.slot[SL_Y] == phys[L_NATIVE][x] && f.il.splits > 1;
+                const bool lds = il.avec && (rides || (short_k && (ov || behind_split)) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256);
+                const bool lp_next = in_dt == RL_BF16 && p.K % 64 == 0 && p.N % 8 == 0 && epi_any && T(vout).dtype == RL_BF16 && !plan.opts.no_lp;
+                if (lp_next && !plan.opts.direct_all) {
+                    if (!lds && relu_form) direct = direct_before_lp(p.M, p.N, p.K, 1, false, 0.8);
+                } else if (plan.opts.direct_all || !lds)
+                    direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false, ov && beside_weights_gradient(x), false,
+                                         short_k ? 0.95 : 0.0);
             }
             if (pad && !direct.tile) {
                 int ld;

@@ -170,6 +170,49 @@ def test_weight_of_two_convolutions_stays_in_rows(dtype):
     check(spec, data, dtype, f"shared weight {dtype}")
 
 
+# ---- bf16 layers of whole K tiles, and short K, on the kernel without LDS tiles: from channels in planes, inside a channel-last network, dense;
+# the larger neighbour of each stays on LDS tiles
+@pytest.mark.parametrize("small,case", [(True, (2, 128, 72, 9, 9, 3, 1, 1)), (True, (1, 64, 112, 24, 24, 3, 2, 0)), (False, (64, 128, 128, 28, 28, 3, 1, 1)), (False, (3, 64, 64, 14, 14, 3, 1, 1))])
+def test_small_bf16_convolutions_of_whole_k_tiles(small, case):
+    spec, data = W.conv_group(*case, dtype="bf16", residual=True)
+    assert any("_direct" in x for x in steps_of(spec)) == small, steps_of(spec)
+    check(spec, data, "bf16", f"small {case}")
+
+
+@pytest.mark.parametrize("small,batch,c,h", [(True, 2, 128, 7), (True, 4, 192, 14), (True, 1, 512, 7), (False, 32, 128, 28)])
+def test_small_bf16_convolutions_of_a_channel_last_network(small, batch, c, h):
+    import numpy as np
+    rng = np.random.default_rng(22)
+    spec, t = W.GraphSpec("chain"), ("bf16", (batch, c, h, h))
+    data = {"x": W.as_dtype(rng.standard_normal(t[1]), "bf16")}
+    y = spec.input("x", *t)
+    for i in range(3):
+        data[f"w{i}"], data[f"b{i}"] = W.as_dtype(rng.standard_normal((c, c, 3, 3)) * (2 / (9 * c)) ** 0.5, "bf16"), W.as_dtype(rng.uniform(-1, 1, c), "f32")
+        o0, (v,) = spec.op("conv2d", [y, spec.param(f"w{i}", "bf16", (c, c, 3, 3))], [t], pad=(1, 1))
+        o1, (v,) = spec.op("bias_add", [v, spec.param(f"b{i}", "f32", (c,))], [t], axis=1)
+        o2, (y,) = spec.op("relu", [v], [t])
+        spec.group([o0, o1, o2])
+    spec.output(y)
+    assert any("_direct" in x for x in steps_of(spec)) == small, steps_of(spec)
+    check(spec, data, "bf16", f"chain {batch} {c} {h}")
+
+
+@pytest.mark.parametrize("small,dtype,dims", [(True, "bf16", (28, 320, 446)), (True, "bf16", (16, 1024, 64)), (True, "f32", (616, 128, 16)), (True, "bf16", (48, 1280, 980)),
+                                              (False, "bf16", (657, 1728, 1152)), (False, "bf16", (341, 320, 832)), (False, "f32", (1000, 128, 1000))])
+def test_small_dense_layers_of_whole_or_few_k_tiles(small, dtype, dims):
+    import numpy as np
+    m, k, n = dims
+    rng = np.random.default_rng(23)
+    spec, t = W.GraphSpec("dense"), (dtype, (m, n))
+    data = {"x": W.as_dtype(rng.standard_normal((m, k)), dtype), "w": W.as_dtype(rng.standard_normal((n, k)) / k ** 0.5, dtype), "b": W.as_dtype(rng.uniform(-1, 1, n), "f32")}
+    o0, (v,) = spec.op("dense", [spec.input("x", dtype, (m, k)), spec.param("w", dtype, (n, k))], [t])
+    o1, (v,) = spec.op("bias_add", [v, spec.param("b", "f32", (n,))], [t], axis=1)
+    o2, (v,) = spec.op("relu", [v], [t])
+    spec.group([o0, o1, o2]); spec.output(v)
+    assert any("_direct" in x for x in steps_of(spec)) == small, steps_of(spec)
+    check(spec, data, dtype, f"dense {dims} {dtype}")
+
+
 # ---- direct-load tiles of 64x64 with the steps of a K tile over two halves of the waves: grids of up to 256 workgroups, and one past it; the
 # fewest K tiles, a part-filled last one, one beyond a round of the stages; rows of channels, any order, K tiles across taps, K slices
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
