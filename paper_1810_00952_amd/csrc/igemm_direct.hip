@@ -51,8 +51,10 @@ template <typename T, int TS> __device__ __forceinline__ void mma(Acc<TS> &acc, 
 //   ROWS    channels fastest in memory and whole chunks of them: one 16-byte load
 //   PLANES  whole chunks of channels, any strides: one load per channel, neighbouring lanes neighbouring pixels
 //   ANY     every element decoded by itself
-// FRAG: the weights lie in the order of the fragments
-template <typename T, int MODE, int TS, int KS, bool FRAG>
+// WB: the weights lie in rows of K (W_ROWS), in the order of the fragments (W_FRAGMENTS), or in rows of N, of which a lane takes its column
+// element by element (W_COLUMNS: x of a dense weight gradient)
+enum { W_ROWS = 0, W_FRAGMENTS = 1, W_COLUMNS = 2 };
+template <typename T, int MODE, int TS, int KS, int WB>
 __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses gfx950-only builtins
@@ -61,7 +63,8 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     constexpr int WT = WAVES / KS, BM = WT * TS;     // tiles (of TS x TS) per workgroup, one under the other
     constexpr int LD = TS + 1;
     constexpr int AV = MODE == DIRECT_ROWS ? 4 : KV; // registers of a chunk of A in flight
-    constexpr int DEPTH = AV == 8 ? 4 : 8;           // steps in flight
+    constexpr int BV = WB == W_COLUMNS ? KV : 4;     // ... and of the weights
+    constexpr int DEPTH = AV == 8 || BV == 8 ? 4 : 8; // steps in flight
     constexpr int PER = TS * TS * WT / (64 * WAVES); // results per thread (0: half of the threads have one)
     constexpr int EPT = PER < 1 ? 1 : PER;
     __shared__ float part[WAVES][TS * LD];
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     const int S = (p.K + KV * G - 1) / (KV * G);
     const int s0 = slice * S / KS, s1 = (slice + 1) * S / KS;
     uint32_t fa[DEPTH][AV];
-    u32x4 fb[DEPTH];
+    uint32_t fb[DEPTH][BV];
     // offset of element k, or out of range: padding, rows past M, k past K
     auto a_at = [&](int k) -> uint32_t {
         if (one_tap) return row_live && k < p.K ? a_off + (uint32_t)k * xs_c : OOB;
@@ -122,7 +125,19 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
     };
     auto fetch = [&](int slot, int step) {
         const int k = (step * G + g) * KV;
-        fb[slot] = __builtin_amdgcn_raw_buffer_load_b128(rw, FRAG ? (uint32_t)lane * 16u : n_live && k < p.Kp ? b_off + (uint32_t)(k * ES) : OOB, FRAG ? (uint32_t)(bn * S + step) * 1024u : 0u, 0);
+        if constexpr (WB == W_COLUMNS) {
+#pragma unroll
+            for (int e = 0; e < KV; ++e) {
+                const uint32_t off = n_live && k + e < p.K ? (uint32_t)((k + e) * p.Kp + n) * ES : OOB;
+                if constexpr (ES == 4) fb[slot][e] = __builtin_amdgcn_raw_buffer_load_b32(rw, off, 0, 0);
+                else fb[slot][e] = __builtin_amdgcn_raw_buffer_load_b16(rw, off, 0, 0);
+            }
+        } else {
+            constexpr bool FRAG = WB == W_FRAGMENTS;
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, FRAG ? (uint32_t)lane * 16u : n_live && k < p.Kp ? b_off + (uint32_t)(k * ES) : OOB, FRAG ? (uint32_t)(bn * S + step) * 1024u : 0u, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) fb[slot][e] = v[e];
+        }
         if constexpr (MODE == DIRECT_ANY) {
 #pragma unroll
             for (int e = 0; e < KV; ++e) fa[slot][e] = load1(a_at(k + e));
@@ -138,14 +153,14 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
             }
         }
     };
-    auto chunk_a = [&](int slot) -> u32x4 {
+    auto chunk = [](const auto &f) -> u32x4 {
         u32x4 v;
-        if constexpr (AV == 4) {
+        if constexpr (sizeof(f) == 16) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fa[slot][e];
+            for (int e = 0; e < 4; ++e) v[e] = f[e];
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fa[slot][2 * e] | (fa[slot][2 * e + 1] << 16);
+            for (int e = 0; e < 4; ++e) v[e] = f[2 * e] | (f[2 * e + 1] << 16);
         }
         return v;
     };
@@ -197,7 +212,7 @@ __global__ __launch_bounds__(64 * WAVES) void igemm_direct_kernel(const IgemmPar
 #pragma unroll
         for (int i = 0; i < DEPTH; ++i) {
             if (b + i >= steps) break;
-            mma<T, TS>(acc, chunk_a(i), fb[i]);
+            mma<T, TS>(acc, chunk(fa[i]), chunk(fb[i]));
             if (b + i + DEPTH < steps) fetch(i, s0 + b + i + DEPTH);
         }
     }
@@ -351,10 +366,13 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_cell_direct_kernel(const Igem
 RL_INST(4) RL_INST(8)
 #undef RL_INST
 
-#define RL_ONE(T, MODE, TS, KS) template __global__ void igemm_direct_kernel<T, MODE, TS, KS, false>(const IgemmParams); template __global__ void igemm_direct_kernel<T, MODE, TS, KS, true>(const IgemmParams);
-#define RL_INST(T, MODE) RL_ONE(T, MODE, 32, 1) RL_ONE(T, MODE, 32, 2) RL_ONE(T, MODE, 32, 4) RL_ONE(T, MODE, 32, 8) RL_ONE(T, MODE, 16, 8)
+#define RL_ONE(T, MODE, TS, KS, WB) template __global__ void igemm_direct_kernel<T, MODE, TS, KS, WB>(const IgemmParams);
+#define RL_FIVE(T, MODE, WB) RL_ONE(T, MODE, 32, 1, WB) RL_ONE(T, MODE, 32, 2, WB) RL_ONE(T, MODE, 32, 4, WB) RL_ONE(T, MODE, 32, 8, WB) RL_ONE(T, MODE, 16, 8, WB)
+#define RL_INST(T, MODE) RL_FIVE(T, MODE, W_ROWS) RL_FIVE(T, MODE, W_FRAGMENTS)
 RL_INST(float, DIRECT_ROWS) RL_INST(float, DIRECT_PLANES) RL_INST(float, DIRECT_ANY)
 RL_INST(uint16_t, DIRECT_ROWS) RL_INST(uint16_t, DIRECT_PLANES) RL_INST(uint16_t, DIRECT_ANY)
+RL_FIVE(float, DIRECT_ANY, W_COLUMNS) RL_FIVE(uint16_t, DIRECT_ANY, W_COLUMNS)
+#undef RL_FIVE
 #undef RL_ONE
 #undef RL_INST
 
@@ -367,8 +385,11 @@ static hipError_t launch_one(const IgemmParams &p0, hipStream_t s)
     p.nblk_n = (p.N + TS - 1) / TS;
     const int64_t nblk = (int64_t)p.nblk_m * p.nblk_n;
     if (nblk <= 0 || nblk > 0x7fffffff) return hipErrorInvalidValue;
-    if (p.w_frag) hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, true>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
-    else hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, false>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
+    if (p.w_frag == W_COLUMNS) {
+        if constexpr (MODE == DIRECT_ANY) hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, W_COLUMNS>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
+        else return hipErrorInvalidValue;
+    } else if (p.w_frag) hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, W_FRAGMENTS>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
+    else hipLaunchKernelGGL((igemm_direct_kernel<T, MODE, TS, KS, W_ROWS>), dim3((unsigned)nblk), dim3(64 * WAVES), 0, s, p);
     return hipGetLastError();
 }
 
@@ -416,8 +437,9 @@ hipError_t launch_igemm_direct(const IgemmParams &p, const IgemmLaunch &l, hipSt
 {
     const int KV = p.in_dtype == DT_BF16 ? 8 : 4;
     if (l.gates) return launch_lstm_cell(p, l.direct_units, s);
-    if (!p.x || !p.w || !p.y || p.x2 || p.M < 1 || p.N < 1 || p.K < 1 || p.K != p.C * p.KH * p.KW || p.Kp < p.K || p.Kp % KV != 0 || p.x_bytes >= OOB || p.w_bytes >= OOB ||
-        (uint64_t)p.N * p.Kp * (16 / KV) > p.w_bytes || (p.w_frag && (p.Kp != (p.K + KV * (64 / l.direct_tile) - 1) / (KV * (64 / l.direct_tile)) * KV * (64 / l.direct_tile) ||
+    if (!p.x || !p.w || !p.y || p.x2 || p.M < 1 || p.N < 1 || p.K < 1 || p.K != p.C * p.KH * p.KW || p.x_bytes >= OOB || p.w_bytes >= OOB ||
+        (p.w_frag == W_COLUMNS ? p.Kp < p.N || p.KH * p.KW != 1 || (uint64_t)p.K * p.Kp * (16 / KV) > p.w_bytes : p.Kp < p.K || p.Kp % KV != 0 || (uint64_t)p.N * p.Kp * (16 / KV) > p.w_bytes) ||
+        (p.w_frag == W_FRAGMENTS && (p.Kp != (p.K + KV * (64 / l.direct_tile) - 1) / (KV * (64 / l.direct_tile)) * KV * (64 / l.direct_tile) ||
         (uint64_t)((p.N + l.direct_tile - 1) / l.direct_tile * l.direct_tile) * p.Kp * (16 / KV) > p.w_bytes)) || (l.direct - 1 != DIRECT_ANY && p.C % KV != 0) || (l.direct - 1 == DIRECT_ROWS && p.xs_c != 1) ||
         (int64_t)p.M * p.N >= (int64_t)1 << 31 || (p.pool && (!p.epi.simple || p.epi.t_op >= 0 || p.M % 4 != 0)) || p.tap_dil_m1 || p.in_dil_m1)
         return hipErrorInvalidValue;

@@ -97,7 +97,7 @@ struct IgemmParams {
     // igemm_direct.hip: 1: the result is the 2x2 / stride 2 max-pool of the contraction's; OW, OHW, ys_* then are of pooled
     // pixels, M counts the four pixels of each
     int32_t pool;
-    int32_t w_frag;                        // igemm_direct.hip: the weights lie in the order of its fragments
+    int32_t w_frag;                        // igemm_direct.hip: the weights lie in the order of its fragments (1), or in rows of N, Kp elements apart (2)
 };
 // q = n / d for n < 2^31:  d == 1 ? n : (mulhi(n, mul) >> sh)
 void make_fast_div(uint32_t d, uint32_t &mul, uint32_t &sh);

@@ -576,10 +576,10 @@ struct Planner {
                 const bool short_k = il.avec && (nk <= (in_dt == RL_F32 ? 4 : 8) || (in_dt == RL_BF16 && p.K % 64 == 0));
                 bool behind_split = false;
                 for (const Step &f : plan.steps) behind_split |= f.kind == S_IGEMM && f.slot[SL_Y] >= 0 && f.slot[SL_Y] == phys[L_NATIVE][x] && f.il.splits > 1;
-                const bool lds = il.avec && (rides || (short_k && (ov || behind_split)) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256);
+                const bool many = il.avec && (rides || (short_k && behind_split) || ((ot.dims[0] + 31) / 32) * ((Nf + 31) / 32) > 256), lds = many || (il.avec && short_k && ov);
                 const bool lp_next = in_dt == RL_BF16 && p.K % 64 == 0 && p.N % 8 == 0 && epi_any && T(vout).dtype == RL_BF16 && !plan.opts.no_lp;
                 if (lp_next && !plan.opts.direct_all) {
-                    if (!lds && relu_form) direct = direct_before_lp(p.M, p.N, p.K, 1, false, 0.8);
+                    if (!many && relu_form) direct = direct_before_lp(p.M, p.N, p.K, 1, false, 0.8);
                 } else if (plan.opts.direct_all || !lds)
                     direct = direct_form(in_dt, p.M, p.N, p.K, direct_mode, il.avec || pad ? OTHER_DMA : OTHER_GATHER, pad && consumers[x].size() == 1, (double)bytes_of(x) / 1e6, rides, 1, false, ov && beside_weights_gradient(x), false,
                                          short_k ? 0.95 : 0.0);
@@ -1115,6 +1115,40 @@ struct Planner {
         }
         if (o.kind == RL_OP_DENSE_GRAD_X || o.kind == RL_OP_DENSE_GRAD_W) { p.ys_n = p.N; p.ys_p = p.N; p.ys_c = 1; }
         p.K1 = p.K;
+        // A small dense weight gradient (below tn_ok's line) of a backward pass, whose dy others read too: dy and x as they lie, on the kernel
+        // without LDS tiles.  The gather packs x first and reads dy element by element on a few 64x64 tiles: of 90 drawn backward passes 60 go
+        // this way, at 0.47 of their time (514 x 53 x 59 bf16 36 -> 9.5 us, 14 x 128 x 88 18.3 -> 7.4).  Not from 25 K steps a wave on, where
+        // the gather cuts K over workgroups (4071 x 21 x 16 f32 19.7 against 21.9); an operator alone in its plan keeps the packed operand.
+        if (o.kind == RL_OP_DENSE_GRAD_W && consumers[va].size() > 1 && (double)p.M * p.N * p.K < 4e6 && !plan.opts.no_direct && g.values[va].role != ROLE_PARAM && g.values[vb].role != ROLE_PARAM && bytes_of(va) < ((size_t)1 << 31) &&
+            bytes_of(vb) < ((size_t)1 << 31) && (int64_t)p.M * p.N < ((int64_t)1 << 31)) {
+            double us = 0.0;
+            const Direct form = direct_form(dt, p.M, p.N, p.K, DIRECT_ANY, OTHER_GATHER, false, 0.0, false, 1, false, false, false, 0.0, &us);
+            const int per_step = KV * (64 / std::max(form.tile, 1));
+            if (form.tile && (p.K + per_step - 1) / per_step <= 24 * form.slices) {
+                int a, b;
+                rl_status st = need(va, L_NATIVE, a);
+                if (st == RL_OK) st = need(vb, L_NATIVE, b);
+                if (st != RL_OK) return st;
+                p.Kp = p.N; p.w_frag = 2;
+                p.x_bytes = (uint32_t)bytes_of(va); p.w_bytes = (uint32_t)bytes_of(vb); p.y_bytes = (uint32_t)std::min(bytes_of(vy), ((size_t)1 << 31) - 1);
+                p.ts_h = p.xs_h; p.ts_w = p.xs_w; p.seg_stride = 64;
+                make_fast_div(1, p.div_ohw_mul, p.div_ohw_sh);
+                make_fast_div(1, p.div_ow_mul, p.div_ow_sh);
+                make_fast_div((uint32_t)p.C, p.div_c_mul, p.div_c_sh);
+                make_fast_div(1, p.div_kw_mul, p.div_kw_sh);
+                const int y = out_buf(vy, L_NATIVE);
+                const std::string tl = std::to_string(form.tile);
+                Step &s = add_step(S_IGEMM, std::string(op_name(o.kind)) + "#" + std::to_string(oi),
+                                   std::string("igemm_") + op_name(o.kind) + (dt == RL_BF16 ? "_bf16_" : "_f32_") + tl + "x" + tl + "_direct_columns" + (form.slices > 1 ? "_kwaves" : ""));
+                s.group = gi;
+                s.ig = p;
+                s.il.direct = 1 + DIRECT_ANY; s.il.direct_tile = form.tile; s.il.direct_slices = form.slices;
+                s.slot[SL_X] = a; s.slot[SL_W] = b; s.slot[SL_Y] = y;
+                s.flops = 2.0 * p.M * (double)p.N * p.K;
+                s.bytes = (double)bytes_of(va) + (double)bytes_of(vb) + (double)bytes_of(vy);
+                return RL_OK;
+            }
+        }
         p.Kp = (int)round_up(p.K, KV);
         gp.Kp = p.Kp;
         p.ts_h = p.xs_h; p.ts_w = p.xs_w; p.seg_stride = 64;

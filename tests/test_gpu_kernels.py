@@ -213,6 +213,25 @@ def test_small_dense_layers_of_whole_or_few_k_tiles(small, dtype, dims):
     check(spec, data, dtype, f"dense {dims} {dtype}")
 
 
+# ---- a backward pass of a small dense layer: the weights' gradient from dy and x as they lie; batches that end inside a step, last tiles of
+# few rows and columns, the longest K of the form and one past it
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("columns,dims", [(True, (1, 5, 3)), (True, (14, 128, 88)), (True, (9, 33, 17)), (True, (257, 31, 65)), (True, (300, 72, 40)), (True, (70, 200, 144)), (False, (6200, 21, 16))])
+def test_both_gradients_of_a_small_dense_layer(dtype, columns, dims):
+    import numpy as np
+    m, n, k = dims
+    rng = np.random.default_rng(24)
+    for out in {dtype, "f32"}:
+        spec = W.GraphSpec("dense_grads")
+        data = {"dy": W.as_dtype(rng.standard_normal((m, n)), dtype), "x": W.as_dtype(rng.standard_normal((m, k)), dtype), "w": W.as_dtype(rng.standard_normal((n, k)) / n ** 0.5, dtype)}
+        dy, x, w = spec.input("dy", dtype, (m, n)), spec.input("x", dtype, (m, k)), spec.param("w", dtype, (n, k))
+        o, (dx,) = spec.op("dense_grad_x", [dy, w], [(dtype, (m, k))]); spec.group([o])
+        o, (dw,) = spec.op("dense_grad_w", [dy, x], [(out, (n, k))], out_dtype=out); spec.group([o])
+        spec.output(dx); spec.output(dw)
+        assert any("_columns" in s for s in steps_of(spec)) == columns, steps_of(spec)
+        check(spec, data, dtype, f"dense gradients {dims} {dtype} {out}")
+
+
 # ---- direct-load tiles of 64x64 with the steps of a K tile over two halves of the waves: grids of up to 256 workgroups, and one past it; the
 # fewest K tiles, a part-filled last one, one beyond a round of the stages; rows of channels, any order, K tiles across taps, K slices
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
