@@ -1253,7 +1253,9 @@ struct Planner {
         const bool conv = o.kind == RL_OP_CONV2D_GRAD_W;
         const int64_t P = conv ? ta.dims[0] * ta.dims[2] * ta.dims[3] : ta.dims[0], T_ = conv ? numel(T(o.out[0])) / (ta.dims[1] * tb.dims[1]) : 1;
         const double macs = (double)P * ta.dims[1] * tb.dims[1] * T_;
-        if (macs < (conv ? 3.3e7 : 4e6)) return false;
+        // a convolution's backward pass, whose dy others read too (its rows are there, or their copy is shared): at any size (90 drawn ones
+        // below 33 M multiply-adds take 0.51 of the gather's time, the worst 0.90: 25x12x51x51 -> 10 1x1 bf16 75 -> 26 us)
+        if (macs < (conv ? 3.3e7 : 4e6) && !(conv && consumers[va].size() > 1)) return false;
         const int es = (int)dtype_size(ta.dtype), KV = kv_of(ta.dtype);
         const int64_t lda = round_up(ta.dims[1], KV), ldb = round_up(tb.dims[1], KV), lim = (int64_t)1 << 31;
         const int64_t brows = conv ? tb.dims[0] * tb.dims[2] * tb.dims[3] : P;

@@ -232,6 +232,27 @@ def test_both_gradients_of_a_small_dense_layer(dtype, columns, dims):
         check(spec, data, dtype, f"dense gradients {dims} {dtype} {out}")
 
 
+# ---- a backward pass of a small convolution: the weights' gradient over the rows of dy and x however few they are
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(1, 3, 4, 4, 2, 3, 1, 1), (2, 16, 12, 12, 24, 3, 1, 1), (3, 9, 15, 14, 17, 3, 2, 1), (5, 31, 7, 9, 33, 1, 1, 0), (4, 12, 11, 11, 10, 5, 2, 0), (1, 64, 9, 9, 8, 1, 2, 0)])
+def test_both_gradients_of_a_small_convolution(dtype, case):
+    import numpy as np
+    b, c, h, w, o, k, s, p = case
+    rng = np.random.default_rng(25)
+    oh, ow = W.conv_out(h, k, s, p), W.conv_out(w, k, s, p)
+    at = dict(stride=(s, s), pad=(p, p))
+    for out in {dtype, "f32"}:
+        spec = W.GraphSpec("conv_grads")
+        shapes = dict(dy=(b, o, oh, ow), x=(b, c, h, w), w=(o, c, k, k))
+        data = {n: W.as_dtype(rng.standard_normal(t) * ((o * k * k) ** -0.5 if n == "w" else 1.0), dtype) for n, t in shapes.items()}
+        dy, x, wt = spec.input("dy", dtype, shapes["dy"]), spec.input("x", dtype, shapes["x"]), spec.param("w", dtype, shapes["w"])
+        q, (dx,) = spec.op("conv2d_grad_x", [dy, wt], [(dtype, shapes["x"])], **at); spec.group([q])
+        q, (dw,) = spec.op("conv2d_grad_w", [dy, x], [(out, shapes["w"])], out_dtype=out, **at); spec.group([q])
+        spec.output(dx); spec.output(dw)
+        assert any("_rows" in n for n in steps_of(spec)), steps_of(spec)
+        check(spec, data, dtype, f"convolution gradients {case} {dtype} {out}")
+
+
 # ---- direct-load tiles of 64x64 with the steps of a K tile over two halves of the waves: grids of up to 256 workgroups, and one past it; the
 # fewest K tiles, a part-filled last one, one beyond a round of the stages; rows of channels, any order, K tiles across taps, K slices
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
