@@ -1835,6 +1835,20 @@ struct Planner {
         if (plan.opts.no_pair || plan.lean) return;
         auto moves = [](const Step &s) { return s.kind == S_TO_NHWC || s.kind == S_TO_NCHW || s.kind == S_PAD_NHWC; };
         for (size_t si = 0; si + 1 < plan.steps.size(); ++si) {
+            // a move behind a contraction that it has nothing to do with (x of a weight gradient behind the input gradient) comes before it,
+            // and so beside the move that the contraction waits for (64x128x28x28 3x3 bf16, both gradients 61.2 -> 58.4 us)
+            if (moves(plan.steps[si]) && !plan.steps[si].pair && plan.steps[si + 1].kind == S_IGEMM && !plan.steps[si + 1].pair && !plan.steps[si + 1].chain) {
+                size_t sj = si + 2;
+                while (sj < plan.steps.size() && moves(plan.steps[sj]) && plan.steps[sj].pair == 2) ++sj;      // (stored by the contraction)
+                if (sj < plan.steps.size() && moves(plan.steps[sj]) && !plan.steps[sj].pair) {
+                    bool apart = true;
+                    for (size_t k = si; k < sj; ++k)
+                        for (int q : plan.steps[k].slot)
+                            if (q >= 0 && (q == plan.steps[sj].slot[SL_Y] || (q == plan.steps[sj].slot[SL_X] && (q == plan.steps[k].slot[SL_Y] || q == plan.steps[k].slot[SL_PART])))) apart = false;
+                    if (apart && moves_pair_ok(move_params(plan.steps[si]), move_params(plan.steps[sj])))
+                        std::rotate(plan.steps.begin() + (long)si + 1, plan.steps.begin() + (long)sj, plan.steps.begin() + (long)sj + 1);
+                }
+            }
             Step &a = plan.steps[si], &b = plan.steps[si + 1];
             if (!moves(a) || !moves(b) || a.pair || b.pair || a.slot[SL_Y] == b.slot[SL_Y] || a.slot[SL_Y] == b.slot[SL_X] || a.slot[SL_X] == b.slot[SL_Y]) continue;
             if (!moves_pair_ok(move_params(a), move_params(b))) continue;

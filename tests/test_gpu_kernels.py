@@ -232,6 +232,24 @@ def test_both_gradients_of_a_small_dense_layer(dtype, columns, dims):
         check(spec, data, dtype, f"dense gradients {dims} {dtype} {out}")
 
 
+# ---- x of a weight gradient changes its layout beside dy, ahead of the input gradient that stands between them
+@pytest.mark.parametrize("case", [(8, 128, 28, 28, 128, 3), (3, 64, 20, 20, 64, 3)])
+def test_both_operands_of_a_backward_pass_change_layout_in_one_launch(case):
+    import numpy as np
+    b, c, h, w, o, k = case
+    rng = np.random.default_rng(26)
+    spec, at, dtype = W.GraphSpec("moves"), dict(pad=(1, 1)), "bf16"
+    shapes = dict(dy=(b, o, h, w), x=(b, c, h, w), w=(o, c, k, k))
+    data = {n: W.as_dtype(rng.standard_normal(t) * ((o * k * k) ** -0.5 if n == "w" else 1.0), dtype) for n, t in shapes.items()}
+    dy, x, wt = spec.input("dy", dtype, shapes["dy"]), spec.input("x", dtype, shapes["x"]), spec.param("w", dtype, shapes["w"])
+    q, (dx,) = spec.op("conv2d_grad_x", [dy, wt], [(dtype, shapes["x"])], **at); spec.group([q])
+    q, (dw,) = spec.op("conv2d_grad_w", [dy, x], [("f32", shapes["w"])], out_dtype="f32", **at); spec.group([q])
+    spec.output(dx); spec.output(dw)
+    steps = steps_of(spec)
+    assert steps[0] == "nchw_to_nhwc | nchw_to_nhwc" and not any("_to_nhwc" in s for s in steps[2:]), steps
+    check(spec, data, dtype, f"moves {case}")
+
+
 # ---- a backward pass of a small convolution: the weights' gradient over the rows of dy and x however few they are
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("case", [(1, 3, 4, 4, 2, 3, 1, 1), (2, 16, 12, 12, 24, 3, 1, 1), (3, 9, 15, 14, 17, 3, 2, 1), (5, 31, 7, 9, 33, 1, 1, 0), (4, 12, 11, 11, 10, 5, 2, 0), (1, 64, 9, 9, 8, 1, 2, 0)])
