@@ -610,8 +610,9 @@ struct Planner {
         if (dual) pack.perm_block = -1;
         pack.bytes = (size_t)pack.O * pack.Kp * dtype_size(in_dt);
         // a convolution's weights for the kernel without LDS tiles, used by it alone: packed in the order of its fragments (where they
-        // are packed in any case: which params are is the same in every form of a plan)
-        p.w_frag = akind == RL_OP_CONV2D && !ov && direct.tile && need_pack && pack.perm_block == 0 && !dual && consumers[wv].size() == 1 ? 1 : 0;
+        // are packed in any case: which params are is the same in every form of a plan).  Not of a single pixel through one tap, which is a
+        // dense layer and may ride on the adding launch of the one before it (chain_small_dense), whose kernel reads rows
+        p.w_frag = akind == RL_OP_CONV2D && !ov && direct.tile && need_pack && pack.perm_block == 0 && !dual && consumers[wv].size() == 1 && (p.OHW > 1 || p.KH * p.KW > 1) ? 1 : 0;
         if (p.w_frag) {
             pack.perm_block = -direct.tile;
             p.Kp = pack.Kp = (int)round_up(p.K, KV * (64 / direct.tile));
@@ -1879,7 +1880,7 @@ struct Planner {
             if (pa.OHW != 1 || pb.OHW != 1 || pa.KH * pa.KW != 1 || pb.KH * pb.KW != 1) continue;                       // two dense layers
             if (pa.ys_c != 1 || pa.ys_n != pa.N || pa.N > REDUCE_DENSE_MAX_N1 || pa.M > 65535) continue;
             if (pb.M != pa.M || pb.K != pa.N || pb.K1 != pb.K || pb.N > REDUCE_DENSE_MAX_N2 || pb.xs_c != 1 || pb.xs_n != pa.N) continue;
-            if (b.slot[SL_X2] >= 0 || pb.in_dtype != pa.y_dtype) continue;
+            if (b.slot[SL_X2] >= 0 || pb.in_dtype != pa.y_dtype || pb.w_frag) continue;                                // its weights in rows
             const int h = a.slot[SL_Y];
             if (h < 0 || plan.bufs[h].bound_value >= 0 || b.slot[SL_X] != h) continue;                               // the result is the plan's own
             bool other = false;                                                                                        // ... and nobody else's

@@ -157,6 +157,15 @@ def test_convolution_weights_in_fragment_order(dtype, form):
         check(spec, data, dtype, f"fragments {ci} {co} {k} {form}", {"direct_all": form})
 
 
+# a single pixel's second layer on the adding launch of the first, ragged channels between them; by itself; and where there is no slice to add
+@pytest.mark.parametrize("dtype,dims,chained", [("f32", (8, 2048, 50, 10), True), ("bf16", (8, 4096, 100, 30), True), ("f32", (70, 4096, 33, 64), True), ("bf16", (5, 72, 50, 10), False)])
+def test_layers_of_a_single_pixel(dtype, dims, chained):
+    spec, data = W.pixel_layers(*dims, dtype)
+    assert any(k.endswith("+dense") for k in steps_of(spec)) == chained, steps_of(spec)
+    check(spec, data, dtype, f"pixel {dims} {dtype}")
+    check(spec, data, dtype, f"pixel {dims} {dtype}", {"no_dense_chain": 1})
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_weight_of_two_convolutions_stays_in_rows(dtype):
     import numpy as np

@@ -566,6 +566,16 @@ def test_k_over_the_waves_of_a_workgroup_is_not_called_a_split_over_workgroups()
     assert "_direct_any" in _steps(W.conv_group(3, 1, 20, 28, 28, 5, 1, 0, "f32")[0])[0]["kernel"]
 
 
+@pytest.mark.parametrize("dtype,dims", [("f32", (8, 2048, 50, 10)), ("bf16", (8, 4096, 100, 30))])
+def test_a_single_pixel_layer_on_the_adding_launch_before_it_keeps_its_weights_in_rows(dtype, dims):
+    # the launch that adds the first layer's slices reads the second layer's weights row by row: the same packing as without the
+    # kernel that has an order of its own for them
+    spec, _ = W.pixel_layers(*dims, dtype)
+    plans = [B.Plan(B.graph_from_spec(B.Context(), spec), opts).describe() for opts in (None, {"no_direct": 1})]
+    assert any(s["kernel"].endswith("+dense") for s in plans[0]["steps"]), plans[0]
+    assert plans[0]["packed_params"] == plans[1]["packed_params"]
+
+
 def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty():
     def dense(m, n, k, dtype="f32"):
         g = W.GraphSpec("dense")

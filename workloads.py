@@ -217,6 +217,20 @@ def conv_group(batch=1, cin=64, cout=64, h=56, w=56, k=3, stride=1, pad=1, dtype
     return g, data
 
 
+def pixel_layers(batch, cin, mid, cout, dtype="f32", config=27):
+    """Two 1x1 convolutions of single pixels, a group each: a classifier's head behind a global pool, left in rank 4."""
+    g = GraphSpec("pixel_layers")
+    rng = rng_for(config)
+    data = {"x": as_dtype(normal(rng, (batch, cin, 1, 1)), dtype),
+            "w1": as_dtype(normal(rng, (mid, cin, 1, 1), cin ** -0.5), dtype), "w2": as_dtype(normal(rng, (cout, mid, 1, 1), mid ** -0.5), dtype)}
+    y = g.input("x", dtype, (batch, cin, 1, 1))
+    for name, c, k in (("w1", mid, cin), ("w2", cout, mid)):
+        o, (y,) = g.op("conv2d", [y, g.param(name, dtype, (c, k, 1, 1))], [(dtype, (batch, c, 1, 1))])
+        g.group([o])
+    g.output(y)
+    return g, data
+
+
 def downsample_block(batch=4, cin=64, cout=128, h=32, w=32, dtype="bf16", config=10, taps=False):
     """The first block of a ResNet stage on its own: y = relu(conv3x3(relu(conv3x3/2(x) + b1)) + b3 + (conv1x1/2(x) + b2)).
     The stride-2 convolution and the 1x1 projection both read x and neither needs the other.
