@@ -1842,10 +1842,13 @@ struct Planner {
                 size_t sj = si + 2;
                 while (sj < plan.steps.size() && moves(plan.steps[sj]) && plan.steps[sj].pair == 2) ++sj;      // (stored by the contraction)
                 if (sj < plan.steps.size() && moves(plan.steps[sj]) && !plan.steps[sj].pair) {
+                    // no step before it touches what it writes, or writes what it reads (a cell's result is its h or c)
+                    const int *mv = plan.steps[sj].slot;
                     bool apart = true;
-                    for (size_t k = si; k < sj; ++k)
-                        for (int q : plan.steps[k].slot)
-                            if (q >= 0 && (q == plan.steps[sj].slot[SL_Y] || (q == plan.steps[sj].slot[SL_X] && (q == plan.steps[k].slot[SL_Y] || q == plan.steps[k].slot[SL_PART])))) apart = false;
+                    for (size_t k = si; k < sj; ++k) {
+                        for (int q : plan.steps[k].slot) apart &= q < 0 || q != mv[SL_Y];
+                        for (int q : {SL_Y, SL_COUT, SL_HOUT, SL_PART}) apart &= mv[SL_X] < 0 || plan.steps[k].slot[q] != mv[SL_X];
+                    }
                     if (apart && moves_pair_ok(move_params(plan.steps[si]), move_params(plan.steps[sj])))
                         std::rotate(plan.steps.begin() + (long)si + 1, plan.steps.begin() + (long)sj, plan.steps.begin() + (long)sj + 1);
                 }

@@ -259,6 +259,15 @@ def test_both_operands_of_a_backward_pass_change_layout_in_one_launch(case):
     check(spec, data, dtype, f"moves {case}")
 
 
+# ---- a change of layout does not overtake the cell whose h or c it turns
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("out", ["h", "c"])
+def test_a_cells_result_changes_its_layout_behind_the_cell(dtype, out):
+    for dims in ((16, 64, 128), (33, 128, 256)):
+        spec, data = W.lstm_cell_transposed(*dims, dtype, out)
+        check(spec, data, dtype, f"transposed {out} {dims} {dtype}")
+
+
 # ---- a backward pass of a small convolution: the weights' gradient over the rows of dy and x however few they are
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("case", [(1, 3, 4, 4, 2, 3, 1, 1), (2, 16, 12, 12, 24, 3, 1, 1), (3, 9, 15, 14, 17, 3, 2, 1), (5, 31, 7, 9, 33, 1, 1, 0), (4, 12, 11, 11, 10, 5, 2, 0), (1, 64, 9, 9, 8, 1, 2, 0)])

@@ -541,6 +541,15 @@ def test_two_changes_of_layout_in_one_launch_are_one_step_and_share_no_workspace
                 assert p["offset"] + p["bytes"] <= q["offset"] or q["offset"] + q["bytes"] <= p["offset"], (p, q)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("out", ["h", "c"])
+def test_a_cells_result_changes_its_layout_behind_the_cell(dtype, out):
+    # x is turned ahead of the cell, its h or c after it: not both in the launch ahead of it
+    d = B.Plan(B.graph_from_spec(B.Context(), W.lstm_cell_transposed(dtype=dtype, out=out)[0])).describe()
+    kernels = [s["kernel"] for s in d["steps"]]
+    assert kernels[0] == kernels[2] == "transpose_tiled" and kernels[1].endswith("_gates") and len(kernels) == 3, kernels
+
+
 def test_many_small_tiles_are_turned_by_a_launch_each():
     def moves(dtype, *shapes):
         g = W.GraphSpec("moves")

@@ -593,6 +593,30 @@ def lstm_cell_graph(batch=64, d_in=1024, hidden=1024, dtype="bf16", fused=True):
     return g
 
 
+def lstm_cell_transposed(batch=16, d_in=64, hidden=128, dtype="bf16", out="h"):
+    """One fused time step between two changes of layout: x arrives with its features first, and `out` (h or c) leaves so."""
+    g = GraphSpec("lstm_cell_transposed")
+    rng = rng_for(28)
+    data = {"xt": as_dtype(normal(rng, (d_in, batch)), dtype), "h": as_dtype(uniform(rng, (batch, hidden), -1, 1), dtype), "c": as_dtype(normal(rng, (batch, hidden)), "f32"),
+            "w": as_dtype(uniform(rng, (4 * hidden, d_in + hidden), -0.1, 0.1), dtype)}
+    xt = g.input("xt", dtype, (d_in, batch))
+    h = g.input("h", dtype, (batch, hidden))
+    c = g.input("c", "f32", (batch, hidden))
+    w = g.param("w", dtype, (4 * hidden, d_in + hidden))
+    o, (x,) = g.op("layout_transform", [xt], [(dtype, (batch, d_in))], perm=(1, 0))
+    g.group([o])
+    o0, (xh,) = g.op("concat", [x, h], [(dtype, (batch, d_in + hidden))], axis=1)
+    o1, (z,) = g.op("dense", [xh, w], [("f32", (batch, 4 * hidden))], out_dtype="f32")
+    o2, (c2, h2) = g.op("lstm_gates", [z, c], [("f32", (batch, hidden)), (dtype, (batch, hidden))])
+    g.group([o0, o1, o2])
+    src, dt = (h2, dtype) if out == "h" else (c2, "f32")
+    o, (y,) = g.op("layout_transform", [src], [(dt, (hidden, batch))], perm=(1, 0))
+    g.group([o])
+    g.output(y)
+    g.output(c2 if out == "h" else h2)
+    return g, data
+
+
 def lstm_unrolled_graph(steps, batch, d_in, hidden, dtype="bf16", fused=True):
     """The same recurrence written out as `steps` chained cells with
     h_0 = c_0 = 0 supplied as inputs; outputs every h_t and the last c."""
