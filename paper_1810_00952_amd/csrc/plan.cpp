@@ -613,11 +613,13 @@ struct Planner {
         // are packed in any case: which params are is the same in every form of a plan).  Not of a single pixel through one tap, which is a
         // dense layer and may ride on the adding launch of the one before it (chain_small_dense), whose kernel reads rows
         p.w_frag = akind == RL_OP_CONV2D && !ov && direct.tile && need_pack && pack.perm_block == 0 && !dual && consumers[wv].size() == 1 && (p.OHW > 1 || p.KH * p.KW > 1) ? 1 : 0;
-        if (p.w_frag) {
+        const int64_t frag_k = round_up(p.K, KV * (64 / std::max(direct.tile, 1)));
+        const size_t frag_bytes = (size_t)round_up(pack.O, std::max(direct.tile, 1)) * frag_k * dtype_size(in_dt);
+        if (p.w_frag && frag_bytes < lim) {
             pack.perm_block = -direct.tile;
-            p.Kp = pack.Kp = (int)round_up(p.K, KV * (64 / direct.tile));
-            pack.bytes = (size_t)round_up(pack.O, direct.tile) * pack.Kp * dtype_size(in_dt);
-        }
+            p.Kp = pack.Kp = (int)frag_k;
+            pack.bytes = frag_bytes;
+        } else p.w_frag = 0;                 // filled up to whole tiles they would pass what the kernel's offsets reach
         // the vector-load kernel addresses its operands with 32-bit byte offsets and wants a K tile
         // (128 bytes per row) to lie inside one operand of a concatenation
         {

@@ -575,6 +575,19 @@ def test_k_over_the_waves_of_a_workgroup_is_not_called_a_split_over_workgroups()
     assert "_direct_any" in _steps(W.conv_group(3, 1, 20, 28, 28, 5, 1, 0, "f32")[0])[0]["kernel"]
 
 
+def test_weights_stay_in_rows_where_whole_tiles_of_them_would_pass_two_gib():
+    # 45857 x 2926 x 2 x 2 f32 rows end just below 2 GiB, 45888 rows of them behind it
+    def packed(channels):
+        g = W.GraphSpec("wide")
+        x, w = g.input("x", "f32", (2, 2926, 5, 5)), g.param("w", "f32", (channels, 2926, 2, 2))
+        o, (y,) = g.op("conv2d", [x, w], [("f32", (2, channels, 4, 4))]); g.group([o]); g.output(y)
+        d = B.Plan(B.graph_from_spec(B.Context(), g)).describe()
+        assert "_direct" in d["steps"][-1]["kernel"], d["steps"]
+        return d["packed_params"][0]["bytes"]
+    assert packed(45587) == 45600 * 2926 * 4 * 4                      # in whole tiles of 32
+    assert packed(45857) == 45857 * 2926 * 4 * 4 < 1 << 31            # in rows
+
+
 @pytest.mark.parametrize("dtype,dims", [("f32", (8, 2048, 50, 10)), ("bf16", (8, 4096, 100, 30))])
 def test_a_single_pixel_layer_on_the_adding_launch_before_it_keeps_its_weights_in_rows(dtype, dims):
     # the launch that adds the first layer's slices reads the second layer's weights row by row: the same packing as without the
