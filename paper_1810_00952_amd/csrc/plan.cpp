@@ -1912,8 +1912,9 @@ struct Planner {
             for (int b : plan.steps[si].slot)
                 if (b >= 0) {
                     BufDesc &d = plan.bufs[b];
-                    // the second step of a pair runs when the first is launched
-                    const int at = plan.steps[si].pair == 2 ? (int)si - 1 : (int)si;
+                    // the second step of a pair runs when the first is launched; so does a small layer on the adding launch before it, which writes
+                    // rows of its result while others still read the partial sums
+                    const int at = plan.steps[si].pair == 2 || plan.steps[si].chain == 2 ? (int)si - 1 : (int)si;
                     if (d.first < 0) d.first = at;
                     d.last = (int)si;
                 }

@@ -622,6 +622,25 @@ def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty
         assert direct(dense(m, n, k, "bf16")), (m, n, k)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("batch", [8, 512])
+def test_a_small_layers_result_shares_no_workspace_with_the_partial_sums_it_is_made_of(dtype, batch):
+    # three layers: the second one's result, which the third reads, is written by the launch that adds the first one's slices
+    g = W.GraphSpec("three_layers")
+    y, k = g.input("x", dtype, (batch, 784)), 784
+    for i, n in enumerate((128, 10, 7)):
+        o, (y,) = g.op("dense", [y, g.param(f"w{i}", dtype, (n, k))], [(dtype, (batch, n))]); g.group([o])
+        k = n
+    g.output(y)
+    d = B.Plan(B.graph_from_spec(B.Context(), g)).describe()
+    assert d["steps"][0]["kernel"].endswith("_splitk+dense") and len(d["steps"]) == 3, d["steps"]
+    live = [b for b in d["buffers"] if b["first"] <= 1]
+    assert len(live) == 3                          # the tensor between the layers, the partial sums, the result
+    for i, p in enumerate(live):
+        for q in live[i + 1:]:
+            assert p["offset"] + p["bytes"] <= q["offset"] or q["offset"] + q["bytes"] <= p["offset"], (p, q)
+
+
 def test_both_gradients_of_a_layer_share_no_workspace():
     # the two run at once: whatever either reads or writes is apart from what the other writes
     for dtype, (b, c, h, o) in (("f32", (32, 64, 28, 64)), ("bf16", (16, 40, 20, 72))):
