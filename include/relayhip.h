@@ -213,7 +213,8 @@ typedef struct rl_plan_opts {
                                the small layer too */
     int32_t no_seq;         /* rl_plan_run_recurrent, hoisted form: 1: one launch per step, never one for the whole sequence; 2: the
                                one-launch form without waiting for all of its workgroups to be resident: those that are there
-                               share the work (what it falls back to); n > 2: on its first n workgroups.  All give the same bits */
+                               share the work (what it falls back to); n > 2: on its first n workgroups; -n (1 to 7): on those that the
+                               first n XCDs are dealt.  All give the same bits */
     int32_t no_direct;      /* never the contraction kernel that loads its operands straight into registers */
     int32_t direct_all;     /* that kernel wherever it can run, for tests and measurements: 1: with the tile and K slices the
                                planner would take; 16 * tile + slices: with those (tile 32: 1, 2, 4 or 8 slices; tile 16: 8).  Of a

@@ -521,6 +521,7 @@ rl_status rl_plan_run_recurrent(const rl_plan *cell, int32_t steps, const rl_rec
                         q.B = (int32_t)B; q.H = (int32_t)H; q.Kp = g0.Kp; q.k_off = (int32_t)I; q.T = (int32_t)tc;
                         q.save = lstm_seq_save_slot(q);
                         q.let_in = p.opts.no_seq > 2 ? p.opts.no_seq : 0;
+                        q.xcds = p.opts.no_seq < 0 && p.opts.no_seq > -8 ? -p.opts.no_seq : 0;
                         q.patience = p.opts.no_seq == 2 ? 0 : (int32_t)std::min<int64_t>(300 * tc, 1 << 30);      // 3 us a step
                         er = launch_lstm_seq(q, (hipStream_t)stream);
                         if (er == hipSuccess) continue;

@@ -242,6 +242,7 @@ struct LstmSeqParams {
     uint32_t *ctl, *save;               // control words (at zx of step T-1) and where what they displace is kept (a slot of h_seq that is not h0)
     int32_t B, H, Kp, k_off, T;
     int32_t let_in;                     // only that many workgroups take part (0: all)
+    int32_t xcds;                       // 1 to 7: those that the first so many XCDs are dealt, in place of let_in (0: all)
     int32_t patience;                   // 10 ns ticks to wait for all of them; that many times longer as a part of them is there
 };
 bool lstm_seq_ok(int64_t B, int64_t H, int64_t T);

@@ -115,7 +115,8 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 
     if (t == 0) {
         s_in = 0;
-        const uint32_t before = blockIdx.x < (unsigned)p.let_in ? RL_CTL_ADD(CTL_ENTERED) : CLOSED;
+        const bool may_enter = p.xcds < N_XCD ? (int)(blockIdx.x % N_XCD) < p.xcds : blockIdx.x < (unsigned)p.let_in;
+        const uint32_t before = may_enter ? RL_CTL_ADD(CTL_ENTERED) : CLOSED;
         if (!(before & CLOSED)) {
             s_slot = RL_CTL_ADD(xcc);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // all of this is about the control words alone: their order, no caches
@@ -383,6 +384,11 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
 #pragma unroll
             for (int u = 0; u < NU; ++u)
                 if (glive) p.c[(size_t)row * H + unit_of(member, u)] = lost ? __uint_as_float(0x7fc00000u) : c_r[u];
+            // the last step's sums are read out before the next group's first step writes there: with an odd number of steps both are part[0]
+            if (grp + n_active < groups) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                wg_barrier();
+            }
         } else {
             // fewer workgroups than blocks of units: the same block after block, the weights fetched every time,
             // one column tile ahead of the products
@@ -475,7 +481,7 @@ static bool whole_device(hipStream_t s)
 hipError_t launch_lstm_seq(const LstmSeqParams &p0, hipStream_t s)
 {
     LstmSeqParams p = p0;
-    if (!lstm_seq_ok(p.B, p.H, p.T) || !p.h0 || !p.h_seq || !p.w || !p.zx || !p.c || !p.ctl || !p.save || p.let_in < 0 || p.patience < 0 || p.Kp < p.k_off + p.H || p.k_off < 0 || p.k_off % 8 != 0 ||
+    if (!lstm_seq_ok(p.B, p.H, p.T) || !p.h0 || !p.h_seq || !p.w || !p.zx || !p.c || !p.ctl || !p.save || p.let_in < 0 || p.xcds < 0 || p.patience < 0 || p.Kp < p.k_off + p.H || p.k_off < 0 || p.k_off % 8 != 0 ||
         p.Kp % 8 != 0 || (uint64_t)4 * p.H * p.Kp * 2 != p.w_bytes || p.w_bytes >= 0x7fffffffu || p.h_step_bytes < (size_t)p.B * p.H * 2 ||
         ((uintptr_t)p.ctl & 255) || ((uintptr_t)p.save & 3))
         return hipErrorInvalidValue;
@@ -485,6 +491,8 @@ hipError_t launch_lstm_seq(const LstmSeqParams &p0, hipStream_t s)
     const void *kern = kerns[p.H / 256 - 1][p.B <= 8 * N_XCD];
     const int grid = N_XCD * (p.H / UNITS);
     p.let_in = p.let_in == 0 || p.let_in > grid ? grid : p.let_in;
+    p.xcds = p.xcds == 0 || p.xcds > N_XCD ? N_XCD : p.xcds;
+    if (p.xcds < N_XCD) p.let_in = p.xcds * (p.H / UNITS);
     hipLaunchKernelGGL(lstm_seq_prepare_kernel, dim3(1), dim3(256), 0, s, p.ctl, p.save, lstm_seq_ctl_words(p.H), 0);
     hipError_t er = hipGetLastError();
     if (er != hipSuccess) return er;

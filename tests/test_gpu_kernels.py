@@ -409,6 +409,23 @@ def test_lstm_sequence_in_one_launch(case):
         np.testing.assert_array_equal(first[1], again[1])
 
 
+# whole XCDs beside ones without a workgroup: each works off several groups of rows, one behind the other, its weights in registers and the
+# exchange in that group's ring; odd and even step counts, at most eight rows a group and more, last groups of fewer rows
+@pytest.mark.parametrize("T,B,H", [(17, 64, 256), (18, 64, 256), (19, 70, 512), (17, 9, 1024), (16, 128, 768)])
+def test_lstm_sequence_of_several_groups_of_rows_an_xcd(T, B, H):
+    import numpy as np
+    I = 128
+    d = W.lstm_data(T, B, I, H, "bf16")
+    rng = np.random.default_rng(13)
+    c0, h0 = W.as_dtype(rng.standard_normal((B, H)), "f32"), W.as_dtype(rng.uniform(-1, 1, (B, H)), "bf16")
+    first = run_sequence(T, B, I, H, d, {"no_seq": 1}, None, c0, h0)
+    for n in (1, 3, 7):
+        print(f"sequence {T} {B} {H} on {n} XCDs", flush=True)
+        again = run_sequence(T, B, I, H, d, {"no_seq": -n}, None, c0, h0)
+        np.testing.assert_array_equal(first[0], again[0])
+        np.testing.assert_array_equal(first[1], again[1])
+
+
 # what the waiting members must not take for a word that is still to come: NaN in a row's h and c from some step on, infinite c, h at
 # its largest (1 exactly in bf16), the sign of zero; rows beside them stay what they are
 @pytest.mark.parametrize("B", [5, 64, 70])
