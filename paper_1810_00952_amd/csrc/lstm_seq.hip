@@ -324,6 +324,7 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
                             if (by_word) write_out(tt - 1);
                         } else if (i == 1) {
                             if (by_word || tt >= BY_WORD - 2) __builtin_amdgcn_raw_buffer_store_b32(NOT_YET, rr, word_at, ring(tt + 1), 0);
+                            __builtin_amdgcn_sched_barrier(0);   // ahead of every load below: the wait before the step's words counts on that
                         } else {
                             zn[(i - 2) / 4][(i - 2) % 4] = zx_at(min(tt + 1, p.T - 1), unit_of(member, (i - 2) / 4), (i - 2) % 4);
                         }
@@ -365,7 +366,8 @@ __global__ __launch_bounds__(256, 1) void lstm_seq_kernel(const LstmSeqParams p)
                     hb[u] = (h & 0x7fffffffu) > 0x7f800000u ? nan : up;
                 }
                 word = two_units(hb);
-                // the next step's words are cleared before this step's are written
+                // the next step's words are cleared before this step's are written: the 4 NU loads of projections behind the clearing store may be
+                // on their way still, it may not
                 asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * NU) : "memory");
                 if (by_word || tt >= BY_WORD - 1) __builtin_amdgcn_raw_buffer_store_b32(word, rr, word_at, ring(tt), 0);
                 else write_out(tt);
