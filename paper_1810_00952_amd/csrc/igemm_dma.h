@@ -316,6 +316,7 @@ __global__ __launch_bounds__(256 * TEAMS) void igemm_dma_kernel(const IgemmParam
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[0][0][4 * r + e] += v[e];
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // read out before the barrier behind which stage 1 is written again
     }
 
     // ---- epilogue: 32 rows at a time through LDS (stage 0's array), then 8 channels per thread;
