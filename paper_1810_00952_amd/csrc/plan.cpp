@@ -1623,7 +1623,7 @@ struct Planner {
                     make_fast_div((uint32_t)p.OHW, p.div_ohw_mul, p.div_ohw_sh);
                     make_fast_div((uint32_t)p.OW, p.div_ow_mul, p.div_ow_sh);
                     c.kernel += "_maxpool";
-                } else if (m.kind == S_TO_NCHW && p.ys_c == 1 && p.ys_p == p.N) {
+                } else if (m.kind == S_TO_NCHW && p.ys_c == 1 && p.ys_p == p.N && m.t_C == p.N && m.t_P == p.OHW) {      // (not of another view of one channel's pixels)
                     p.ys_n = (int64_t)p.N * p.OHW; p.ys_p = 1; p.ys_c = p.OHW;
                 } else {
                     break;

@@ -259,6 +259,14 @@ def test_both_operands_of_a_backward_pass_change_layout_in_one_launch(case):
     check(spec, data, dtype, f"moves {case}")
 
 
+# ---- one channel's pixels turned behind the convolution that computes them
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_one_channels_pixels_are_turned(dtype):
+    for dims in ((5, 7, 5, 8), (2, 64, 9, 12)):
+        spec, data = W.one_channel_turned(*dims, dtype)
+        check(spec, data, dtype, f"one channel {dims} {dtype}")
+
+
 # ---- a change of layout does not overtake the cell whose h or c it turns
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("out", ["h", "c"])

@@ -442,6 +442,13 @@ def test_layout_transform_kernel_choice():
     assert kern((2, 1, 4, 5), (0, 2, 3, 1)) == ["eltwise_chain"]            # one channel: same order in memory
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_one_channels_pixels_are_turned_by_a_launch_of_their_own(dtype):
+    # a contraction stores in the order that a change of layout behind it asks for only where that is of its own channels and pixels
+    kernels = [k for _, k in _plan_steps(W.one_channel_turned(dtype=dtype)[0])]
+    assert kernels[-1] == "nhwc_to_nchw" and len(kernels) == 2, kernels
+
+
 # ---------------------------------------------------------------- K split over workgroups (host logic only)
 def test_channels_are_padded_only_where_the_copy_pays():
     # the copy is written whole, whatever the layer reads of it: not for a 1x1 layer at stride 2, nor for one channel of f32

@@ -327,6 +327,20 @@ def layout_case(shape=(3, 5, 7, 4), perm=(0, 2, 3, 1), dtype="f32", config=11):
     return g, data
 
 
+def one_channel_turned(batch=5, cin=7, h=5, w=8, dtype="f32", config=29):
+    """A convolution to one channel whose pixels then change their layout: [N,1,H,W] read as channel-last [N,1,H,W] and turned to
+    [N,W,1,H]."""
+    g = GraphSpec("one_channel_turned")
+    rng = rng_for(config)
+    data = {"x": as_dtype(normal(rng, (batch, cin, h, w)), dtype), "w": as_dtype(normal(rng, (1, cin, 3, 3), (9 * cin) ** -0.5), dtype)}
+    o, (y,) = g.op("conv2d", [g.input("x", dtype, (batch, cin, h, w)), g.param("w", dtype, (1, cin, 3, 3))], [(dtype, (batch, 1, h - 2, w - 2))])
+    g.group([o])
+    o, (y,) = g.op("layout_transform", [y], [(dtype, (batch, w - 2, 1, h - 2))], perm=(0, 3, 1, 2))
+    g.group([o])
+    g.output(y)
+    return g, data
+
+
 def channel_last_maxpool(batch=64, c=64, h=112, w=112, k=3, stride=2, pad=1, dtype="bf16", config=14):
     """A max-pool between channel-last tensors (typed views around it): y = to_last(maxpool(to_first(x)))."""
     rng = rng_for(config)
