@@ -1035,7 +1035,7 @@ struct Planner {
             // At a stride: the same stride-1 convolution of dy spread out with zeros (a step of its own writes that
             // tensor; three of four products are with zeros, on kernels that are many times faster than the gather).
             if (o.kind == RL_OP_CONV2D_GRAD_X && o.attrs.stride[0] == o.attrs.stride[1] && o.attrs.stride[0] > 1 &&
-                ((ta.dims[1] * (int64_t)dtype_size(dt)) % 16 == 0 || (!plan.lean && ta.dims[0] <= 65535))) {
+                ((ta.dims[1] * (int64_t)dtype_size(dt)) % 16 == 0 || (!plan.lean && moves_to_rows(ta)))) {
                 const int Nb = (int)ta.dims[0], O = (int)ta.dims[1], OH = (int)ta.dims[2], OW = (int)ta.dims[3];
                 const int C = (int)tb.dims[1], KH = (int)tb.dims[2], KW = (int)tb.dims[3], H = (int)ty.dims[2], W = (int)ty.dims[3];
                 const int sd = o.attrs.stride[0];
@@ -1221,6 +1221,14 @@ struct Planner {
         return RL_OK;
     }
 
+    // Whether need_rows' change of layout of a tensor of rank 4 fits the grid of its launch (launch_move): images and, but for whole vectors
+    // either way, tiles of channels in two dimensions of at most 65535.
+    static bool moves_to_rows(const rl_type &t)
+    {
+        const int64_t KV = kv_of(t.dtype), C = t.dims[1], P = t.dims[2] * t.dims[3];
+        return C % KV != 0 ? t.dims[0] <= 65535 && (round_up(C, KV) + 63) / 64 <= 65535 : P == 1 || P % KV == 0 || (t.dims[0] <= 65535 && (C + 31) / 32 <= 65535);
+    }
+
     // Rows of value v with its channels (features) fastest, each a whole number of 16-byte vectors long: v's own storage where
     // it has that form, else a copy padded with zeros by a step of the plan.  ld: elements per row.
     rl_status need_rows(int gi, int v, int &buf, int &ld)
@@ -1267,7 +1275,7 @@ struct Planner {
         const int es = (int)dtype_size(ta.dtype), KV = kv_of(ta.dtype);
         const int64_t lda = round_up(ta.dims[1], KV), ldb = round_up(tb.dims[1], KV), lim = (int64_t)1 << 31;
         const int64_t brows = conv ? tb.dims[0] * tb.dims[2] * tb.dims[3] : P;
-        return P * lda * es < lim && brows * ldb * es < lim && lda * ldb * T_ < ((int64_t)1 << 28) && ta.dims[0] <= 65535;
+        return P * lda * es < lim && brows * ldb * es < lim && lda * ldb * T_ < ((int64_t)1 << 28) && ta.dims[0] <= 65535 && (!conv || (moves_to_rows(ta) && moves_to_rows(tb)));
     }
 
     rl_status plan_tn(int gi, int oi)

@@ -605,6 +605,19 @@ def test_a_single_pixel_layer_on_the_adding_launch_before_it_keeps_its_weights_i
     assert plans[0]["packed_params"] == plans[1]["packed_params"]
 
 
+@pytest.mark.parametrize("channels,dims,stride", [(3000000, (5, 2, 1, 2, 1), 1), (2, (5000001, 3, 3, 1, 1), 2)])
+def test_gradients_of_more_channels_than_a_change_of_layout_has_workgroups_for_read_them_where_they_lie(channels, dims, stride):
+    o, h, w, kh, kw = dims
+    oh, ow = (h - kh) // stride + 1, (w - kw) // stride + 1
+    g = W.GraphSpec("many_channels")
+    dy, x, wt = g.input("dy", "f32", (1, o, oh, ow)), g.input("x", "f32", (1, channels, h, w)), g.param("w", "f32", (o, channels, kh, kw))
+    q, (dx,) = g.op("conv2d_grad_x", [dy, wt], [("f32", (1, channels, h, w))], stride=(stride, stride)); g.group([q])
+    g.output(dx)
+    q, (dw,) = g.op("conv2d_grad_w", [dy, x], [("f32", (o, channels, kh, kw))], out_dtype="f32", stride=(stride, stride)); g.group([q])
+    g.output(dw)
+    assert not any("nhwc" in k for _, k in _plan_steps(g)), _plan_steps(g)
+
+
 def test_kernel_without_lds_tiles_leaves_layers_whose_last_round_is_nearly_empty():
     def dense(m, n, k, dtype="f32"):
         g = W.GraphSpec("dense")
