@@ -34,7 +34,8 @@ enum { STORE_ROWS = 0, STORE_GATES = 1, STORE_ANY = 2 };
 
 // TEAMS: 2: eight waves, of which each half takes two of the four steps of every K tile; the halves' sums meet at the end.  With one workgroup
 // on a CU a K tile is a serial chain per wave (four direct loads, eight fragment reads, the MFMAs, the barrier: 690 cycles, however
-// many tiles are requested ahead), which this halves.  Grids of at most 256 workgroups without K slices (82 drawn dense layers 0.95 to 0.99 of
+// many tiles are requested ahead).  Each wave then has half of the loads, reads and MFMAs; the latency of each link and the barrier stay, and
+// of the 690 cycles about 45 go (13 K tiles, the meeting of the sums included).  Grids of at most 256 workgroups without K slices (82 drawn dense layers 0.95 to 0.99 of
 // their time by the number of K tiles; slices, whose K tiles are two or three, would lose 2 %): dense 1000 x 1000 x 784 bf16 8.04 -> 7.76 us,
 // 4x96x29x29 -> 136 3x3 with a residual 17.9 -> 16.3; 17 images (672 workgroups, which cover each other's chains) 24.4 against 26.8.
 // BESIDE: the workgroups of another contraction in the same grid (igemm_grads.hip).  Its take() does the work of those and returns false,

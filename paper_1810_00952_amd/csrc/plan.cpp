@@ -220,7 +220,8 @@ struct Planner {
     };
 
     // Shader cycles per K tile of the direct-load kernel on the fullest of 256 CUs: `alone` where a CU holds one workgroup, `share`
-    // per workgroup where it holds several (measured; f32 is the MFMA's own 1024 / 2048 / 4096 and a few percent)
+    // per workgroup where it holds several (measured; f32 is the MFMA's own 1024 / 2048 / 4096 and a few percent).  Of four waves, as K slices and
+    // larger grids run: whole grids of up to 256 workgroups of 64x64 tiles run eight (TEAMS in igemm_dma.h) and take 0.95 to 0.99 of it
     static double tile_cost(int tile, int dtype, int64_t workgroups)
     {
         static const double alone[2][3] = {{4400, 2300, 1450}, {1400, 900, 680}}, share[2][3] = {{4400, 2100, 1100}, {1200, 600, 390}};
@@ -1124,7 +1125,7 @@ struct Planner {
         if (o.kind == RL_OP_DENSE_GRAD_X || o.kind == RL_OP_DENSE_GRAD_W) { p.ys_n = p.N; p.ys_p = p.N; p.ys_c = 1; }
         p.K1 = p.K;
         // A small dense weight gradient (below tn_ok's line) of a backward pass, whose dy others read too: dy and x as they lie, on the kernel
-        // without LDS tiles.  The gather packs x first and reads dy element by element on a few 64x64 tiles: of 90 drawn backward passes 60 go
+        // without LDS tiles.  The gather packs x first and reads dy element by element on a few 64x64 tiles: of 90 drawn backward passes some 60 go
         // this way, at 0.47 of their time (514 x 53 x 59 bf16 36 -> 9.5 us, 14 x 128 x 88 18.3 -> 7.4).  Not from 25 K steps a wave on, where
         // the gather cuts K over workgroups (4071 x 21 x 16 f32 19.7 against 21.9); an operator alone in its plan keeps the packed operand.
         if (o.kind == RL_OP_DENSE_GRAD_W && consumers[va].size() > 1 && (double)p.M * p.N * p.K < 4e6 && !plan.opts.no_direct && g.values[va].role != ROLE_PARAM && g.values[vb].role != ROLE_PARAM && bytes_of(va) < ((size_t)1 << 31) &&

@@ -223,7 +223,7 @@ def test_small_dense_layers_of_whole_or_few_k_tiles(small, dtype, dims):
 
 
 # ---- a backward pass of a small dense layer: the weights' gradient from dy and x as they lie; batches that end inside a step, last tiles of
-# few rows and columns, the longest K of the form and one past it
+# few rows and columns, and a batch past the form
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("columns,dims", [(True, (1, 5, 3)), (True, (14, 128, 88)), (True, (9, 33, 17)), (True, (257, 31, 65)), (True, (300, 72, 40)), (True, (70, 200, 144)), (False, (6200, 21, 16))])
 def test_both_gradients_of_a_small_dense_layer(dtype, columns, dims):
@@ -239,6 +239,21 @@ def test_both_gradients_of_a_small_dense_layer(dtype, columns, dims):
         spec.output(dx); spec.output(dw)
         assert any("_columns" in s for s in steps_of(spec)) == columns, steps_of(spec)
         check(spec, data, dtype, f"dense gradients {dims} {dtype} {out}")
+
+
+# the longest batches of the column form, 24 steps a wave (whole, and ending inside the last step), and one row past it
+@pytest.mark.parametrize("dtype,batch,columns", [("bf16", 6143, True), ("bf16", 6144, True), ("bf16", 6145, False), ("f32", 3070, True), ("f32", 3072, True), ("f32", 3073, False)])
+def test_longest_batches_of_the_column_form(dtype, batch, columns):
+    import numpy as np
+    rng = np.random.default_rng(30)
+    spec = W.GraphSpec("dense_grads")
+    data = {"dy": W.as_dtype(rng.standard_normal((batch, 21)), dtype), "x": W.as_dtype(rng.standard_normal((batch, 16)), dtype), "w": W.as_dtype(rng.standard_normal((21, 16)) / 21 ** 0.5, dtype)}
+    dy, x, w = spec.input("dy", dtype, (batch, 21)), spec.input("x", dtype, (batch, 16)), spec.param("w", dtype, (21, 16))
+    o, (dx,) = spec.op("dense_grad_x", [dy, w], [(dtype, (batch, 16))]); spec.group([o])
+    o, (dw,) = spec.op("dense_grad_w", [dy, x], [("f32", (21, 16))], out_dtype="f32"); spec.group([o])
+    spec.output(dx); spec.output(dw)
+    assert any("_columns" in s for s in steps_of(spec)) == columns, steps_of(spec)
+    check(spec, data, dtype, f"columns {batch} {dtype}")
 
 
 # ---- x of a weight gradient changes its layout beside dy, ahead of the input gradient that stands between them
